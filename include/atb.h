@@ -80,6 +80,10 @@ typedef struct atb_gemm atb_gemm; /* opaque plan, HOST memory */
  * (M * round_up(K, 64), K * N, M * N; also N * round_up(K, 64) and
  * M * round_up(N, 64) for the BFP16 forms of B and C), and
  * 2 * N * (T_K + 1) < 2^31.
+ * Problems of few rows and a long reduction (M <= 64, K > 1024) on the instances (64, 64, 128, 128),
+ * (32, 64, 256, 64) and (32, 32, 256, 64), and with b_format BF16_T on any, are run by a kernel of their
+ * own that streams B through registers: the factors then only select it, and its sums are added in a
+ * different order (several shorter fp32 chains per element instead of one).
  * On success *out is a new plan, else *out = NULL.
  * Environment (read here, both optional): ATB_LOG=1 prints the plan to
  * stderr; ATB_GROUP_M=<tile rows, 1..65536> overrides the height of the
@@ -120,7 +124,7 @@ typedef enum atb_format {
  *                   linear layer.  The kernel then reads its B fragments with plain
  *                   16-byte LDS reads instead of transposing ones (half the LDS read
  *                   instructions for B).  Same values, same summation order, same
- *                   result bits as b_format BF16.  Needs c_format BF16, an instance
+ *                   result bits as b_format BF16 (but for few rows and a long reduction, see above).  Needs c_format BF16, an instance
  *                   with T_K = 64 and a C tile of at least 128 x 256, and
  *                   2 * T_N * K < 2^31 (else ATB_ERR_BAD_TILE / ATB_ERR_INVALID_ARG).
  *   c_format BF16 : C, M x N bf16 row-major.
@@ -140,7 +144,7 @@ atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, int64_t K,
 /* Launch geometry of a plan, for benches and tests: number of C tiles the
  * launch walks, rounded up to a multiple of 8 (the grid is persistent: it has
  * min(that, workgroups resident on the chip) workgroups, each looping over its
- * tiles), threads per workgroup, static LDS bytes per workgroup. Any pointer
+ * tiles; a problem that the kernel for few rows takes is launched differently), threads per workgroup, static LDS bytes per workgroup. Any pointer
  * may be NULL. */
 atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroups, int *threads, int *lds_bytes);
 

@@ -1459,9 +1459,16 @@ hipError_t launch_kernel(const GemmParams &p, hipStream_t stream)
     return hipGetLastError();
 }
 
+// Few rows and a long K go to the streaming kernel from the instances that the selector picks for such problems, and
+// from every instance that takes B^T in bf16 (all of them tiles of 128 rows and more).
+template <class S>
+constexpr bool kSkinnyRoute = (S::HW > 0 && S::T_K >= 128);
+
 template <class S>
 hipError_t launch_instance(const GemmParams &p, hipStream_t stream)
 {
+    if constexpr (kSkinnyRoute<S>)
+        if (skinny_applies(p, ATB_FMT_BF16)) return launch_skinny(p, ATB_FMT_BF16, stream);
     // 16-byte requests need dword-aligned addresses: B rows start at multiples of 2 N bytes, chunks at
     // multiples of 16 bytes within a row, so any even N qualifies (a chunk that straddles the end of
     // a row only feeds output columns >= N, which are never stored)
@@ -1474,9 +1481,12 @@ template <class S>
 hipError_t launch_instance_fmt(const GemmParams &p, int b_format, int c_format, hipStream_t stream)
 {
     const bool bb = (b_format == ATB_FMT_BFP16), cb = (c_format == ATB_FMT_BFP16);
+    if constexpr (kSkinnyRoute<S>)
+        if (b_format != ATB_FMT_BF16_T && skinny_applies(p, b_format)) return launch_skinny(p, b_format, stream);
     if (b_format == ATB_FMT_BF16_T) {
         // bf16 B handed over transposed: compiled for the tiles with K-steps of 64 and a bf16 C
         if constexpr (S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256) {
+            if (!cb && skinny_applies(p, b_format)) return launch_skinny(p, b_format, stream);
             if (!cb) return launch_kernel<S, true, false, false, true>(p, stream);
         }
         return hipErrorInvalidValue;
@@ -1616,9 +1626,10 @@ const Instance g_instances[] = {
     // B buffers (NB; it fits because the ATB A buffers are small, and it is what lets the symmetric 32-row tile's
     // single phase per K-step await its B tile two K-steps after the request), four helper waves next to the 1 x 2
     // grid (which alone would leave two SIMDs idle), and take the dead-row-skipping variant of the kernel body.
-    // Measured at N = K = 8192 (64 x 64 x 64 tile: 72 us at every M <= 128): M <= 64: 27 - 29 us with the 32-row
-    // tile (4.7 - 5.0 TB/s of B), M = 128: 39 us with the 64-row tile.  Factors from the issue model: 0.52 and 0.48
-    // (measured: 0.42 - 0.49 of the fit from M = 16 to 8192).
+    // Up to 64 rows and K > 1024 they hand over to the streaming kernel (launch_instance); what is left to them are
+    // 65 to about 128 rows, bf16 B of up to 8192 columns at 49 to 64 rows, and short reductions.  Measured at N = K =
+    // 8192, operands in turns so that B comes from memory: M <= 64: 40 - 41 us with the 32-row tile.  Factors from the
+    // issue model: 0.52 and 0.48 (measured: 0.42 - 0.49 of the fit from M = 16 to 8192).
     make_instance<Shape<32, 64, 256, 64, 1, 2, 2, 2, -1, 0, 2, 3, 4>, true>(),
     make_instance<Shape<32, 32, 256, 64, 1, 2, 2, 2, -1, 0, 2, 3, 4>, true>(),
 #endif

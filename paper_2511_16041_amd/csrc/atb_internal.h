@@ -47,6 +47,11 @@ const Instance &instance(int i);
 // index of the instance with these factors, or -1
 int find_instance(int T_MA, int T_MC, int T_K, int T_N);
 
+// The streaming kernel for few rows (atb_skinny.hip): whether a problem is one of its own, and its launch.  Takes every
+// storage format that the plan admits; b_format as in atb_format, C in BFP16 where p.Cm is set.
+bool skinny_applies(const GemmParams &p, int b_format);
+hipError_t launch_skinny(const GemmParams &p, int b_format, hipStream_t stream);
+
 hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae, int64_t M, int64_t K,
                            hipStream_t stream);
 hipError_t launch_decode(const int8_t *Am, const uint8_t *Ae, uint16_t *out, int64_t M, int64_t K,

@@ -1,0 +1,365 @@
+// GEMM for few rows (M <= 64) and a long reduction (K > 1024): a streaming kernel, bound by the bytes of B.
+//
+// With one band of 16 to 64 rows of C there is nothing to share a B tile with, so the tile pipeline of atb_gemm.hip (B
+// through LDS, a barrier per K-step, a workgroup per 64 columns) only adds waits.  Here every wave is on its own: the
+// W waves of a workgroup share a tile of 16 NB columns and take the 64-wide panels of K in turn, each loads its
+// operands straight into registers in MFMA layout, and the W partial C tiles are added once at the end through LDS, in
+// wave order (the sums of a result are therefore W shorter chains; the tile pipeline adds in one).
+//
+// What bounds it: a CU keeps about 200 lines of 128 bytes in flight (measured: 27 GB/s per CU from HBM whatever the
+// number of waves or of panels in flight per wave, 1 to 4), so all CUs have to take part and every line that is asked for should
+// be used whole.  Hence the tile width (column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
+// <= 8192 that is 32 columns, half a line per row, and the rate stays at 3.9 TB/s against 5.1 with B^T.
+// Measured in us, operands cold in the caches (three sets in turns), the tile pipeline before / this kernel now:
+//   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5     M 64, 14336, 4096: 34.7 / 30.0     M 16, 5001, 4096: 23.7 / 12.9
+//   B^T bf16  M 16, N 8192, K 8192: 105 / 29        M 64, 14336, 4096: 57.7 / 29.4
+//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.5    M 64, 14336, 4096: 26.0 / 21.1 (decoding A takes as long as B's bytes)
+//
+// MFMA v_mfma_f32_16x16x32_bf16: lane l supplies index l % 16 of its operand and 8 k values of group l / 16.  Which k
+// a group holds is free as long as both operands agree: lane group q takes k = 16 q .. 16 q + 15 of the panel, the
+// first half in one MFMA, the second in the next, so that a lane's A operands of a panel are one 16-byte request
+// (a wave's requests are then the panel's rows, one contiguous KiB).
+//   B row-major bf16   lane c of a group takes the NB neighbouring columns NB c .. of 16 rows; v_perm_b32 pairs the
+//                      rows up, which makes MFMA operand p the columns NB c + p.  Odd N: every odd row starts in the
+//                      middle of a dword; its lanes fetch the two dwords around their two columns, and the same
+//                      v_perm_b32 picks the halves
+//   B^T bf16           two 16-byte requests per 16 columns are the operands as they are
+//   B^T BFP16          one 16-byte request per 16 columns, decoded in registers like A
+#include "atb_internal.h"
+
+namespace atb {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef int intx2 __attribute__((ext_vector_type(2)));
+
+#define ATB_DEV __device__ __forceinline__
+
+constexpr int kRsrcFlags = 0x00020000;           // raw buffer, 32-bit data format
+
+template <class T>
+ATB_DEV __amdgpu_buffer_rsrc_t uniform_rsrc(const T *ptr, int64_t bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(ptr);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    const int n = __builtin_amdgcn_readfirstlane((int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, n, kRsrcFlags);
+}
+
+// 8 mantissas (two dwords) times 2^shift, as bf16: exact, |m| <= 127 has 7 significant bits
+ATB_DEV bf16x8 decode_block(int lo, int hi, int shift)
+{
+    bf16x8 r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        r[t] = (__bf16)ldexpf((float)(int)(signed char)(lo >> (8 * t)), shift);
+        r[4 + t] = (__bf16)ldexpf((float)(int)(signed char)(hi >> (8 * t)), shift);
+    }
+    return r;
+}
+
+enum { kBRow = 0, kBT = 1, kBBfp = 2, kBRowOdd = 3 };
+
+// One panel's operands of a lane.
+template <int FMT, int MB, int NB>
+struct Panel {
+    intx4 am[MB];                      // 16 mantissas of a row of A
+    unsigned ae[MB];                   // the aligned dword that holds their two exponents
+    int b[FMT == kBRow ? 16 * (NB / 2) : FMT == kBRowOdd ? 24 : 1];      // odd N: rows 2 i in b[i], rows 2 i + 1 in b[8 + 2 i], b[9 + 2 i]
+    intx4 bt[FMT == kBT ? 2 * NB : FMT == kBBfp ? NB : 1];
+    unsigned be[FMT == kBBfp ? NB : 1];
+};
+
+template <int FMT, int MB, int NB, int W>
+struct Skinny {
+    const GemmParams &p;
+    int lane, c, q, wave, n0;
+    static constexpr bool ROWS = (FMT == kBRow || FMT == kBRowOdd);
+    static_assert(NB % 2 == 0 && (FMT != kBRowOdd || NB == 2), "column pairs; odd N is written for one pair per lane");
+    int a_off[MB], e_off[MB], b_off[ROWS ? 16 : NB], be_off[NB];
+    floatx4 acc[MB][NB];
+    Panel<FMT, MB, NB> st;
+
+    ATB_DEV Skinny(const GemmParams &p_, int n0_) : p(p_), n0(n0_)
+    {
+        lane = threadIdx.x & 63;
+        c = lane & 15;
+        q = lane >> 4;
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        // rows >= M and columns >= N repeat a valid one: they only feed elements of C that are never stored
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            const int row = min(16 * i + c, p.M - 1);
+            a_off[i] = row * kPanelK + 16 * q;
+            e_off[i] = row * (kPanelK / 8) + 4 * (q >> 1);
+        }
+        if constexpr (ROWS) {
+            const int col = min(NB * c, ((p.N - 1) & ~1) - n0);   // even; relative to the tile
+#pragma unroll
+            for (int j = 0; j < 16; ++j) b_off[j] = (((16 * q + j) * p.N + col) * 2) & ~3;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int col = min(16 * i + c, p.N - 1 - n0);
+                if constexpr (FMT == kBT) {
+                    b_off[i] = (col * p.K + 16 * q) * 2;
+                } else {
+                    b_off[i] = col * kPanelK + 16 * q;
+                    be_off[i] = col * (kPanelK / 8) + 4 * (q >> 1);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    // Panel k of the reduction into st[s]; panels past the last read zeros without touching memory.
+    ATB_DEV void load(Panel<FMT, MB, NB> &s, int k)
+    {
+        const bool live = k < p.k_panels;
+        const int64_t kp = live ? k : 0;
+        const __amdgpu_buffer_rsrc_t am = uniform_rsrc(p.Am + kp * p.M * kPanelK, live ? (int64_t)p.M * kPanelK : 0);
+        const __amdgpu_buffer_rsrc_t ae = uniform_rsrc(p.Ae + kp * p.M * (kPanelK / 8), live ? (int64_t)p.M * (kPanelK / 8) : 0);
+        if constexpr (ROWS) {
+            // rows >= K lie past the end of B and read as zero
+            const int64_t first = kp * kPanelK * p.N + n0;
+            const __amdgpu_buffer_rsrc_t b = uniform_rsrc(p.B + first, live ? ((int64_t)p.K * p.N - first) * 2 : 0);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                if constexpr (FMT == kBRowOdd) {
+                    if (j % 2 == 0) {
+                        s.b[j / 2] = __builtin_amdgcn_raw_buffer_load_b32(b, b_off[j], 0, 0);
+                    } else {
+                        const intx2 v = __builtin_amdgcn_raw_buffer_load_b64(b, b_off[j], 0, 0);
+                        s.b[7 + j] = v.x;
+                        s.b[8 + j] = v.y;
+                    }
+                } else if constexpr (NB == 8) {
+                    const intx4 v = __builtin_amdgcn_raw_buffer_load_b128(b, b_off[j], 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s.b[4 * j + e] = v[e];
+                } else if constexpr (NB == 4) {
+                    const intx2 v = __builtin_amdgcn_raw_buffer_load_b64(b, b_off[j], 0, 0);
+                    s.b[2 * j] = v.x;
+                    s.b[2 * j + 1] = v.y;
+                } else {
+                    s.b[j] = __builtin_amdgcn_raw_buffer_load_b32(b, b_off[j], 0, 0);
+                }
+            }
+        } else if constexpr (FMT == kBT) {
+            // k >= K runs into the next row of B^T (or past its end, which reads as zero): finite values against the
+            // zero tail of A
+            const int64_t first = (int64_t)n0 * p.K + kp * kPanelK;
+            const __amdgpu_buffer_rsrc_t b = uniform_rsrc(p.B + first, live ? ((int64_t)p.N * p.K - first) * 2 : 0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                s.bt[2 * i] = __builtin_amdgcn_raw_buffer_load_b128(b, b_off[i], 0, 0);
+                s.bt[2 * i + 1] = __builtin_amdgcn_raw_buffer_load_b128(b, b_off[i] + 16, 0, 0);
+            }
+        } else {
+            const int64_t row = kp * p.N + n0;
+            const __amdgpu_buffer_rsrc_t bm = uniform_rsrc(p.Bm + row * kPanelK, live ? (int64_t)(p.N - n0) * kPanelK : 0);
+            const __amdgpu_buffer_rsrc_t be = uniform_rsrc(p.Be + row * (kPanelK / 8), live ? (int64_t)(p.N - n0) * (kPanelK / 8) : 0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                s.bt[i] = __builtin_amdgcn_raw_buffer_load_b128(bm, b_off[i], 0, 0);
+                s.be[i] = __builtin_amdgcn_raw_buffer_load_b32(be, be_off[i], 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            s.am[i] = __builtin_amdgcn_raw_buffer_load_b128(am, a_off[i], 0, 0);
+            s.ae[i] = __builtin_amdgcn_raw_buffer_load_b32(ae, e_off[i], 0, 0);
+        }
+    }
+
+    ATB_DEV static int shift_of(unsigned e, int q, int h) { return (int)((e >> (16 * (q & 1) + 8 * h)) & 0xFFu) - 133; }
+
+    ATB_DEV void multiply(const Panel<FMT, MB, NB> &s)
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            bf16x8 bf[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                if constexpr (FMT == kBRowOdd) {
+                    union { unsigned w[4]; bf16x8 v; } u;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int i = 4 * h + t;
+                        u.w[t] = j == 0 ? __builtin_amdgcn_perm(s.b[8 + 2 * i], s.b[i], 0x07060100u) : __builtin_amdgcn_perm(s.b[9 + 2 * i], s.b[i], 0x05040302u);
+                    }
+                    bf[j] = u.v;
+                } else if constexpr (FMT == kBRow) {
+                    union { unsigned w[4]; bf16x8 v; } u;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const unsigned r0 = s.b[(8 * h + 2 * t) * (NB / 2) + j / 2], r1 = s.b[(8 * h + 2 * t + 1) * (NB / 2) + j / 2];
+                        u.w[t] = __builtin_amdgcn_perm(r1, r0, (j & 1) ? 0x07060302u : 0x05040100u);
+                    }
+                    bf[j] = u.v;
+                } else if constexpr (FMT == kBT) {
+                    union { intx4 w; bf16x8 v; } u;
+                    u.w = s.bt[2 * j + h];
+                    bf[j] = u.v;
+                } else {
+                    bf[j] = decode_block(s.bt[j][2 * h], s.bt[j][2 * h + 1], shift_of(s.be[j], q, h));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const bf16x8 af = decode_block(s.am[i][2 * h], s.am[i][2 * h + 1], shift_of(s.ae[i], q, h));
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af, acc[i][j], 0, 0, 0);
+            }
+        }
+    }
+
+    ATB_DEV void run()
+    {
+        load(st, wave);
+        for (int k = wave; k < p.k_panels; k += W) {
+            multiply(st);
+            load(st, k + W);
+        }
+    }
+
+    // Column of the tile that register t of acc[.][j] holds in this lane (its row is lane % 16 of the row block).
+    ATB_DEV int column(int j, int t) const { return ROWS ? NB * (4 * q + t) + j : 16 * j + 4 * q + t; }
+};
+
+template <int FMT, int MB, int NB, int W>
+__global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
+{
+    constexpr int TN = 16 * NB, PITCH = TN + 4;
+    __shared__ __attribute__((aligned(16))) float part[W][16][PITCH];
+    // consecutive tiles on one XCD: neighbours share the 128-byte lines of a row of B in that XCD's L2
+    const int per_xcd = ((int)gridDim.x + 7) / 8;
+    const int tile = (int)(blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8;
+    const int cols = p.Cm ? p.n_panels * kPanelK : p.N;          // C in BFP16: the zero tail of the last panel as well
+    const int n0 = tile * TN;
+    if (n0 >= cols) return;                                       // the whole workgroup
+    const bool any = n0 < p.N;                                    // else a tile of that tail: nothing to multiply
+    Skinny<FMT, MB, NB, W> sk(p, any ? n0 : 0);
+    if (any) sk.run();
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        if (i > 0) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[sk.wave][sk.c][sk.column(j, v)] = sk.acc[i][j][v];
+        __syncthreads();
+        // item t of 64 NB: row t / (TN / 4) of the row block, four columns from 4 (t % (TN / 4))
+        for (int t = threadIdx.x; t < 64 * NB; t += W * 64) {
+            const int rr = t / (TN / 4), cc = 4 * (t % (TN / 4));
+            floatx4 sum = *reinterpret_cast<const floatx4 *>(&part[0][rr][cc]);
+#pragma unroll
+            for (int w = 1; w < W; ++w) sum += *reinterpret_cast<const floatx4 *>(&part[w][rr][cc]);
+            const int m = 16 * i + rr, n = n0 + cc;
+            if (p.Cm) {
+                // BFP16 C, as TileKernel::store_c_bfp: a block is this thread's four columns and its neighbour's
+                unsigned e = 0;
+                float x[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    x[v] = n < p.N ? sum[v] : 0.0f;               // whole blocks: N % 8 == 0
+                    e = max(e, (__float_as_uint(x[v]) >> 23) & 0xFFu);
+                }
+                e = max(e, (unsigned)__shfl_xor((int)e, 1));
+                unsigned w = 0;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float r = rintf(ldexpf(x[v], 133 - (int)e));
+                    r = fminf(fmaxf(r, -127.0f), 127.0f);
+                    w |= ((unsigned)((int)r) & 0xFFu) << (8 * v);
+                }
+                if (m < p.M && n < cols) {
+                    const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;
+                    *reinterpret_cast<unsigned *>(p.Cm + rec * kPanelK + n % kPanelK) = w;
+                    if ((t & 1) == 0) p.Ce[rec * (kPanelK / 8) + (n % kPanelK) / 8] = (uint8_t)e;
+                }
+            } else if (m < p.M) {
+                union { bf16x4 v; uint16_t h[4]; } u;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) u.v[v] = (__bf16)sum[v];
+                uint16_t *dst = p.C + (int64_t)m * p.N + n;
+                if (p.N % 4 == 0 && n + 4 <= p.N) {
+                    *reinterpret_cast<bf16x4 *>(dst) = u.v;
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (n + v < p.N) dst[v] = u.h[v];
+                }
+            }
+        }
+    }
+}
+
+template <int FMT, int MB, int NB, int W>
+hipError_t launch(const GemmParams &p, hipStream_t stream)
+{
+    const int cols = p.Cm ? p.n_panels * kPanelK : p.N;
+    const int tiles = (cols + 16 * NB - 1) / (16 * NB);
+    hipLaunchKernelGGL((skinny_kernel<FMT, MB, NB, W>), dim3((tiles + 7) / 8 * 8), dim3(W * 64), 0, stream, p);
+    return hipGetLastError();
+}
+
+template <int FMT, int NB, int W>
+hipError_t launch_rows(const GemmParams &p, hipStream_t stream)
+{
+    if (p.M <= 16) return launch<FMT, 1, NB, W>(p, stream);
+    if (p.M <= 32) return launch<FMT, 2, NB, W>(p, stream);
+    if (p.M <= 48) return launch<FMT, 3, NB, W>(p, stream);
+    if constexpr (FMT == kBBfp && NB == 8)
+        return hipErrorInvalidValue;       // skinny_applies keeps it away: registers
+    else
+        return launch<FMT, 4, NB, W>(p, stream);
+}
+
+// 16 NB columns per workgroup: the narrowest of 32, 64 and 128 that needs no more workgroups than there are CUs.
+// Measured (us, M = 16, bf16 B): N = 14336, K = 4096: 35.4 / 24.4 / 31.9 with 32 / 64 / 128 columns; N = 28672: 59 / 54 / 44.
+// W: four waves where their requests already fill the CU's share (64 and 128 columns of bf16 B: 24.4 against 28.1 us
+// with eight), eight or sixteen where more hands are needed to decode B.
+int column_blocks(int N) { return N <= 32 * 256 ? 2 : N <= 64 * 256 ? 4 : 8; }
+
+}  // namespace
+
+// Where this kernel takes over from the tile pipeline.  K <= 1024: there every instance adds in the same order and gives
+// the same bits, and the call is bound by its launch either way (M 16, N 8192, K 1088: 8.3 / 5.7 us).  The two
+// exceptions are where the pipeline is the faster one: M 64, N 8192, K 8192 bf16 41.0 / 43.5 us (every workgroup decodes
+// all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
+bool skinny_applies(const GemmParams &p, int b_format)
+{
+    if (p.M > 64 || p.K <= 1024) return false;
+    if (b_format == ATB_FMT_BF16 && p.N % 2 == 0 && p.N <= 32 * 256) return p.M <= 48;
+    if (b_format == ATB_FMT_BFP16 && p.N > 64 * 256) return p.M <= 48;
+    return true;
+}
+
+hipError_t launch_skinny(const GemmParams &p, int b_format, hipStream_t stream)
+{
+    const int nb = column_blocks(p.N);
+    if (b_format == ATB_FMT_BFP16) {
+        if (nb == 2) return launch_rows<kBBfp, 2, 16>(p, stream);
+        if (nb == 4) return launch_rows<kBBfp, 4, 8>(p, stream);
+        return launch_rows<kBBfp, 8, 8>(p, stream);
+    }
+    if (b_format == ATB_FMT_BF16_T) {
+        if (nb == 2) return launch_rows<kBT, 2, 8>(p, stream);
+        if (nb == 4) return launch_rows<kBT, 4, 4>(p, stream);
+        return launch_rows<kBT, 8, 4>(p, stream);
+    }
+    if (p.N % 2 != 0) return launch_rows<kBRowOdd, 2, 8>(p, stream);
+    if (nb == 2) return launch_rows<kBRow, 2, 8>(p, stream);
+    if (nb == 4) return launch_rows<kBRow, 4, 4>(p, stream);
+    return launch_rows<kBRow, 8, 4>(p, stream);
+}
+
+}  // namespace atb
