@@ -5,7 +5,7 @@ import pytest
 import oracle
 import paper_2511_16041_amd as atb
 import workloads
-from helpers import bf16_tensor_bits, unpack_a_bfp
+from helpers import bf16_tensor_bits, pack_a_bfp, unpack_a_bfp
 
 pytestmark = pytest.mark.gpu
 
@@ -72,6 +72,21 @@ def test_decode_exact():
     torch.cuda.synchronize()
     got = oracle.bf16_to_double(bf16_tensor_bits(dec))
     assert np.array_equal(got, oracle.decode(mant, expo))
+
+
+@pytest.mark.parametrize("M,K", [(1, 8), (15, 64), (17, 264), (33, 320), (4101, 4160), (4101, 4168)])
+def test_decode_shapes(M, K):
+    """Edges of the decoder's 16 rows x 4 panels, tails of the last panel, and outputs above 32 MiB with whole and with
+    shared 128-byte lines (the first are stored past the caches)."""
+    import torch
+    print(f"decode {(M, K)}", flush=True)
+    rng = np.random.default_rng(4)
+    mant = rng.integers(-127, 128, size=(M, K), dtype=np.int8)
+    expo = rng.integers(100, 160, size=(M, K // 8), dtype=np.uint8)
+    dec = atb.bfp16_decode(torch.from_numpy(pack_a_bfp(mant, expo)).cuda(), M, K)
+    torch.cuda.synchronize()
+    want = np.ldexp(mant.astype(np.float32).reshape(M, -1, 8), expo.astype(np.int32)[:, :, None] - 133).reshape(M, K)
+    assert np.array_equal(dec.float().cpu().numpy(), want)
 
 
 def test_quantizer_rejects_bad_arguments():
