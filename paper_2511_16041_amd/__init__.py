@@ -7,6 +7,7 @@ shared library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 from typing import List, Optional, Tuple
@@ -126,11 +127,28 @@ def _check(status: int, where: str) -> None:
         raise AtbError(status, where)
 
 
-def _stream_ptr(stream) -> Optional[int]:
-    if stream is None:
+_torch = None
+
+
+def _t():
+    """torch, imported at the first device call."""
+    global _torch
+    if _torch is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        _torch = torch
+    return _torch
+
+
+def _stream_ptr(stream) -> int:
+    """hipStream_t of `stream`, by default of the current device's current stream.  (torch.cuda.current_stream() makes a
+    Stream object, about 2 us of a call that is launched in 3; the raw handle is what torch's own launchers use.)"""
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _t()
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 # ------------------------------------------------------------------ host-only calls
@@ -151,6 +169,7 @@ def bfp16_layout(M: int, K: int) -> Bfp16Layout:
     return lay
 
 
+@functools.lru_cache(maxsize=1024)
 def bfp16_bytes(M: int, K: int) -> int:
     return int(lib().atb_bfp16_bytes(M, K))
 
@@ -227,7 +246,7 @@ def select_tiles(M: int, N: int, K: int, hw: Optional[HwParams] = None) -> List[
 def bfp16_quantize(A_f32, stream=None, out=None):
     """A_f32: CUDA fp32 tensor [M][K] (row stride a multiple of 4) -> uint8 tensor holding the A_bfp buffer
     (`out`, if given: a CUDA uint8 tensor of bfp16_bytes(M, K) elements, else a new one)."""
-    import torch
+    torch = _t()
     assert A_f32.is_cuda and A_f32.dtype == torch.float32 and A_f32.dim() == 2 and A_f32.stride(1) == 1
     M, K = A_f32.shape
     nbytes = bfp16_bytes(M, K)
@@ -236,16 +255,15 @@ def bfp16_quantize(A_f32, stream=None, out=None):
     if out is None:
         out = torch.empty(nbytes, dtype=torch.uint8, device=A_f32.device)
     assert out.is_cuda and out.dtype == torch.uint8 and out.is_contiguous() and out.numel() == nbytes
-    _check(lib().atb_bfp16_quantize(ctypes.c_void_p(A_f32.data_ptr()), A_f32.stride(0),
-                                    ctypes.c_void_p(out.data_ptr()), M, K, _stream_ptr(stream)), "atb_bfp16_quantize")
+    _check((_lib or lib()).atb_bfp16_quantize(A_f32.data_ptr(), A_f32.stride(0), out.data_ptr(), M, K, _stream_ptr(stream)),
+           "atb_bfp16_quantize")
     return out
 
 
 def bfp16_decode(A_bfp, M: int, K: int, stream=None):
-    import torch
+    torch = _t()
     out = torch.empty((M, K), dtype=torch.bfloat16, device=A_bfp.device)
-    _check(lib().atb_bfp16_decode(ctypes.c_void_p(A_bfp.data_ptr()), ctypes.c_void_p(out.data_ptr()), M, K,
-                                  _stream_ptr(stream)), "atb_bfp16_decode")
+    _check((_lib or lib()).atb_bfp16_decode(A_bfp.data_ptr(), out.data_ptr(), M, K, _stream_ptr(stream)), "atb_bfp16_decode")
     return out
 
 
@@ -292,26 +310,34 @@ class Gemm:
             _check(lib().atb_gemm_create_fmt(ctypes.byref(self._h), M, N, K, T_MA, T_MC, T_K, T_N,
                                              FORMATS[b_format], FORMATS[c_format]), "atb_gemm_create_fmt")
 
+        # what run() checks its operands against, and the bound call: a small problem is launched in about 3 us, and
+        # working these out again took longer than that
+        self._a_bytes = bfp16_bytes(M, K)
+        self._b_shape = (K, N) if b_format == "bf16" else (N, K)
+        self._b_bytes = bfp16_bytes(N, K) if b_format == "bfp16" else 0
+        self._c_bytes = bfp16_bytes(M, N) if c_format == "bfp16" else 0
+        self._call = lib().atb_gemm_run
+
     def run(self, A_bfp, B, C=None, stream=None):
-        import torch
-        M, N, K = self.shape
-        assert A_bfp.is_cuda and A_bfp.dtype == torch.uint8 and A_bfp.numel() == bfp16_bytes(M, K)
-        if self.b_format == "bf16":
-            assert B.is_cuda and B.dtype == torch.bfloat16 and tuple(B.shape) == (K, N) and B.is_contiguous()
-        elif self.b_format == "bf16_t":
-            assert B.is_cuda and B.dtype == torch.bfloat16 and tuple(B.shape) == (N, K) and B.is_contiguous()
+        torch = _torch or _t()
+        uint8, bfloat16 = torch.uint8, torch.bfloat16
+        assert A_bfp.is_cuda and A_bfp.dtype == uint8 and A_bfp.numel() == self._a_bytes
+        if self._b_bytes:
+            assert B.is_cuda and B.dtype == uint8 and B.numel() == self._b_bytes
         else:
-            assert B.is_cuda and B.dtype == torch.uint8 and B.numel() == bfp16_bytes(N, K)
-        if self.c_format == "bf16":
+            assert B.is_cuda and B.dtype == bfloat16 and B.shape == self._b_shape and B.is_contiguous()
+        if self._c_bytes:
             if C is None:
-                C = torch.empty((M, N), dtype=torch.bfloat16, device=A_bfp.device)
-            assert C.dtype == torch.bfloat16 and tuple(C.shape) == (M, N) and C.is_contiguous()
+                C = torch.empty(self._c_bytes, dtype=uint8, device=A_bfp.device)
+            assert C.dtype == uint8 and C.numel() == self._c_bytes
         else:
+            M, N, _ = self.shape
             if C is None:
-                C = torch.empty(bfp16_bytes(M, N), dtype=torch.uint8, device=A_bfp.device)
-            assert C.dtype == torch.uint8 and C.numel() == bfp16_bytes(M, N)
-        _check(lib().atb_gemm_run(self._h, ctypes.c_void_p(A_bfp.data_ptr()), ctypes.c_void_p(B.data_ptr()),
-                                  ctypes.c_void_p(C.data_ptr()), _stream_ptr(stream)), "atb_gemm_run")
+                C = torch.empty((M, N), dtype=bfloat16, device=A_bfp.device)
+            assert C.dtype == bfloat16 and C.shape == (M, N) and C.is_contiguous()
+        st = self._call(self._h, A_bfp.data_ptr(), B.data_ptr(), C.data_ptr(), _stream_ptr(stream))
+        if st != 0:
+            raise AtbError(st, "atb_gemm_run")
         return C
 
     def launch_info(self) -> LaunchInfo:
