@@ -80,9 +80,9 @@ typedef struct atb_gemm atb_gemm; /* opaque plan, HOST memory */
  * (M * round_up(K, 64), K * N, M * N; also N * round_up(K, 64) and
  * M * round_up(N, 64) for the BFP16 forms of B and C), and
  * 2 * N * (T_K + 1) < 2^31.
- * Problems of few rows and a long reduction (M <= 64, K > 1024) on the instances (64, 64, 128, 128),
- * (32, 64, 256, 64) and (32, 32, 256, 64), and with b_format BF16_T on any, are run by a kernel of their
- * own that streams B through registers: the factors then only select it, and its sums are added in a
+ * Problems of few rows and a long reduction (K > 1024; M <= 64, or few enough rows and columns for one
+ * small tile per CU) on the instances (64, 64, 128, 128), (32, 64, 256, 64) and (32, 32, 256, 64), and with
+ * b_format BF16_T on any, are run by a kernel of their own that streams B through registers: the factors then only select it, and its sums are added in a
  * different order (several shorter fp32 chains per element instead of one).
  * On success *out is a new plan, else *out = NULL.
  * Environment (read here, both optional): ATB_LOG=1 prints the plan to

@@ -11,9 +11,12 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libatb.so")
 OBJ_DIR = os.path.join(HERE, "_build")
+# accumulators stay in ordinary vector registers: with up to 470 of a wave's 512 in use the compiler otherwise parks other
+# values in the accumulation half and moves the accumulators out and in again around every panel (208 moves to 64 MFMAs)
+SKINNY_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 # (source, object name, extra flags): the GEMM instance table is cut into three groups that compile side by side
 SOURCES = [("atb_gemm.hip", "atb_gemm_g0", ["-DATB_GROUP=0"]), ("atb_gemm.hip", "atb_gemm_g1", ["-DATB_GROUP=1"]),
-           ("atb_gemm.hip", "atb_gemm_g2", ["-DATB_GROUP=2"]), ("atb_skinny.hip", "atb_skinny", []), ("atb_bfp16.hip", "atb_bfp16", []), ("atb_probe.hip", "atb_probe", []),
+           ("atb_gemm.hip", "atb_gemm_g2", ["-DATB_GROUP=2"]), ("atb_skinny.hip", "atb_skinny", SKINNY_FLAGS), ("atb_bfp16.hip", "atb_bfp16", []), ("atb_probe.hip", "atb_probe", []),
            ("atb_model.cpp", "atb_model", []), ("atb_api.cpp", "atb_api", [])]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -1,4 +1,5 @@
-// GEMM for few rows (M <= 64) and a long reduction (K > 1024): a streaming kernel, bound by the bytes of B.
+// GEMM for few rows and a long reduction (K > 1024): a streaming kernel, bound by the bytes of B.  For M <= 64, and above
+// that for problems of at most one 64 x 32 to 128 x 64 tile per CU (tile_of).
 //
 // With one band of 16 to 64 rows of C there is nothing to share a B tile with, so the tile pipeline of atb_gemm.hip (B
 // through LDS, a barrier per K-step, a workgroup per 64 columns) only adds waits.  Here every wave is on its own: the
@@ -74,17 +75,17 @@ struct Panel {
     unsigned be[FMT == kBBfp ? NB : 1];
 };
 
-template <int FMT, int MB, int NB, int W>
+template <int FMT, int MB, int NB, int W, int D>
 struct Skinny {
     const GemmParams &p;
-    int lane, c, q, wave, n0;
+    int lane, c, q, wave, m0, n0;
     static constexpr bool ROWS = (FMT == kBRow || FMT == kBRowOdd);
     static_assert(NB % 2 == 0 && (FMT != kBRowOdd || NB == 2), "column pairs; odd N is written for one pair per lane");
     int a_off[MB], e_off[MB], b_off[ROWS ? 16 : NB], be_off[NB];
     floatx4 acc[MB][NB];
-    Panel<FMT, MB, NB> st;
+    Panel<FMT, MB, NB> st[D];          // D panels of this wave in flight
 
-    ATB_DEV Skinny(const GemmParams &p_, int n0_) : p(p_), n0(n0_)
+    ATB_DEV Skinny(const GemmParams &p_, int m0_, int n0_) : p(p_), m0(m0_), n0(n0_)
     {
         lane = threadIdx.x & 63;
         c = lane & 15;
@@ -93,7 +94,7 @@ struct Skinny {
         // rows >= M and columns >= N repeat a valid one: they only feed elements of C that are never stored
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            const int row = min(16 * i + c, p.M - 1);
+            const int row = min(m0 + 16 * i + c, p.M - 1);
             a_off[i] = row * kPanelK + 16 * q;
             e_off[i] = row * (kPanelK / 8) + 4 * (q >> 1);
         }
@@ -223,10 +224,14 @@ struct Skinny {
 
     ATB_DEV void run()
     {
-        load(st, wave);
-        for (int k = wave; k < p.k_panels; k += W) {
-            multiply(st);
-            load(st, k + W);
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(st[d], wave + d * W);
+        for (int k = wave; k < p.k_panels; k += D * W) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                multiply(st[d]);
+                load(st[d], k + (D + d) * W);
+            }
         }
     }
 
@@ -234,19 +239,20 @@ struct Skinny {
     ATB_DEV int column(int j, int t) const { return ROWS ? NB * (4 * q + t) + j : 16 * j + 4 * q + t; }
 };
 
-template <int FMT, int MB, int NB, int W>
+template <int FMT, int MB, int NB, int W, int D>
 __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
 {
     constexpr int TN = 16 * NB, PITCH = TN + 4;
     __shared__ __attribute__((aligned(16))) float part[W][16][PITCH];
-    // consecutive tiles on one XCD: neighbours share the 128-byte lines of a row of B in that XCD's L2
+    // consecutive tiles on one XCD, rows of tiles first: they share B's columns, and neighbouring columns the 128-byte
+    // lines of a row of B, in that XCD's L2
     const int per_xcd = ((int)gridDim.x + 7) / 8;
     const int tile = (int)(blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8;
     const int cols = p.Cm ? p.n_panels * kPanelK : p.N;          // C in BFP16: the zero tail of the last panel as well
-    const int n0 = tile * TN;
+    const int rows = (p.M + 16 * MB - 1) / (16 * MB), m0 = tile % rows * (16 * MB), n0 = tile / rows * TN;
     if (n0 >= cols) return;                                       // the whole workgroup
     const bool any = n0 < p.N;                                    // else a tile of that tail: nothing to multiply
-    Skinny<FMT, MB, NB, W> sk(p, any ? n0 : 0);
+    Skinny<FMT, MB, NB, W, D> sk(p, m0, any ? n0 : 0);
     if (any) sk.run();
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
@@ -262,7 +268,7 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
             floatx4 sum = *reinterpret_cast<const floatx4 *>(&part[0][rr][cc]);
 #pragma unroll
             for (int w = 1; w < W; ++w) sum += *reinterpret_cast<const floatx4 *>(&part[w][rr][cc]);
-            const int m = 16 * i + rr, n = n0 + cc;
+            const int m = m0 + 16 * i + rr, n = n0 + cc;
             if (p.Cm) {
                 // BFP16 C, as TileKernel::store_c_bfp: a block is this thread's four columns and its neighbour's
                 unsigned e = 0;
@@ -302,12 +308,14 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
     }
 }
 
-template <int FMT, int MB, int NB, int W>
+int columns(const GemmParams &p) { return p.Cm ? p.n_panels * kPanelK : p.N; }
+int64_t tiles(const GemmParams &p, int rows, int cols) { return (int64_t)((p.M + rows - 1) / rows) * ((columns(p) + cols - 1) / cols); }
+
+template <int FMT, int MB, int NB, int W, int D = 1>
 hipError_t launch(const GemmParams &p, hipStream_t stream)
 {
-    const int cols = p.Cm ? p.n_panels * kPanelK : p.N;
-    const int tiles = (cols + 16 * NB - 1) / (16 * NB);
-    hipLaunchKernelGGL((skinny_kernel<FMT, MB, NB, W>), dim3((tiles + 7) / 8 * 8), dim3(W * 64), 0, stream, p);
+    const unsigned n = (unsigned)tiles(p, 16 * MB, 16 * NB);
+    hipLaunchKernelGGL((skinny_kernel<FMT, MB, NB, W, D>), dim3((n + 7) / 8 * 8), dim3(W * 64), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -329,15 +337,38 @@ hipError_t launch_rows(const GemmParams &p, hipStream_t stream)
 // with eight), eight or sixteen where more hands are needed to decode B.
 int column_blocks(int N) { return N <= 32 * 256 ? 2 : N <= 64 * 256 ? 4 : 8; }
 
+// More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
+// none (0) where the tile pipeline is as good or better.  Measured in us, the pipeline before / this kernel now:
+//   B bf16    M 128, N 8192, K 8192: 54.4 / 47.0 (64 x 64)   M 256, 4096, 4096: 22.3 / 19.5 (64 x 64)
+//             M 512, 4096, 14336: 120 / 80 (64 x 128)        M 256, 8192, 8192: 70.3 / 54.9 (64 x 128)
+//             not 64 x 32 (M 256, 2048, 2048: 9.9 / 10.4), nor 64 x 128 below K = 4096 (M 1024, 2048, 2048: 16.3 / 17.5),
+//             nor odd N (M 512, 5001, 4096: 61 / 70)
+//   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
+//             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
+//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64)
+enum { kNone = 0, k64x32, k64x64, k64x128, k128x64 };
+int tile_of(const GemmParams &p, int b_format)
+{
+    constexpr int kCUs = 256;
+    const bool rows_of_b = (b_format == ATB_FMT_BF16);
+    if (rows_of_b && p.N % 2 != 0) return kNone;
+    if (tiles(p, 64, 32) <= kCUs) return rows_of_b ? kNone : k64x32;
+    if (tiles(p, 64, 64) <= kCUs) return k64x64;
+    if (rows_of_b && p.K >= 4096 && tiles(p, 64, 128) <= kCUs) return k64x128;
+    if (b_format == ATB_FMT_BF16_T && tiles(p, 128, 64) <= kCUs) return k128x64;
+    return kNone;
+}
+
 }  // namespace
 
 // Where this kernel takes over from the tile pipeline.  K <= 1024: there every instance adds in the same order and gives
 // the same bits, and the call is bound by its launch either way (M 16, N 8192, K 1088: 8.3 / 5.7 us).  The two
-// exceptions are where the pipeline is the faster one: M 64, N 8192, K 8192 bf16 41.0 / 43.5 us (every workgroup decodes
-// all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
+// exceptions at M <= 64 are where the pipeline is the faster one: M 64, N 8192, K 8192 bf16 41.0 / 43.5 us (every workgroup
+// decodes all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
 bool skinny_applies(const GemmParams &p, int b_format)
 {
-    if (p.M > 64 || p.K <= 1024) return false;
+    if (p.K <= 1024) return false;
+    if (p.M > 64) return tile_of(p, b_format) != kNone;
     if (b_format == ATB_FMT_BF16 && p.N % 2 == 0 && p.N <= 32 * 256) return p.M <= 48;
     if (b_format == ATB_FMT_BFP16 && p.N > 64 * 256) return p.M <= 48;
     return true;
@@ -345,6 +376,13 @@ bool skinny_applies(const GemmParams &p, int b_format)
 
 hipError_t launch_skinny(const GemmParams &p, int b_format, hipStream_t stream)
 {
+    if (p.M > 64) {
+        const int t = tile_of(p, b_format);
+        if (b_format == ATB_FMT_BFP16) return t == k64x32 ? launch<kBBfp, 4, 2, 8>(p, stream) : launch<kBBfp, 4, 4, 8>(p, stream);
+        if (b_format == ATB_FMT_BF16)
+            return t == k64x64 ? launch<kBRow, 4, 4, 8>(p, stream) : launch<kBRow, 4, 8, 4, 2>(p, stream);
+        return t == k64x32 ? launch<kBT, 4, 2, 8>(p, stream) : t == k64x64 ? launch<kBT, 4, 4, 8>(p, stream) : launch<kBT, 8, 4, 4>(p, stream);
+    }
     const int nb = column_blocks(p.N);
     if (b_format == ATB_FMT_BFP16) {
         if (nb == 2) return launch_rows<kBBfp, 2, 16>(p, stream);

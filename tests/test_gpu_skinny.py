@@ -1,4 +1,4 @@
-"""The streaming kernel for few rows (M <= 64, K > 1024) against the oracle: every row-block count, every tile width and
+"""The streaming kernel for few rows (K > 1024; M <= 64, or one tile per CU) against the oracle: every row-block count, every tile width and
 the edges of each, K tails, odd N, every storage format.  Exact (small-integer) inputs must give the oracle's bits,
 since every order of the sums is then exact; random ones the GEMM tolerance (and half a mantissa step of a BFP16 C)."""
 import numpy as np
@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 # (M, N, K): 32, 64 and 128 columns per workgroup; M on both sides of a row block; N below, at and past a tile, odd, and
 # not a multiple of 4; K of one panel past the threshold, with and without a tail
 SHAPES = [(1, 2, 1032), (16, 32, 1088), (17, 33, 1032), (48, 34, 1096), (64, 264, 1024 + 64), (33, 1001, 1160), (64, 8191, 1032),
-          (48, 8194, 1032), (49, 8264, 1032), (64, 16386, 1032), (16, 16448, 1096)]
+          (48, 8194, 1032), (49, 8264, 1032), (64, 16386, 1032), (16, 16448, 1096),
+          # above 64 rows: 64 x 32 and 64 x 64 tiles, then (B row-major / transposed) 64 x 128 / 128 x 64
+          (65, 72, 1032), (130, 2802, 1096), (260, 3400, 4104)]
 
 
 @pytest.mark.parametrize("exact", [True, False])
