@@ -33,6 +33,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef bf16x4 bf16x4_u __attribute__((aligned(2)));     // at any element of a row of C
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
@@ -296,8 +297,8 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) u.v[v] = (__bf16)sum[v];
                 uint16_t *dst = p.C + (int64_t)m * p.N + n;
-                if (p.N % 4 == 0 && n + 4 <= p.N) {
-                    *reinterpret_cast<bf16x4 *>(dst) = u.v;
+                if (n + 4 <= p.N) {
+                    *reinterpret_cast<bf16x4_u *>(dst) = u.v;
                 } else {
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
