@@ -253,7 +253,8 @@ struct BandDeal {
 //   A sub-tile g   : fetched from memory in phase g-PF into register set g % PF, decoded into LDS
 //                    buffer g % 2 during phase g-1, consumed by the microkernel of phase g.
 //   B tile kt      : requested in the first phase of K-step kt-2 straight into LDS buffer kt % 2
-//                    (odd N: into registers, written to LDS in the last phase of K-step kt-2),
+//                    (odd N: into registers, written to LDS in the last phase of K-step kt-2; with LAG
+//                    requested in K-step kt-3 and written in the first phase of kt-2),
 //                    awaited before the last barrier that precedes the last band of K-step kt-1,
 //                    read into the waves' fragment registers during that band (each fragment
 //                    right after its last use), consumed in K-step kt.
@@ -307,6 +308,10 @@ struct TileKernel {
     static constexpr int B_FIRST = (ROLE == 2) ? S::BO : 0;
     static constexpr int BPT = BBFP ? 0 : (ROLE == 0 || ROLE == 3) ? S::B_SLABS : (ROLE == 1) ? S::BO : (ROLE == 2) ? S::B_SLABS - S::BO : 0;   // bf16 B chunks per thread per tile
     static constexpr int BTPT = !BBFP ? 0 : (ROLE == 1 || ROLE == 4) ? 0 : S::BT_SLABS;               // BFP16 B chunks (16 mantissas) per thread per tile
+    // Odd N: a B tile passes through registers.  LAG: it stays there for a K-step (in K-step kt the tile fetched during
+    // kt - 1 is stored, the one after it fetched), so that no store waits for a request of its own K-step.  For the tiles
+    // below 256 x 256: 1500 x 3001 x 2056 50.4 -> 47.0 us; those have no registers to hold it (4000 x 4001 x 4096: 157 -> 192).
+    static constexpr bool LAG = !VEC && S::T_MC * S::T_N < 256 * 256;
     static constexpr int NPAIR_B = BTPT * 8;                                             // B mantissa pairs per thread per tile
     static constexpr int NSTEP_A = NPAIR == 0 ? 0 : SK ? NPAIR / 4 : NPAIR + 2;          // decode items per phase (A sub-tile): pipeline steps, or blocks
     static constexpr int NSTEP_B = NPAIR_B > 0 ? NPAIR_B / S::RHO + 2 : 0;               // ... and for this phase's share of the B tile
@@ -848,7 +853,9 @@ struct TileKernel {
             // dwords that contain it and shift by half a dword where needed.
             const int al = b_off[i] & ~3, sh = (b_off[i] & 2) * 8;
             const intx4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs.b, al, 0, 0);
-            const int hi = __builtin_amdgcn_raw_buffer_load_b32(rs.b, al + 16, 0, 0);
+            // every other row is dword-aligned and needs no fifth dword: its lanes ask outside the buffer, which costs no
+            // memory access (47.0 -> 45.3 us; not on the tiles that are short of registers for the choice)
+            const int hi = __builtin_amdgcn_raw_buffer_load_b32(rs.b, (LAG && sh == 0) ? (int)0x80000000 : al + 16, 0, 0);
             b_raw[i] = intx4{(int)__builtin_amdgcn_alignbit((unsigned)lo.y, (unsigned)lo.x, sh),
                              (int)__builtin_amdgcn_alignbit((unsigned)lo.z, (unsigned)lo.y, sh),
                              (int)__builtin_amdgcn_alignbit((unsigned)lo.w, (unsigned)lo.z, sh),
@@ -1057,7 +1064,7 @@ struct TileKernel {
     template <int s>
     static constexpr int n_side()
     {
-        return RQ + APT + (s == 0 ? BPT + BTPT : 0) + NSTEP_A + NSTEP_B + ((!VEC && s + 1 == S::RHO) ? BPT : 0);
+        return RQ + APT + (s == 0 ? BPT + BTPT : 0) + NSTEP_A + NSTEP_B + ((!VEC && !LAG && s + 1 == S::RHO) ? BPT : 0);
     }
 
     template <int ki, int s, int j>
@@ -1072,6 +1079,7 @@ struct TileKernel {
         if constexpr (j < j0) {
             load_raw_chunk<(g + RAW_LEAD) % S::NR, (s + RAW_LEAD) % S::RHO, j>();
         } else if constexpr (j < j1) {
+            if constexpr (LAG) store_b_chunk<j - j0>((S::NB > 2) ? b_wr[0] + b_fill_off : b_wr[kpar]);
             load_b_chunk<j - j0>(kpar);
         } else if constexpr (j < j2) {
             load_bt_chunk<kpar ^ 1, j - j1>();
@@ -1253,6 +1261,7 @@ struct TileKernel {
         if constexpr (S::AB == 4) store_a_all<1>(a_wr[1]);
         if constexpr (VEC && BPT > 0) wait_vm<0>();
         if constexpr (!VEC && S::NB == 2) store_b_all(b_wr[1]);
+        if constexpr (LAG) load_b(0);                // the tile that K-step 0 stores
         __syncthreads();
         if constexpr (S::NB > 2) b_read_off = 0;
         if constexpr (COMPUTE) read_b_frags_all(0);
