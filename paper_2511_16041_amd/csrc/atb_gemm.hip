@@ -144,7 +144,8 @@ struct Shape {
     static constexpr int LDS_BYTES = AB * A_BYTES + NB * B_BYTES + RAW_RING;
     // B given as BFP16 (B^T, N x K, blocks along K): the tile is staged like A, [n][k] with pitch PA
     static constexpr int BT_BYTES = T_N * PBF;
-    static constexpr int LDS_BYTES_BT = AB * A_BYTES + 2 * BT_BYTES;
+    static constexpr bool EB_BT = (CW == 8 && AB == 2);        // early switch barrier with B in BFP16 (see TileKernel::EB): a third B buffer
+    static constexpr int LDS_BYTES_BT = AB * A_BYTES + (EB_BT ? 3 : 2) * BT_BYTES;
     static constexpr int BT_SLABS = T_N * T_K / 16 / NTS;      // 16-mantissa chunks of the tile per staging thread
     // staging work per thread: A in chunks of ACE mantissas (ACE/8 BFP16 blocks), B in chunks of 8 bf16
     static constexpr int ACE = (T_MA * T_K / NTS >= 16) ? 16 : 8;
@@ -328,6 +329,23 @@ struct TileKernel {
     static constexpr int PBT = S::T_K * 2;                                                // LDS pitch of a B^T tile row
     typedef BandDeal<S, ROLE, VEC, BBFP> D;
     static constexpr bool SKEWED = D::SKEWED;
+    // EB: the switch barrier comes ahead of the phase's end.  The MFMAs after it (tail) need nothing that it publishes, so
+    // the first A fragments of the next sub-tile, and the B fragments of the next K-step, are read under them instead of
+    // after a barrier at which all waves wait.  B fragments are then still being read when other waves begin to decode the
+    // next tile, which therefore goes to a third buffer: tile kt is decoded during K-step kt-2 into buffer kt % 3, last read
+    // in K-step kt-4 and behind two barriers by then.  A is as before: a sub-tile's last fragments are read before the last
+    // band of its phase, ahead of the barrier, and its buffer is written from the next phase on.
+    // For the 8-wave tiles with B in BFP16 (both wave groups decode, the most even phases).  Measured (us, barrier last /
+    // early): 2048 x 4096 x 14336 at 64,128,64,256 268.9 / 261.4; 8192^3 at 256 x 256 935 / 918; 2048 x 14336 x 4096, C in
+    // BFP16 too, 226.1 / 222.6.  With bf16 B it is level (8192^3, rho = 2: 845 / 849, symmetric 840 / 849; 64,128,64,256: 1018
+    // / 1008) and stays out.  Smaller tiles have no room for the buffer.
+    static constexpr bool EB = BBFP && S::EB_BT;
+    static constexpr bool RING = BBFP ? EB : S::NB > 2;                                   // B buffers indexed at run time
+    static constexpr int NBUF = BBFP ? (EB ? 3 : 2) : S::NB;
+    static constexpr int BAND = S::HB * S::KS * S::NC;                                    // MFMAs of a band
+    // MFMAs of phase s after its barrier: with one sub-tile per K-step its last band (in which the B fragments change), with
+    // several a quarter of every phase.
+    static constexpr int tail(int s) { return !EB ? 0 : (S::RHO == 1 && D::per(s) > 1) ? BAND : (D::per(s) * BAND) / 4; }
     static constexpr int MTW = D::first_local(S::RHO);                                    // accumulator bands of this wave
     static constexpr int per(int s) { return D::per(s); }
     static constexpr int first_local(int s) { return D::first_local(s); }
@@ -357,7 +375,8 @@ struct TileKernel {
     // change: the K-step advance is applied to the (scalar) buffer descriptors instead, base up and
     // size down, so the hardware range check keeps masking panels past the last of A and rows >= K of B, and no
     // vector register that a memory instruction has just read is written right after it.
-    int a_moff[S::RHO][APTN], a_eoff[S::RHO][APTN], b_off[BPTN];
+    // One per operand for A and B^T in BFP16: a thread's chunks are constant distances apart (chunk_m, chunk_e).
+    int a_moff, a_eoff, b_off[BPTN];
     // ADMA, ROLE 2: byte offsets of this lane's raw requests (mantissas: request e of sub-tile sub; exponents) in the
     // planes, relative to the K-step the A descriptors point at; LDS address of this wave's first mantissa request
     // and of its exponent request in raw buffer 0.  ROLE 1: where this thread reads its first chunk and its exponent
@@ -377,7 +396,7 @@ struct TileKernel {
     const char *bt_rd[2];
     const char *bt_rdk[S::KS];         // ASWZ: fragment read address per k-slice, in B^T buffer 0, column block 0
     int bt_d1;                         // ASWZ: +16 or -16, where the second piece of this thread's chunk of the B^T tile sits (bt_wr points at the first)
-    int bt_moff[BTPTN], bt_eoff[BTPTN];
+    int bt_moff, bt_eoff;
     const int8_t *bm_ptr;
     const uint8_t *be_ptr;
     int bm_left, be_left, eb_shift;
@@ -497,29 +516,21 @@ struct TileKernel {
                     bt_rdk[ks] = lds + S::AB * S::A_BYTES + n * S::PBF + ((((S::KM / 8) * ks + lane / S::MB) ^ (n & 7)) * 16);
             }
             // rows >= N of B^T lie beyond the end of the planes and read as zero
-#pragma unroll
-            for (int i = 0; i < BTPT; ++i) {
-                const int grow = b_row + i * (NTS / CPR);
-                const int pnl = (b_q * 16) / kPanelK, kin = (b_q * 16) % kPanelK;
-                bt_moff[i] = (pnl * p.N + grow) * kPanelK + kin;
-                bt_eoff[i] = (pnl * p.N + grow) * (kPanelK / 8) + ((kin / 8) & ~3);
-            }
+            const int pnl = (b_q * 16) / kPanelK, kin = (b_q * 16) % kPanelK;
+            bt_moff = (pnl * p.N + b_row) * kPanelK + kin;
+            bt_eoff = (pnl * p.N + b_row) * (kPanelK / 8) + ((kin / 8) & ~3);
         }
         // Offsets of sub-tile 0 / K-step 0 in the K-panel-major planes: the chunks of a sub-tile follow
         // each other in memory in the order of the staging threads, so a wave's request is one
         // contiguous KiB.  Rows >= M run into the next panel's rows (or past the end of the plane, which
         // reads as zero): they only feed rows of C that are never stored.  The tail of the last panel
         // (k >= K) is zero by the layout's contract, panels past the last read as zero.
-#pragma unroll
-        for (int sub = 0; sub < S::RHO; ++sub)
-#pragma unroll
-            for (int i = 0; i < APT; ++i) {
-                const int grow = sub * S::T_MA + a_row + (PAIRK ? 0 : (A_FIRST + i) * (NTS / A_CPR));
-                const int cq = PAIRK ? a_q + i : a_q;                  // chunk index within the row
-                const int pnl = (cq * ACE) / kPanelK, kin = (cq * ACE) % kPanelK;
-                a_moff[sub][i] = (pnl * p.M + grow) * kPanelK + kin;
-                a_eoff[sub][i] = (pnl * p.M + grow) * (kPanelK / 8) + ((kin / 8) & ~3);
-            }
+        {
+            const int grow = a_row + (PAIRK ? 0 : A_FIRST * (NTS / A_CPR));
+            const int pnl = (a_q * ACE) / kPanelK, kin = (a_q * ACE) % kPanelK;
+            a_moff = (pnl * p.M + grow) * kPanelK + kin;
+            a_eoff = (pnl * p.M + grow) * (kPanelK / 8) + ((kin / 8) & ~3);
+        }
         // B rows >= K lie beyond the end of B and read as zero; columns >= N wrap into the next row
         // and only feed output columns that are never stored.
 #pragma unroll
@@ -597,13 +608,8 @@ struct TileKernel {
         if (tile_at(t, tm0, tn0)) {
             const int d = tm0 - a_m0;
             a_m0 = tm0;
-#pragma unroll
-            for (int sub = 0; sub < S::RHO; ++sub)
-#pragma unroll
-                for (int i = 0; i < APT; ++i) {
-                    a_moff[sub][i] += d * kPanelK;
-                    a_eoff[sub][i] += d * (kPanelK / 8);
-                }
+            a_moff += d * kPanelK;
+            a_eoff += d * (kPanelK / 8);
             if constexpr (RQ > 0) {
 #pragma unroll
                 for (int sub = 0; sub < S::RHO; ++sub) {
@@ -635,11 +641,8 @@ struct TileKernel {
             be_ptr = p.Be;
             bm_left = live ? p.k_panels * p.N * kPanelK : 0;
             be_left = live ? p.k_panels * p.N * (kPanelK / 8) : 0;
-#pragma unroll
-            for (int i = 0; i < BTPT; ++i) {
-                bt_moff[i] += d * kPanelK;
-                bt_eoff[i] += d * (kPanelK / 8);
-            }
+            bt_moff += d * kPanelK;
+            bt_eoff += d * (kPanelK / 8);
         } else if constexpr (BTR) {
             // the tile's first row goes into the base, not into the offsets: rows are K elements apart, and 32-bit
             // offsets from the start of B^T would not reach the far end of a large operand
@@ -757,8 +760,8 @@ struct TileKernel {
     template <int set, int i>
     ATB_DEV void load_bt_chunk()
     {
-        bt_mant[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rs.bm, bt_moff[i], 0, 0);
-        bt_expo[set][i] = __builtin_amdgcn_raw_buffer_load_b32(rs.be, bt_eoff[i], 0, 0);
+        bt_mant[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rs.bm, plus<i * (NTS / (S::T_K / 16)) * kPanelK>(bt_moff), 0, 0);
+        bt_expo[set][i] = __builtin_amdgcn_raw_buffer_load_b32(rs.be, plus<i * (NTS / (S::T_K / 16)) * (kPanelK / 8)>(bt_eoff), 0, 0);
         if constexpr (i == BTPT - 1) {
             if (--b_steps == 0) {
                 open_b(b_t + t_stride);
@@ -781,6 +784,26 @@ struct TileKernel {
         }
     }
 
+    // Byte distance of chunk i of sub-tile sub from the thread's first one, in the mantissa and the exponent plane.
+    static constexpr int chunk_m(int sub, int i) { return (sub * S::T_MA + (PAIRK ? 0 : i * (NTS / A_CPR))) * kPanelK + (PAIRK ? i * ACE : 0); }
+    static constexpr int chunk_e(int sub, int i) { return (sub * S::T_MA + (PAIRK ? 0 : i * (NTS / A_CPR))) * (kPanelK / 8); }
+
+    // x + c for an offset in a request.  Up to 4095 goes into the instruction; above, the 256 x 256 tiles make the sum where
+    // it is used: hoisted out of the K loop, as the compiler would, it holds a register per chunk for the whole kernel (six
+    // of the symmetric tile's 256, which made the BFP16 forms of B spill).
+    template <int c>
+    static ATB_DEV int plus(int x)
+    {
+#if defined(__HIP_DEVICE_COMPILE__)
+        if constexpr (c >= 4096 && S::T_MC * S::T_N >= 256 * 256) {
+            int r;
+            asm volatile("v_add_u32 %0, %2, %1" : "=v"(r) : "v"(x), "s"(c));
+            return r;
+        }
+#endif
+        return x + c;
+    }
+
     // Chunk i of sub-tile `sub` of the K-step the A descriptors point at, into register set `set`.
     // After the last chunk of the last sub-tile the descriptors move on to the next K-step.
     // ADMA (ROLE 1): the chunk comes from raw buffer `slot` in LDS instead; the request stream is the other group's.
@@ -793,14 +816,14 @@ struct TileKernel {
             return;
         }
         if constexpr (ACE == 16) {
-            a_mant[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rs.am, a_moff[sub][i], 0, 0);
+            a_mant[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rs.am, plus<chunk_m(sub, i)>(a_moff), 0, 0);
         } else {
-            intx2 t = __builtin_amdgcn_raw_buffer_load_b64(rs.am, a_moff[sub][i], 0, 0);
+            intx2 t = __builtin_amdgcn_raw_buffer_load_b64(rs.am, plus<chunk_m(sub, i)>(a_moff), 0, 0);
             a_mant[set][i] = intx4{t.x, t.y, 0, 0};
         }
         // the aligned dword that holds this chunk's exponent byte(s): sub-dword loads are far slower
         if constexpr (!PAIRK || i == 0)
-            a_expo[set][i] = __builtin_amdgcn_raw_buffer_load_b32(rs.ae, a_eoff[sub][i], 0, 0);
+            a_expo[set][i] = __builtin_amdgcn_raw_buffer_load_b32(rs.ae, plus<chunk_e(sub, i)>(a_eoff), 0, 0);
         if constexpr (sub == S::RHO - 1 && i == APT - 1) advance_a();
     }
 
@@ -824,7 +847,7 @@ struct TileKernel {
         if constexpr (VEC) {
 #if defined(__HIP_DEVICE_COMPILE__)
             typedef __attribute__((address_space(3))) void lds_void;
-            char *dst = (S::NB > 2) ? b_req[0] + b_fill_off : b_req[buf];
+            char *dst = RING ? b_req[0] + b_fill_off : b_req[buf];
             if constexpr (ASM_DMA) {
                 // Issued by hand so that the compiler does not know of it: it cannot tell the buffer being
                 // filled from the one being read and puts a vmcnt(0) in front of every transposing fragment
@@ -1009,14 +1032,14 @@ struct TileKernel {
     {
         if constexpr (BBFP) {
             if constexpr (S::ASWZ)
-                bfrag[ks][nt] = *reinterpret_cast<const bf16x8 *>(bt_rdk[ks] + buf * B_BYTES + nt * S::MB * S::PBF);
+                bfrag[ks][nt] = *reinterpret_cast<const bf16x8 *>(bt_rdk[ks] + (RING ? b_read_off : buf * B_BYTES) + nt * S::MB * S::PBF);
             else
-                bfrag[ks][nt] = *reinterpret_cast<const bf16x8 *>(bt_rd[buf] + nt * S::MB * S::PBF + ks * S::KM * 2);
+                bfrag[ks][nt] = *reinterpret_cast<const bf16x8 *>((RING ? bt_rd[0] + b_read_off : bt_rd[buf]) + nt * S::MB * S::PBF + ks * S::KM * 2);
         } else if constexpr (BTR) {
-            const char *base = (S::NB > 2) ? b_rd[0][ks] + b_read_off : b_rd[buf][ks];
+            const char *base = RING ? b_rd[0][ks] + b_read_off : b_rd[buf][ks];
             bfrag[ks][nt] = *reinterpret_cast<const bf16x8 *>(base + nt * S::MB * PBT);
         } else {
-            const char *base = (S::NB > 2) ? b_rd[0][nt % S::NBASE] + b_read_off : b_rd[buf][nt % S::NBASE];
+            const char *base = RING ? b_rd[0][nt % S::NBASE] + b_read_off : b_rd[buf][nt % S::NBASE];
             const char *src = base + ks * S::KM * S::PB + (nt / S::NBASE) * (S::NBASE * 64);
             typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
             union { shortx4 s[2]; bf16x8 b; } u;
@@ -1079,7 +1102,7 @@ struct TileKernel {
         if constexpr (j < j0) {
             load_raw_chunk<(g + RAW_LEAD) % S::NR, (s + RAW_LEAD) % S::RHO, j>();
         } else if constexpr (j < j1) {
-            if constexpr (LAG) store_b_chunk<j - j0>((S::NB > 2) ? b_wr[0] + b_fill_off : b_wr[kpar]);
+            if constexpr (LAG) store_b_chunk<j - j0>(RING ? b_wr[0] + b_fill_off : b_wr[kpar]);
             load_b_chunk<j - j0>(kpar);
         } else if constexpr (j < j2) {
             load_bt_chunk<kpar ^ 1, j - j1>();
@@ -1091,9 +1114,9 @@ struct TileKernel {
             else
                 decode_step<false, (g + S::DA) % S::PF, 0, NPAIR, j - j3>(a_wr[(g + S::DA) % S::AB]);
         } else if constexpr (j < j5) {
-            decode_step<true, kpar, s * n_dt, n_dt, j - j4>(bt_wr[kpar]);
+            decode_step<true, kpar, s * n_dt, n_dt, j - j4>(RING ? bt_wr[0] + b_fill_off : bt_wr[kpar]);
         } else {
-            store_b_chunk<j - j5>((S::NB > 2) ? b_wr[0] + b_fill_off : b_wr[kpar]);
+            store_b_chunk<j - j5>(RING ? b_wr[0] + b_fill_off : b_wr[kpar]);
         }
     }
 
@@ -1114,40 +1137,73 @@ struct TileKernel {
     static constexpr int MG = ATB_MFMA_GROUP;
     static_assert(S::NC % MG == 0 && (!S::KIN || S::KS % MG == 0), "a slot's MFMAs share one A fragment or one accumulator block");
 
+    // Which MFMA slot mm of phase s is.  EB: in the band that the next K-step's B fragments replace this one's, the column
+    // blocks come one after the other, so that a fragment is free after its 1 / NC of the band and the reads spread over it.
+    template <int s, int mm>
+    struct Slot {
+        static constexpr int il = mm / BAND, f = mm % BAND;
+        static constexpr bool LAST = EB && s + 1 == S::RHO && il + 1 == D::per(s);
+        static constexpr int ks = LAST ? (S::KIN ? f % S::KS : (f / S::HB) % S::KS) : S::KIN ? f % S::KS : (f / (S::HB * S::NC)) % S::KS;
+        static constexpr int h = LAST ? (S::KIN ? (f / S::KS) % S::HB : f % S::HB) : S::KIN ? (f / (S::KS * S::NC)) % S::HB : (f / S::NC) % S::HB;
+        static constexpr int nt = LAST ? f / (S::HB * S::KS) : S::KIN ? (f / S::KS) % S::NC : f % S::NC;
+    };
+
     template <int ki, int s, int mm>
     ATB_DEV void slot_mfma()
     {
-        constexpr int il = mm / (S::HB * S::KS * S::NC), ks = S::KIN ? mm % S::KS : (mm / (S::HB * S::NC)) % S::KS,
-                      h = S::KIN ? (mm / (S::KS * S::NC)) % S::HB : (mm / S::NC) % S::HB, nt = S::KIN ? (mm / S::KS) % S::NC : mm % S::NC;
-        constexpr int local = first_local(s) + il;            // accumulator band of this wave
-        constexpr int par = (bands_before(ki * S::RHO + s) + il) % 2;       // which half of afrag this band uses
+        typedef Slot<s, mm> L;
+        constexpr int local = first_local(s) + L::il;            // accumulator band of this wave
+        constexpr int par = (bands_before(ki * S::RHO + s) + L::il) % 2;       // which half of afrag this band uses
         if constexpr (S::MB == 16)
-            acc[local][h][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfrag[ks][nt], afrag[par][h][ks], acc[local][h][nt], 0, 0, 0);
+            acc[local][L::h][L::nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfrag[L::ks][L::nt], afrag[par][L::h][L::ks], acc[local][L::h][L::nt], 0, 0, 0);
         else
-            acc[local][h][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag[ks][nt], afrag[par][h][ks], acc[local][h][nt], 0, 0, 0);
+            acc[local][L::h][L::nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag[L::ks][L::nt], afrag[par][L::h][L::ks], acc[local][L::h][L::nt], 0, 0, 0);
+    }
+
+    // A fragments [f, fend) of a band (in the order of their first use) from A buffer buf
+    template <int par, int bd, int f, int fend>
+    ATB_DEV void read_a_frags(int buf)
+    {
+        if constexpr (f < fend) {
+            read_a_frag<par, bd, S::KIN ? f / S::KS : f % S::HB, S::KIN ? f % S::KS : f / S::HB>(buf);
+            read_a_frags<par, bd, f + 1, fend>(buf);
+        }
     }
 
     template <int ki, int s, int mm>
     ATB_DEV void slot_reads()
     {
-        constexpr int il = mm / (S::HB * S::KS * S::NC), ks = S::KIN ? mm % S::KS : (mm / (S::HB * S::NC)) % S::KS,
-                      h = S::KIN ? (mm / (S::KS * S::NC)) % S::HB : (mm / S::NC) % S::HB, nt = S::KIN ? (mm / S::KS) % S::NC : mm % S::NC;
+        typedef Slot<s, mm> L;
+        constexpr int il = L::il, ks = L::ks, h = L::h, nt = L::nt, NA = S::HB * S::KS;
         constexpr int g = ki * S::RHO + s;
         constexpr int par = (bands_before(g) + il) % 2;
-        if constexpr (nt == S::NC - 1) {
-            if constexpr (il + 1 < per(s))
-                read_a_frag<par ^ 1, band(s, il + 1), h, ks>(g % S::AB);
-            else if constexpr (S::AB == 4)      // first band of the next sub-tile, already complete in LDS
-                read_a_frag<par ^ 1, band((s + 1) % S::RHO, 0), h, ks>((g + 1) % S::AB);
+        if constexpr (EB) {
+            // the fragments of the next band, or of the next sub-tile's first, in the first half of the band / of the tail
+            constexpr int T = tail(s), t = mm - (nm(s) - T);
+            if constexpr (il + 1 < per(s)) {
+                constexpr int H = BAND / 2, f0 = L::f * NA / H, f1 = (L::f + 1) * NA / H;
+                read_a_frags<par ^ 1, band(s, il + 1), (f0 < NA ? f0 : NA), (f1 < NA ? f1 : NA)>(g % S::AB);
+            } else if constexpr (t >= 0) {
+                constexpr int H = T / 2, f0 = t * NA / H, f1 = (t + 1) * NA / H;
+                read_a_frags<par ^ 1, band((s + 1) % S::RHO, 0), (f0 < NA ? f0 : NA), (f1 < NA ? f1 : NA)>((g + 1) % S::AB);
+            }
+            if constexpr (L::LAST && h == S::HB - 1) read_b_frag<ks, nt>((ki & 1) ^ 1);
+        } else {
+            if constexpr (nt == S::NC - 1) {
+                if constexpr (il + 1 < per(s))
+                    read_a_frag<par ^ 1, band(s, il + 1), h, ks>(g % S::AB);
+                else if constexpr (S::AB == 4)      // first band of the next sub-tile, already complete in LDS
+                    read_a_frag<par ^ 1, band((s + 1) % S::RHO, 0), h, ks>((g + 1) % S::AB);
+            }
+            if constexpr (s + 1 == S::RHO && il + 1 == per(s) && h == S::HB - 1) read_b_frag<ks, nt>((ki & 1) ^ 1);
         }
-        if constexpr (s + 1 == S::RHO && il + 1 == per(s) && h == S::HB - 1) read_b_frag<ks, nt>((ki & 1) ^ 1);
     }
 
-    template <int ki, int s, int m>
+    template <int ki, int s, int m, int mend>
     ATB_DEV void slots()
     {
-        constexpr int nslot = nm(s) / MG;
-        if constexpr (m < nslot) {
+        constexpr int nslot = (nm(s) - tail(s)) / MG;         // slots that carry side work
+        if constexpr (m < mend) {
             constexpr int nside = n_side<s>();
             if constexpr (COMPUTE) {
                 slot_mfma<ki, s, m * MG>();
@@ -1167,7 +1223,7 @@ struct TileKernel {
                 if constexpr (MG >= 4) { slot_reads<ki, s, m * MG + 2>(); slot_reads<ki, s, m * MG + 3>(); }
             }
             ATB_FENCE();
-            slots<ki, s, m + 1>();
+            slots<ki, s, m + 1, mend>();
         }
     }
 
@@ -1177,9 +1233,9 @@ struct TileKernel {
     {
         if constexpr (s < S::RHO) {
             constexpr int g = ki * S::RHO + s;
-            if constexpr (S::AB == 2 && COMPUTE) read_first_band<bands_before(g) % 2, s>(g % 2);
+            if constexpr (S::AB == 2 && !EB && COMPUTE) read_first_band<bands_before(g) % 2, s>(g % 2);
             ATB_FENCE();
-            slots<ki, s, 0>();
+            slots<ki, s, 0, (nm(s) - tail(s)) / MG>();
             // The B tile requested (straight into LDS) in the first phase of a K-step is read in the
             // last band of the next K-step, so the last barrier before that band has to publish it.
             // With NB buffers the tile read in K-step kt + 1 was requested at the start of K-step kt + 2 - NB.
@@ -1194,6 +1250,7 @@ struct TileKernel {
             else if constexpr (VEC && BPT > 0 && S::RHO >= 2 && s == S::RHO - 2)
                 wait_vm<vm_cap((S::NB * S::RHO - 1) * A_VMEM + (S::NB - 1) * BPT)>();
             switch_barrier();   // the "kernel switch" of the ATB nest
+            if constexpr (COMPUTE) slots<ki, s, (nm(s) - tail(s)) / MG, nm(s) / MG>();
             phases<ki, s + 1>();
         }
     }
@@ -1203,8 +1260,8 @@ struct TileKernel {
     // NB > 2: the ring moves on by one buffer per K-step
     ATB_DEV void advance_b_ring()
     {
-        b_fill_off = (b_fill_off + B_BYTES == S::NB * B_BYTES) ? 0 : b_fill_off + B_BYTES;
-        b_read_off = (b_read_off + B_BYTES == S::NB * B_BYTES) ? 0 : b_read_off + B_BYTES;
+        b_fill_off = (b_fill_off + B_BYTES == NBUF * B_BYTES) ? 0 : b_fill_off + B_BYTES;
+        b_read_off = (b_read_off + B_BYTES == NBUF * B_BYTES) ? 0 : b_read_off + B_BYTES;
     }
 
     template <int ki>
@@ -1212,7 +1269,7 @@ struct TileKernel {
     {
         if constexpr (ki < S::KU) {
             phases<ki, 0>();
-            if constexpr (S::NB > 2) advance_b_ring();
+            if constexpr (RING) advance_b_ring();
             ksteps<ki + 1>();
         }
     }
@@ -1230,7 +1287,7 @@ struct TileKernel {
     {
         // prologue: the first NB B tiles into LDS, the first PF A sub-tiles into registers, sub-tile 0
         // into LDS, B tile 0 into fragment registers
-        if constexpr (S::NB > 2) b_fill_off = 0;
+        if constexpr (RING) b_fill_off = 0;
         if constexpr (ADMA_ON) {
             // the first RAW_LEAD raw sub-tiles into the ring, landed and published before the decoding group reads them
             if constexpr (RQ > 0) load_raw_first();
@@ -1241,7 +1298,7 @@ struct TileKernel {
         if constexpr (BBFP) { load_bt<0>(); load_bt<1>(); }
         prologue_loads();
         if constexpr (!VEC) store_b_all(b_wr[0]);
-        if constexpr (S::NB > 2) {
+        if constexpr (RING && !BBFP) {
 #pragma unroll
             for (int t = 1; t < S::NB; ++t) {
                 b_fill_off = t * B_BYTES;
@@ -1260,19 +1317,19 @@ struct TileKernel {
         store_a_all<0>(a_wr[0]);
         if constexpr (S::AB == 4) store_a_all<1>(a_wr[1]);
         if constexpr (VEC && BPT > 0) wait_vm<0>();
-        if constexpr (!VEC && S::NB == 2) store_b_all(b_wr[1]);
+        if constexpr (!VEC && !RING) store_b_all(b_wr[1]);
         if constexpr (LAG) load_b(0);                // the tile that K-step 0 stores
         __syncthreads();
-        if constexpr (S::NB > 2) b_read_off = 0;
+        if constexpr (RING) b_read_off = 0;
         if constexpr (COMPUTE) read_b_frags_all(0);
-        if constexpr (S::NB > 2) {
-            // K-step 0 refills buffer 0 and reads the fragments of K-step 1 from buffer 1
-            b_fill_off = 0;
+        if constexpr (RING) {
+            // K-step 0 refills buffer 0 (EB: decodes tile 2 into buffer 2) and reads the fragments of K-step 1 from buffer 1
+            b_fill_off = EB ? 2 * B_BYTES : 0;
             b_read_off = B_BYTES;
         }
         // B buffer 0 is refilled from the first phase on: every wave must have its fragments first
         switch_barrier();
-        if constexpr (S::AB == 4 && COMPUTE) read_first_band<0, 0>(0);
+        if constexpr ((S::AB == 4 || EB) && COMPUTE) read_first_band<0, 0>(0);
 
         // The number of K-steps is rounded up to a whole loop body: the extra steps multiply by B rows
         // >= K, which read as zero.  The last K-steps of a tile already request, decode and stage the
