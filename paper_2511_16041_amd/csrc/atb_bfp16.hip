@@ -18,26 +18,31 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ unsigned exp_field(float x) { return (__float_as_uint(x) >> 23) & 0xFFu; }
 
-// Quantiser.  A wave covers 16 rows x 128 k (two panels of the K-panel-major output); the 4 waves of a
+// Quantiser.  A wave covers 2 STEPS rows x 128 k (two panels of the K-panel-major output); the 4 waves of a
 // workgroup sit side by side along k.  In step v lanes 0-31 take row 2v and lanes 32-63 row 2v + 1, four
 // consecutive k each, so a load instruction reads two contiguous runs of 512 B and the mantissa store of the
 // same step writes, per panel, the 2 x 64 B of the row pair, which are one 128-byte line of the output.  A
-// BFP16 block is the 8 values of two neighbouring lanes, which exchange their exponent maxima.  The 16 x 16
-// exponent bytes of the wave are collected in LDS and leave as two contiguous runs of 128 B.  Chunks beyond K
+// BFP16 block is the 8 values of two neighbouring lanes, which exchange their exponent maxima.  The
+// exponent bytes of the wave, 16 per row, are collected in LDS and leave as two contiguous runs.  Chunks beyond K
 // (the tail of the last panel) are written as zero.
+// STEPS: a wave holds few loads, so waves are what fills the chip; more rows per wave only save workgroups.  Measured, cold
+// inputs, STEPS = 2 / 4 / 8 (us): 512 x 4096 4.1 / 5.0 / 7.4, 1024 x 4096 5.3 / 5.9 / 8.3, 2048 x 4096 9.0 / 8.4 / 9.8, 8192 x 8192
+// 53.7 / 53.4 / 57.4 (6.4 TB/s).
+template <int STEPS>
 __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__ A, int64_t lda,
                                                        int8_t *__restrict__ Am, uint8_t *__restrict__ Ae,
                                                        int64_t M, int64_t K, int64_t panels, int64_t kblocks)
 {
-    __shared__ __attribute__((aligned(8))) uint8_t exps[4][2][16][8];
+    constexpr int ROWS = 2 * STEPS;
+    __shared__ __attribute__((aligned(8))) uint8_t exps[4][2][ROWS][8];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, q = lane & 31;
-    const int64_t r0 = ((int64_t)blockIdx.x / kblocks) * 16;
+    const int64_t r0 = ((int64_t)blockIdx.x / kblocks) * ROWS;
     const int64_t kg = ((int64_t)blockIdx.x % kblocks) * 4 + wave;       // group of 128 k
     const int64_t k = kg * 128 + 4 * q;
     const int64_t panel = kg * 2 + (q >> 4);
     const int kin = 4 * (q & 15);
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
+    for (int v = 0; v < STEPS; ++v) {
         const int64_t row = r0 + 2 * v + half;
         // the input is read once: non-temporal loads (+12 % whether or not the input was in a cache before the
         // launch); the output keeps ordinary stores, its reader comes next
@@ -58,8 +63,8 @@ __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__
         if ((q & 1) == 0) exps[wave][q >> 4][2 * v + half][(q & 15) >> 1] = (uint8_t)e;
     }
     __syncthreads();
-    if (lane < 32) {
-        const int pl = lane >> 4, rl = lane & 15;
+    if (lane < 2 * ROWS) {
+        const int pl = lane / ROWS, rl = lane % ROWS;
         const int64_t row = r0 + rl, pn = kg * 2 + pl;
         if (row < M && pn < panels)
             *reinterpret_cast<uint2 *>(Ae + (pn * M + row) * (kPanelK / 8)) = *reinterpret_cast<const uint2 *>(&exps[wave][pl][rl][0]);
@@ -116,9 +121,13 @@ hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae,
 {
     const int64_t panels = (K + kPanelK - 1) / kPanelK;
     if (M == 0 || panels == 0) return hipSuccess;
-    const int64_t kblocks = (panels + 7) / 8;            // a workgroup covers 16 rows x 512 k = 8 panels
-    const int64_t blocks = ((M + 15) / 16) * kblocks;
-    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, kblocks);
+    const int64_t kblocks = (panels + 7) / 8;            // a workgroup covers 2 STEPS rows x 512 k = 8 panels
+    // workgroups of 8 rows, or of 4 while those are no more than 12 per CU
+    const int64_t small = ((M + 3) / 4) * kblocks;
+    if (small <= 12 * 256)
+        hipLaunchKernelGGL(quantize_kernel<2>, dim3((unsigned)small), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, kblocks);
+    else
+        hipLaunchKernelGGL(quantize_kernel<4>, dim3((unsigned)(((M + 7) / 8) * kblocks)), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, kblocks);
     return hipGetLastError();
 }
 

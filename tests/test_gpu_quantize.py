@@ -74,6 +74,16 @@ def test_decode_exact():
     assert np.array_equal(got, oracle.decode(mant, expo))
 
 
+@pytest.mark.parametrize("M,K", [(3, 520), (4, 512), (6, 1032), (6150, 2056), (6145, 2048)])
+def test_quantizer_rows_per_workgroup(M, K):
+    """Workgroups of 4 rows (small problems) and of 8 (above 3072 of the small ones), with whole and partial last ones."""
+    print(f"quantize {(M, K)}", flush=True)
+    A, _ = workloads.make_inputs(workloads.CONFIGS["ragged"], M=M, N=8, K=K)
+    mant, expo = oracle.quantize(A)
+    _, (gm, ge, pad) = _quantize_gpu(A)
+    assert np.array_equal(ge, expo) and np.array_equal(gm, mant) and not pad.any()
+
+
 @pytest.mark.parametrize("M,K", [(1, 8), (15, 64), (17, 264), (33, 320), (4101, 4160), (4101, 4168)])
 def test_decode_shapes(M, K):
     """Edges of the decoder's 16 rows x 4 panels, tails of the last panel, and outputs above 32 MiB with whole and with
