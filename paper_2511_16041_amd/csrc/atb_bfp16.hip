@@ -6,9 +6,9 @@
 //       for normal x; fp32 subnormals and zeros contribute 0),
 //   m = clamp(round_to_nearest_even(x * 2^(133 - E)), -127, 127),
 //   value = m * 2^(E - 133).
-// Both kernels are HBM-bound streaming kernels.  The BFP16
+// All kernels here are HBM-bound streaming kernels.  The BFP16
 // buffer is K-panel-major (see include/atb.h): [panel of 64 k][row][64] mantissas, [panel][row][8] exponents.
-#include "atb_internal.h"
+#include "atb_route.h"
 
 namespace atb {
 namespace {
@@ -71,18 +71,45 @@ __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__
     }
 }
 
-// Decoder.  Bound: HBM, 1.125 B read and 2 B written per element.  A lane takes one block: eight lanes a row of a panel,
-// so that a wave's requests are 8 rows of one panel (512 + 64 contiguous bytes) and each of its stores whole 128-byte
-// lines of the output, 8 rows x 64 k.  A wave does two such groups of rows, the workgroup's waves neighbouring panels.
+// 8 mantissas times 2^shift, as bf16 (exact)
+__device__ __forceinline__ bf16x8 decode8(int2 w, int shift)
+{
+    bf16x8 r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        r[t] = (__bf16)ldexpf((float)(int)(signed char)(w.x >> (8 * t)), shift);
+        r[4 + t] = (__bf16)ldexpf((float)(int)(signed char)(w.y >> (8 * t)), shift);
+    }
+    return r;
+}
+
+// Decoders.  Bound: HBM, 1.125 B read and 2 B written per element; a small one is its launch (2.1 us).  decode_route says
+// which of the two takes a problem.
+// A lane takes a block in row order: every store of a wave is contiguous, its requests are pieces of 64 bytes of each panel.
+__global__ void __launch_bounds__(256) decode_lanes(const int8_t *__restrict__ Am, const uint8_t *__restrict__ Ae,
+                                                    uint16_t *__restrict__ out, int64_t M, int64_t K)
+{
+    const unsigned blocks_per_row = (unsigned)(K / 8), n = (unsigned)M * blocks_per_row;      // fewer than 2^32: one launch
+    const unsigned c = blockIdx.x * 256u + threadIdx.x;
+    if (c >= n) return;
+    const unsigned row = c / blocks_per_row, kb = c % blocks_per_row;
+    const int64_t rec = (int64_t)(kb / 8) * M + row;                                          // (panel, row)
+    const int2 w = *reinterpret_cast<const int2 *>(Am + rec * kPanelK + (kb % 8) * 8);
+    const int shift = (int)Ae[rec * (kPanelK / 8) + kb % 8] - 133;
+    *reinterpret_cast<bf16x8 *>(out + (int64_t)row * K + (int64_t)kb * 8) = decode8(w, shift);  // K % 8 == 0: 16-byte aligned as `out` is
+}
+
+// A wave takes 8 rows of a panel: a lane one block, eight lanes a row, so that its requests are contiguous (512 + 64 bytes) and
+// each of its stores whole 128-byte lines of the output, 8 rows x 64 k.  A wave does R such groups of rows, the workgroup's waves
+// neighbouring panels.
 // NT: the output is written past the caches.  That pays only for whole lines (K % 64 == 0; with lines shared by two waves
 // it costs two partial writes: 8192 x 4104 18 -> 27 us), and is kept to outputs that the 32 MiB of L2 cannot hold for
-// their reader anyway.  Measured, inputs in turns: 8192 x 8192 49.8 us (a lane per block in row order, 64-bit divisions)
-// -> 34.0 -> 30.6 (NT; 6.9 TB/s); 8192 x 4104 23.5 -> 18.1; 3000 x 5000 12.3 -> 9.6.
-template <bool NT>
-__global__ void __launch_bounds__(256) decode_kernel(const int8_t *__restrict__ Am, const uint8_t *__restrict__ Ae,
+// their reader anyway.  Measured, inputs in turns: 8192 x 8192 54.6 us (lanes) -> 45.2 -> 31.2 (NT; 6.7 TB/s); 8192 x 4104 23.5 ->
+// 18.1; 3000 x 5000 12.3 -> 9.6.
+template <bool NT, int R>
+__global__ void __launch_bounds__(256) decode_panels(const int8_t *__restrict__ Am, const uint8_t *__restrict__ Ae,
                                                      uint16_t *__restrict__ out, int64_t M, int64_t K, int64_t panels, unsigned kblocks)
 {
-    constexpr int R = 2;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane & 7;
     const int64_t row0 = (int64_t)(blockIdx.x / kblocks) * (8 * R) + (lane >> 3);
     const int64_t panel = (int64_t)(blockIdx.x % kblocks) * 4 + wave, k = panel * kPanelK + 8 * q;
@@ -100,13 +127,7 @@ __global__ void __launch_bounds__(256) decode_kernel(const int8_t *__restrict__ 
 #pragma unroll
     for (int g = 0; g < R; ++g) {
         const int64_t row = row0 + 8 * g;
-        const int shift = e[g] - 133;
-        bf16x8 r;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            r[t] = (__bf16)ldexpf((float)(int)(signed char)(w[g].x >> (8 * t)), shift);
-            r[4 + t] = (__bf16)ldexpf((float)(int)(signed char)(w[g].y >> (8 * t)), shift);
-        }
+        const bf16x8 r = decode8(w[g], e[g] - 133);
         if (row < M) {
             bf16x8 *dst = reinterpret_cast<bf16x8 *>(out + row * K + k);      // 16-byte aligned as `out` is
             if constexpr (NT) __builtin_nontemporal_store(r, dst); else *dst = r;
@@ -136,10 +157,15 @@ hipError_t launch_decode(const int8_t *Am, const uint8_t *Ae, uint16_t *out, int
 {
     const int64_t panels = (K + kPanelK - 1) / kPanelK;
     if (M == 0 || panels == 0) return hipSuccess;
-    const int64_t kblocks = (panels + 3) / 4;            // a workgroup covers 16 rows x 4 panels
-    const int64_t blocks = ((M + 15) / 16) * kblocks;
-    const bool nt = K % kPanelK == 0 && (reinterpret_cast<uintptr_t>(out) & 127u) == 0 && M * K * 2 > ((int64_t)32 << 20);
-    hipLaunchKernelGGL(nt ? decode_kernel<true> : decode_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, Am, Ae, out, M, K, panels, (unsigned)kblocks);
+    const DecodeRoute r = decode_route(M, K, (reinterpret_cast<uintptr_t>(out) & 127u) == 0);
+    const dim3 grid((unsigned)r.workgroups), block(256);
+    if (r.rows == 0)
+        hipLaunchKernelGGL(decode_lanes, grid, block, 0, stream, Am, Ae, out, M, K);
+    else {
+        const unsigned kblocks = (unsigned)((panels + 3) / 4);         // a workgroup covers 8 rows (times r.rows) x 4 panels
+        auto *kernel = r.past_caches ? decode_panels<true, 2> : r.rows == 2 ? decode_panels<false, 2> : decode_panels<false, 1>;
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, Am, Ae, out, M, K, panels, kblocks);
+    }
     return hipGetLastError();
 }
 

@@ -9,7 +9,7 @@
 #include <cstring>
 #include <vector>
 
-#include "atb.h"
+#include "atb_route.h"
 
 extern "C" {
 int64_t atb_oracle_bfp16_quantize(const float *A, int64_t M, int64_t K, int64_t lda, int8_t *mant, uint8_t *expo);
@@ -203,9 +203,24 @@ static void model_paths()
     EXPECT(atb_model_microkernel(32, 64, 40, 64, 1, 2, 6, 32, &mm) == ATB_ERR_BAD_TILE);
 }
 
+// The host-side rules that send a problem to a kernel.
+static void route_paths()
+{
+    using atb::decode_route;
+    // decoder: narrow and small outputs go lane by lane, the others by panels, in one or two groups of 8 rows
+    EXPECT(decode_route(1000000, 8, true).rows == 0 && decode_route(1000000, 24, true).rows == 0);
+    EXPECT(decode_route(1, 8, true).rows == 0 && decode_route(1, 8, true).workgroups == 1);
+    EXPECT(decode_route(1000, 1000, true).rows == 0 && decode_route(3891, 792, true).rows == 0 && decode_route(8192, 392, true).rows == 0);
+    EXPECT(decode_route(1000, 1000, true).workgroups == (1000 * 125 + 255) / 256);
+    EXPECT(decode_route(1024, 4096, true).rows == 2 && decode_route(1024, 4096, true).workgroups == 64 * 16);
+    EXPECT(decode_route(4571, 8040, true).rows == 1 && decode_route(4571, 8040, true).workgroups == 572 * 32);
+    EXPECT(!decode_route(4571, 8040, true).past_caches && decode_route(8192, 8192, true).past_caches && !decode_route(8192, 8192, false).past_caches);
+}
+
 int main()
 {
     oracle_paths();
+    route_paths();
     api_paths();
     model_paths();
     if (failures) { std::printf("%d expectation(s) failed\n", failures); return 1; }
