@@ -25,9 +25,7 @@ __device__ __forceinline__ unsigned exp_field(float x) { return (__float_as_uint
 // BFP16 block is the 8 values of two neighbouring lanes, which exchange their exponent maxima.  The
 // exponent bytes of the wave, 16 per row, are collected in LDS and leave as two contiguous runs.  Chunks beyond K
 // (the tail of the last panel) are written as zero.
-// STEPS: a wave holds few loads, so waves are what fills the chip; more rows per wave only save workgroups.  Measured, cold
-// inputs, STEPS = 2 / 4 / 8 (us): 512 x 4096 4.1 / 5.0 / 7.4, 1024 x 4096 5.3 / 5.9 / 8.3, 2048 x 4096 9.0 / 8.4 / 9.8, 8192 x 8192
-// 53.7 / 53.4 / 57.4 (6.4 TB/s).
+// STEPS: quantize_route chooses; 8192 x 8192 53.4 us = 6.4 TB/s.
 template <int STEPS>
 __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__ A, int64_t lda,
                                                        int8_t *__restrict__ Am, uint8_t *__restrict__ Ae,
@@ -142,13 +140,9 @@ hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae,
 {
     const int64_t panels = (K + kPanelK - 1) / kPanelK;
     if (M == 0 || panels == 0) return hipSuccess;
-    const int64_t kblocks = (panels + 7) / 8;            // a workgroup covers 2 STEPS rows x 512 k = 8 panels
-    // workgroups of 8 rows, or of 4 while those are no more than 12 per CU
-    const int64_t small = ((M + 3) / 4) * kblocks;
-    if (small <= 12 * 256)
-        hipLaunchKernelGGL(quantize_kernel<2>, dim3((unsigned)small), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, kblocks);
-    else
-        hipLaunchKernelGGL(quantize_kernel<4>, dim3((unsigned)(((M + 7) / 8) * kblocks)), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, kblocks);
+    const QuantizeRoute r = quantize_route(M, K);
+    auto *kernel = r.steps == 2 ? quantize_kernel<2> : r.steps == 4 ? quantize_kernel<4> : quantize_kernel<8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)r.workgroups), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, (panels + 7) / 8);
     return hipGetLastError();
 }
 

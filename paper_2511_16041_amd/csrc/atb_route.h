@@ -6,6 +6,29 @@
 
 namespace atb {
 
+// CUs that the rules are reckoned with where there is no device to ask
+constexpr int kDefaultCUs = 256;
+
+// Quantiser: steps of two rows that a wave takes, and workgroups of 2 steps rows x 512 k (four waves side by side along k).
+struct QuantizeRoute {
+    int steps;
+    int64_t workgroups;
+};
+
+// Measured, cold inputs, us, steps = 2 / 4 / 8:
+//   512 x 4096 4.1 / 5.0 / 7.4   4096 x 1024 5.2 / 5.8 / 7.7   8192 x 8192 54.0 / 53.4 / 57.9: a wave holds few loads, so waves are
+//   what fills the chip; more rows per wave only save workgroups.
+//   Up to 256 columns, where half of a workgroup's waves or more have nothing to do, saving workgroups is what counts once there are
+//   many: 10^6 x 8 186 / 157 / 149, 200000 x 256 58.9 / 54.5 / 52.5, 65536 x 200 21.1 / 19.4 / 19.0 (32768 x 64 8.2 / 7.4 / 8.0;
+//   150000 x 384 53.8 / 51.1 / 51.3).
+inline QuantizeRoute quantize_route(int64_t M, int64_t K)
+{
+    const int64_t panels = (K + kPanelK - 1) / kPanelK, kblocks = (panels + 7) / 8;
+    const int64_t small = ((M + 3) / 4) * kblocks;
+    const int steps = small <= 12 * kDefaultCUs ? 2 : (K <= 256 && small >= 16384) ? 8 : 4;
+    return {steps, ((M + 2 * steps - 1) / (2 * steps)) * kblocks};
+}
+
 // Decoder.  rows == 0: a lane takes a block of 8 in row order (decode_lanes); else a wave takes 8 rows of a panel, `rows` of them
 // one after the other (decode_panels), with `past_caches` written non-temporally. 
 struct DecodeRoute {

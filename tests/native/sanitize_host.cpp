@@ -207,6 +207,13 @@ static void model_paths()
 static void route_paths()
 {
     using atb::decode_route;
+    using atb::quantize_route;
+    // quantiser: 4 rows per workgroup while those are few, 16 for many narrow rows, else 8
+    EXPECT(quantize_route(512, 4096).steps == 2 && quantize_route(512, 4096).workgroups == 128 * 8);
+    EXPECT(quantize_route(8192, 8192).steps == 4 && quantize_route(8192, 8192).workgroups == 1024 * 16);
+    EXPECT(quantize_route(1000000, 8).steps == 8 && quantize_route(1000000, 8).workgroups == 62500);
+    EXPECT(quantize_route(200000, 256).steps == 8 && quantize_route(150000, 384).steps == 4 && quantize_route(32768, 64).steps == 4);
+    EXPECT(quantize_route(1, 8).steps == 2 && quantize_route(1, 8).workgroups == 1);
     // decoder: narrow and small outputs go lane by lane, the others by panels, in one or two groups of 8 rows
     EXPECT(decode_route(1000000, 8, true).rows == 0 && decode_route(1000000, 24, true).rows == 0);
     EXPECT(decode_route(1, 8, true).rows == 0 && decode_route(1, 8, true).workgroups == 1);

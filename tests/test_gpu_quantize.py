@@ -74,9 +74,10 @@ def test_decode_exact():
     assert np.array_equal(got, oracle.decode(mant, expo))
 
 
-@pytest.mark.parametrize("M,K", [(3, 520), (4, 512), (6, 1032), (6150, 2056), (6145, 2048)])
+@pytest.mark.parametrize("M,K", [(3, 520), (4, 512), (6, 1032), (6150, 2056), (6145, 2048), (65533, 72), (65552, 256), (65537, 8)])
 def test_quantizer_rows_per_workgroup(M, K):
-    """Workgroups of 4 rows (small problems) and of 8 (above 3072 of the small ones), with whole and partial last ones."""
+    """Workgroups of 4 rows (small problems), of 8 (above 3072 of the small ones) and of 16 (many narrow rows), with whole and partial
+    last ones."""
     print(f"quantize {(M, K)}", flush=True)
     A, _ = workloads.make_inputs(workloads.CONFIGS["ragged"], M=M, N=8, K=K)
     mant, expo = oracle.quantize(A)
