@@ -141,6 +141,7 @@ hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae,
     const int64_t panels = (K + kPanelK - 1) / kPanelK;
     if (M == 0 || panels == 0) return hipSuccess;
     const QuantizeRoute r = quantize_route(M, K);
+    if (r.workgroups == 0) return hipErrorInvalidConfiguration;
     auto *kernel = r.steps == 2 ? quantize_kernel<2> : r.steps == 4 ? quantize_kernel<4> : quantize_kernel<8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)r.workgroups), dim3(256), 0, stream, A, lda, Am, Ae, M, K, panels, (panels + 7) / 8);
     return hipGetLastError();
@@ -152,6 +153,7 @@ hipError_t launch_decode(const int8_t *Am, const uint8_t *Ae, uint16_t *out, int
     const int64_t panels = (K + kPanelK - 1) / kPanelK;
     if (M == 0 || panels == 0) return hipSuccess;
     const DecodeRoute r = decode_route(M, K, (reinterpret_cast<uintptr_t>(out) & 127u) == 0);
+    if (r.workgroups == 0) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)r.workgroups), block(256);
     if (r.rows == 0)
         hipLaunchKernelGGL(decode_lanes, grid, block, 0, stream, Am, Ae, out, M, K);

@@ -9,6 +9,9 @@ namespace atb {
 // CUs that the rules are reckoned with where there is no device to ask
 constexpr int kDefaultCUs = 256;
 
+// HIP takes fewer than 2^32 threads in a launch: what fits, in workgroups of 256 threads.  A route that needs more has workgroups == 0.
+constexpr int64_t kMaxWorkgroups256 = ((int64_t)1 << 24) - 1;
+
 // Quantiser: steps of two rows that a wave takes, and workgroups of 2 steps rows x 512 k (four waves side by side along k).
 struct QuantizeRoute {
     int steps;
@@ -25,8 +28,10 @@ inline QuantizeRoute quantize_route(int64_t M, int64_t K)
 {
     const int64_t panels = (K + kPanelK - 1) / kPanelK, kblocks = (panels + 7) / 8;
     const int64_t small = ((M + 3) / 4) * kblocks;
-    const int steps = small <= 12 * kDefaultCUs ? 2 : (K <= 256 && small >= 16384) ? 8 : 4;
-    return {steps, ((M + 2 * steps - 1) / (2 * steps)) * kblocks};
+    int steps = small <= 12 * kDefaultCUs ? 2 : (K <= 256 && small >= 16384) ? 8 : 4;
+    if (((M + 7) / 8) * kblocks > kMaxWorkgroups256) steps = 8;          // up to 2^28 rows of at most 512 columns in one launch
+    const int64_t n = ((M + 2 * steps - 1) / (2 * steps)) * kblocks;
+    return {steps, n <= kMaxWorkgroups256 ? n : 0};
 }
 
 // Decoder.  rows == 0: a lane takes a block of 8 in row order (decode_lanes); else a wave takes 8 rows of a panel, `rows` of them
@@ -50,9 +55,11 @@ inline DecodeRoute decode_route(int64_t M, int64_t K, bool out_on_lines)
     const bool past_caches = K % kPanelK == 0 && out_on_lines && bytes > ((int64_t)32 << 20);
     if (past_caches || (K >= 512 && M * K >= ((int64_t)7 << 19))) {
         const int rows = (past_caches || bytes <= ((int64_t)64 << 20)) ? 2 : 1;
-        return {rows, past_caches, ((M + 8 * rows - 1) / (8 * rows)) * ((panels + 3) / 4)};
+        const int64_t n = ((M + 8 * rows - 1) / (8 * rows)) * ((panels + 3) / 4);
+        if (n <= kMaxWorkgroups256) return {rows, past_caches, n};       // 2^28 rows of a few panels are more than that
     }
-    return {0, false, (M * (K / 8) + 255) / 256};
+    const int64_t n = (M * (K / 8) + 255) / 256;
+    return {0, false, n <= kMaxWorkgroups256 ? n : 0};
 }
 
 }  // namespace atb

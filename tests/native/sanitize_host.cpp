@@ -214,6 +214,20 @@ static void route_paths()
     EXPECT(quantize_route(1000000, 8).steps == 8 && quantize_route(1000000, 8).workgroups == 62500);
     EXPECT(quantize_route(200000, 256).steps == 8 && quantize_route(150000, 384).steps == 4 && quantize_route(32768, 64).steps == 4);
     EXPECT(quantize_route(1, 8).steps == 2 && quantize_route(1, 8).workgroups == 1);
+    // as many rows as one launch can take: 2^28 of up to 512 columns to quantise, M K / 8 < 2^32 blocks to decode
+    EXPECT(quantize_route(((int64_t)1 << 27) + 8, 512).steps == 8 && quantize_route(((int64_t)1 << 27) + 8, 512).workgroups == (1 << 23) + 1);
+    EXPECT(quantize_route(((int64_t)1 << 28) - 16, 8).workgroups == (1 << 24) - 1 && quantize_route((int64_t)1 << 28, 8).workgroups == 0);
+    EXPECT(decode_route(((int64_t)1 << 28) + 16, 64, true).rows == 0 && decode_route(((int64_t)1 << 28) + 16, 64, true).workgroups == (1 << 23) + 1);
+    EXPECT(decode_route(((int64_t)1 << 32) - 256, 8, true).workgroups == (1 << 24) - 1 && decode_route((int64_t)1 << 32, 8, true).workgroups == 0);
+    const int64_t sizes[] = {1, 7, 1000, 1 << 20, (1 << 27) - 1, 1 << 27, (1 << 28) - 17, 1 << 28, (int64_t)1 << 29, ((int64_t)1 << 32) - 1};
+    for (int64_t m : sizes)
+        for (int64_t k : {8, 24, 64, 192, 256, 512, 520, 4096}) {
+            const auto q = quantize_route(m, k);
+            const auto d = decode_route(m, k, true);
+            EXPECT(q.workgroups < (1 << 24) && d.workgroups < (1 << 24));
+            EXPECT((q.workgroups == 0) == (((m + 15) / 16) * ((k + 511) / 512) >= (1 << 24)));
+            if ((m * k / 8 + 255) / 256 < (1 << 24)) EXPECT(d.workgroups > 0);
+        }
     // decoder: narrow and small outputs go lane by lane, the others by panels, in one or two groups of 8 rows
     EXPECT(decode_route(1000000, 8, true).rows == 0 && decode_route(1000000, 24, true).rows == 0);
     EXPECT(decode_route(1, 8, true).rows == 0 && decode_route(1, 8, true).workgroups == 1);

@@ -102,6 +102,39 @@ def test_decode_shapes(M, K):
     assert np.array_equal(dec.float().cpu().numpy(), want)
 
 
+def test_tall_matrices_fit_one_launch():
+    """A launch takes fewer than 2^32 threads: 2^27 + 8 rows to quantise and 2^28 + 16 rows of one panel to decode need the forms
+    with more rows, or blocks, per thread.  The rows repeat a pattern, so the first and the last of them say whether all were reached."""
+    import torch
+    M, K = 2 ** 27 + 8, 8
+    print(f"quantize {(M, K)}", flush=True)
+    rows = torch.randn((1024, K), device="cuda")
+    x = rows.repeat(M // 1024 + 1, 1)[:M]
+    buf = atb.bfp16_quantize(x)
+    want = atb.bfp16_quantize(rows)
+    lay, few = atb.bfp16_layout(M, K), atb.bfp16_layout(1024, K)
+    man, exp = buf[:M * 64].view(M, 64), buf[lay.exp_off:lay.exp_off + M * 8].view(M, 8)
+    wman, wexp = want[:1024 * 64].view(1024, 64), want[few.exp_off:few.exp_off + 1024 * 8].view(1024, 8)
+    for first in (0, M // 2 // 1024 * 1024, M // 1024 * 1024 - 1024):
+        assert torch.equal(man[first:first + 1024], wman) and torch.equal(exp[first:first + 1024], wexp)
+    assert torch.equal(man[-8:], wman[:8]) and torch.equal(exp[-8:], wexp[:8])
+    del x, buf, man, exp
+    M, K = 2 ** 28 + 16, 64
+    print(f"decode {(M, K)}", flush=True)
+    lay = atb.bfp16_layout(M, K)
+    buf = torch.zeros(lay.bytes, dtype=torch.uint8, device="cuda")
+    man, exp = buf[:M * 64].view(M, 64), buf[lay.exp_off:lay.exp_off + M * 8].view(M, 8)
+    man.view(torch.int64).copy_(torch.randint(-2 ** 62, 2 ** 62, (1, 8), device="cuda").expand(M, 8))
+    exp.fill_(130)
+    dec = atb.bfp16_decode(buf, M, K)
+    want = man[:1].view(torch.int8).float() * 0.125
+    for first in (0, M // 2, M - 4096):
+        assert torch.equal(dec[first:first + 4096].float(), want.expand(4096, K))
+    torch.cuda.synchronize()
+    del buf, man, exp, dec
+    torch.cuda.empty_cache()
+
+
 def test_quantizer_rejects_bad_arguments():
     import ctypes
     import torch
