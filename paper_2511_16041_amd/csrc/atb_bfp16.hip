@@ -100,10 +100,11 @@ __global__ void __launch_bounds__(256) decode_lanes(const int8_t *__restrict__ A
 // A wave takes 8 rows of a panel: a lane one block, eight lanes a row, so that its requests are contiguous (512 + 64 bytes) and
 // each of its stores whole 128-byte lines of the output, 8 rows x 64 k.  A wave does R such groups of rows, the workgroup's waves
 // neighbouring panels.
-// NT: the output is written past the caches.  That pays only for whole lines (K % 64 == 0; with lines shared by two waves
-// it costs two partial writes: 8192 x 4104 18 -> 27 us), and is kept to outputs that the 32 MiB of L2 cannot hold for
-// their reader anyway.  Measured, inputs in turns: 8192 x 8192 54.6 us (lanes) -> 45.2 -> 31.2 (NT; 6.7 TB/s); 8192 x 4104 23.5 ->
-// 18.1; 3000 x 5000 12.3 -> 9.6.
+// NT: the output is written past the caches.  That pays only for whole lines (K % 64 == 0; with lines shared by two waves it costs
+// two partial writes: 8192 x 8104 cold 56.4, hot 34 -> 54), and only for outputs so large that their next reader would not have found
+// them in the 256 MiB memory-side cache.  Measured, us, decode / decode and then one pass that reads the output, stores through the
+// caches -> past them: 64 MiB 25.3 / 43.0 -> 16.4 / 44.4, 96 MiB - / 66.9 -> - / 64.6, 128 MiB (8192 x 8192) 45.2 / 94.0 -> 31.2 / 85.7
+// (6.7 TB/s), 192 MiB - / 134.0 -> - / 130.4: below 96 MiB the reader pays for what the decoder saves.
 template <bool NT, int R>
 __global__ void __launch_bounds__(256) decode_panels(const int8_t *__restrict__ Am, const uint8_t *__restrict__ Ae,
                                                      uint16_t *__restrict__ out, int64_t M, int64_t K, int64_t panels, unsigned kblocks)

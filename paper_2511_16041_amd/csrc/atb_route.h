@@ -52,7 +52,7 @@ struct DecodeRoute {
 inline DecodeRoute decode_route(int64_t M, int64_t K, bool out_on_lines)
 {
     const int64_t panels = (K + kPanelK - 1) / kPanelK, bytes = 2 * M * K;
-    const bool past_caches = K % kPanelK == 0 && out_on_lines && bytes > ((int64_t)32 << 20);
+    const bool past_caches = K % kPanelK == 0 && out_on_lines && bytes >= ((int64_t)96 << 20);
     if (past_caches || (K >= 512 && M * K >= ((int64_t)7 << 19))) {
         const int rows = (past_caches || bytes <= ((int64_t)64 << 20)) ? 2 : 1;
         const int64_t n = ((M + 8 * rows - 1) / (8 * rows)) * ((panels + 3) / 4);

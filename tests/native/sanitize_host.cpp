@@ -236,6 +236,8 @@ static void route_paths()
     EXPECT(decode_route(1024, 4096, true).rows == 2 && decode_route(1024, 4096, true).workgroups == 64 * 16);
     EXPECT(decode_route(4571, 8040, true).rows == 1 && decode_route(4571, 8040, true).workgroups == 572 * 32);
     EXPECT(!decode_route(4571, 8040, true).past_caches && decode_route(8192, 8192, true).past_caches && !decode_route(8192, 8192, false).past_caches);
+    // past the caches only where the output's next reader would not have found it in one
+    EXPECT(!decode_route(8192, 4096, true).past_caches && !decode_route(8192, 6143 / 64 * 64, true).past_caches && decode_route(8192, 6144, true).past_caches);
 }
 
 int main()

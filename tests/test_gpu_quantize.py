@@ -86,10 +86,10 @@ def test_quantizer_rows_per_workgroup(M, K):
 
 
 @pytest.mark.parametrize("M,K", [(1, 8), (15, 64), (17, 264), (33, 320), (4101, 4160), (4101, 4168),
-                                 (100003, 24), (3660, 1000), (3675, 1000), (7169, 512), (7169, 520), (4201, 8200)])
+                                 (100003, 24), (3660, 1000), (3675, 1000), (7169, 512), (7169, 520), (4201, 8200), (8201, 6144), (8201, 6152)])
 def test_decode_shapes(M, K):
     """Lane by lane (small and narrow), by panels of 16 rows x 4 panels (above 3.67 million values and from 512 columns) and of 8 rows
-    (above 64 MiB): edges, tails of the last panel, and outputs above 32 MiB with whole and with shared 128-byte lines (the first are
+    (above 64 MiB): edges, tails of the last panel, and outputs above 96 MiB with whole and with shared 128-byte lines (the first are
     stored past the caches)."""
     import torch
     print(f"decode {(M, K)}", flush=True)
