@@ -142,11 +142,15 @@ atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, int64_t K,
                                atb_format b_format, atb_format c_format);
 
 /* Launch geometry of a plan, for benches and tests: number of C tiles the
- * launch walks, rounded up to a multiple of 8 (the grid is persistent: it has
+ * launch walks, rounded up to a multiple of 8 (the grid of the large tiles is persistent: it has
  * min(that, workgroups resident on the chip) workgroups, each looping over its
- * tiles; a problem that the kernel for few rows takes is launched differently), threads per workgroup, static LDS bytes per workgroup. Any pointer
- * may be NULL. */
+ * tiles), threads per workgroup, static LDS bytes per workgroup: of the kernel for few rows where
+ * that is what atb_gemm_run launches (atb_gemm_streams). Any pointer may be NULL. */
 atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroups, int *threads, int *lds_bytes);
+
+/* 1 if atb_gemm_run sends this plan to the kernel for few rows and a long reduction (see
+ * atb_gemm_create), which has no tile buffers and no use for the plan's factors; else 0 (also g == NULL). */
+int atb_gemm_streams(const atb_gemm *g);
 
 /* The compiled (T_MA, T_MC, T_K, T_N) instances. */
 int atb_instance_count(void);

@@ -65,7 +65,7 @@ class Bfp16Layout(ctypes.Structure):
 # every symbol include/atb.h declares
 EXPORTS = [
     "atb_status_string", "atb_last_hip_error", "atb_gemm_create", "atb_gemm_create_fmt", "atb_gemm_run", "atb_gemm_destroy",
-    "atb_gemm_launch_info", "atb_instance_count", "atb_instance_get", "atb_bfp16_layout", "atb_bfp16_bytes",
+    "atb_gemm_launch_info", "atb_gemm_streams", "atb_instance_count", "atb_instance_get", "atb_bfp16_layout", "atb_bfp16_bytes",
     "atb_bfp16_quantize", "atb_bfp16_decode", "atb_hw_params_xdna2", "atb_hw_params_mi355x",
     "atb_model_eval", "atb_select_tiles", "atb_model_microkernel", "atb_instance_geometry", "atb_mfma_probe",
 ]
@@ -93,6 +93,8 @@ def lib() -> ctypes.CDLL:
     L.atb_gemm_destroy.argtypes = [vp]
     L.atb_gemm_launch_info.restype = ci
     L.atb_gemm_launch_info.argtypes = [vp, ctypes.POINTER(i64), pi, pi]
+    L.atb_gemm_streams.restype = ci
+    L.atb_gemm_streams.argtypes = [vp]
     L.atb_instance_count.restype = ci
     L.atb_instance_get.restype = ci
     L.atb_instance_get.argtypes = [ci, pi, pi, pi, pi]
@@ -345,6 +347,10 @@ class Gemm:
         _check(lib().atb_gemm_launch_info(self._h, ctypes.byref(wg), ctypes.byref(th), ctypes.byref(lds)),
                "atb_gemm_launch_info")
         return LaunchInfo(wg.value, th.value, lds.value)
+
+    def streams(self) -> bool:
+        """Whether run() launches the kernel for few rows and a long reduction instead of the instance of `tiles`."""
+        return bool(lib().atb_gemm_streams(self._h))
 
     def close(self):
         if self._h:

@@ -4,7 +4,7 @@
 #include <cstdlib>
 #include <new>
 
-#include "atb_internal.h"
+#include "atb_route.h"
 
 struct atb_gemm {
     int64_t M, N, K;
@@ -25,6 +25,13 @@ atb_status hip_status(hipError_t e)
     if (e == hipSuccess) return ATB_OK;
     g_last_hip_error = (int)e;
     return ATB_ERR_HIP;
+}
+
+// The streaming kernel's form for this plan; it does not stream where the tile pipeline runs it.
+atb::StreamRoute plan_route(const atb_gemm *g)
+{
+    const bool over = g->b_format == ATB_FMT_BF16_T || atb::instance(g->instance).hands_over;
+    return over ? atb::stream_route(g->proto, g->b_format) : atb::StreamRoute{};
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -174,10 +181,14 @@ extern "C" atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, 
     if (const char *log = std::getenv("ATB_LOG"); log && log[0] == '1') {
         const atb::Instance &x = atb::instance(idx);
         std::fprintf(stderr, "atb_gemm_create: M=%lld N=%lld K=%lld T_MA=%d T_MC=%d T_K=%d T_N=%d rho=%d b=%s c=%s "
-                             "instance=%d waves=%dx%d threads=%d lds=%d tiles=%dx%d group_m=%d k_panels=%d\n",
+                             "instance=%d waves=%dx%d threads=%d lds=%d tiles=%dx%d group_m=%d k_panels=%d",
                      (long long)M, (long long)N, (long long)K, T_MA, T_MC, T_K, T_N, T_MC / T_MA,
                      b_format == ATB_FMT_BFP16 ? "bfp16" : b_format == ATB_FMT_BF16_T ? "bf16_t" : "bf16", c_format == ATB_FMT_BFP16 ? "bfp16" : "bf16", idx,
                      x.wave_m, x.wave_n, x.threads, x.lds_bytes, p.tiles_m, p.tiles_n, p.group_m, p.k_panels);
+        const atb::StreamRoute r = plan_route(g);
+        if (r.streams())       // what runs instead of the instance
+            std::fprintf(stderr, " streaming: tile=%dx%d threads=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.lds_bytes(), (long long)atb::stream_workgroups(p, r));
+        std::fputc('\n', stderr);
     }
     *out = g;
     return ATB_OK;
@@ -202,6 +213,8 @@ extern "C" atb_status atb_gemm_run(const atb_gemm *g, const void *A_bfp, const v
     } else {
         p.C = static_cast<uint16_t *>(C);
     }
+    const atb::StreamRoute r = plan_route(g);
+    if (r.streams()) return hip_status(atb::launch_skinny(p, g->b_format, r, static_cast<hipStream_t>(stream)));
     const atb::Instance &x = atb::instance(g->instance);
     if (g->b_format != ATB_FMT_BF16 || g->c_format != ATB_FMT_BF16)
         return hip_status(x.launch_fmt(p, g->b_format, g->c_format, static_cast<hipStream_t>(stream)));
@@ -214,12 +227,15 @@ extern "C" atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroup
 {
     if (!g) return ATB_ERR_INVALID_ARG;
     const atb::Instance &x = atb::instance(g->instance);
+    const atb::StreamRoute r = plan_route(g);
     const int64_t total = (int64_t)g->proto.tiles_m * g->proto.tiles_n;
-    if (workgroups) *workgroups = (total + 7) / 8 * 8;
-    if (threads) *threads = x.threads;
-    if (lds_bytes) *lds_bytes = x.lds_bytes;
+    if (workgroups) *workgroups = r.streams() ? atb::stream_workgroups(g->proto, r) : (total + 7) / 8 * 8;
+    if (threads) *threads = r.streams() ? r.threads() : x.threads;
+    if (lds_bytes) *lds_bytes = r.streams() ? r.lds_bytes() : x.lds_bytes;
     return ATB_OK;
 }
+
+extern "C" int atb_gemm_streams(const atb_gemm *g) { return g && plan_route(g).streams() ? 1 : 0; }
 
 extern "C" atb_status atb_mfma_probe(void *sink, void *clocks, int workgroups, int iters, int random_operands,
                                      int mfma_rows, void *stream, double *flop)

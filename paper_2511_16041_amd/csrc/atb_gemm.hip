@@ -1530,16 +1530,9 @@ hipError_t launch_kernel(const GemmParams &p, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Few rows and a long K go to the streaming kernel from the instances that the selector picks for such problems, and
-// from every instance that takes B^T in bf16 (all of them tiles of 128 rows and more).
-template <class S>
-constexpr bool kSkinnyRoute = (S::HW > 0 && S::T_K >= 128);
-
 template <class S>
 hipError_t launch_instance(const GemmParams &p, hipStream_t stream)
 {
-    if constexpr (kSkinnyRoute<S>)
-        if (skinny_applies(p, ATB_FMT_BF16)) return launch_skinny(p, ATB_FMT_BF16, stream);
     // 16-byte requests need dword-aligned addresses: B rows start at multiples of 2 N bytes, chunks at
     // multiples of 16 bytes within a row, so any even N qualifies (a chunk that straddles the end of
     // a row only feeds output columns >= N, which are never stored)
@@ -1552,12 +1545,9 @@ template <class S>
 hipError_t launch_instance_fmt(const GemmParams &p, int b_format, int c_format, hipStream_t stream)
 {
     const bool bb = (b_format == ATB_FMT_BFP16), cb = (c_format == ATB_FMT_BFP16);
-    if constexpr (kSkinnyRoute<S>)
-        if (b_format != ATB_FMT_BF16_T && skinny_applies(p, b_format)) return launch_skinny(p, b_format, stream);
     if (b_format == ATB_FMT_BF16_T) {
         // bf16 B handed over transposed: compiled for the tiles with K-steps of 64 and a bf16 C
         if constexpr (S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256) {
-            if (!cb && skinny_applies(p, b_format)) return launch_skinny(p, b_format, stream);
             if (!cb) return launch_kernel<S, true, false, false, true>(p, stream);
         }
         return hipErrorInvalidValue;
@@ -1589,6 +1579,9 @@ Instance make_instance(double eff_scale = 0.0, double lone_cap = 0.0)
     i.mfma_rows = S::MB;
     i.launch = &launch_instance<S>;
     if constexpr (FMT) i.launch_fmt = &launch_instance_fmt<S>; else i.launch_fmt = nullptr;
+    // few rows and a long K go to the streaming kernel from the instances that the selector picks for such problems, and from every
+    // instance that takes B^T in bf16 (all of them tiles of 128 rows and more)
+    i.hands_over = S::HW > 0 && S::T_K >= 128;
     i.has_b_transposed = FMT && S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256;
     return i;
 }
@@ -1697,7 +1690,7 @@ const Instance g_instances[] = {
     // B buffers (NB; it fits because the ATB A buffers are small, and it is what lets the symmetric 32-row tile's
     // single phase per K-step await its B tile two K-steps after the request), four helper waves next to the 1 x 2
     // grid (which alone would leave two SIMDs idle), and take the dead-row-skipping variant of the kernel body.
-    // Above K = 1024 they hand most problems over to the streaming kernel (launch_instance); what is left to them are
+    // Above K = 1024 they hand most problems over to the streaming kernel (stream_route); what is left to them are
     // bf16 B of up to 8192 columns at 49 to 64 rows, of up to 4096 at 65 to 128, and short reductions.  Measured at N = K =
     // 8192, operands in turns so that B comes from memory: M <= 64: 40 - 41 us with the 32-row tile.  Factors from the
     // issue model: 0.52 and 0.48 (measured: 0.42 - 0.49 of the fit from M = 16 to 8192).

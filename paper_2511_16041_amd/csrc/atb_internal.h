@@ -37,6 +37,7 @@ struct Instance {
     double eff_scale;       // measured full-load throughput of this instance relative to Eq. (12)'s fit; 0: taken from the issue model
     double lone_cap;        // measured largest gain of a workgroup in a sparsely filled round; 0: the default for wg_per_cu
     hipError_t (*launch)(const GemmParams &p, hipStream_t stream);
+    bool hands_over;        // problems that stream_route takes go to the streaming kernel (with b_format BF16_T: from every instance)
     bool has_b_transposed;  // launch_fmt also takes b_format = ATB_FMT_BF16_T (with a bf16 C)
     // other storage formats (b_format, c_format as in atb_format); null where the instance has none
     hipError_t (*launch_fmt)(const GemmParams &p, int b_format, int c_format, hipStream_t stream);
@@ -47,10 +48,10 @@ const Instance &instance(int i);
 // index of the instance with these factors, or -1
 int find_instance(int T_MA, int T_MC, int T_K, int T_N);
 
-// The streaming kernel for few rows (atb_skinny.hip): whether a problem is one of its own, and its launch.  Takes every
-// storage format that the plan admits; b_format as in atb_format, C in BFP16 where p.Cm is set.
-bool skinny_applies(const GemmParams &p, int b_format);
-hipError_t launch_skinny(const GemmParams &p, int b_format, hipStream_t stream);
+// The streaming kernel for few rows (atb_skinny.hip), in the form that stream_route (atb_route.h) chose.  Takes every storage format
+// that a plan admits; b_format as in atb_format, C in BFP16 where p.Cm is set.
+struct StreamRoute;
+hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r, hipStream_t stream);
 
 hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae, int64_t M, int64_t K,
                            hipStream_t stream);

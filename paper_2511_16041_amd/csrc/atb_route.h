@@ -1,5 +1,5 @@
-// Which kernel takes a problem, and in what launch: host-only rules on sizes and formats, shared by the launches
-// (atb_skinny.hip, atb_gemm.hip) and by what a plan reports (atb_api.cpp).
+// Which kernel takes a problem, and in what launch: host-only rules on sizes and formats, shared by the launches and
+// by what a plan reports.
 #pragma once
 
 #include "atb_internal.h"
@@ -60,6 +60,67 @@ inline DecodeRoute decode_route(int64_t M, int64_t K, bool out_on_lines)
     }
     const int64_t n = (M * (K / 8) + 255) / 256;
     return {0, false, n <= kMaxWorkgroups256 ? n : 0};
+}
+
+// The streaming kernel's variant for a problem: a workgroup takes a tile of 16 mb rows x 16 nb columns with `waves` waves,
+// each with `depth` panels of K in flight.  mb == 0: the problem stays with the tile pipeline.
+struct StreamRoute {
+    int mb, nb, waves, depth;
+    bool streams() const { return mb > 0; }
+    int threads() const { return 64 * waves; }
+    int lds_bytes() const { return waves * 16 * (16 * nb + 4) * 4; }         // the partial C tiles
+};
+
+inline int64_t tile_count(const GemmParams &p, int rows, int cols)
+{
+    const int64_t columns = p.n_panels > 0 ? (int64_t)p.n_panels * kPanelK : p.N;      // C in BFP16: the zero tail of its last panel as well
+    return (int64_t)((p.M + rows - 1) / rows) * ((columns + cols - 1) / cols);
+}
+
+inline int64_t stream_workgroups(const GemmParams &p, const StreamRoute &r) { return (tile_count(p, 16 * r.mb, 16 * r.nb) + 7) / 8 * 8; }
+
+// M <= 64: 16 nb columns per workgroup, the narrowest of 32, 64 and 128 that needs no more workgroups than there are CUs.
+// Measured (us, M = 16, bf16 B): N = 14336, K = 4096: 35.4 / 24.4 / 31.9 with 32 / 64 / 128 columns; N = 28672: 59 / 54 / 44.
+inline int stream_column_blocks(int N) { return N <= 32 * kDefaultCUs ? 2 : N <= 64 * kDefaultCUs ? 4 : 8; }
+
+// More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
+// none where the tile pipeline is as good or better.  Measured in us, the pipeline before / this kernel now:
+//   B bf16    M 128, N 8192, K 8192: 54.4 / 47.0 (64 x 64)   M 256, 4096, 4096: 22.3 / 19.5 (64 x 64)
+//             M 512, 4096, 14336: 120 / 80 (64 x 128)        M 256, 8192, 8192: 70.3 / 54.9 (64 x 128)
+//             not 64 x 32 (M 256, 2048, 2048: 9.9 / 10.4), nor 64 x 128 below K = 4096 (M 1024, 2048, 2048: 16.3 / 17.5),
+//             nor odd N (M 512, 5001, 4096: 61 / 70)
+//   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
+//             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
+//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64)
+inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format)
+{
+    const bool rows_of_b = (b_format == ATB_FMT_BF16);
+    if (rows_of_b && p.N % 2 != 0) return {};
+    if (tile_count(p, 64, 32) <= kDefaultCUs) return rows_of_b ? StreamRoute{} : StreamRoute{4, 2, 8, 1};
+    if (tile_count(p, 64, 64) <= kDefaultCUs) return {4, 4, 8, 1};
+    if (rows_of_b && p.K >= 4096 && tile_count(p, 64, 128) <= kDefaultCUs) return {4, 8, 4, 2};
+    if (b_format == ATB_FMT_BF16_T && tile_count(p, 128, 64) <= kDefaultCUs) return {8, 4, 4, 1};
+    return {};
+}
+
+// Where the streaming kernel takes over from the tile pipeline, and in what form.  K <= 1024: there every instance adds in the same order and gives
+// the same bits, and the call is bound by its launch either way (M 16, N 8192, K 1088: 8.3 / 5.7 us).  The two
+// exceptions at M <= 64 are where the pipeline is the faster one: M 64, N 8192, K 8192 bf16 41.0 / 43.5 us (every workgroup
+// decodes all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
+// Waves: four where their requests already fill the CU's share (64 and 128 columns of bf16 B: 24.4 against 28.1 us with
+// eight), eight or sixteen where more hands are needed to decode B.
+inline StreamRoute stream_route(const GemmParams &p, int b_format)
+{
+    if (p.K <= 1024) return {};
+    if (p.M > 64) return stream_route_many_rows(p, b_format);
+    const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N);
+    if (b_format == ATB_FMT_BFP16) {
+        if (nb == 8 && mb == 4) return {};
+        return {mb, nb, nb == 2 ? 16 : 8, 1};
+    }
+    if (b_format == ATB_FMT_BF16 && p.N % 2 != 0) return {mb, 2, 8, 1};
+    if (b_format == ATB_FMT_BF16 && nb == 2 && mb == 4) return {};
+    return {mb, nb, nb == 2 ? 8 : 4, 1};
 }
 
 }  // namespace atb

@@ -1,5 +1,5 @@
 // GEMM for few rows and a long reduction (K > 1024): a streaming kernel, bound by the bytes of B.  For M <= 64, and above
-// that for problems of at most one 64 x 32 to 128 x 64 tile per CU (tile_of).
+// that for problems of at most one 64 x 32 to 128 x 64 tile per CU (stream_route).
 //
 // With one band of 16 to 64 rows of C there is nothing to share a B tile with, so the tile pipeline of atb_gemm.hip (B
 // through LDS, a barrier per K-step, a workgroup per 64 columns) only adds waits.  Here every wave is on its own: the
@@ -9,7 +9,7 @@
 //
 // What bounds it: a CU keeps about 200 lines of 128 bytes in flight (measured: 27 GB/s per CU from HBM whatever the
 // number of waves or of panels in flight per wave, 1 to 4), so all CUs have to take part and every line that is asked for should
-// be used whole.  Hence the tile width (column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
+// be used whole.  Hence the tile width (stream_column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
 // <= 8192 that is 32 columns, half a line per row, and the rate stays at 3.9 TB/s against 5.1 with B^T.
 // Measured in us, operands cold in the caches (three sets in turns), the tile pipeline before / this kernel now:
 //   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5     M 64, 14336, 4096: 34.7 / 30.0     M 16, 5001, 4096: 23.7 / 12.9
@@ -26,7 +26,7 @@
 //                      v_perm_b32 picks the halves
 //   B^T bf16           two 16-byte requests per 16 columns are the operands as they are
 //   B^T BFP16          one 16-byte request per 16 columns, decoded in registers like A
-#include "atb_internal.h"
+#include "atb_route.h"
 
 namespace atb {
 namespace {
@@ -309,96 +309,52 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
     }
 }
 
-int columns(const GemmParams &p) { return p.Cm ? p.n_panels * kPanelK : p.N; }
-int64_t tiles(const GemmParams &p, int rows, int cols) { return (int64_t)((p.M + rows - 1) / rows) * ((columns(p) + cols - 1) / cols); }
-
 template <int FMT, int MB, int NB, int W, int D = 1>
-hipError_t launch(const GemmParams &p, hipStream_t stream)
+hipError_t launch(const GemmParams &p, const StreamRoute &r, hipStream_t stream)
 {
-    const unsigned n = (unsigned)tiles(p, 16 * MB, 16 * NB);
-    hipLaunchKernelGGL((skinny_kernel<FMT, MB, NB, W, D>), dim3((n + 7) / 8 * 8), dim3(W * 64), 0, stream, p);
+    hipLaunchKernelGGL((skinny_kernel<FMT, MB, NB, W, D>), dim3((unsigned)stream_workgroups(p, r)), dim3(W * 64), 0, stream, p);
     return hipGetLastError();
 }
 
-template <int FMT, int NB, int W>
-hipError_t launch_rows(const GemmParams &p, hipStream_t stream)
+// One of 1 to MAX blocks of 16 rows.
+template <int FMT, int NB, int W, int MAX>
+hipError_t launch_rows(const GemmParams &p, const StreamRoute &r, hipStream_t stream)
 {
-    if (p.M <= 16) return launch<FMT, 1, NB, W>(p, stream);
-    if (p.M <= 32) return launch<FMT, 2, NB, W>(p, stream);
-    if (p.M <= 48) return launch<FMT, 3, NB, W>(p, stream);
-    if constexpr (FMT == kBBfp && NB == 8)
-        return hipErrorInvalidValue;       // skinny_applies keeps it away: registers
-    else
-        return launch<FMT, 4, NB, W>(p, stream);
-}
-
-// 16 NB columns per workgroup: the narrowest of 32, 64 and 128 that needs no more workgroups than there are CUs.
-// Measured (us, M = 16, bf16 B): N = 14336, K = 4096: 35.4 / 24.4 / 31.9 with 32 / 64 / 128 columns; N = 28672: 59 / 54 / 44.
-// W: four waves where their requests already fill the CU's share (64 and 128 columns of bf16 B: 24.4 against 28.1 us
-// with eight), eight or sixteen where more hands are needed to decode B.
-int column_blocks(int N) { return N <= 32 * 256 ? 2 : N <= 64 * 256 ? 4 : 8; }
-
-// More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
-// none (0) where the tile pipeline is as good or better.  Measured in us, the pipeline before / this kernel now:
-//   B bf16    M 128, N 8192, K 8192: 54.4 / 47.0 (64 x 64)   M 256, 4096, 4096: 22.3 / 19.5 (64 x 64)
-//             M 512, 4096, 14336: 120 / 80 (64 x 128)        M 256, 8192, 8192: 70.3 / 54.9 (64 x 128)
-//             not 64 x 32 (M 256, 2048, 2048: 9.9 / 10.4), nor 64 x 128 below K = 4096 (M 1024, 2048, 2048: 16.3 / 17.5),
-//             nor odd N (M 512, 5001, 4096: 61 / 70)
-//   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
-//             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
-//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64)
-enum { kNone = 0, k64x32, k64x64, k64x128, k128x64 };
-int tile_of(const GemmParams &p, int b_format)
-{
-    constexpr int kCUs = 256;
-    const bool rows_of_b = (b_format == ATB_FMT_BF16);
-    if (rows_of_b && p.N % 2 != 0) return kNone;
-    if (tiles(p, 64, 32) <= kCUs) return rows_of_b ? kNone : k64x32;
-    if (tiles(p, 64, 64) <= kCUs) return k64x64;
-    if (rows_of_b && p.K >= 4096 && tiles(p, 64, 128) <= kCUs) return k64x128;
-    if (b_format == ATB_FMT_BF16_T && tiles(p, 128, 64) <= kCUs) return k128x64;
-    return kNone;
+    if (r.mb == 1) return launch<FMT, 1, NB, W>(p, r, stream);
+    if (r.mb == 2) return launch<FMT, 2, NB, W>(p, r, stream);
+    if (r.mb == 3) return launch<FMT, 3, NB, W>(p, r, stream);
+    if constexpr (MAX == 4)
+        if (r.mb == 4) return launch<FMT, 4, NB, W>(p, r, stream);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// Where this kernel takes over from the tile pipeline.  K <= 1024: there every instance adds in the same order and gives
-// the same bits, and the call is bound by its launch either way (M 16, N 8192, K 1088: 8.3 / 5.7 us).  The two
-// exceptions at M <= 64 are where the pipeline is the faster one: M 64, N 8192, K 8192 bf16 41.0 / 43.5 us (every workgroup
-// decodes all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
-bool skinny_applies(const GemmParams &p, int b_format)
+// The variants that stream_route chooses from; no others are compiled, and a route to another is refused.
+hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r, hipStream_t stream)
 {
-    if (p.K <= 1024) return false;
-    if (p.M > 64) return tile_of(p, b_format) != kNone;
-    if (b_format == ATB_FMT_BF16 && p.N % 2 == 0 && p.N <= 32 * 256) return p.M <= 48;
-    if (b_format == ATB_FMT_BFP16 && p.N > 64 * 256) return p.M <= 48;
-    return true;
-}
-
-hipError_t launch_skinny(const GemmParams &p, int b_format, hipStream_t stream)
-{
-    if (p.M > 64) {
-        const int t = tile_of(p, b_format);
-        if (b_format == ATB_FMT_BFP16) return t == k64x32 ? launch<kBBfp, 4, 2, 8>(p, stream) : launch<kBBfp, 4, 4, 8>(p, stream);
-        if (b_format == ATB_FMT_BF16)
-            return t == k64x64 ? launch<kBRow, 4, 4, 8>(p, stream) : launch<kBRow, 4, 8, 4, 2>(p, stream);
-        return t == k64x32 ? launch<kBT, 4, 2, 8>(p, stream) : t == k64x64 ? launch<kBT, 4, 4, 8>(p, stream) : launch<kBT, 8, 4, 4>(p, stream);
-    }
-    const int nb = column_blocks(p.N);
+    const int form = 100 * r.nb + r.waves;
     if (b_format == ATB_FMT_BFP16) {
-        if (nb == 2) return launch_rows<kBBfp, 2, 16>(p, stream);
-        if (nb == 4) return launch_rows<kBBfp, 4, 8>(p, stream);
-        return launch_rows<kBBfp, 8, 8>(p, stream);
+        if (form == 216) return launch_rows<kBBfp, 2, 16, 4>(p, r, stream);
+        if (form == 408) return launch_rows<kBBfp, 4, 8, 4>(p, r, stream);
+        if (form == 808) return launch_rows<kBBfp, 8, 8, 3>(p, r, stream);
+        if (form == 208 && r.mb == 4) return launch<kBBfp, 4, 2, 8>(p, r, stream);
+    } else if (b_format == ATB_FMT_BF16_T) {
+        if (form == 208) return launch_rows<kBT, 2, 8, 4>(p, r, stream);
+        if (form == 404 && r.mb == 8) return launch<kBT, 8, 4, 4>(p, r, stream);
+        if (form == 404) return launch_rows<kBT, 4, 4, 4>(p, r, stream);
+        if (form == 804) return launch_rows<kBT, 8, 4, 4>(p, r, stream);
+        if (form == 408 && r.mb == 4) return launch<kBT, 4, 4, 8>(p, r, stream);
+    } else if (p.N % 2 != 0) {
+        if (form == 208) return launch_rows<kBRowOdd, 2, 8, 4>(p, r, stream);
+    } else {
+        if (form == 208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
+        if (form == 404) return launch_rows<kBRow, 4, 4, 4>(p, r, stream);
+        if (form == 804 && r.depth == 2) return launch<kBRow, 4, 8, 4, 2>(p, r, stream);
+        if (form == 804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
+        if (form == 408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
     }
-    if (b_format == ATB_FMT_BF16_T) {
-        if (nb == 2) return launch_rows<kBT, 2, 8>(p, stream);
-        if (nb == 4) return launch_rows<kBT, 4, 4>(p, stream);
-        return launch_rows<kBT, 8, 4>(p, stream);
-    }
-    if (p.N % 2 != 0) return launch_rows<kBRowOdd, 2, 8>(p, stream);
-    if (nb == 2) return launch_rows<kBRow, 2, 8>(p, stream);
-    if (nb == 4) return launch_rows<kBRow, 4, 4>(p, stream);
-    return launch_rows<kBRow, 8, 4>(p, stream);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace atb

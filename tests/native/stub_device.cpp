@@ -2,7 +2,7 @@
 // argument handling (atb_api.cpp) and the model / selector (atb_model.cpp) can be linked into a plain
 // host program and run under AddressSanitizer + UndefinedBehaviorSanitizer.  Every launch "fails" with
 // hipErrorNoDevice, which is also what the real library reports on a machine without a GPU.
-#include "atb_internal.h"
+#include "atb_route.h"
 
 namespace atb {
 namespace {
@@ -19,6 +19,7 @@ Instance make(int T_MA, int T_MC, int T_K, int T_N, int wm, int wn, int lds, boo
     i.eff_scale = 1.0; i.lone_cap = 0.0;
     i.launch = &no_device;
     i.launch_fmt = fmt ? &no_device_fmt : nullptr;
+    i.hands_over = (wm * wn < 4);
     i.has_b_transposed = fmt && T_K == 64 && T_MC * T_N >= 128 * 256;
     return i;
 }
@@ -38,6 +39,7 @@ int find_instance(int T_MA, int T_MC, int T_K, int T_N)
 }
 hipError_t launch_quantize(const float *, int64_t, int8_t *, uint8_t *, int64_t, int64_t, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_decode(const int8_t *, const uint8_t *, uint16_t *, int64_t, int64_t, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_skinny(const GemmParams &, int, const StreamRoute &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_mfma_probe(float *, unsigned long long *, int, int, int, int, hipStream_t) { return hipErrorNoDevice; }
 double mfma_probe_flop(int workgroups, int iters) { return 8.0 * workgroups * iters * 32.0 * 32768.0; }
 size_t mfma_probe_sink_bytes(int workgroups) { return (size_t)workgroups * 512 * 4; }

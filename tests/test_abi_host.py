@@ -284,3 +284,33 @@ def test_selector_against_measured_sweep():
         got = meas[inst.index(pick.tiles())]
         assert got >= 0.95 * max(meas), ((M, N, K), pick.tiles(), got, inst[meas.index(max(meas))], max(meas))
         assert abs(pick.pred_flops / 1e12 / got - 1) < (0.30 if M < 32 else 0.20), ((M, N, K), pick.tiles(), pick.pred_flops / 1e12, got)
+
+
+def test_plans_report_the_kernel_that_runs():
+    """A plan that the streaming kernel takes says so, with that kernel's launch; the others report their instance's."""
+    info = {i: None for i in atb.instances()}
+    for tiles in info:
+        g = atb.Gemm(256, 256, 256, *tiles)
+        assert not g.streams()
+        info[tiles] = g.launch_info()
+        g.close()
+    def plan(M, N, K, tiles, b="bf16", c="bf16"):
+        g = atb.Gemm(M, N, K, *tiles, b_format=b, c_format=c)
+        out = g.streams(), g.launch_info()
+        g.close()
+        return out
+    # (M, N, K), tiles, b, c -> rows x columns of a workgroup's tile, waves
+    for shape, tiles, b, c, rows, cols, waves in [
+            ((16, 8192, 8192), (32, 32, 256, 64), "bf16", "bf16", 16, 32, 8), ((16, 8192, 8192), (64, 64, 128, 128), "bf16", "bf16", 16, 32, 8),
+            ((64, 14336, 4096), (64, 64, 128, 128), "bfp16", "bf16", 64, 64, 8), ((16, 5001, 4096), (32, 32, 256, 64), "bf16", "bf16", 16, 32, 8),
+            ((16, 2000, 4096), (32, 32, 256, 64), "bfp16", "bfp16", 16, 32, 16), ((128, 4096, 4096), (256, 256, 64, 256), "bf16_t", "bf16", 64, 32, 8),
+            ((500, 4096, 14336), (64, 64, 128, 128), "bf16", "bf16", 64, 128, 4)]:
+        M, N, K = shape
+        streams, i = plan(M, N, K, tiles, b, c)
+        n = -(-N // 64) * 64 if c == "bfp16" else N
+        assert streams and i.threads == 64 * waves and i.lds_bytes == waves * 16 * (cols + 4) * 4
+        assert i.workgroups == -(-(-(-M // rows) * -(-n // cols)) // 8) * 8
+    for shape, tiles in [((16, 8192, 1024), (32, 32, 256, 64)), ((16, 8192, 8192), (32, 64, 64, 64)), ((8192, 8192, 8192), (64, 64, 128, 128))]:
+        streams, i = plan(*shape, tiles)
+        assert not streams and (i.threads, i.lds_bytes) == (info[tiles].threads, info[tiles].lds_bytes)
+    assert atb.lib().atb_gemm_streams(None) == 0
