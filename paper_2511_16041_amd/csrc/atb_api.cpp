@@ -31,7 +31,9 @@ atb_status hip_status(hipError_t e)
 atb::StreamRoute plan_route(const atb_gemm *g)
 {
     const bool over = g->b_format == ATB_FMT_BF16_T || atb::instance(g->instance).hands_over;
-    return over ? atb::stream_route(g->proto, g->b_format) : atb::StreamRoute{};
+    if (!over || g->proto.K <= atb::kStreamMinK) return {};
+    const int cus = atb::compute_units();
+    return atb::stream_route(g->proto, g->b_format, cus > 0 ? cus : atb::kDefaultCUs);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

@@ -8,6 +8,8 @@
 //   value = m * 2^(E - 133).
 // All kernels here are HBM-bound streaming kernels.  The BFP16
 // buffer is K-panel-major (see include/atb.h): [panel of 64 k][row][64] mantissas, [panel][row][8] exponents.
+#include <mutex>
+
 #include "atb_route.h"
 
 namespace atb {
@@ -135,6 +137,25 @@ __global__ void __launch_bounds__(256) decode_panels(const int8_t *__restrict__ 
 }
 
 }  // namespace
+
+// Looked up once per device; the table is
+// guarded, so concurrent first launches from several threads are fine, and the lookup enqueues nothing
+// (a first launch inside a stream capture is as good as any other).
+int compute_units()
+{
+    constexpr int kMaxDevices = 64;
+    static std::mutex guard;
+    static int cached[kMaxDevices] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+    std::lock_guard<std::mutex> lock(guard);
+    if (cached[dev] == 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) return 0;
+        cached[dev] = cus;
+    }
+    return cached[dev];
+}
 
 hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae, int64_t M, int64_t K,
                            hipStream_t stream)

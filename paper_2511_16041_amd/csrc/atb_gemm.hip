@@ -32,7 +32,6 @@
 // the first operand and the A fragment as the second, so a lane of the result holds one row m
 // (= l % MB) and groups of 4 consecutive columns (n = 8*g + 4*(l/MB) + 0..3) -> 8-byte bf16 stores.
 #include <algorithm>
-#include <mutex>
 
 #include "atb_internal.h"
 
@@ -1487,25 +1486,6 @@ __global__ void __launch_bounds__(S::NT, S::OCC) atb_gemm_kernel(const GemmParam
     } else {
         tile_loop<S, VEC, 0, BBFP, CBFP, BTR>(p, lds);
     }
-}
-
-// Compute units of the current device (0 if there is none).  Looked up once per device; the table is
-// guarded, so concurrent first launches from several threads are fine, and the lookup enqueues nothing
-// (a first launch inside a stream capture is as good as any other).
-inline int compute_units()
-{
-    constexpr int kMaxDevices = 64;
-    static std::mutex guard;
-    static int cached[kMaxDevices] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-    std::lock_guard<std::mutex> lock(guard);
-    if (cached[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) return 0;
-        cached[dev] = cus;
-    }
-    return cached[dev];
 }
 
 template <class S, bool VEC, bool BBFP, bool CBFP, bool BTR = false>

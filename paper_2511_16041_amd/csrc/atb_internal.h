@@ -48,6 +48,9 @@ const Instance &instance(int i);
 // index of the instance with these factors, or -1
 int find_instance(int T_MA, int T_MC, int T_K, int T_N);
 
+// Compute units of the current device, 0 if there is none.
+int compute_units();
+
 // The streaming kernel for few rows (atb_skinny.hip), in the form that stream_route (atb_route.h) chose.  Takes every storage format
 // that a plan admits; b_format as in atb_format, C in BFP16 where p.Cm is set.
 struct StreamRoute;

@@ -62,6 +62,8 @@ inline DecodeRoute decode_route(int64_t M, int64_t K, bool out_on_lines)
     return {0, false, n <= kMaxWorkgroups256 ? n : 0};
 }
 
+constexpr int kStreamMinK = 1024;        // reductions up to here stay with the tile pipeline
+
 // The streaming kernel's variant for a problem: a workgroup takes a tile of 16 mb rows x 16 nb columns with `waves` waves,
 // each with `depth` panels of K in flight.  mb == 0: the problem stays with the tile pipeline.
 struct StreamRoute {
@@ -81,7 +83,7 @@ inline int64_t stream_workgroups(const GemmParams &p, const StreamRoute &r) { re
 
 // M <= 64: 16 nb columns per workgroup, the narrowest of 32, 64 and 128 that needs no more workgroups than there are CUs.
 // Measured (us, M = 16, bf16 B): N = 14336, K = 4096: 35.4 / 24.4 / 31.9 with 32 / 64 / 128 columns; N = 28672: 59 / 54 / 44.
-inline int stream_column_blocks(int N) { return N <= 32 * kDefaultCUs ? 2 : N <= 64 * kDefaultCUs ? 4 : 8; }
+inline int stream_column_blocks(int N, int cus) { return N <= 32 * cus ? 2 : N <= 64 * cus ? 4 : 8; }
 
 // More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
 // none where the tile pipeline is as good or better.  Measured in us, the pipeline before / this kernel now:
@@ -92,14 +94,14 @@ inline int stream_column_blocks(int N) { return N <= 32 * kDefaultCUs ? 2 : N <=
 //   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
 //             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
 //   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64)
-inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format)
+inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int cus)
 {
     const bool rows_of_b = (b_format == ATB_FMT_BF16);
     if (rows_of_b && p.N % 2 != 0) return {};
-    if (tile_count(p, 64, 32) <= kDefaultCUs) return rows_of_b ? StreamRoute{} : StreamRoute{4, 2, 8, 1};
-    if (tile_count(p, 64, 64) <= kDefaultCUs) return {4, 4, 8, 1};
-    if (rows_of_b && p.K >= 4096 && tile_count(p, 64, 128) <= kDefaultCUs) return {4, 8, 4, 2};
-    if (b_format == ATB_FMT_BF16_T && tile_count(p, 128, 64) <= kDefaultCUs) return {8, 4, 4, 1};
+    if (tile_count(p, 64, 32) <= cus) return rows_of_b ? StreamRoute{} : StreamRoute{4, 2, 8, 1};
+    if (tile_count(p, 64, 64) <= cus) return {4, 4, 8, 1};
+    if (rows_of_b && p.K >= 4096 && tile_count(p, 64, 128) <= cus) return {4, 8, 4, 2};
+    if (b_format == ATB_FMT_BF16_T && tile_count(p, 128, 64) <= cus) return {8, 4, 4, 1};
     return {};
 }
 
@@ -109,11 +111,12 @@ inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format)
 // decodes all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
 // Waves: four where their requests already fill the CU's share (64 and 128 columns of bf16 B: 24.4 against 28.1 us with
 // eight), eight or sixteen where more hands are needed to decode B.
-inline StreamRoute stream_route(const GemmParams &p, int b_format)
+// cus: CUs of the device (a partition of the chip has fewer than 256).
+inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
 {
-    if (p.K <= 1024) return {};
-    if (p.M > 64) return stream_route_many_rows(p, b_format);
-    const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N);
+    if (p.K <= kStreamMinK) return {};
+    if (p.M > 64) return stream_route_many_rows(p, b_format, cus);
+    const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N, cus);
     if (b_format == ATB_FMT_BFP16) {
         if (nb == 8 && mb == 4) return {};
         return {mb, nb, nb == 2 ? 16 : 8, 1};

@@ -204,8 +204,21 @@ static void model_paths()
 }
 
 // The host-side rules that send a problem to a kernel.
+static atb::GemmParams problem(int M, int N, int K, bool c_bfp16 = false)
+{
+    atb::GemmParams p{};
+    p.M = M; p.N = N; p.K = K;
+    p.k_panels = (K + 63) / 64;
+    p.n_panels = c_bfp16 ? (N + 63) / 64 : 0;
+    return p;
+}
+
 static void route_paths()
 {
+    // streaming kernel: the CUs that there are decide what one tile per CU means
+    EXPECT(atb::stream_route(problem(16, 14336, 4096), ATB_FMT_BFP16, 256).nb == 4 && atb::stream_route(problem(16, 14336, 4096), ATB_FMT_BFP16, 512).nb == 2);
+    EXPECT(atb::stream_route(problem(256, 4096, 4096), ATB_FMT_BF16, 256).streams() && !atb::stream_route(problem(256, 4096, 4096), ATB_FMT_BF16, 32).streams());
+    EXPECT(atb::stream_route(problem(128, 4096, 4096), ATB_FMT_BF16_T, 256).nb == 2 && !atb::stream_route(problem(128, 4096, 4096), ATB_FMT_BF16_T, 32).streams());
     using atb::decode_route;
     using atb::quantize_route;
     // quantiser: 4 rows per workgroup while those are few, 16 for many narrow rows, else 8

@@ -39,6 +39,7 @@ int find_instance(int T_MA, int T_MC, int T_K, int T_N)
 }
 hipError_t launch_quantize(const float *, int64_t, int8_t *, uint8_t *, int64_t, int64_t, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_decode(const int8_t *, const uint8_t *, uint16_t *, int64_t, int64_t, hipStream_t) { return hipErrorNoDevice; }
+int compute_units() { return 0; }
 hipError_t launch_skinny(const GemmParams &, int, const StreamRoute &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_mfma_probe(float *, unsigned long long *, int, int, int, int, hipStream_t) { return hipErrorNoDevice; }
 double mfma_probe_flop(int workgroups, int iters) { return 8.0 * workgroups * iters * 32.0 * 32768.0; }
