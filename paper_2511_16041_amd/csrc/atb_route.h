@@ -86,21 +86,30 @@ inline int64_t stream_workgroups(const GemmParams &p, const StreamRoute &r) { re
 inline int stream_column_blocks(int N, int cus) { return N <= 32 * cus ? 2 : N <= 64 * cus ? 4 : 8; }
 
 // More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
-// none where the tile pipeline is as good or better.  Measured in us, the pipeline before / this kernel now:
-//   B bf16    M 128, N 8192, K 8192: 54.4 / 47.0 (64 x 64)   M 256, 4096, 4096: 22.3 / 19.5 (64 x 64)
-//             M 512, 4096, 14336: 120 / 80 (64 x 128)        M 256, 8192, 8192: 70.3 / 54.9 (64 x 128)
-//             not 64 x 32 (M 256, 2048, 2048: 9.9 / 10.4), nor 64 x 128 below K = 4096 (M 1024, 2048, 2048: 16.3 / 17.5),
-//             nor odd N (M 512, 5001, 4096: 61 / 70)
+// none where the tile pipeline is as good or better.  Measured in us, the pipeline / this kernel:
+//   B bf16    64 x 64: M 128, 8192, 8192 54.4 / 47.0, M 256, 4096, 4096 22.3 / 19.5, M 1024, 1024, 1032 1.10 x as fast; but where the
+//             pipeline has whole K-steps and little K it is level in memory and behind in cache: M 192 .. 4096 with 144 .. 256 tiles,
+//             K 1296 .. 2048: 0.96 - 1.09 x cold, 0.91 - 1.02 x hot (the pipeline pads K to 512: K 1032 .. 1152 1.05 - 1.16 x, from
+//             2560 on 1.04 - 1.3 x)
+//             64 x 128: M 512, 4096, 14336 120 / 80, M 256, 8192, 8192 70.3 / 54.9; K 4096 .. 4864 0.94 - 1.1 x over 14 shapes, 5120
+//             1.0 - 1.1 x, 5632 and 6144 1.02 - 1.2 x
+//             not 64 x 32 (M 256, 2048, 2048 9.9 / 10.4) nor odd N (M 512, 5001, 4096 61 / 70), nor 64 x 64 where the pipeline's 32 x 64
+//             tiles fit one to a CU (rows just above a multiple of 64: M 193, 2304 and M 129, 3000, K 1032 .. 8192 0.72 - 0.91 x)
 //   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
 //             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
-//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64)
+//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64); 32 x 64 tiles one to a CU: K 1032 and 1152
+//             1.04 - 1.16 x, from 1296 on 0.92 - 1.07 x
 inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int cus)
 {
-    const bool rows_of_b = (b_format == ATB_FMT_BF16);
-    if (rows_of_b && p.N % 2 != 0) return {};
-    if (tile_count(p, 64, 32) <= cus) return rows_of_b ? StreamRoute{} : StreamRoute{4, 2, 8, 1};
-    if (tile_count(p, 64, 64) <= cus) return {4, 4, 8, 1};
-    if (rows_of_b && p.K >= 4096 && tile_count(p, 64, 128) <= cus) return {4, 8, 4, 2};
+    const bool small_tiles = tile_count(p, 32, 64) <= cus;            // the pipeline's 32 x 64 tiles: one per CU or fewer
+    if (b_format == ATB_FMT_BF16) {
+        if (p.N % 2 != 0 || tile_count(p, 64, 32) <= cus) return {};
+        if (tile_count(p, 64, 64) <= cus) return !small_tiles && (p.K <= 1152 || p.K > 2048) ? StreamRoute{4, 4, 8, 1} : StreamRoute{};
+        if (tile_count(p, 64, 128) <= cus && p.K >= 5632) return {4, 8, 4, 2};
+        return {};
+    }
+    if (tile_count(p, 64, 32) <= cus) return {4, 2, 8, 1};
+    if (tile_count(p, 64, 64) <= cus) return b_format == ATB_FMT_BFP16 && small_tiles && p.K > 1152 ? StreamRoute{} : StreamRoute{4, 4, 8, 1};
     if (b_format == ATB_FMT_BF16_T && tile_count(p, 128, 64) <= cus) return {8, 4, 4, 1};
     return {};
 }

@@ -227,6 +227,20 @@ static void route_paths()
     EXPECT(quantize_route(1000000, 8).steps == 8 && quantize_route(1000000, 8).workgroups == 62500);
     EXPECT(quantize_route(200000, 256).steps == 8 && quantize_route(150000, 384).steps == 4 && quantize_route(32768, 64).steps == 4);
     EXPECT(quantize_route(1, 8).steps == 2 && quantize_route(1, 8).workgroups == 1);
+    // above 64 rows: {row blocks, column blocks}, {0, 0} for the tile pipeline
+    const struct { int M, N, K, fmt, mb, nb; } many[] = {
+        {256, 4096, 4096, ATB_FMT_BF16, 4, 4},   {1024, 1024, 1032, ATB_FMT_BF16, 4, 4},  {1024, 1024, 1152, ATB_FMT_BF16, 4, 4},
+        {1024, 1024, 1160, ATB_FMT_BF16, 0, 0},  {1024, 1024, 2048, ATB_FMT_BF16, 0, 0},  {1024, 1024, 2056, ATB_FMT_BF16, 4, 4},
+        {193, 2304, 4096, ATB_FMT_BF16, 0, 0},   {129, 3000, 1032, ATB_FMT_BF16, 0, 0},   {300, 3000, 4096, ATB_FMT_BF16, 4, 4},
+        {1024, 2048, 4096, ATB_FMT_BF16, 0, 0},  {512, 4096, 4096, ATB_FMT_BF16, 0, 0},   {1024, 2048, 5624, ATB_FMT_BF16, 0, 0},
+        {1024, 2048, 5632, ATB_FMT_BF16, 4, 8},  {512, 4096, 14336, ATB_FMT_BF16, 4, 8},  {256, 4097, 4096, ATB_FMT_BF16, 0, 0},
+        {256, 2048, 4096, ATB_FMT_BF16, 0, 0},   {256, 2048, 4096, ATB_FMT_BFP16, 4, 2},  {193, 2304, 1152, ATB_FMT_BFP16, 4, 4},
+        {193, 2304, 1160, ATB_FMT_BFP16, 0, 0},  {300, 3000, 4096, ATB_FMT_BFP16, 4, 4},  {1024, 2048, 8192, ATB_FMT_BFP16, 0, 0},
+        {193, 2304, 4096, ATB_FMT_BF16_T, 4, 4}, {512, 4096, 4096, ATB_FMT_BF16_T, 8, 4}, {1024, 4096, 4096, ATB_FMT_BF16_T, 0, 0}};
+    for (const auto &c : many) {
+        const atb::StreamRoute r = atb::stream_route(problem(c.M, c.N, c.K), c.fmt, 256);
+        if (r.mb != c.mb || r.nb != c.nb) { std::printf("route of %d x %d x %d, format %d: %d x %d blocks\n", c.M, c.N, c.K, c.fmt, r.mb, r.nb); ++failures; }
+    }
     // as many rows as one launch can take: 2^28 of up to 512 columns to quantise, M K / 8 < 2^32 blocks to decode
     EXPECT(quantize_route(((int64_t)1 << 27) + 8, 512).steps == 8 && quantize_route(((int64_t)1 << 27) + 8, 512).workgroups == (1 << 23) + 1);
     EXPECT(quantize_route(((int64_t)1 << 28) - 16, 8).workgroups == (1 << 24) - 1 && quantize_route((int64_t)1 << 28, 8).workgroups == 0);

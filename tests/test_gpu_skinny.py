@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1, 2, 1032), (16, 32, 1088), (17, 33, 1032), (48, 34, 1096), (64, 264, 1024 + 64), (33, 1001, 1160), (64, 8191, 1032),
           (48, 8194, 1032), (49, 8264, 1032), (64, 16386, 1032), (16, 16448, 1096),
           # above 64 rows: 64 x 32 and 64 x 64 tiles, then (B row-major / transposed) 64 x 128 / 128 x 64
-          (65, 72, 1032), (130, 2802, 1096), (260, 3400, 4104)]
+          (65, 72, 1032), (130, 2802, 1096), (260, 3400, 4104), (130, 4802, 1096), (260, 3400, 5640)]
 
 
 @pytest.mark.parametrize("exact", [True, False])
