@@ -114,10 +114,45 @@ inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int
     return {};
 }
 
-// Where the streaming kernel takes over from the tile pipeline, and in what form.  K <= 1024: there every instance adds in the same order and gives
-// the same bits, and the call is bound by its launch either way (M 16, N 8192, K 1088: 8.3 / 5.7 us).  The two
-// exceptions at M <= 64 are where the pipeline is the faster one: M 64, N 8192, K 8192 bf16 41.0 / 43.5 us (every workgroup
-// decodes all of A, at 32 columns too often), and M 64, N 28672, K 8192 BFP16 72.3 / 82.8 us (out of registers at 128 columns).
+// At most 64 rows: whether the streaming kernel is at least as fast as the pipeline.  The lines lie where both sides were measured, over
+// M 1 .. 64, N 32 .. 151936, K 1032 .. 14336, operands from memory (cold) and from a cache (hot); figures are the pipeline's time over
+// this kernel's.  What they come down to: one tile per CU is where this kernel is at its best; with fewer tiles than CUs, or a second
+// round of them that is nearly empty, CUs idle, and the pipeline, whose requests go straight to LDS, gets more out of the others.
+inline bool stream_few_rows(const GemmParams &p, int b_format, int cus)
+{
+    const int M = p.M, N = p.N, K = p.K;
+    if (b_format == ATB_FMT_BFP16) return N <= 64 * cus || M <= 48;        // 1.0 - 1.9; M 64, N 28672, K 8192 0.87: out of registers
+    if (b_format == ATB_FMT_BF16_T) {
+        // 1.35 - 3 up to one tile per CU; beyond, N 33000 .. 48000 0.70 - 0.99, 57344 and 128256 0.90 - 1.17, but 1.01 - 1.29 for N 66000 ..
+        // 90000 and 151936, where 256 columns (the pipeline's tile) come to more rounds than 128
+        if (N <= 128 * cus) return true;
+        const int64_t rounds128 = ((N + 127) / 128 + cus - 1) / cus, rounds256 = ((N + 255) / 256 + cus - 1) / cus;
+        return rounds128 < 2 * rounds256;
+    }
+    if (N % 2 != 0) {
+        // 32 columns per workgroup whatever N is: 1.03 - 2.1 up to N = 24576.  Then the pipeline's 128-column tiles fill more than three
+        // quarters of the CUs, until they need a second round: M > 32 0.78 - 1.0 cold (1.04 - 1.2 at K = 1032), M <= 32 1.01 - 1.4 up to
+        // 30720, 0.91 - 1.02 cold from there at K >= 4096.  Beyond: M <= 48 0.98 - 1.5, M 49 .. 64 at K >= 4096 0.94 - 1.05.
+        if (N <= 96 * cus) return true;
+        if (N > 128 * cus) return M <= 48 || K < 4096;
+        return M > 32 ? K < 1536 : N <= 120 * cus || K < 4096;
+    }
+    if (N <= 32 * cus) return M <= 48;                                     // 0.97 - 2.2; M 64, N = K = 8192 0.94: every workgroup decodes all of A
+    if (N <= 64 * cus) {
+        if (M > 32) return true;                                           // 1.0 - 1.3
+        // 129 to 256 workgroups of 64 columns.  Rows of B that are not whole lines and one or two rows of A: the pipeline skips the
+        // dead rows of its tile, 0.88 - 1.0 from K = 2560 (under 208 workgroups) or above 4096 on.
+        const bool ragged = N % 64 != 0 && M <= 2;
+        if (N < 36 * cus) return K < 2048;                                 // 0.97 - 1.25 cold below, 0.71 - 1.09 from 2048 on
+        if (N < 52 * cus) return K < (ragged ? 2560 : 4096);               // 0.98 - 1.17 below, 0.92 - 1.05 cold from 4096 on
+        return !ragged || K <= 4096;                                       // 0.96 - 1.19
+    }
+    if (N <= 128 * cus) return M <= 48;                                    // 1.03 - 1.6; M 49 .. 64 0.78 - 1.08
+    // more than one workgroup of 128 columns per CU: 0.76 - 1.0 (K < 2048 1.18 - 1.3) until the second round is half full, 0.97 - 1.4 then
+    return M <= 48 && (K < 2048 || N >= 192 * cus);
+}
+
+// Where the streaming kernel takes over from the tile pipeline, and in what form.
 // Waves: four where their requests already fill the CU's share (64 and 128 columns of bf16 B: 24.4 against 28.1 us with
 // eight), eight or sixteen where more hands are needed to decode B.
 // cus: CUs of the device (a partition of the chip has fewer than 256).
@@ -125,13 +160,10 @@ inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
 {
     if (p.K <= kStreamMinK) return {};
     if (p.M > 64) return stream_route_many_rows(p, b_format, cus);
+    if (!stream_few_rows(p, b_format, cus)) return {};
     const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N, cus);
-    if (b_format == ATB_FMT_BFP16) {
-        if (nb == 8 && mb == 4) return {};
-        return {mb, nb, nb == 2 ? 16 : 8, 1};
-    }
+    if (b_format == ATB_FMT_BFP16) return {mb, nb, nb == 2 ? 16 : 8, 1};
     if (b_format == ATB_FMT_BF16 && p.N % 2 != 0) return {mb, 2, 8, 1};
-    if (b_format == ATB_FMT_BF16 && nb == 2 && mb == 4) return {};
     return {mb, nb, nb == 2 ? 8 : 4, 1};
 }
 

@@ -351,7 +351,7 @@ hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r
         if (form == 208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
         if (form == 404) return launch_rows<kBRow, 4, 4, 4>(p, r, stream);
         if (form == 804 && r.depth == 2) return launch<kBRow, 4, 8, 4, 2>(p, r, stream);
-        if (form == 804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
+        if (form == 804) return launch_rows<kBRow, 8, 4, 3>(p, r, stream);
         if (form == 408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
     }
     return hipErrorInvalidValue;

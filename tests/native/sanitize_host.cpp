@@ -213,6 +213,17 @@ static atb::GemmParams problem(int M, int N, int K, bool c_bfp16 = false)
     return p;
 }
 
+struct Expected { int M, N, K, fmt, mb, nb; };
+
+static void expect_route(const Expected &c)
+{
+    const atb::StreamRoute r = atb::stream_route(problem(c.M, c.N, c.K), c.fmt, 256);
+    if (r.mb != c.mb || r.nb != c.nb) {
+        std::printf("route of %d x %d x %d, format %d: %d x %d blocks\n", c.M, c.N, c.K, c.fmt, r.mb, r.nb);
+        ++failures;
+    }
+}
+
 static void route_paths()
 {
     // streaming kernel: the CUs that there are decide what one tile per CU means
@@ -228,7 +239,7 @@ static void route_paths()
     EXPECT(quantize_route(200000, 256).steps == 8 && quantize_route(150000, 384).steps == 4 && quantize_route(32768, 64).steps == 4);
     EXPECT(quantize_route(1, 8).steps == 2 && quantize_route(1, 8).workgroups == 1);
     // above 64 rows: {row blocks, column blocks}, {0, 0} for the tile pipeline
-    const struct { int M, N, K, fmt, mb, nb; } many[] = {
+    const Expected many[] = {
         {256, 4096, 4096, ATB_FMT_BF16, 4, 4},   {1024, 1024, 1032, ATB_FMT_BF16, 4, 4},  {1024, 1024, 1152, ATB_FMT_BF16, 4, 4},
         {1024, 1024, 1160, ATB_FMT_BF16, 0, 0},  {1024, 1024, 2048, ATB_FMT_BF16, 0, 0},  {1024, 1024, 2056, ATB_FMT_BF16, 4, 4},
         {193, 2304, 4096, ATB_FMT_BF16, 0, 0},   {129, 3000, 1032, ATB_FMT_BF16, 0, 0},   {300, 3000, 4096, ATB_FMT_BF16, 4, 4},
@@ -237,10 +248,25 @@ static void route_paths()
         {256, 2048, 4096, ATB_FMT_BF16, 0, 0},   {256, 2048, 4096, ATB_FMT_BFP16, 4, 2},  {193, 2304, 1152, ATB_FMT_BFP16, 4, 4},
         {193, 2304, 1160, ATB_FMT_BFP16, 0, 0},  {300, 3000, 4096, ATB_FMT_BFP16, 4, 4},  {1024, 2048, 8192, ATB_FMT_BFP16, 0, 0},
         {193, 2304, 4096, ATB_FMT_BF16_T, 4, 4}, {512, 4096, 4096, ATB_FMT_BF16_T, 8, 4}, {1024, 4096, 4096, ATB_FMT_BF16_T, 0, 0}};
-    for (const auto &c : many) {
-        const atb::StreamRoute r = atb::stream_route(problem(c.M, c.N, c.K), c.fmt, 256);
-        if (r.mb != c.mb || r.nb != c.nb) { std::printf("route of %d x %d x %d, format %d: %d x %d blocks\n", c.M, c.N, c.K, c.fmt, r.mb, r.nb); ++failures; }
-    }
+    const Expected few[] = {
+        // even N, row-major: one tile of 32, 64, 128 columns per CU, and where the pipeline takes its place
+        {16, 8192, 8192, ATB_FMT_BF16, 1, 2},    {48, 8192, 8192, ATB_FMT_BF16, 3, 2},    {49, 8192, 8192, ATB_FMT_BF16, 0, 0},
+        {16, 8192, 1024, ATB_FMT_BF16, 0, 0},    {16, 8194, 2040, ATB_FMT_BF16, 1, 4},    {16, 8256, 2048, ATB_FMT_BF16, 0, 0},
+        {33, 8256, 8192, ATB_FMT_BF16, 3, 4},    {64, 8256, 8192, ATB_FMT_BF16, 4, 4},    {16, 9216, 4088, ATB_FMT_BF16, 1, 4},
+        {16, 9216, 4096, ATB_FMT_BF16, 0, 0},    {2, 9218, 2560, ATB_FMT_BF16, 0, 0},     {3, 9218, 2560, ATB_FMT_BF16, 1, 4},
+        {16, 13312, 9984, ATB_FMT_BF16, 1, 4},   {1, 13500, 5632, ATB_FMT_BF16, 0, 0},    {1, 13504, 5632, ATB_FMT_BF16, 1, 4},
+        {16, 14336, 4096, ATB_FMT_BF16, 1, 4},   {48, 32768, 4096, ATB_FMT_BF16, 3, 8},   {49, 28672, 4096, ATB_FMT_BF16, 0, 0},
+        {16, 33000, 4096, ATB_FMT_BF16, 0, 0},   {16, 33000, 2040, ATB_FMT_BF16, 1, 8},   {16, 49152, 4096, ATB_FMT_BF16, 1, 8},
+        // odd N
+        {64, 24575, 8192, ATB_FMT_BF16, 4, 2},   {33, 24577, 1536, ATB_FMT_BF16, 0, 0},   {33, 24577, 1528, ATB_FMT_BF16, 3, 2},
+        {32, 30719, 8192, ATB_FMT_BF16, 2, 2},   {32, 30721, 4096, ATB_FMT_BF16, 0, 0},   {64, 50257, 4096, ATB_FMT_BF16, 0, 0},
+        {48, 50257, 4096, ATB_FMT_BF16, 3, 2},   {64, 50257, 2048, ATB_FMT_BF16, 4, 2},
+        // B^T in bf16 and in BFP16
+        {64, 32768, 8192, ATB_FMT_BF16_T, 4, 8}, {1, 33000, 4096, ATB_FMT_BF16_T, 0, 0},  {16, 65536, 4096, ATB_FMT_BF16_T, 0, 0},
+        {16, 70000, 4096, ATB_FMT_BF16_T, 1, 8}, {16, 100000, 4096, ATB_FMT_BF16_T, 0, 0}, {64, 16384, 4096, ATB_FMT_BFP16, 4, 4},
+        {48, 50000, 4096, ATB_FMT_BFP16, 3, 8},  {49, 16448, 4096, ATB_FMT_BFP16, 0, 0}};
+    for (const auto &c : many) expect_route(c);
+    for (const auto &c : few) expect_route(c);
     // as many rows as one launch can take: 2^28 of up to 512 columns to quantise, M K / 8 < 2^32 blocks to decode
     EXPECT(quantize_route(((int64_t)1 << 27) + 8, 512).steps == 8 && quantize_route(((int64_t)1 << 27) + 8, 512).workgroups == (1 << 23) + 1);
     EXPECT(quantize_route(((int64_t)1 << 28) - 16, 8).workgroups == (1 << 24) - 1 && quantize_route((int64_t)1 << 28, 8).workgroups == 0);
