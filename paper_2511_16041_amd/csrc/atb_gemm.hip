@@ -309,9 +309,12 @@ struct TileKernel {
     static constexpr int BPT = BBFP ? 0 : (ROLE == 0 || ROLE == 3) ? S::B_SLABS : (ROLE == 1) ? S::BO : (ROLE == 2) ? S::B_SLABS - S::BO : 0;   // bf16 B chunks per thread per tile
     static constexpr int BTPT = !BBFP ? 0 : (ROLE == 1 || ROLE == 4) ? 0 : S::BT_SLABS;               // BFP16 B chunks (16 mantissas) per thread per tile
     // Odd N: a B tile passes through registers.  LAG: it stays there for a K-step (in K-step kt the tile fetched during
-    // kt - 1 is stored, the one after it fetched), so that no store waits for a request of its own K-step.  For the tiles
-    // below 256 x 256: 1500 x 3001 x 2056 50.4 -> 47.0 us; those have no registers to hold it (4000 x 4001 x 4096: 157 -> 192).
-    static constexpr bool LAG = !VEC && S::T_MC * S::T_N < 256 * 256;
+    // kt - 1 is shifted and stored, the one after it fetched), so that nothing waits for a request of its own K-step.  For the tiles
+    // between: 1500 x 3001 x 2056 50.4 -> 42.7 us.  256 x 256 has no registers to hold it (4000 x 4001 x 4096: 157 -> 192).  The 64 x 64 tiles
+    // share a CU with three to five others, which cover the wait for a request, and a store first thing in a K-step is in the way at
+    // most sizes the selector gives them: 49 x 39829 x 784 -7 %, 8 x 33001 x 1032 -6 % (but 1500 x 4001 x 2056 +10 %); 73 such sizes
+    // are 3 to 5 % faster without.
+    static constexpr bool LAG = !VEC && S::T_MC * S::T_N < 256 * 256 && !(S::T_MC * S::T_N <= 64 * 64 && S::T_K == 64);
     static constexpr int NPAIR_B = BTPT * 8;                                             // B mantissa pairs per thread per tile
     static constexpr int NSTEP_A = NPAIR == 0 ? 0 : SK ? NPAIR / 4 : NPAIR + 2;          // decode items per phase (A sub-tile): pipeline steps, or blocks
     static constexpr int NSTEP_B = NPAIR_B > 0 ? NPAIR_B / S::RHO + 2 : 0;               // ... and for this phase's share of the B tile
@@ -409,6 +412,7 @@ struct TileKernel {
     intx4 a_mant[S::PF][APTN];
     unsigned a_expo[S::PF][APTN];
     intx4 b_raw[BPTN];
+    int b_fifth[BPTN];                 // LAG: the dword after b_raw's four
     unsigned dec[4];                   // bf16 pairs of the BFP16 block being decoded
     float cvf[2][2], ldf[2][2];        // decode pipeline: converted and scaled pairs in flight
     int shift;
@@ -878,10 +882,12 @@ struct TileKernel {
             // every other row is dword-aligned and needs no fifth dword: its lanes ask outside the buffer, which costs no
             // memory access (47.0 -> 45.3 us; not on the tiles that are short of registers for the choice)
             const int hi = __builtin_amdgcn_raw_buffer_load_b32(rs.b, (LAG && sh == 0) ? (int)0x80000000 : al + 16, 0, 0);
-            b_raw[i] = intx4{(int)__builtin_amdgcn_alignbit((unsigned)lo.y, (unsigned)lo.x, sh),
-                             (int)__builtin_amdgcn_alignbit((unsigned)lo.z, (unsigned)lo.y, sh),
-                             (int)__builtin_amdgcn_alignbit((unsigned)lo.w, (unsigned)lo.z, sh),
-                             (int)__builtin_amdgcn_alignbit((unsigned)hi, (unsigned)lo.w, sh)};
+            if constexpr (LAG) {         // shifted when it is stored: here the shift would wait for the request
+                b_raw[i] = lo;
+                b_fifth[i] = hi;
+            } else {
+                b_raw[i] = shifted(lo, hi, sh);
+            }
         }
         if constexpr (i == BPT - 1) {
             if (--b_steps == 0) {
@@ -1002,10 +1008,17 @@ struct TileKernel {
         }
     }
 
+    // Odd N: the 16 bytes that start sh bits into five dwords.
+    static ATB_DEV intx4 shifted(intx4 lo, int hi, int sh)
+    {
+        return intx4{(int)__builtin_amdgcn_alignbit((unsigned)lo.y, (unsigned)lo.x, sh), (int)__builtin_amdgcn_alignbit((unsigned)lo.z, (unsigned)lo.y, sh),
+                     (int)__builtin_amdgcn_alignbit((unsigned)lo.w, (unsigned)lo.z, sh), (int)__builtin_amdgcn_alignbit((unsigned)hi, (unsigned)lo.w, sh)};
+    }
+
     template <int i>
     ATB_DEV void store_b_chunk(char *b_dst)
     {
-        *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16)) = b_raw[i];
+        *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16)) = LAG ? shifted(b_raw[i], b_fifth[i], (b_off[i] & 2) * 8) : b_raw[i];
     }
 
     template <int set>
@@ -1317,7 +1330,10 @@ struct TileKernel {
         if constexpr (S::AB == 4) store_a_all<1>(a_wr[1]);
         if constexpr (VEC && BPT > 0) wait_vm<0>();
         if constexpr (!VEC && !RING) store_b_all(b_wr[1]);
-        if constexpr (LAG) load_b(0);                // the tile that K-step 0 stores
+        // the tile that K-step 0 stores; where the reduction ends before it, nobody reads what is stored, and a request of zeros is a
+        // round trip all the same (8 x 1001 x 72 at 32,32,256,64: 6.9 -> 6.3 us)
+        if constexpr (LAG)
+            if (kt_steps > S::NB) load_b(0);
         __syncthreads();
         if constexpr (RING) b_read_off = 0;
         if constexpr (COMPUTE) read_b_frags_all(0);
