@@ -310,7 +310,7 @@ struct TileKernel {
     static constexpr int BTPT = !BBFP ? 0 : (ROLE == 1 || ROLE == 4) ? 0 : S::BT_SLABS;               // BFP16 B chunks (16 mantissas) per thread per tile
     // Odd N: a B tile passes through registers.  LAG: it stays there for a K-step (in K-step kt the tile fetched during
     // kt - 1 is shifted and stored, the one after it fetched), so that nothing waits for a request of its own K-step.  For the tiles
-    // between: 1500 x 3001 x 2056 50.4 -> 42.7 us.  256 x 256 has no registers to hold it (4000 x 4001 x 4096: 157 -> 192).  The 64 x 64 tiles
+    // between: 1500 x 3001 x 2056 50.4 -> 46.1 us, 1000 x 2001 x 4000 42.6 -> 36.8.  256 x 256 has no registers to hold it (4000 x 4001 x 4096: 157 -> 192).  The 64 x 64 tiles
     // share a CU with three to five others, which cover the wait for a request, and a store first thing in a K-step is in the way at
     // most sizes the selector gives them: 49 x 39829 x 784 -7 %, 8 x 33001 x 1032 -6 % (but 1500 x 4001 x 2056 +10 %); 73 such sizes
     // are 3 to 5 % faster without.
