@@ -171,7 +171,7 @@ def bfp16_layout(M: int, K: int) -> Bfp16Layout:
     return lay
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)      # typed: 8.0 is refused, whether or not 8 has been asked for
 def bfp16_bytes(M: int, K: int) -> int:
     return int(lib().atb_bfp16_bytes(M, K))
 

@@ -314,3 +314,10 @@ def test_plans_report_the_kernel_that_runs():
         streams, i = plan(*shape, tiles)
         assert not streams and (i.threads, i.lds_bytes) == (info[tiles].threads, info[tiles].lds_bytes)
     assert atb.lib().atb_gemm_streams(None) == 0
+
+
+def test_bfp16_bytes_refuses_floats_also_from_its_cache():
+    assert atb.bfp16_bytes(24, 136) == atb.bfp16_layout(24, 136).bytes
+    for bad in ((24.0, 136), (24, 136.0)):
+        with pytest.raises(ctypes.ArgumentError):
+            atb.bfp16_bytes(*bad)
