@@ -321,3 +321,28 @@ def test_bfp16_bytes_refuses_floats_also_from_its_cache():
     for bad in ((24.0, 136), (24, 136.0)):
         with pytest.raises(ctypes.ArgumentError):
             atb.bfp16_bytes(*bad)
+
+
+def test_gpu_cases_reach_every_streaming_variant():
+    """The shapes of test_gpu_skinny.py go where that file says, and reach every variant that any problem is sent to."""
+    import test_gpu_skinny as t
+    reached = set()
+    for shape in t.SHAPES:
+        for b, c in t.COMBOS:
+            g = t.plan(shape, b, c)
+            assert g.streams() == (c not in t.PIPELINE.get((shape, b), ())), (shape, b, c)
+            reached.add(t.variant(g))
+            g.close()
+    reached.discard(None)
+    sent = set()
+    for M in (1, 17, 33, 49, 65, 100, 128, 193, 256, 300, 512, 1000, 4100, 16384):
+        for N in (32, 65, 200, 1024, 2050, 4096, 8001, 8194, 12288, 16384, 16448, 24001, 32768, 33000, 50000, 50257, 70000):
+            for K in (1032, 1288, 2560, 4096, 5632, 14336):
+                if M * -(-N // 64) * 64 >= 2 ** 31:
+                    continue
+                for b in ("bf16", "bf16_t", "bfp16"):
+                    g = t.plan((M, N, K), b, "bf16")
+                    sent.add(t.variant(g))
+                    g.close()
+    sent.discard(None)
+    assert len(reached) == 42 and sent <= reached, sent - reached

@@ -132,7 +132,8 @@ def test_bfp16_b_with_ragged_n(tiles, shape):
 @pytest.mark.parametrize("shape", [(16, 520, 776), (64, 264, 1032), (9, 72, 256)])
 def test_skinny_problems_with_bfp16_weights(tiles, fmt, shape):
     """Few rows of activations against a wide weight matrix stored as BFP16 (the paper's Config 1 orientation is this
-    problem transposed): the instances built for skinny problems, on tiles that lie mostly beyond M."""
+    problem transposed): the instances built for skinny problems, on tiles that lie mostly beyond M.  At (64, 264, 1032) B in BFP16
+    streams."""
     b_format, c_format = fmt
     M, N, K = shape
     print(f"formats skinny {shape} tiles={tiles} B={b_format} C={c_format}", flush=True)
@@ -162,7 +163,8 @@ BT_TILES = [(256, 256, 64, 256), (128, 256, 64, 256), (64, 256, 64, 256), (128, 
                                    (700, 1032, 320), (4300, 4400, 136)])
 def test_transposed_bf16_b(tiles, shape):
     """bf16 B handed over as B^T (N x K): the same values reach the same MFMAs in the same order, so the result must
-    equal the row-major path's bit for bit, besides meeting the oracle's tolerance.  Shapes with ragged M and N, K tails
+    equal the row-major path's bit for bit (K <= 1024: above, few rows stream, and agree where as many waves share the sum), besides meeting
+    the oracle's tolerance.  Shapes with ragged M and N, K tails
     that are not whole K-steps (the tile rows of B^T then run into their neighbours, which meet the zero tail of A), a
     single block of K, and more tiles than resident workgroups."""
     import torch
