@@ -81,9 +81,14 @@ typedef struct atb_gemm atb_gemm; /* opaque plan, HOST memory */
  * M * round_up(N, 64) for the BFP16 forms of B and C), and
  * 2 * N * (T_K + 1) < 2^31.
  * Problems of few rows and a long reduction (K > 1024; M <= 64, or few enough rows and columns for one
- * small tile per CU) on the instances (64, 64, 128, 128), (32, 64, 256, 64) and (32, 32, 256, 64), and with
- * b_format BF16_T on any, are run by a kernel of their own that streams B through registers: the factors then only select it, and its sums are added in a
- * different order (several shorter fp32 chains per element instead of one).
+ * small tile per CU; not all of them, atb_gemm_streams tells) on the instances (64, 64, 128, 128), (32, 64, 256, 64)
+ * and (32, 32, 256, 64), and with b_format BF16_T on any, are run by a kernel of their own that streams B through
+ * registers; the factors then only select it.
+ * Bits: a plan gives the same bits on every run.  Plans that do not stream -- all of them up to K = 1024 -- add the
+ * products of an element of C in one fp32 chain, k ascending: the same operands give the same bits on every instance,
+ * with B row-major or transposed, and a row of C does not depend on M.  Plans that stream add one chain per wave, in
+ * wave order: they agree among each other where the kernel has as many threads (atb_gemm_launch_info), and differ
+ * from the others in the last bits.
  * On success *out is a new plan, else *out = NULL.
  * Environment (read here, both optional): ATB_LOG=1 prints the plan to
  * stderr; ATB_GROUP_M=<tile rows, 1..65536> overrides the height of the
@@ -123,8 +128,8 @@ typedef enum atb_format {
  *                   contiguous) -- the layout in which frameworks keep the weight of a
  *                   linear layer.  The kernel then reads its B fragments with plain
  *                   16-byte LDS reads instead of transposing ones (half the LDS read
- *                   instructions for B).  Same values, same summation order, same
- *                   result bits as b_format BF16 (but for few rows and a long reduction, see above).  Needs c_format BF16, an instance
+ *                   instructions for B).  Same values, and (atb_gemm_create: bits) the
+ *                   result bits of b_format BF16.  Needs c_format BF16, an instance
  *                   with T_K = 64 and a C tile of at least 128 x 256, and
  *                   2 * T_N * K < 2^31 (else ATB_ERR_BAD_TILE / ATB_ERR_INVALID_ARG).
  *   c_format BF16 : C, M x N bf16 row-major.

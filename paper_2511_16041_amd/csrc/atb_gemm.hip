@@ -325,7 +325,7 @@ struct TileKernel {
     static constexpr int APTN = APT > 0 ? APT : 1, BPTN = BPT > 0 ? BPT : 1, BTPTN = BTPT > 0 ? BTPT : 1;   // array extents
     static constexpr int B_BYTES = BBFP ? S::BT_BYTES : S::B_BYTES;
     static_assert(!BBFP || (NPAIR_B % S::RHO == 0 && S::T_K % 16 == 0 && (S::T_N * S::T_K / 16) % NTS == 0), "BFP16 B staging must split evenly");
-    static_assert(!BBFP || S::LDS_BYTES_BT <= 160 * 1024, "LDS budget of a gfx950 CU (the BFP16 B path always has two buffers)");
+    static_assert(!BBFP || S::LDS_BYTES_BT <= 160 * 1024, "LDS budget of a gfx950 CU (BFP16 B: two buffers, three in the 8-wave tiles)");
     static_assert((ROLE == 0) == (S::CW != 8 && S::HW == 0) && (ROLE >= 3) == (S::HW > 0), "two staging groups exactly when two waves share a SIMD; helper roles exactly with helper waves");
     static_assert(!BTR || (VEC && !BBFP && !SK && S::T_K == 64), "the transposed-B path: bf16 B^T, K-steps of 64 (8 chunks per LDS row, swizzled over 8 row pairs)");
     static constexpr int PBT = S::T_K * 2;                                                // LDS pitch of a B^T tile row
@@ -334,13 +334,15 @@ struct TileKernel {
     // EB: the switch barrier comes ahead of the phase's end.  The MFMAs after it (tail) need nothing that it publishes, so
     // the first A fragments of the next sub-tile, and the B fragments of the next K-step, are read under them instead of
     // after a barrier at which all waves wait.  B fragments are then still being read when other waves begin to decode the
-    // next tile, which therefore goes to a third buffer: tile kt is decoded during K-step kt-2 into buffer kt % 3, last read
-    // in K-step kt-4 and behind two barriers by then.  A is as before: a sub-tile's last fragments are read before the last
+    // next tile, which therefore goes to a third buffer: tile kt is decoded during K-step kt-2 into buffer kt % 3, whose last reads (of
+    // tile kt-3) were issued in the tail of K-step kt-4, after that K-step's last barrier.  The barriers of K-step kt-3 lie between, one at
+    // rho = 1 and rho of them otherwise; one is enough, as a wave passes it only with its own LDS reads done (lgkmcnt(0)).  A is as before: a sub-tile's last fragments are read before the last
     // band of its phase, ahead of the barrier, and its buffer is written from the next phase on.
     // For the 8-wave tiles with B in BFP16 (both wave groups decode, the most even phases).  Measured (us, barrier last /
     // early): 2048 x 4096 x 14336 at 64,128,64,256 268.9 / 261.4; 8192^3 at 256 x 256 935 / 918; 2048 x 14336 x 4096, C in
-    // BFP16 too, 226.1 / 222.6.  With bf16 B it is level (8192^3, rho = 2: 845 / 849, symmetric 840 / 849; 64,128,64,256: 1018
-    // / 1008) and stays out.  Smaller tiles have no room for the buffer.
+    // BFP16 too, 226.1 / 222.6.  With row-major bf16 B it is level (8192^3, rho = 2: 845 / 849, symmetric 840 / 849; 64,128,64,256: 1018
+    // / 1008) and stays out.  With B^T in bf16 it is not built; a trial gave 867 / 831 and 868 / 837 (8192^3, rho = 1, 2) and 73.8 / 69.2
+    // (2048 x 4096 x 4096 at 64,128,64,256).  Smaller tiles have no room for the buffer.
     static constexpr bool EB = BBFP && S::EB_BT;
     static constexpr bool RING = BBFP ? EB : S::NB > 2;                                   // B buffers indexed at run time
     static constexpr int NBUF = BBFP ? (EB ? 3 : 2) : S::NB;
