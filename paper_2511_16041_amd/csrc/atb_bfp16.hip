@@ -10,15 +10,11 @@
 // buffer is K-panel-major (see include/atb.h): [panel of 64 k][row][64] mantissas, [panel][row][8] exponents.
 #include <mutex>
 
+#include "atb_device.h"
 #include "atb_route.h"
 
 namespace atb {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ unsigned exp_field(float x) { return (__float_as_uint(x) >> 23) & 0xFFu; }
 
 // Quantiser.  A wave covers 2 STEPS rows x 128 k (two panels of the K-panel-major output); the 4 waves of a
 // workgroup sit side by side along k.  In step v lanes 0-31 take row 2v and lanes 32-63 row 2v + 1, four
@@ -52,13 +48,7 @@ __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__
         e = max(e, (unsigned)__shfl_xor((int)e, 1));
         const int shift = 133 - (int)e;
         const float x[4] = {f.x, f.y, f.z, f.w};
-        unsigned w = 0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            float r = rintf(ldexpf(x[t], shift));           // exact power-of-two scaling, then RNE
-            r = fminf(fmaxf(r, -127.0f), 127.0f);
-            w |= ((unsigned)((int)r) & 0xFFu) << (8 * t);
-        }
+        const unsigned w = bfp16_mantissas4(x, shift);
         if (row < M && panel < panels) *reinterpret_cast<unsigned *>(Am + (panel * M + row) * kPanelK + kin) = w;
         if ((q & 1) == 0) exps[wave][q >> 4][2 * v + half][(q & 15) >> 1] = (uint8_t)e;
     }
@@ -69,18 +59,6 @@ __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__
         if (row < M && pn < panels)
             *reinterpret_cast<uint2 *>(Ae + (pn * M + row) * (kPanelK / 8)) = *reinterpret_cast<const uint2 *>(&exps[wave][pl][rl][0]);
     }
-}
-
-// 8 mantissas times 2^shift, as bf16 (exact)
-__device__ __forceinline__ bf16x8 decode8(int2 w, int shift)
-{
-    bf16x8 r;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        r[t] = (__bf16)ldexpf((float)(int)(signed char)(w.x >> (8 * t)), shift);
-        r[4 + t] = (__bf16)ldexpf((float)(int)(signed char)(w.y >> (8 * t)), shift);
-    }
-    return r;
 }
 
 // Decoders.  Bound: HBM, 1.125 B read and 2 B written per element; a small one is its launch (2.1 us).  decode_route says
@@ -96,7 +74,7 @@ __global__ void __launch_bounds__(256) decode_lanes(const int8_t *__restrict__ A
     const int64_t rec = (int64_t)(kb / 8) * M + row;                                          // (panel, row)
     const int2 w = *reinterpret_cast<const int2 *>(Am + rec * kPanelK + (kb % 8) * 8);
     const int shift = (int)Ae[rec * (kPanelK / 8) + kb % 8] - 133;
-    *reinterpret_cast<bf16x8 *>(out + (int64_t)row * K + (int64_t)kb * 8) = decode8(w, shift);  // K % 8 == 0: 16-byte aligned as `out` is
+    *reinterpret_cast<bf16x8 *>(out + (int64_t)row * K + (int64_t)kb * 8) = bfp16_decode8(w.x, w.y, shift);  // K % 8 == 0: 16-byte aligned as `out` is
 }
 
 // A wave takes 8 rows of a panel: a lane one block, eight lanes a row, so that its requests are contiguous (512 + 64 bytes) and
@@ -128,7 +106,7 @@ __global__ void __launch_bounds__(256) decode_panels(const int8_t *__restrict__ 
 #pragma unroll
     for (int g = 0; g < R; ++g) {
         const int64_t row = row0 + 8 * g;
-        const bf16x8 r = decode8(w[g], e[g] - 133);
+        const bf16x8 r = bfp16_decode8(w[g].x, w[g].y, e[g] - 133);
         if (row < M) {
             bf16x8 *dst = reinterpret_cast<bf16x8 *>(out + row * K + k);      // 16-byte aligned as `out` is
             if constexpr (NT) __builtin_nontemporal_store(r, dst); else *dst = r;

@@ -1,0 +1,58 @@
+// Device code that the kernels share: vector types, buffer descriptors and the two directions of the BFP16 format.
+#pragma once
+
+#include "atb_internal.h"
+
+namespace atb {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef bf16x4 bf16x4_u __attribute__((aligned(2)));     // at any element of a row of C
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef int intx2 __attribute__((ext_vector_type(2)));
+
+#define ATB_DEV __device__ __forceinline__
+
+constexpr int kRsrcFlags = 0x00020000;           // raw buffer, 32-bit data format
+
+// Descriptor of the `bytes` bytes at ptr.  It is wave-uniform by construction; saying so keeps it in scalar registers.
+template <class T>
+ATB_DEV __amdgpu_buffer_rsrc_t uniform_rsrc(const T *ptr, int bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(ptr);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    void *u = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
+    return __builtin_amdgcn_make_buffer_rsrc(u, 0, __builtin_amdgcn_readfirstlane(bytes), kRsrcFlags);
+}
+
+// 8 mantissas (two dwords) times 2^shift, as bf16: exact, |m| <= 127 has 7 significant bits
+ATB_DEV bf16x8 bfp16_decode8(int lo, int hi, int shift)
+{
+    bf16x8 r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        r[t] = (__bf16)ldexpf((float)(int)(signed char)(lo >> (8 * t)), shift);
+        r[4 + t] = (__bf16)ldexpf((float)(int)(signed char)(hi >> (8 * t)), shift);
+    }
+    return r;
+}
+
+ATB_DEV unsigned exp_field(float x) { return (__float_as_uint(x) >> 23) & 0xFFu; }
+
+// Four mantissas of a block with exponent E = 133 - shift: clamp(rne(x * 2^(133 - E)), -127, 127), one byte each
+ATB_DEV unsigned bfp16_mantissas4(const float x[4], int shift)
+{
+    unsigned w = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        float r = rintf(ldexpf(x[t], shift));           // exact power-of-two scaling, then RNE
+        r = fminf(fmaxf(r, -127.0f), 127.0f);
+        w |= ((unsigned)((int)r) & 0xFFu) << (8 * t);
+    }
+    return w;
+}
+
+}  // namespace atb

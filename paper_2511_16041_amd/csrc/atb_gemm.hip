@@ -33,19 +33,13 @@
 // (= l % MB) and groups of 4 consecutive columns (n = 8*g + 4*(l/MB) + 0..3) -> 8-byte bf16 stores.
 #include <algorithm>
 
-#include "atb_internal.h"
+#include "atb_device.h"
 
 namespace atb {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef bf16x4 bf16x4_u __attribute__((aligned(2)));     // at any element of a row of C
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
-
-#define ATB_DEV __device__ __forceinline__
 
 // Sign-extended byte `byte` of word w as float (one v_cvt_f32_i32 with a byte select).
 ATB_DEV float mant_to_float(int w, int byte) { return (float)(int)(signed char)(w >> (8 * byte)); }
@@ -193,10 +187,6 @@ struct Shape {
     static_assert(SKEW == 0 || (CW == 8 && WM == 2 && HW == 0 && AB == 2 && SKEW < MTW), "the uneven deal is between the two wave groups of a 2 x 4 grid");
 };
 
-typedef int intx4 __attribute__((ext_vector_type(4)));
-typedef int intx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
 // Buffer descriptors (V#) of the three inputs.  A load whose byte offset lies outside
 // [0, num_records) returns zero without touching memory, which is what masks the edges.
 struct Rsrc {
@@ -204,8 +194,6 @@ struct Rsrc {
     intx4 b_words;      // the B descriptor once more as four dwords, for the hand-issued requests of the symmetric instances
     intx4 am_words, ae_words;   // likewise the A descriptors, for the raw requests (ADMA)
 };
-
-constexpr int kRsrcFlags = 0x00020000;           // raw buffer, 32-bit data format
 
 #define ATB_FENCE() __builtin_amdgcn_sched_barrier(0)
 
@@ -662,17 +650,6 @@ struct TileKernel {
     }
 
     // ---- global -> registers -------------------------------------------------------------
-    // Descriptors are wave-uniform by construction; saying so keeps them in scalar registers.
-    template <class T>
-    ATB_DEV __amdgpu_buffer_rsrc_t make_rsrc(const T *ptr, int bytes)
-    {
-        const uint64_t a = reinterpret_cast<uint64_t>(ptr);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-        void *u = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
-        return __builtin_amdgcn_make_buffer_rsrc(u, 0, __builtin_amdgcn_readfirstlane(bytes), kRsrcFlags);
-    }
-
     ATB_DEV void remake_a()
     {
         if constexpr (RQ > 0) {
@@ -682,8 +659,8 @@ struct TileKernel {
             rs.ae_words = intx4{__builtin_amdgcn_readfirstlane((int)(uint32_t)e), __builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32) & 0xFFFF),
                                 __builtin_amdgcn_readfirstlane(ae_left), kRsrcFlags};
         } else {
-            rs.am = make_rsrc(am_ptr, am_left);
-            rs.ae = make_rsrc(ae_ptr, ae_left);
+            rs.am = uniform_rsrc(am_ptr, am_left);
+            rs.ae = uniform_rsrc(ae_ptr, ae_left);
         }
     }
 
@@ -746,7 +723,7 @@ struct TileKernel {
     ATB_DEV void remake_b()
     {
         const int bytes = (int)min(b_left, (int64_t)0x7fffffff);
-        rs.b = make_rsrc(b_ptr, bytes);
+        rs.b = uniform_rsrc(b_ptr, bytes);
         if constexpr (ASM_DMA) {
             const uint64_t a = reinterpret_cast<uint64_t>(b_ptr);
             rs.b_words = intx4{__builtin_amdgcn_readfirstlane((int)(uint32_t)a), __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xFFFF),
@@ -756,8 +733,8 @@ struct TileKernel {
 
     ATB_DEV void remake_bt()
     {
-        rs.bm = make_rsrc(bm_ptr, bm_left);
-        rs.be = make_rsrc(be_ptr, be_left);
+        rs.bm = uniform_rsrc(bm_ptr, bm_left);
+        rs.be = uniform_rsrc(be_ptr, be_left);
     }
 
     // Chunk i of the BFP16 B tile the B descriptors point at, into register set `set`; after the
@@ -1436,18 +1413,12 @@ struct TileKernel {
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         x[t] = live ? acc[a / S::HB][a % S::HB][b][4 * g + t] : 0.0f;
-                        e = max(e, (__float_as_uint(x[t]) >> 23) & 0xFFu);
+                        e = max(e, exp_field(x[t]));
                     }
                     const unsigned other = (unsigned)__builtin_amdgcn_ds_bpermute((lane ^ S::MB) << 2, (int)e);
                     e = max(e, other);
                     const int sh = 133 - (int)e;
-                    unsigned w = 0;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        float r = rintf(ldexpf(x[t], sh));
-                        r = fminf(fmaxf(r, -127.0f), 127.0f);
-                        w |= ((unsigned)((int)r) & 0xFFu) << (8 * t);
-                    }
+                    const unsigned w = bfp16_mantissas4(x, sh);
                     if (m < p.M && n < p.n_panels * kPanelK) {
                         const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;       // (panel, row)
                         *reinterpret_cast<unsigned *>(p.Cm + rec * kPanelK + n % kPanelK) = w;

@@ -26,42 +26,17 @@
 //                      v_perm_b32 picks the halves
 //   B^T bf16           two 16-byte requests per 16 columns are the operands as they are
 //   B^T BFP16          one 16-byte request per 16 columns, decoded in registers like A
+#include "atb_device.h"
 #include "atb_route.h"
 
 namespace atb {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef bf16x4 bf16x4_u __attribute__((aligned(2)));     // at any element of a row of C
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef int intx4 __attribute__((ext_vector_type(4)));
-typedef int intx2 __attribute__((ext_vector_type(2)));
-
-#define ATB_DEV __device__ __forceinline__
-
-constexpr int kRsrcFlags = 0x00020000;           // raw buffer, 32-bit data format
-
+// (a tile's rows of a panel may lie further from the end of B than 2^31 bytes; its offsets do not reach that far)
 template <class T>
-ATB_DEV __amdgpu_buffer_rsrc_t uniform_rsrc(const T *ptr, int64_t bytes)
+ATB_DEV __amdgpu_buffer_rsrc_t panel_rsrc(const T *ptr, int64_t bytes)
 {
-    const uint64_t a = reinterpret_cast<uint64_t>(ptr);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    const int n = __builtin_amdgcn_readfirstlane((int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, n, kRsrcFlags);
-}
-
-// 8 mantissas (two dwords) times 2^shift, as bf16: exact, |m| <= 127 has 7 significant bits
-ATB_DEV bf16x8 decode_block(int lo, int hi, int shift)
-{
-    bf16x8 r;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        r[t] = (__bf16)ldexpf((float)(int)(signed char)(lo >> (8 * t)), shift);
-        r[4 + t] = (__bf16)ldexpf((float)(int)(signed char)(hi >> (8 * t)), shift);
-    }
-    return r;
+    return uniform_rsrc(ptr, (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
 }
 
 enum { kBRow = 0, kBT = 1, kBBfp = 2, kBRowOdd = 3 };
@@ -126,12 +101,12 @@ struct Skinny {
     {
         const bool live = k < p.k_panels;
         const int64_t kp = live ? k : 0;
-        const __amdgpu_buffer_rsrc_t am = uniform_rsrc(p.Am + kp * p.M * kPanelK, live ? (int64_t)p.M * kPanelK : 0);
-        const __amdgpu_buffer_rsrc_t ae = uniform_rsrc(p.Ae + kp * p.M * (kPanelK / 8), live ? (int64_t)p.M * (kPanelK / 8) : 0);
+        const __amdgpu_buffer_rsrc_t am = panel_rsrc(p.Am + kp * p.M * kPanelK, live ? (int64_t)p.M * kPanelK : 0);
+        const __amdgpu_buffer_rsrc_t ae = panel_rsrc(p.Ae + kp * p.M * (kPanelK / 8), live ? (int64_t)p.M * (kPanelK / 8) : 0);
         if constexpr (ROWS) {
             // rows >= K lie past the end of B and read as zero
             const int64_t first = kp * kPanelK * p.N + n0;
-            const __amdgpu_buffer_rsrc_t b = uniform_rsrc(p.B + first, live ? ((int64_t)p.K * p.N - first) * 2 : 0);
+            const __amdgpu_buffer_rsrc_t b = panel_rsrc(p.B + first, live ? ((int64_t)p.K * p.N - first) * 2 : 0);
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 if constexpr (FMT == kBRowOdd) {
@@ -158,7 +133,7 @@ struct Skinny {
             // k >= K runs into the next row of B^T (or past its end, which reads as zero): finite values against the
             // zero tail of A
             const int64_t first = (int64_t)n0 * p.K + kp * kPanelK;
-            const __amdgpu_buffer_rsrc_t b = uniform_rsrc(p.B + first, live ? ((int64_t)p.N * p.K - first) * 2 : 0);
+            const __amdgpu_buffer_rsrc_t b = panel_rsrc(p.B + first, live ? ((int64_t)p.N * p.K - first) * 2 : 0);
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 s.bt[2 * i] = __builtin_amdgcn_raw_buffer_load_b128(b, b_off[i], 0, 0);
@@ -166,8 +141,8 @@ struct Skinny {
             }
         } else {
             const int64_t row = kp * p.N + n0;
-            const __amdgpu_buffer_rsrc_t bm = uniform_rsrc(p.Bm + row * kPanelK, live ? (int64_t)(p.N - n0) * kPanelK : 0);
-            const __amdgpu_buffer_rsrc_t be = uniform_rsrc(p.Be + row * (kPanelK / 8), live ? (int64_t)(p.N - n0) * (kPanelK / 8) : 0);
+            const __amdgpu_buffer_rsrc_t bm = panel_rsrc(p.Bm + row * kPanelK, live ? (int64_t)(p.N - n0) * kPanelK : 0);
+            const __amdgpu_buffer_rsrc_t be = panel_rsrc(p.Be + row * (kPanelK / 8), live ? (int64_t)(p.N - n0) * (kPanelK / 8) : 0);
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 s.bt[i] = __builtin_amdgcn_raw_buffer_load_b128(bm, b_off[i], 0, 0);
@@ -211,12 +186,12 @@ struct Skinny {
                     u.w = s.bt[2 * j + h];
                     bf[j] = u.v;
                 } else {
-                    bf[j] = decode_block(s.bt[j][2 * h], s.bt[j][2 * h + 1], shift_of(s.be[j], q, h));
+                    bf[j] = bfp16_decode8(s.bt[j][2 * h], s.bt[j][2 * h + 1], shift_of(s.be[j], q, h));
                 }
             }
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
-                const bf16x8 af = decode_block(s.am[i][2 * h], s.am[i][2 * h + 1], shift_of(s.ae[i], q, h));
+                const bf16x8 af = bfp16_decode8(s.am[i][2 * h], s.am[i][2 * h + 1], shift_of(s.ae[i], q, h));
 #pragma unroll
                 for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af, acc[i][j], 0, 0, 0);
             }
@@ -277,16 +252,10 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     x[v] = n < p.N ? sum[v] : 0.0f;               // whole blocks: N % 8 == 0
-                    e = max(e, (__float_as_uint(x[v]) >> 23) & 0xFFu);
+                    e = max(e, exp_field(x[v]));
                 }
                 e = max(e, (unsigned)__shfl_xor((int)e, 1));
-                unsigned w = 0;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float r = rintf(ldexpf(x[v], 133 - (int)e));
-                    r = fminf(fmaxf(r, -127.0f), 127.0f);
-                    w |= ((unsigned)((int)r) & 0xFFu) << (8 * v);
-                }
+                const unsigned w = bfp16_mantissas4(x, 133 - (int)e);
                 if (m < p.M && n < cols) {
                     const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;
                     *reinterpret_cast<unsigned *>(p.Cm + rec * kPanelK + n % kPanelK) = w;
