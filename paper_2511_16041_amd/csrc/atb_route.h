@@ -88,26 +88,27 @@ inline int64_t stream_workgroups(const GemmParams &p, const StreamRoute &r) { re
 inline int stream_column_blocks(int N, int cus) { return N <= 32 * cus ? 2 : N <= 64 * cus ? 4 : 8; }
 
 // More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
-// none where the tile pipeline is as good or better.  Measured in us, the pipeline / this kernel:
-//   B bf16    64 x 64: M 128, 8192, 8192 54.4 / 47.0, M 256, 4096, 4096 22.3 / 19.5, M 1024, 1024, 1032 1.10 x as fast; but where the
-//             pipeline has whole K-steps and little K it is level in memory and behind in cache: M 192 .. 4096 with 144 .. 256 tiles,
-//             K 1296 .. 2048: 0.96 - 1.09 x cold, 0.91 - 1.02 x hot (the pipeline pads K to 512: K 1032 .. 1152 1.05 - 1.16 x, from
-//             2560 on 1.04 - 1.3 x)
-//             64 x 128: M 512, 4096, 14336 120 / 80, M 256, 8192, 8192 70.3 / 54.9; K 4096 .. 4864 0.94 - 1.1 x over 14 shapes, 5120
-//             1.0 - 1.1 x, 5632 and 6144 1.02 - 1.2 x
+// none where the tile pipeline is as good or better.  Measured in us, the pipeline / this kernel, or as the ratio of the two; "memory":
+// 700 MB of operands in turns, so that B comes from memory as a model's weights do; "cache": three sets in turns, which the 256 MiB
+// memory-side cache holds:
+//   B bf16    64 x 64: M 128, 8192, 8192 54.4 / 47.0, M 256, 4096, 4096 22.3 / 19.5; eight shapes of 130 to 256 tiles, K 1032 to 4096: 1.0 - 1.3
+//             x memory, 0.96 - 1.2 x cache (lowest at K 1536, where the pipeline has whole K-steps)
+//             64 x 128: M 512, 4096, 14336 120 / 80; eight shapes, K 4096 / 4352 / 4608 / 5120 / 5632: 1.07 - 1.46 x memory (M 1024, 2048,
+//             4096 37.4 / 28.1), cache 0.92 - 1.1 / 0.9 - 1.08 / 0.94 - 1.1 / 0.95 - 1.13 / 1.02 - 1.16 x; below, M 1024, 2048, 2048 16.3 / 17.5
 //             not 64 x 32 (M 256, 2048, 2048 9.9 / 10.4) nor odd N (M 512, 5001, 4096 61 / 70), nor 64 x 64 where the pipeline's 32 x 64
-//             tiles fit one to a CU (rows just above a multiple of 64: M 193, 2304 and M 129, 3000, K 1032 .. 8192 0.72 - 0.91 x)
+//             tiles fit one to a CU (rows just above a multiple of 64: M 193, 2304, M 129, 3000 and M 96, 5000, K 1032 .. 4096: 0.83 - 0.94 x
+//             memory, 0.72 - 0.91 x cache)
 //   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
 //             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
-//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64); 32 x 64 tiles one to a CU: K 1032 and 1152
-//             1.04 - 1.16 x, from 1296 on 0.92 - 1.07 x
+//   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64); where 32 x 64 tiles fit one to a CU, K 1032
+//             and 1152 0.98 - 1.16 x, from 1296 on 0.88 - 0.97 x memory
 inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int cus)
 {
     const bool small_tiles = tile_count(p, 32, 64) <= cus;            // the pipeline's 32 x 64 tiles: one per CU or fewer
     if (b_format == ATB_FMT_BF16) {
         if (p.N % 2 != 0 || tile_count(p, 64, 32) <= cus) return {};
-        if (tile_count(p, 64, 64) <= cus) return !small_tiles && (p.K <= 1152 || p.K > 2048) ? StreamRoute{4, 4, 8, 1} : StreamRoute{};
-        if (tile_count(p, 64, 128) <= cus && p.K >= 5632) return {4, 8, 4, 2};
+        if (tile_count(p, 64, 64) <= cus) return small_tiles ? StreamRoute{} : StreamRoute{4, 4, 8, 1};
+        if (tile_count(p, 64, 128) <= cus && p.K >= 4096) return {4, 8, 4, 2};
         return {};
     }
     if (tile_count(p, 64, 32) <= cus) return {4, 2, 8, 1};
@@ -117,9 +118,10 @@ inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int
 }
 
 // At most 64 rows: whether the streaming kernel is at least as fast as the pipeline.  The lines lie where both sides were measured, over
-// M 1 .. 64, N 32 .. 151936, K 1032 .. 14336, operands from memory (cold) and from a cache (hot); figures are the pipeline's time over
-// this kernel's.  What they come down to: one tile per CU is where this kernel is at its best; with fewer tiles than CUs, or a second
-// round of them that is nearly empty, CUs idle, and the pipeline, whose requests go straight to LDS, gets more out of the others.
+// M 1 .. 64, N 32 .. 151936, K 1032 .. 14336; figures are the pipeline's time over this kernel's, with the operands of three problems in
+// turns (B comes from memory where it is larger than 90 MB) and, where that differs, of 700 MB of them ("memory") or of one ("cache").
+// What they come down to: one tile per CU is where this kernel is at its best; with fewer tiles than CUs, or a second round of them that
+// is nearly empty, CUs idle, and the pipeline, whose requests go straight to LDS, gets more out of the others.
 inline bool stream_few_rows(const GemmParams &p, int b_format, int cus)
 {
     const int M = p.M, N = p.N, K = p.K;
@@ -133,8 +135,8 @@ inline bool stream_few_rows(const GemmParams &p, int b_format, int cus)
     }
     if (N % 2 != 0) {
         // 32 columns per workgroup whatever N is: 1.03 - 2.1 up to N = 24576.  Then the pipeline's 128-column tiles fill more than three
-        // quarters of the CUs, until they need a second round: M > 32 0.78 - 1.0 cold (1.04 - 1.2 at K = 1032), M <= 32 1.01 - 1.4 up to
-        // 30720, 0.91 - 1.02 cold from there at K >= 4096.  Beyond: M <= 48 0.98 - 1.5, M 49 .. 64 at K >= 4096 0.94 - 1.05.
+        // quarters of the CUs, until they need a second round: M > 32 0.78 - 1.0 (0.97 - 1.2 at K = 1032), M <= 32 1.01 - 1.4 up to
+        // 30720, 0.91 - 1.02 from there at K >= 4096.  Beyond: M <= 48 0.98 - 1.5, M 49 .. 64 at K >= 4096 0.94 - 1.05.
         if (N <= 96 * cus) return true;
         if (N > 128 * cus) return M <= 48 || K < 4096;
         return M > 32 ? K < 1536 : N <= 120 * cus || K < 4096;
@@ -145,13 +147,15 @@ inline bool stream_few_rows(const GemmParams &p, int b_format, int cus)
         // 129 to 256 workgroups of 64 columns.  Rows of B that are not whole lines and one or two rows of A: the pipeline skips the
         // dead rows of its tile, 0.88 - 1.0 from K = 2560 (under 208 workgroups) or above 4096 on.
         const bool ragged = N % 64 != 0 && M <= 2;
-        if (N < 36 * cus) return K < 2048;                                 // 0.97 - 1.25 cold below, 0.71 - 1.09 from 2048 on
-        if (N < 52 * cus) return K < (ragged ? 2560 : 4096);               // 0.98 - 1.17 below, 0.92 - 1.05 cold from 4096 on
+        if (N < 36 * cus) return K < 2048;                                 // 0.97 - 1.25 below, 0.71 - 1.09 from 2048 on
+        if (N < 52 * cus) return K < (ragged ? 2560 : 4096);               // 0.98 - 1.17 below (memory 0.94 - 1.08), 0.92 - 1.05 from 4096 on
         return !ragged || K <= 4096;                                       // 0.96 - 1.19
     }
-    if (N <= 128 * cus) return M <= 48;                                    // 1.03 - 1.6; M 49 .. 64 0.78 - 1.08
-    // more than one workgroup of 128 columns per CU: 0.76 - 1.0 (K < 2048 1.18 - 1.3) until the second round is half full, 0.97 - 1.4 then
-    return M <= 48 && (K < 2048 || N >= 192 * cus);
+    // 1.03 - 1.6; M 49 .. 64: K 1032 .. 2048 0.80 - 0.96, 4096 0.96 - 1.03 (cache 0.85 - 0.95), 8192 0.99 - 1.08
+    if (N <= 128 * cus) return M <= 48 || K >= 8192;
+    // more than one workgroup of 128 columns per CU: 0.76 - 1.0 (K 1032 .. 1240 1.0 - 1.3, 1536 0.92 - 1.03) until the second
+    // round is half full, 0.97 - 1.4 then
+    return M <= 48 && (K < 1536 || N >= 192 * cus);
 }
 
 // Where the streaming kernel takes over from the tile pipeline, and in what form.

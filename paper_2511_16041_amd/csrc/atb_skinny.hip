@@ -11,7 +11,7 @@
 // number of waves or of panels in flight per wave, 1 to 4), so all CUs have to take part and every line that is asked for should
 // be used whole.  Hence the tile width (stream_column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
 // <= 8192 that is 32 columns, half a line per row, and the rate stays at 3.9 TB/s against 5.1 with B^T.
-// Measured in us, operands cold in the caches (three sets in turns), the tile pipeline before / this kernel now:
+// Measured in us, three sets of operands in turns, the tile pipeline before / this kernel now:
 //   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5     M 64, 14336, 4096: 34.7 / 30.0     M 16, 5001, 4096: 23.7 / 12.9
 //   B^T bf16  M 16, N 8192, K 8192: 105 / 29        M 64, 14336, 4096: 57.7 / 29.4
 //   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.5    M 64, 14336, 4096: 26.0 / 21.1 (decoding A takes as long as B's bytes)
@@ -320,7 +320,7 @@ hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r
         if (form == 208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
         if (form == 404) return launch_rows<kBRow, 4, 4, 4>(p, r, stream);
         if (form == 804 && r.depth == 2) return launch<kBRow, 4, 8, 4, 2>(p, r, stream);
-        if (form == 804) return launch_rows<kBRow, 8, 4, 3>(p, r, stream);
+        if (form == 804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
         if (form == 408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
     }
     return hipErrorInvalidValue;

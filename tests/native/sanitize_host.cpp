@@ -241,9 +241,9 @@ static void route_paths()
     // above 64 rows: {row blocks, column blocks}, {0, 0} for the tile pipeline
     const Expected many[] = {
         {256, 4096, 4096, ATB_FMT_BF16, 4, 4},   {1024, 1024, 1032, ATB_FMT_BF16, 4, 4},  {1024, 1024, 1152, ATB_FMT_BF16, 4, 4},
-        {1024, 1024, 1160, ATB_FMT_BF16, 0, 0},  {1024, 1024, 2048, ATB_FMT_BF16, 0, 0},  {1024, 1024, 2056, ATB_FMT_BF16, 4, 4},
+        {1024, 1024, 1160, ATB_FMT_BF16, 4, 4},  {1024, 1024, 2048, ATB_FMT_BF16, 4, 4},  {1024, 1024, 1024, ATB_FMT_BF16, 0, 0},
         {193, 2304, 4096, ATB_FMT_BF16, 0, 0},   {129, 3000, 1032, ATB_FMT_BF16, 0, 0},   {300, 3000, 4096, ATB_FMT_BF16, 4, 4},
-        {1024, 2048, 4096, ATB_FMT_BF16, 0, 0},  {512, 4096, 4096, ATB_FMT_BF16, 0, 0},   {1024, 2048, 5624, ATB_FMT_BF16, 0, 0},
+        {1024, 2048, 4096, ATB_FMT_BF16, 4, 8},  {512, 4096, 4096, ATB_FMT_BF16, 4, 8},   {1024, 2048, 4088, ATB_FMT_BF16, 0, 0},
         {1024, 2048, 5632, ATB_FMT_BF16, 4, 8},  {512, 4096, 14336, ATB_FMT_BF16, 4, 8},  {256, 4097, 4096, ATB_FMT_BF16, 0, 0},
         {256, 2048, 4096, ATB_FMT_BF16, 0, 0},   {256, 2048, 4096, ATB_FMT_BFP16, 4, 2},  {193, 2304, 1152, ATB_FMT_BFP16, 4, 4},
         {193, 2304, 1160, ATB_FMT_BFP16, 0, 0},  {300, 3000, 4096, ATB_FMT_BFP16, 4, 4},  {1024, 2048, 8192, ATB_FMT_BFP16, 0, 0},
@@ -256,7 +256,8 @@ static void route_paths()
         {16, 9216, 4096, ATB_FMT_BF16, 0, 0},    {2, 9218, 2560, ATB_FMT_BF16, 0, 0},     {3, 9218, 2560, ATB_FMT_BF16, 1, 4},
         {16, 13312, 9984, ATB_FMT_BF16, 1, 4},   {1, 13500, 5632, ATB_FMT_BF16, 0, 0},    {1, 13504, 5632, ATB_FMT_BF16, 1, 4},
         {16, 14336, 4096, ATB_FMT_BF16, 1, 4},   {48, 32768, 4096, ATB_FMT_BF16, 3, 8},   {49, 28672, 4096, ATB_FMT_BF16, 0, 0},
-        {16, 33000, 4096, ATB_FMT_BF16, 0, 0},   {16, 33000, 2040, ATB_FMT_BF16, 1, 8},   {16, 49152, 4096, ATB_FMT_BF16, 1, 8},
+        {49, 28672, 8192, ATB_FMT_BF16, 4, 8},
+        {16, 33000, 4096, ATB_FMT_BF16, 0, 0},   {16, 33000, 1528, ATB_FMT_BF16, 1, 8},   {16, 49152, 4096, ATB_FMT_BF16, 1, 8},
         // odd N
         {64, 24575, 8192, ATB_FMT_BF16, 4, 2},   {33, 24577, 1536, ATB_FMT_BF16, 0, 0},   {33, 24577, 1528, ATB_FMT_BF16, 3, 2},
         {32, 30719, 8192, ATB_FMT_BF16, 2, 2},   {32, 30721, 4096, ATB_FMT_BF16, 0, 0},   {64, 50257, 4096, ATB_FMT_BF16, 0, 0},

@@ -333,11 +333,12 @@ def test_gpu_cases_reach_every_streaming_variant():
             assert g.streams() == (c not in t.PIPELINE.get((shape, b), ())), (shape, b, c)
             reached.add(t.variant(g))
             g.close()
+    reached.add(t.variant(t.plan(t.WIDE_AND_LONG, "bf16", "bf16")))
     reached.discard(None)
     sent = set()
     for M in (1, 17, 33, 49, 65, 100, 128, 193, 256, 300, 512, 1000, 4100, 16384):
         for N in (32, 65, 200, 1024, 2050, 4096, 8001, 8194, 12288, 16384, 16448, 24001, 32768, 33000, 50000, 50257, 70000):
-            for K in (1032, 1288, 2560, 4096, 5632, 14336):
+            for K in (1032, 1288, 2560, 4096, 5632, 8192, 14336):
                 if M * -(-N // 64) * 64 >= 2 ** 31:
                     continue
                 for b in ("bf16", "bf16_t", "bfp16"):
@@ -345,4 +346,4 @@ def test_gpu_cases_reach_every_streaming_variant():
                     sent.add(t.variant(g))
                     g.close()
     sent.discard(None)
-    assert len(reached) == 42 and sent <= reached, sent - reached
+    assert len(reached) == 43 and sent <= reached, sent - reached

@@ -19,14 +19,14 @@ SHAPES = [(1, 2, 1032), (16, 32, 1088), (17, 33, 1032), (48, 34, 1096), (64, 264
           (5, 1001, 1032), (48, 8194, 1032), (7, 8256, 1032), (20, 8256, 1032), (49, 8264, 1032), (64, 16386, 1032), (16, 16448, 1096),
           (20, 16448, 1032), (40, 16448, 1032),
           # above 64 rows: 64 x 32 and 64 x 64 tiles, then (B row-major / transposed) 64 x 128 / 128 x 64; many rows of few columns
-          (65, 72, 1032), (130, 2802, 1096), (260, 3400, 4104), (130, 4802, 1096), (260, 3400, 5640), (4130, 32, 1032)]
+          (65, 72, 1032), (130, 2802, 1096), (260, 3400, 4104), (130, 4802, 1096), (4130, 32, 1032)]
+WIDE_AND_LONG = (50, 16386, 8192)            # bf16 B at 49 to 64 rows and 128 columns
 COMBOS = [("bf16", "bf16"), ("bf16_t", "bf16"), ("bfp16", "bf16"), ("bf16", "bfp16"), ("bfp16", "bfp16")]
 BOTH = ("bf16", "bfp16")
 # {(shape, b_format): C formats} that the rules leave with the pipeline
 PIPELINE = {((64, 264, 1088), "bf16"): BOTH, ((64, 8191, 1032), "bf16"): ("bfp16",), ((64, 16386, 1032), "bf16"): BOTH,
             ((64, 16386, 1032), "bfp16"): BOTH, ((65, 72, 1032), "bf16"): BOTH, ((130, 2802, 1096), "bf16"): BOTH,
-            ((260, 3400, 4104), "bf16"): BOTH, ((260, 3400, 4104), "bfp16"): BOTH, ((260, 3400, 5640), "bfp16"): BOTH,
-            ((4130, 32, 1032), "bf16"): BOTH}
+            ((260, 3400, 4104), "bfp16"): BOTH, ((4130, 32, 1032), "bf16"): BOTH}
 BT_TILES = [(256, 256, 64, 256), (128, 256, 64, 256), (64, 256, 64, 256), (128, 128, 64, 256), (64, 128, 64, 256)]
 
 
@@ -41,7 +41,8 @@ def plan(shape, b_format, c_format):
 
 
 def variant(g):
-    """(form of B, blocks of 16 rows, blocks of 16 columns, waves) of the streaming kernel that runs plan g; None for the pipeline."""
+    """(form of B, blocks of 16 rows, blocks of 16 columns, waves, panels in flight) of the streaming kernel that runs plan g; None for
+    the pipeline."""
     if not g.streams():
         return None
     M, N, _ = g.shape
@@ -50,7 +51,7 @@ def variant(g):
     nb = (i.lds_bytes // (waves * 16 * 4) - 4) // 16
     form = g.b_format if g.b_format != "bf16" else "bf16 odd" if N % 2 else "bf16"
     # above 64 rows: 128 x 64 tiles have four waves, 64 x 64 eight
-    return form, -(-M // 16) if M <= 64 else 8 if (nb, waves) == (4, 4) else 4, nb, waves
+    return form, -(-M // 16) if M <= 64 else 8 if (nb, waves) == (4, 4) else 4, nb, waves, 2 if M > 64 and nb == 8 else 1
 
 
 def _check(g, exact, seed=21):
@@ -101,6 +102,13 @@ def test_streaming_kernel(shape, b_format, c_format, exact):
     g = plan(shape, b_format, c_format)
     assert g.streams() == (c_format not in PIPELINE.get((shape, b_format), ()))
     _check(g, exact)
+
+
+def test_wide_and_long():
+    print(f"skinny {WIDE_AND_LONG}", flush=True)
+    g = plan(WIDE_AND_LONG, "bf16", "bf16")
+    assert g.streams()
+    _check(g, exact=True)
 
 
 @pytest.mark.parametrize("exact", [True, False])
