@@ -539,19 +539,18 @@ def main():
             fl = 2.0 * Mx * Nx * Kx
             rk = atb.select_tiles(Mx, Nx, Kx)
             prd = {r.tiles(): r.pred_flops / 1e12 for r in rk}
-            # (instances that hand this shape to the streaming kernel say nothing about themselves: not ranked)
+            # instances that hand this shape to the streaming kernel say nothing about themselves: timed, not ranked
             inst = [t for t in atb.instances() if not streams(atb, Mx, Nx, Kx, t)]
-            rk = [r for r in rk if r.tiles() in inst]
             p0 = atb.Gemm(Mx, Nx, Kx, *rk[0].tiles())
             burn_in(p0, Ab, Bd, Cd)
             p0.close()
-            meas = {t: fl / (time_tiles(atb, Mx, Nx, Kx, t, Ab, Bd, Cd, 30, 15) * 1e-3) / 1e12 for t in inst}
+            meas = {t: fl / (time_tiles(atb, Mx, Nx, Kx, t, Ab, Bd, Cd, 30, 15) * 1e-3) / 1e12 for t in atb.instances()}
             best = max(meas, key=meas.get)
             pick = rk[0].tiles()
             # the paper's formulas alone (atb_model_eval: Eqs. 1, 2, 11, 12, 15 with the MI355X constants, none of the
             # measured per-instance factors the selector adds)
             pure = {t: atb.model_eval(Mx, Nx, Kx, *t).pred_flops for t in inst}
-            held.append({"M": Mx, "N": Nx, "K": Kx, "pick": list(pick), "pick_tflops": round(meas[pick], 1),
+            held.append({"M": Mx, "N": Nx, "K": Kx, "pick": list(pick), "pick_kernel": "tiles" if pick in inst else "streaming", "pick_tflops": round(meas[pick], 1),
                          "pick_model_tflops": round(prd[pick], 1), "best": list(best), "best_tflops": round(meas[best], 1),
                          "instances_ranked": len(inst), "pick_vs_best": round(meas[pick] / meas[best], 4),
                          "spearman": round(spearman([prd[t] for t in inst], [meas[t] for t in inst]), 3),
