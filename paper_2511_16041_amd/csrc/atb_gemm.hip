@@ -1659,8 +1659,9 @@ const Instance g_instances[] = {
     // B buffers (NB; it fits because the ATB A buffers are small, and it is what lets the symmetric 32-row tile's
     // single phase per K-step await its B tile two K-steps after the request), four helper waves next to the 1 x 2
     // grid (which alone would leave two SIMDs idle), and take the dead-row-skipping variant of the kernel body.
-    // Above K = 1024 they hand most problems over to the streaming kernel (stream_route); what is left to them are
-    // bf16 B of up to 8192 columns at 49 to 64 rows, of up to 4096 at 65 to 128, and short reductions.  Measured at N = K =
+    // Above K = 1024 they hand most problems over to the streaming kernel (stream_route); what is left to them is what its
+    // rules name -- bf16 B of up to 8192 columns at 49 to 64 rows, of up to 4096 at 65 to 128, wide B that makes a
+    // few tiles too many or too few for the CUs -- and short reductions.  Measured at N = K =
     // 8192, operands in turns so that B comes from memory: M <= 64: 40 - 41 us with the 32-row tile.  Factors from the
     // issue model: 0.52 and 0.48 (measured: 0.42 - 0.49 of the fit from M = 16 to 8192).
     make_instance<Shape<32, 64, 256, 64, 1, 2, 2, 2, -1, 0, 2, 3, 4>, true>(),
