@@ -1353,80 +1353,188 @@ struct TileKernel {
         return s * S::SMT + band(s, a - first_local(s));
     }
 
-    // epilogue: fp32 -> bf16 (round to nearest even) and store, once per tile.  Lane l of block
-    // (a, h, b) holds row l%MB of the block and, in registers 4g .. 4g+3, its columns 8g + 4*(l/MB) + 0..3
-    // (MB = 32: g = 0..3; MB = 16: g = 0 only).
-    // A lane's four columns leave as one 8-byte store wherever the row of C starts: gfx9 stores to any 2-byte address (the
-    // element type's alignment is all that bf16x4_u promises, the compiler picks the instruction).  Only the last columns of
-    // a row are stored one by one.  Rows that are not a multiple of 8 bytes apart took four 2-byte stores, each of a wave's
-    // to 16 lines: 1500 x 3002 x 2056 42.2 -> 34.2 us (3000 columns: 33.9), 4000 x 4002 x 4096 127.5 -> 107.7,
-    // 1500 x 3001 x 2056 57.3 -> 50.4.
-    ATB_DEV void store_c()
+    // Epilogue.  Lane l of block (a, h, b) holds row l%MB of the block and, in registers 4g .. 4g+3, its columns 8g + 4*(l/MB) + 0..3
+    // (MB = 32: g = 0..3; MB = 16: g = 0 only).  Two neighbouring groups of four registers are a pair: one lane swap per register leaves
+    // every lane with eight consecutive columns of one row (piece_col), i.e. 16 bytes of bf16 or a whole BFP16 block.
+    // What bounds it is fetching its instructions: code that runs once per tile is not in the instruction cache, and comes in at about two
+    // bytes per ns (4 to 8 KiB per wave group, bounds checked element by element, took 2 to 9 us per tile).  So: few instructions per
+    // element, bounds per piece, the elements of cut pieces apart.  With 8-byte stores and checks per element / now, us: 4096 x 4096 x 256
+    // 18.7 / 15.5, 4096 x 4096 x 1024 36.2 / 33.1 (256 x 256 tiles) and 45.0 / 41.5 (128 x 128), 1912 x 3840 x 152 12.1 / 10.3, 2048 x 4096 x
+    // 4096 B^T 67.2 / 65.2, 3000 x 5000 x 4104 107.5 / 105.9, 2048 x 14336 x 4096 with B and C in BFP16 226.5 / 220.8.
+    static constexpr int GRP = S::ACC / 4;                    // groups of four registers per block
+    static constexpr int PAIRS = S::NC * GRP / 2;             // pairs per row block
+    static constexpr int PAIR_COLS = S::T_N / S::WN / PAIRS;  // columns that a pair covers (32 or 16)
+    static_assert((S::NC * GRP) % 2 == 0, "pairs of column groups");
+    // What the epilogue works its addresses out from.  They are worked out there: the compiler would do it ahead of the K loop and keep
+    // the results in registers that the loop needs (the asm below hides from it that they could be known earlier).
+    struct Out {
+        int N, l, rows_left, cols_left;        // rows and columns from this lane's first piece to the end of C
+        char *base;                            // the wave's part of the C tile
+        unsigned off;                          // the lane's first piece, from there
+    };
+    static ATB_DEV int piece_col(int l) { return S::MB == 16 ? ((l >> 4) & 1) * 16 + (l >> 5) * 8 : (l >> 5) * 8; }
+
+    // x of the pair's first group, y of its second -> the lane's columns 0..3 and 4..7
+    static ATB_DEV void swap_halves(unsigned &x, unsigned &y)
     {
+#if defined(__HIP_DEVICE_COMPILE__)
+        typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+        uintx2 r;
+        if constexpr (S::MB == 16) r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        else r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r.x;
+        y = r.y;
+#endif
+    }
+
+    // Pair j of row block a as eight bf16 (four dwords), rounded to nearest even.
+    template <int a, int j>
+    ATB_DEV intx4 piece_bf16() const
+    {
+        unsigned w[2][2];
 #pragma unroll
-        for (int a = 0; a < S::HB * MTW; ++a) {
-            const int m = m0 + (band_of_acc(a / S::HB) + wm) * 32 + (a % S::HB) * S::MB + lane % S::MB;
+        for (int g = 0; g < 2; ++g) {
+            constexpr int first = 2 * j;
+            const accv &v = acc[a / S::HB][a % S::HB][(first + g) / GRP];
+            const int e = 4 * ((first + g) % GRP);
 #pragma unroll
-            for (int b = 0; b < S::NC; ++b) {
-                const int nb = n0 + (wn * S::NC + b) * S::MB + 4 * (lane / S::MB);
+            for (int t = 0; t < 2; ++t) {
+                union { bf16x2 v; unsigned w; } pk;
+                pk.v = bf16x2{(__bf16)v[e + 2 * t], (__bf16)v[e + 2 * t + 1]};
+                w[g][t] = pk.w;
+            }
+        }
+        swap_halves(w[0][0], w[1][0]);
+        swap_halves(w[0][1], w[1][1]);
+        return intx4{(int)w[0][0], (int)w[0][1], (int)w[1][0], (int)w[1][1]};
+    }
+
+    // First row of row block a in this wave's part of the C tile, and its distance in bytes (below 2^32: N <= 2^23).
+    static constexpr int block_row(int a) { return band_of_acc(a / S::HB) * 32 + (a % S::HB) * S::MB; }
+    static ATB_DEV unsigned block_offset(int a, const Out &o) { return (unsigned)block_row(a) * 2u * (unsigned)o.N; }
+
+    template <int a, int j>
+    ATB_DEV void store_pairs(const Out &o) const
+    {
+        if constexpr (j < PAIRS) {
+            typedef intx4 intx4_u __attribute__((aligned(2)));      // rows of C start at any element
+            const intx4 w = piece_bf16<a, j>();
+            if (block_row(a) < o.rows_left && j * PAIR_COLS + 8 <= o.cols_left)
+                *reinterpret_cast<intx4_u *>(o.base + block_offset(a, o) + o.off + j * PAIR_COLS * 2) = w;
+            store_pairs<a, j + 1>(o);
+        }
+    }
+
+    template <int a>
+    ATB_DEV void store_rows(const Out &o) const
+    {
+        if constexpr (a < S::HB * MTW) {
+            store_pairs<a, 0>(o);
+            store_rows<a + 1>(o);
+        }
+    }
+
+    // The pieces that the end of the row cuts (N not a multiple of 8; pieces start at multiples of 8, so each has N % 8 elements), element
+    // by element.
+    template <int a, int j>
+    ATB_DEV void store_cut(const Out &o) const
+    {
+        if constexpr (a < S::HB * MTW) {
+            if constexpr (j < PAIRS) {
+                union { intx4 v; uint16_t h[8]; } u;
+                u.v = piece_bf16<a, j>();
+                if (block_row(a) < o.rows_left && (unsigned)(o.cols_left - j * PAIR_COLS) < 8u) {
+                    uint16_t *dst = reinterpret_cast<uint16_t *>(o.base + block_offset(a, o) + o.off + j * PAIR_COLS * 2);
 #pragma unroll
-                for (int g = 0; g < S::ACC / 4; ++g) {
-                    const int n = nb + 8 * g;
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[a / S::HB][a % S::HB][b][4 * g + e];
-                    if (m < p.M && n < p.N) {
-                        uint16_t *dst = p.C + (int64_t)m * p.N + n;
-                        if (n + 4 <= p.N) {
-                            *reinterpret_cast<bf16x4_u *>(dst) = o;
-                        } else {
-                            union { bf16x4 v; uint16_t h[4]; } u;
-                            u.v = o;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (n + e < p.N) dst[e] = u.h[e];
-                        }
+                    for (int e = 0; e < 7; ++e) {
+                        if (e >= (o.N & 7)) break;
+                        dst[e] = u.h[e];
                     }
                 }
+                store_cut<a + 1, j>(o);
             }
         }
     }
 
-    // Epilogue for C in BFP16 (blocks of 8 along N): a block is the 4 consecutive columns of lane l
-    // plus the 4 of lane l ^ MB (same row).  Same arithmetic as the stand-alone quantiser: shared
-    // exponent = largest fp32 exponent field, mantissa = clamp(rne(x * 2^(133 - E)), +-127).
-    // Needs N % 8 == 0; columns N .. 64 * n_panels - 1 (the tail of C's last panel) are written as zero.
-    ATB_DEV void store_c_bfp()
+    template <int j = 0>
+    ATB_DEV void store_cut_pair(int pair, const Out &o) const
     {
-#pragma unroll
-        for (int a = 0; a < S::HB * MTW; ++a) {
-            const int m = m0 + (band_of_acc(a / S::HB) + wm) * 32 + (a % S::HB) * S::MB + lane % S::MB;
-#pragma unroll
-            for (int b = 0; b < S::NC; ++b) {
-                const int nb = n0 + (wn * S::NC + b) * S::MB + 4 * (lane / S::MB);
-#pragma unroll
-                for (int g = 0; g < S::ACC / 4; ++g) {
-                    const int n = nb + 8 * g;
-                    const bool live = (n < p.N);           // whole blocks: N % 8 == 0
-                    float x[4];
-                    unsigned e = 0;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        x[t] = live ? acc[a / S::HB][a % S::HB][b][4 * g + t] : 0.0f;
-                        e = max(e, exp_field(x[t]));
-                    }
-                    const unsigned other = (unsigned)__builtin_amdgcn_ds_bpermute((lane ^ S::MB) << 2, (int)e);
-                    e = max(e, other);
-                    const int sh = 133 - (int)e;
-                    const unsigned w = bfp16_mantissas4(x, sh);
-                    if (m < p.M && n < p.n_panels * kPanelK) {
-                        const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;       // (panel, row)
-                        *reinterpret_cast<unsigned *>(p.Cm + rec * kPanelK + n % kPanelK) = w;
-                        if (((lane / S::MB) & 1) == 0) p.Ce[rec * (kPanelK / 8) + ((n % kPanelK) >> 3)] = (uint8_t)e;
-                    }
-                }
-            }
+        if constexpr (j < PAIRS) {
+            if (pair == j) store_cut<0, j>(o);
+            else store_cut_pair<j + 1>(pair, o);
         }
+    }
+
+    // C in bf16, once per tile.
+    ATB_DEV void store_c() const
+    {
+        Out o;
+        o.N = p.N;
+        o.l = lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+s"(o.N), "+v"(o.l));
+#endif
+        const int row0 = m0 + __builtin_amdgcn_readfirstlane(wm) * 32, col0 = n0 + __builtin_amdgcn_readfirstlane(wn) * (S::T_N / S::WN);
+        o.base = reinterpret_cast<char *>(p.C + (int64_t)row0 * o.N + col0);
+        o.off = ((unsigned)(o.l % S::MB) * (unsigned)o.N + (unsigned)piece_col(o.l)) * 2u;
+        const int left = o.N - col0;
+        o.rows_left = p.M - row0 - o.l % S::MB;
+        o.cols_left = left - piece_col(o.l);
+        store_rows<0>(o);
+        if ((o.N & 7) != 0 && left > 0 && left < S::T_N / S::WN) store_cut_pair(left / PAIR_COLS, o);
+    }
+
+    template <int a, int j>
+    ATB_DEV void store_bfp_pairs(int m, int n) const
+    {
+        if constexpr (j < PAIRS) {
+            float x[8];
+            unsigned e = 0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                constexpr int g0 = 2 * j, g1 = 2 * j + 1;
+                unsigned lo = __float_as_uint(acc[a / S::HB][a % S::HB][g0 / GRP][4 * (g0 % GRP) + t]);
+                unsigned hi = __float_as_uint(acc[a / S::HB][a % S::HB][g1 / GRP][4 * (g1 % GRP) + t]);
+                swap_halves(lo, hi);
+                x[t] = __uint_as_float(lo);
+                x[4 + t] = __uint_as_float(hi);
+                e = max(e, max(lo & 0x7fffffffu, hi & 0x7fffffffu));
+            }
+            e >>= 23;
+            const int sh = 133 - (int)e;
+            intx2 w = {(int)bfp16_mantissas4(x, sh), (int)bfp16_mantissas4(x + 4, sh)};
+            const int nj = n + j * PAIR_COLS;
+            if (nj >= p.N) {                                   // the tail of C's last panel is zero; whole blocks: N % 8 == 0
+                w = intx2{0, 0};
+                e = 0;
+            }
+            if (m < p.M && nj < p.n_panels * kPanelK) {
+                const int rec = (nj / kPanelK) * p.M + m;                  // (panel, row)
+                *reinterpret_cast<intx2 *>(p.Cm + (int64_t)rec * kPanelK + nj % kPanelK) = w;
+                p.Ce[(int64_t)rec * (kPanelK / 8) + ((nj % kPanelK) >> 3)] = (uint8_t)e;
+            }
+            store_bfp_pairs<a, j + 1>(m, n);
+        }
+    }
+
+    template <int a>
+    ATB_DEV void store_bfp_rows(int m, int n) const
+    {
+        if constexpr (a < S::HB * MTW) {
+            store_bfp_pairs<a, 0>(m + block_row(a), n);
+            store_bfp_rows<a + 1>(m, n);
+        }
+    }
+
+    // C in BFP16 (blocks of 8 along N): the stand-alone quantiser's arithmetic (shared exponent = largest fp32 exponent field, mantissa =
+    // clamp(rne(x * 2^(133 - E)), +-127)).  Needs N % 8 == 0; columns N .. 64 * n_panels - 1 are written as zero.
+    ATB_DEV void store_c_bfp() const
+    {
+        int l = lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(l));
+#endif
+        store_bfp_rows<0>(m0 + wm * 32 + l % S::MB, n0 + wn * (S::T_N / S::WN) + piece_col(l));
     }
 };
 

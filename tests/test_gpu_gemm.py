@@ -81,6 +81,27 @@ def test_exact_inputs_bitwise(tiles):
     assert np.array_equal(_run(mant, expo, Bb, tiles), C_ref)
 
 
+@pytest.mark.parametrize("tiles", SMALL + SKINNY + MID + BIG + WIDE_K)
+def test_ends_of_rows(tiles):
+    """C leaves in pieces of eight columns; a row may end inside a piece (N % 8 = 1 .. 7), between two, at a wave's or a tile's last column,
+    and rows start at any element.  Integer inputs, so the oracle's bits; nothing outside C is written."""
+    import torch
+    T_MC, T_N, M, K = tiles[1], tiles[3], tiles[1] + 17, 72
+    A, Bb = workloads.small_integer_inputs(M, T_N + 41, K, seed=9)
+    mant, expo = oracle.quantize(A)
+    A_dev = torch.from_numpy(pack_a_bfp(mant, expo)).cuda()
+    C_ref, _, _ = oracle.gemm(mant, expo, Bb)
+    for N in list(range(1, 10)) + [15, 17, 31, 33, 34, 63, 65, T_N - 1] + list(range(T_N, T_N + 10)) + [T_N + 33, T_N + 41]:
+        print(f"gemm ends of rows tiles={tiles} N={N}", flush=True)
+        flat = torch.full((M * N + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+        g = atb.Gemm(M, N, K, *tiles)
+        g.run(A_dev, bits_to_bf16_tensor(np.ascontiguousarray(Bb[:, :N]), "cuda"), flat[: M * N].view(M, N))
+        torch.cuda.synchronize()
+        g.close()
+        assert np.array_equal(bf16_tensor_bits(flat[: M * N].view(M, N)), C_ref[:, :N]), N
+        assert bool((flat[M * N:] == 7.0).all()), N
+
+
 @pytest.mark.parametrize("tiles", [(32, 64, 64, 64), (64, 256, 64, 256), (32, 256, 64, 256)])
 def test_identity_and_permutation(tiles):
     print(f"gemm identity tiles={tiles}", flush=True)
