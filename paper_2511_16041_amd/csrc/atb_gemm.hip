@@ -1255,13 +1255,16 @@ struct TileKernel {
         b_read_off = (b_read_off + B_BYTES == NBUF * B_BYTES) ? 0 : b_read_off + B_BYTES;
     }
 
+    // K-steps ki .. KU - 1 of the loop body, of which only the first `left` are wanted.
     template <int ki>
-    ATB_DEV void ksteps()
+    ATB_DEV void ksteps(int left)
     {
         if constexpr (ki < S::KU) {
+            if constexpr (ki > 0 && ROLE != 0 && !EB)
+                if (ki >= left) return;
             phases<ki, 0>();
             if constexpr (RING) advance_b_ring();
-            ksteps<ki + 1>();
+            ksteps<ki + 1>(left);
         }
     }
 
@@ -1325,12 +1328,17 @@ struct TileKernel {
         switch_barrier();
         if constexpr ((S::AB == 4 || EB) && COMPUTE) read_first_band<0, 0>(0);
 
-        // The number of K-steps is rounded up to a whole loop body: the extra steps multiply by B rows
-        // >= K, which read as zero.  The last K-steps of a tile already request, decode and stage the
-        // first operands of the workgroup's next tile (the request streams have moved on to it), so the
-        // next tile needs no prologue: the epilogue is all that separates two tiles' arithmetic.
+        // Between tiles the number of K-steps is rounded up to a whole loop body (buffer and register-set indices are constants of the
+        // body): the extra steps multiply by B rows >= K, which read as zero.  The last K-steps of a tile already request, decode and
+        // stage the first operands of the workgroup's next tile (the request streams have moved on to it), so the next tile needs no
+        // prologue: the epilogue is all that separates two tiles' arithmetic.
+        // The workgroup's last tile ends with its last K-step.  us, rounded up / not: 256^3 at T_K = 256, one K-step, 4.4 / 4.0; 88 x 1792 x
+        // 72 B^T at T_K = 64 6.7 / 5.8; 1500 x 3000 x 2056, 33 K-steps, 33.9 / 32.9.  Not in ROLE 0 (with 256 accumulators per wave the way
+        // out in mid-body makes 200 to 400 registers spill) nor with the early barrier, where K-steps overlap (2048 x 4096 x 14336 256.6 / 259.5).
         for (;;) {
-            for (int kt = 0; kt < kt_steps; kt += S::KU) ksteps<0>();
+            int next_m0, next_n0;
+            const int steps = tile_at(c_t + t_stride, next_m0, next_n0) ? kt_steps : (p.K + S::T_K - 1) / S::T_K;
+            for (int kt = 0; kt < steps; kt += S::KU) ksteps<0>(steps - kt);
             if constexpr (!COMPUTE) { } else if constexpr (CBFP) store_c_bfp(); else store_c();
             c_t += t_stride;
             if (!tile_at(c_t, m0, n0)) break;

@@ -102,6 +102,18 @@ def test_ends_of_rows(tiles):
         assert bool((flat[M * N:] == 7.0).all()), N
 
 
+@pytest.mark.parametrize("tiles", SMALL + SKINNY + MID + BIG + WIDE_K)
+def test_numbers_of_k_steps(tiles):
+    """A reduction of one to four K-steps, whole and with a tail of 8: the loop body has two, and a tile may end after the first.  Integer
+    inputs, so the oracle's bits."""
+    T_K, M, N = tiles[2], tiles[1] + 1, tiles[3] + 2
+    for K in (T_K - 8, T_K, T_K + 8, 2 * T_K, 2 * T_K + 8, 3 * T_K, 3 * T_K + 8):
+        print(f"gemm K-steps tiles={tiles} K={K}", flush=True)
+        A, Bb = workloads.small_integer_inputs(M, N, K, seed=K)
+        mant, expo = oracle.quantize(A)
+        assert np.array_equal(_run(mant, expo, Bb, tiles), oracle.gemm(mant, expo, Bb)[0]), K
+
+
 @pytest.mark.parametrize("tiles", [(32, 64, 64, 64), (64, 256, 64, 256), (32, 256, 64, 256)])
 def test_identity_and_permutation(tiles):
     print(f"gemm identity tiles={tiles}", flush=True)
