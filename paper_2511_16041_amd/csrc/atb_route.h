@@ -87,6 +87,12 @@ inline int64_t stream_workgroups(const GemmParams &p, const StreamRoute &r) { re
 // Measured (us, M = 16, bf16 B): N = 14336, K = 4096: 35.4 / 24.4 / 31.9 with 32 / 64 / 128 columns; N = 28672: 59 / 54 / 44.
 inline int stream_column_blocks(int N, int cus) { return N <= 32 * cus ? 2 : N <= 64 * cus ? 4 : 8; }
 
+// Panels of K in flight per wave with B in BFP16, 32 or 64 columns and eight waves.  With one panel a wave either waits or decodes; two
+// are taken where they come out even (a wave's last round may otherwise be one of zeros; a branch around it costs the overlap).
+// Measured, one / two, us: 32 x 14336 x 4096 16.4 / 15.0, 64 x 14336 x 4096 21.2 / 19.8, 128 x 4096 x 4096 16.3 / 14.6, 256 x 2048 x 8192 27.5 /
+// 23.9, 64 x 12288 x 2048 13.3 / 13.0; three rounds: 64 x 10000 x 1536 11.3 / 12.9, 65 x 3000 x 1088 7.4 / 8.0; 16 rows are level.
+inline int stream_depth_bfp16(int k_panels, int mb) { return mb >= 2 && (k_panels + 7) / 8 % 2 == 0 ? 2 : 1; }
+
 // More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
 // none where the tile pipeline is as good or better.  Measured in us, the pipeline / this kernel, or as the ratio of the two; "memory":
 // 700 MB of operands in turns, so that B comes from memory as a model's weights do; "cache": three sets in turns, which the 256 MiB
@@ -111,8 +117,9 @@ inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int
         if (tile_count(p, 64, 128) <= cus && p.K >= 4096) return {4, 8, 4, 2};
         return {};
     }
-    if (tile_count(p, 64, 32) <= cus) return {4, 2, 8, 1};
-    if (tile_count(p, 64, 64) <= cus) return b_format == ATB_FMT_BFP16 && small_tiles && p.K > 1152 ? StreamRoute{} : StreamRoute{4, 4, 8, 1};
+    const int depth = b_format == ATB_FMT_BFP16 ? stream_depth_bfp16(p.k_panels, 4) : 1;
+    if (tile_count(p, 64, 32) <= cus) return {4, 2, 8, depth};
+    if (tile_count(p, 64, 64) <= cus) return b_format == ATB_FMT_BFP16 && small_tiles && p.K > 1152 ? StreamRoute{} : StreamRoute{4, 4, 8, depth};
     if (b_format == ATB_FMT_BF16_T && tile_count(p, 128, 64) <= cus) return {8, 4, 4, 1};
     return {};
 }
@@ -168,7 +175,7 @@ inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
     if (p.M > 64) return stream_route_many_rows(p, b_format, cus);
     if (!stream_few_rows(p, b_format, cus)) return {};
     const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N, cus);
-    if (b_format == ATB_FMT_BFP16) return {mb, nb, nb == 2 ? 16 : 8, 1};
+    if (b_format == ATB_FMT_BFP16) return {mb, nb, nb == 2 ? 16 : 8, nb == 4 ? stream_depth_bfp16(p.k_panels, mb) : 1};
     if (b_format == ATB_FMT_BF16 && p.N % 2 != 0) return {mb, 2, 8, 1};
     return {mb, nb, nb == 2 ? 8 : 4, 1};
 }

@@ -104,6 +104,19 @@ def test_streaming_kernel(shape, b_format, c_format, exact):
     _check(g, exact)
 
 
+@pytest.mark.parametrize("exact", [True, False])
+@pytest.mark.parametrize("c_format", BOTH)
+@pytest.mark.parametrize("shape", [(20, 8264, 1608), (48, 8264, 2048), (49, 8264, 1544), (66, 72, 1608), (129, 1032, 1992), (257, 2120, 1992)])
+def test_two_panels_in_flight(shape, c_format, exact):
+    """B in BFP16, four rounds of eight panels: 20 to 64 rows and more, 64 and 32 columns, the last round whole, of one panel (1544) or with a
+    tail."""
+    print(f"two panels {shape} C={c_format} exact={exact}", flush=True)
+    M, N, K = shape
+    g = atb.Gemm(M, columns(N, c_format), K, 32, 32, 256, 64, b_format="bfp16", c_format=c_format)
+    assert g.streams() and g.launch_info().threads == 512 and (-(-K // 64) + 7) // 8 == 4
+    _check(g, exact, seed=25)
+
+
 def test_wide_and_long():
     print(f"skinny {WIDE_AND_LONG}", flush=True)
     g = plan(WIDE_AND_LONG, "bf16", "bf16")
