@@ -3,6 +3,8 @@ buffering for MI355X).  Argument marshalling only: every step of the path runs
 in the HIP kernels behind the C ABI declared in include/atb.h.  PyTorch is used
 for device memory and streams, nothing else.  There is no CPU fallback: if the
 shared library is missing or a call fails, an exception is raised.
+The calls that launch a GEMM or the quantiser go through a small extension
+module (csrc/atb_binding.cpp), everything else through ctypes.
 """
 from __future__ import annotations
 
@@ -141,6 +143,33 @@ def _t():
     return _torch
 
 
+_ext = None
+_entry_points = (0, 0)                   # addresses of atb_bfp16_quantize, atb_bfp16_decode
+
+
+def _launcher():
+    """The extension module, loaded at the first device call (it links against torch)."""
+    global _ext, _entry_points
+    if _ext is None:
+        _t()
+        lib()
+        from . import _launch
+        _entry_points = (_address("atb_bfp16_quantize"), _address("atb_bfp16_decode"))
+        _ext = _launch
+    return _ext
+
+
+class _RunSpec(ctypes.Structure):       # RunSpec of csrc/atb_binding.cpp
+    _fields_ = [("run", ctypes.c_void_p), ("plan", ctypes.c_void_p), ("a_bytes", ctypes.c_int64),
+                ("b_bytes", ctypes.c_int64), ("b_rows", ctypes.c_int64), ("b_cols", ctypes.c_int64),
+                ("c_bytes", ctypes.c_int64), ("c_rows", ctypes.c_int64), ("c_cols", ctypes.c_int64)]
+
+
+@functools.lru_cache(maxsize=None)
+def _address(name: str) -> int:
+    return ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+
+
 def _stream_ptr(stream) -> int:
     """hipStream_t of `stream`, by default of the current device's current stream.  (torch.cuda.current_stream() makes a
     Stream object, about 2 us of a call that is launched in 3; the raw handle is what torch's own launchers use.)"""
@@ -256,16 +285,17 @@ def bfp16_quantize(A_f32, stream=None, out=None):
         raise AtbError(1, "atb_bfp16_bytes")
     if out is None:
         out = torch.empty(nbytes, dtype=torch.uint8, device=A_f32.device)
-    assert out.is_cuda and out.dtype == torch.uint8 and out.is_contiguous() and out.numel() == nbytes
-    _check((_lib or lib()).atb_bfp16_quantize(A_f32.data_ptr(), A_f32.stride(0), out.data_ptr(), M, K, _stream_ptr(stream)),
-           "atb_bfp16_quantize")
+    ext = _ext or _launcher()            # checks out: CUDA uint8, contiguous, nbytes elements
+    st = ext.quantize(_entry_points[0], A_f32, out, nbytes, None if stream is None else stream.cuda_stream)
+    if st != 0:
+        raise AtbError(st, "atb_bfp16_quantize")
     return out
 
 
 def bfp16_decode(A_bfp, M: int, K: int, stream=None):
-    torch = _t()
-    out = torch.empty((M, K), dtype=torch.bfloat16, device=A_bfp.device)
-    _check((_lib or lib()).atb_bfp16_decode(A_bfp.data_ptr(), out.data_ptr(), M, K, _stream_ptr(stream)), "atb_bfp16_decode")
+    out = (_ext or _launcher()).decode(_entry_points[1], A_bfp, M, K, None if stream is None else stream.cuda_stream)
+    if type(out) is int:
+        raise AtbError(out, "atb_bfp16_decode")
     return out
 
 
@@ -312,35 +342,28 @@ class Gemm:
             _check(lib().atb_gemm_create_fmt(ctypes.byref(self._h), M, N, K, T_MA, T_MC, T_K, T_N,
                                              FORMATS[b_format], FORMATS[c_format]), "atb_gemm_create_fmt")
 
-        # what run() checks its operands against, and the bound call: a small problem is launched in about 3 us, and
-        # working these out again took longer than that
-        self._a_bytes = bfp16_bytes(M, K)
-        self._b_shape = (K, N) if b_format == "bf16" else (N, K)
-        self._b_bytes = bfp16_bytes(N, K) if b_format == "bfp16" else 0
-        self._c_bytes = bfp16_bytes(M, N) if c_format == "bfp16" else 0
-        self._call = lib().atb_gemm_run
+        # what run() checks its operands against, in the form the extension reads; a small problem is launched in under 4 us, and working
+        # this out again for each call took a third of that
+        c_bytes = bfp16_bytes(M, N) if c_format == "bfp16" else 0
+        self._spec = _RunSpec(_address("atb_gemm_run"), self._h, bfp16_bytes(M, K), bfp16_bytes(N, K) if b_format == "bfp16" else 0,
+                              *((K, N) if b_format == "bf16" else (N, K)), c_bytes, M, N)
+        self._spec_address = ctypes.addressof(self._spec)
 
     def run(self, A_bfp, B, C=None, stream=None):
-        torch = _torch or _t()
-        uint8, bfloat16 = torch.uint8, torch.bfloat16
-        assert A_bfp.is_cuda and A_bfp.dtype == uint8 and A_bfp.numel() == self._a_bytes
-        if self._b_bytes:
-            assert B.is_cuda and B.dtype == uint8 and B.numel() == self._b_bytes
-        else:
-            assert B.is_cuda and B.dtype == bfloat16 and B.shape == self._b_shape and B.is_contiguous()
-        if self._c_bytes:
-            if C is None:
-                C = torch.empty(self._c_bytes, dtype=uint8, device=A_bfp.device)
-            assert C.dtype == uint8 and C.numel() == self._c_bytes
-        else:
-            M, N, _ = self.shape
-            if C is None:
-                C = torch.empty((M, N), dtype=bfloat16, device=A_bfp.device)
-            assert C.dtype == bfloat16 and C.shape == (M, N) and C.is_contiguous()
-        st = self._call(self._h, A_bfp.data_ptr(), B.data_ptr(), C.data_ptr(), _stream_ptr(stream))
+        """C = A x B on `stream` (the current one).  Operands that are not what the plan was made for raise AssertionError: A and a BFP16 B
+        are CUDA uint8 tensors of their format's size, a bf16 B is CUDA and contiguous, C (a new tensor if not given) likewise."""
+        if C is None:
+            C = self._new_c(A_bfp.device)
+        st = (_ext or _launcher()).run(self._spec_address, A_bfp, B, C, None if stream is None else stream.cuda_stream)
         if st != 0:
             raise AtbError(st, "atb_gemm_run")
         return C
+
+    def _new_c(self, device):
+        torch = _t()
+        if self._spec.c_bytes:
+            return torch.empty(self._spec.c_bytes, dtype=torch.uint8, device=device)
+        return torch.empty((self._spec.c_rows, self._spec.c_cols), dtype=torch.bfloat16, device=device)
 
     def launch_info(self) -> LaunchInfo:
         wg, th, lds = ctypes.c_int64(), ctypes.c_int(), ctypes.c_int()
@@ -354,6 +377,7 @@ class Gemm:
 
     def close(self):
         if self._h:
+            self._spec.plan = None
             lib().atb_gemm_destroy(self._h)
             self._h = ctypes.c_void_p()
 

@@ -1,4 +1,4 @@
-"""Build libatb.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Build libatb.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's extension module with g++, in-tree."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libatb.so")
+EXT = os.path.join(HERE, "_launch.so")           # the binding's extension module (csrc/atb_binding.cpp)
 OBJ_DIR = os.path.join(HERE, "_build")
 # accumulators stay in ordinary vector registers: with up to 470 of a wave's 512 in use the compiler otherwise parks other
 # values in the accumulation half and moves the accumulators out and in again around every panel (208 moves to 64 MFMAs)
@@ -44,8 +45,27 @@ def _compile(item, extra, verbose: bool) -> str:
     return obj
 
 
+def build_binding(verbose: bool = False) -> str:
+    """The extension module that checks operands and launches; host code only, against torch's headers and libraries."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    includes = include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    for d in includes:
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "atb_binding.cpp"), "-o", EXT, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return EXT
+
+
 def build(verbose: bool = False, extra=()) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
+    build_binding(verbose)
     with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(lambda s: _compile(s, extra, verbose), SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT] + objs
@@ -69,10 +89,10 @@ def build_microbench(verbose: bool = False) -> str:
 
 
 def _stale() -> bool:
-    """True if the library is missing or older than any of its sources (or this file)."""
-    if not os.path.exists(OUT):
+    """True if the library or the extension module is missing or older than any of the sources (or this file)."""
+    if not os.path.exists(OUT) or not os.path.exists(EXT):
         return True
-    built = os.path.getmtime(OUT)
+    built = min(os.path.getmtime(OUT), os.path.getmtime(EXT))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if os.path.isfile(os.path.join(CSRC, f))]
     deps += [os.path.join(ROOT, "include", "atb.h"), os.path.abspath(__file__)]
     return any(os.path.getmtime(d) > built for d in deps)

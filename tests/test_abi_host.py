@@ -347,3 +347,19 @@ def test_gpu_cases_reach_every_streaming_variant():
                     g.close()
     sent.discard(None)
     assert len(reached) == 43 and sent <= reached, sent - reached
+
+
+def test_device_calls_refuse_host_tensors():
+    """What the extension module checks before any launch (no GPU is needed to be refused)."""
+    import torch
+    g = atb.Gemm(8, 16, 64, 32, 64, 64, 64)
+    a, b, c = torch.zeros(atb.bfp16_bytes(8, 64), dtype=torch.uint8), torch.zeros(64, 16, dtype=torch.bfloat16), torch.zeros(8, 16, dtype=torch.bfloat16)
+    with pytest.raises(AssertionError):
+        g.run(a, b, c)
+    with pytest.raises(TypeError):
+        g.run(a, b.float().numpy(), c)
+    with pytest.raises(AssertionError):
+        atb.bfp16_quantize(torch.zeros(8, 64))
+    with pytest.raises(AssertionError):
+        atb.bfp16_decode(a, 8, 64)
+    g.close()

@@ -114,6 +114,40 @@ def test_numbers_of_k_steps(tiles):
         assert np.array_equal(_run(mant, expo, Bb, tiles), oracle.gemm(mant, expo, Bb)[0]), K
 
 
+@pytest.mark.parametrize("b_format,c_format", [("bf16", "bf16"), ("bf16_t", "bf16"), ("bfp16", "bfp16")])
+def test_run_checks_its_operands(b_format, c_format):
+    """Types, sizes, shapes and strides that the plan was not made for, and a plan that is closed; strides, streams and new results that are fine."""
+    import torch
+    M, N, K = 40, 72, 64
+    g = atb.Gemm(M, N, K, 64, 128, 64, 256, b_format=b_format, c_format=c_format)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    a = atb.bfp16_quantize(torch.randn(M, K, generator=gen, device="cuda"))
+    w = torch.randn(N, K, generator=gen, device="cuda")
+    b = {"bf16": w.t().contiguous().bfloat16(), "bf16_t": w.bfloat16(), "bfp16": atb.bfp16_quantize(w)}[b_format]
+    c = g.run(a, b)
+    torch.cuda.synchronize()
+    assert c.is_cuda and (c.dtype, c.numel()) == ((torch.bfloat16, M * N) if c_format == "bf16" else (torch.uint8, atb.bfp16_bytes(M, N)))
+
+    def result(t):               # (between and behind its planes a BFP16 buffer has bytes that nobody writes)
+        return bf16_tensor_bits(t) if c_format == "bf16" else np.concatenate([x.view(np.uint8).ravel() for x in atb.bfp16_unpack_host(t.cpu().numpy(), M, N)])
+    side, e = torch.cuda.Stream(), torch.zeros_like(c)
+    torch.cuda.synchronize()
+    assert g.run(a, b, e, stream=side) is e
+    with torch.cuda.stream(side):
+        d = g.run(a, b)
+    side.synchronize()
+    assert np.array_equal(result(e), result(c)) and np.array_equal(result(d), result(c))
+    bad = [(a[:-256], b, c), (a.view(torch.int8), b, c), (a, b, c.float()), (a, b[:-1] if b.dim() == 2 else b[:-256], c), (a, b, c.flatten()[:-1]), (a.cpu(), b, c), (a, b.cpu(), c)]
+    if b.dim() == 2:
+        bad += [(a, b.t(), c), (a, b.half(), c), (a, torch.empty(b.shape[0], 2 * b.shape[1], dtype=b.dtype, device="cuda")[:, ::2], c)]
+    for args in bad:
+        with pytest.raises(AssertionError):
+            g.run(*args)
+    g.close()
+    with pytest.raises(atb.AtbError):
+        g.run(a, b, c)
+
+
 @pytest.mark.parametrize("tiles", [(32, 64, 64, 64), (64, 256, 64, 256), (32, 256, 64, 256)])
 def test_identity_and_permutation(tiles):
     print(f"gemm identity tiles={tiles}", flush=True)
