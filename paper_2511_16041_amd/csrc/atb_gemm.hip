@@ -303,6 +303,9 @@ struct TileKernel {
     // most sizes the selector gives them: 49 x 39829 x 784 -7 %, 8 x 33001 x 1032 -6 % (but 1500 x 4001 x 2056 +10 %); 73 such sizes
     // are 3 to 5 % faster without.
     static constexpr bool LAG = !VEC && S::T_MC * S::T_N < 256 * 256 && !(S::T_MC * S::T_N <= 64 * 64 && S::T_K == 64);
+    static constexpr int B_ROWS = NTS / S::B_CPR;                                        // rows between a thread's chunks of the B tile
+    // row_shr moves a value by up to 15 lanes of 16; a thread's chunks sit at one chunk position of their rows or at that and the one that differs in bit 1
+    static_assert(!LAG || (BPT <= 8 && BPT <= S::B_CPR && 64 % S::B_CPR == 0 && B_ROWS % 8 == 0 && ((S::b_swz(8) | S::b_swz(16)) & ~2) == 0 && S::b_swz(32) == 0), "odd N: ends of rows, swizzle of a thread's chunks");
     static constexpr int NPAIR_B = BTPT * 8;                                             // B mantissa pairs per thread per tile
     static constexpr int NSTEP_A = NPAIR == 0 ? 0 : SK ? NPAIR / 4 : NPAIR + 2;          // decode items per phase (A sub-tile): pipeline steps, or blocks
     static constexpr int NSTEP_B = NPAIR_B > 0 ? NPAIR_B / S::RHO + 2 : 0;               // ... and for this phase's share of the B tile
@@ -402,7 +405,9 @@ struct TileKernel {
     intx4 a_mant[S::PF][APTN];
     unsigned a_expo[S::PF][APTN];
     intx4 b_raw[BPTN];
-    int b_fifth[BPTN];                 // LAG: the dword after b_raw's four
+    // LAG: the dword after the last four of an odd row of this wave's part of the B tile, chunk i's in the lane i below the row's last (and
+    // where a lane's is, outside the buffer where it has none); from a chunk position to the one that differs in bit 1, in bytes
+    int b_ends, b_end_off, b_flip;
     unsigned dec[4];                   // bf16 pairs of the BFP16 block being decoded
     float cvf[2][2], ldf[2][2];        // decode pipeline: converted and scaled pairs in flight
     int shift;
@@ -457,11 +462,17 @@ struct TileKernel {
 #pragma unroll
             for (int ks = 0; ks < S::KS; ++ks) a_rdk[ks] = lds + rrow * S::PA + ((((S::KM / 8) * ks + lane / S::MB) ^ rswz) * 16);
         }
+        const int wr_row = (slot0 + lane) / S::B_CPR, wr_c = (slot0 + lane) % S::B_CPR;        // LAG: the first chunk this thread stores
+        {
+            const int i = S::B_CPR - 1 - wr_c, off = ((wr_row + i * B_ROWS) * p.N + S::T_N) * 2;
+            b_end_off = (i < BPT && (off & 2) != 0) ? off - 2 : (int)0x80000000;
+        }
+        b_flip = ((wr_c ^ S::b_swz(wr_row)) & 2) ? -32 : 32;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             char *b_base = lds + S::AB * S::A_BYTES + b * B_BYTES;
             b_req[b] = b_base + slot0 * 16;
-            b_wr[b] = b_req[b] + lane * 16;
+            b_wr[b] = !LAG ? b_req[b] + lane * 16 : b_base + wr_row * S::PB + (wr_c ^ S::b_swz(wr_row)) * 16;
             // B fragment through ds_read_b64_tr_b16: within each group of 16 lanes, lane i addresses
             // 4 consecutive columns of row i/4 (8 bytes, half a chunk), and lane j receives column j
             // of those 4 rows; a second read, 4 rows on, completes the lane's 8 k values.
@@ -537,7 +548,9 @@ struct TileKernel {
                 const int row = slot / (S::T_K / 8), c = (slot % (S::T_K / 8)) ^ ((row >> 1) & 7);
                 b_off[i] = (row * p.K + c * 8) * 2;
             } else {
-                const int row = slot / S::B_CPR, c = (slot % S::B_CPR) ^ S::b_swz(row);
+                // the slot is a place in LDS, and its chunk the one that the swizzle keeps there; LAG: neighbouring lanes take
+                // neighbouring chunks, and the swizzle is in the address of the store
+                const int row = slot / S::B_CPR, c = LAG ? slot % S::B_CPR : (slot % S::B_CPR) ^ S::b_swz(row);
                 b_off[i] = (row * p.N + c * 8) * 2;
             }
         }
@@ -646,6 +659,7 @@ struct TileKernel {
             b_left = live ? (int64_t)p.K * p.N * 2 : 0;
 #pragma unroll
             for (int i = 0; i < BPT; ++i) b_off[i] += d * 2;
+            if constexpr (LAG) b_end_off += d * 2;
         }
     }
 
@@ -855,17 +869,17 @@ struct TileKernel {
 #endif
         } else {
             // odd N: a chunk starts at an odd bf16 of its row as often as not.  Fetch the 5 aligned
-            // dwords that contain it and shift by half a dword where needed.
-            const int al = b_off[i] & ~3, sh = (b_off[i] & 2) * 8;
+            // dwords that contain it and shift by half a dword where needed.  The fifth is the next lane's first, but at the end of
+            // a row; those of a tile's odd rows come in one request per wave, spread over lanes (b_ends).  What the requests for it cost was
+            // their number, not their bytes: one per chunk / one per tile, us: 1500 x 3001 x 2056 48.2 / 45.9 (N = 3000: 35.1), 600 x 1501 x 1000
+            // 11.5 / 11.0, 30 x 33001 x 1000 28.2 / 26.7, 300 x 301 x 304 6.3 / 5.9.
+            const int al = b_off[i] & ~3;
             const intx4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs.b, al, 0, 0);
-            // every other row is dword-aligned and needs no fifth dword: its lanes ask outside the buffer, which costs no
-            // memory access (47.0 -> 45.3 us; not on the tiles that are short of registers for the choice)
-            const int hi = __builtin_amdgcn_raw_buffer_load_b32(rs.b, (LAG && sh == 0) ? (int)0x80000000 : al + 16, 0, 0);
             if constexpr (LAG) {         // shifted when it is stored: here the shift would wait for the request
                 b_raw[i] = lo;
-                b_fifth[i] = hi;
+                if constexpr (i == BPT - 1) b_ends = __builtin_amdgcn_raw_buffer_load_b32(rs.b, b_end_off, 0, 0);
             } else {
-                b_raw[i] = shifted(lo, hi, sh);
+                b_raw[i] = shifted(lo, __builtin_amdgcn_raw_buffer_load_b32(rs.b, al + 16, 0, 0), (b_off[i] & 2) * 8);
             }
         }
         if constexpr (i == BPT - 1) {
@@ -997,7 +1011,14 @@ struct TileKernel {
     template <int i>
     ATB_DEV void store_b_chunk(char *b_dst)
     {
-        *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16)) = LAG ? shifted(b_raw[i], b_fifth[i], (b_off[i] & 2) * 8) : b_raw[i];
+        if constexpr (LAG) {
+            const int next = __builtin_amdgcn_update_dpp(0, b_raw[i].x, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
+            const int end = i == 0 ? b_ends : __builtin_amdgcn_update_dpp(0, b_ends, 0x110 + (i == 0 ? 1 : i) /* row_shr:i */, 0xf, 0xf, false);
+            const intx4 v = shifted(b_raw[i], lane % S::B_CPR == S::B_CPR - 1 ? end : next, (b_off[i] & 2) * 8);
+            *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16) + (S::b_swz(i * B_ROWS) != 0 ? b_flip : 0)) = v;
+        } else {
+            *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16)) = b_raw[i];
+        }
     }
 
     template <int set>

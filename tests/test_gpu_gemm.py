@@ -328,6 +328,19 @@ def test_skinny_shapes(tiles, shape):
     _check(_run(mant, expo, Bb, tiles), C_ref, T, f"skinny {shape} {tiles}")
 
 
+@pytest.mark.parametrize("tiles", MID + SKINNY + [(64, 64, 128, 128)])
+@pytest.mark.parametrize("shape", [(40, 65, 712), (140, 129, 1000), (33, 643, 520), (100, 1027, 136)])
+def test_odd_n_ends_of_rows(tiles, shape):
+    """Odd N, B staged a K-step late: the last columns of an inner tile lie across two dwords in every odd row, of which the second belongs to
+    the next tile.  N one past a tile's width and two to sixteen tiles wide, an odd and an even number of K-steps; exact inputs."""
+    M, N, K = shape
+    print(f"gemm odd N {shape} tiles={tiles}", flush=True)
+    A, Bb = workloads.small_integer_inputs(M, N, K, seed=31)
+    mant, expo = oracle.quantize(A)
+    C_ref, T, _ = oracle.gemm(mant, expo, Bb)
+    assert np.array_equal(_run(mant, expo, Bb, tiles), C_ref)
+
+
 def test_every_instance_gives_the_same_bits():
     """Tiling changes data movement, not arithmetic: every instance adds the products of an output element in the
     same order (k ascending, 16 per MFMA, one fp32 accumulator), so on any data all instances must agree bit for
