@@ -30,7 +30,7 @@
 // Operand lane layout: lane l supplies row (l % MB) of its operand and the 8 consecutive k values
 // 8*(l/MB) .. +7, which for the A operand is exactly one BFP16 block.  The B fragment is passed as
 // the first operand and the A fragment as the second, so a lane of the result holds one row m
-// (= l % MB) and groups of 4 consecutive columns (n = 8*g + 4*(l/MB) + 0..3) -> 8-byte bf16 stores.
+// (= l % MB) and groups of 4 consecutive columns (n = 8*g + 4*(l/MB) + 0..3); a lane swap makes 8 of two, 16 bytes of bf16.
 #include <algorithm>
 
 #include "atb_device.h"
