@@ -144,7 +144,7 @@ def _t():
 
 
 _ext = None
-_entry_points = (0, 0)                   # addresses of atb_bfp16_quantize, atb_bfp16_decode
+_entry_points = (0, 0, 0)                # addresses of atb_bfp16_quantize, atb_bfp16_decode, atb_bfp16_bytes
 
 
 def _launcher():
@@ -154,7 +154,7 @@ def _launcher():
         _t()
         lib()
         from . import _launch
-        _entry_points = (_address("atb_bfp16_quantize"), _address("atb_bfp16_decode"))
+        _entry_points = (_address("atb_bfp16_quantize"), _address("atb_bfp16_decode"), _address("atb_bfp16_bytes"))
         _ext = _launch
     return _ext
 
@@ -293,7 +293,9 @@ def bfp16_quantize(A_f32, stream=None, out=None):
 
 
 def bfp16_decode(A_bfp, M: int, K: int, stream=None):
-    out = (_ext or _launcher()).decode(_entry_points[1], A_bfp, M, K, None if stream is None else stream.cuda_stream)
+    """A_bfp: CUDA tensor, contiguous, of at least bfp16_bytes(M, K) bytes (else AssertionError) -> bf16 tensor [M][K]."""
+    ext = _ext or _launcher()
+    out = ext.decode(_entry_points[1], _entry_points[2], A_bfp, M, K, None if stream is None else stream.cuda_stream)
     if type(out) is int:
         raise AtbError(out, "atb_bfp16_decode")
     return out
@@ -350,8 +352,9 @@ class Gemm:
         self._spec_address = ctypes.addressof(self._spec)
 
     def run(self, A_bfp, B, C=None, stream=None):
-        """C = A x B on `stream` (the current one).  Operands that are not what the plan was made for raise AssertionError: A and a BFP16 B
-        are CUDA uint8 tensors of their format's size, a bf16 B is CUDA and contiguous, C (a new tensor if not given) likewise."""
+        """C = A x B on `stream` (the current one).  Operands that are not what the plan was made for raise AssertionError: all are
+        contiguous, A and a BFP16 B CUDA uint8 tensors of their format's size, a bf16 B a CUDA tensor of its shape; C (a new tensor if
+        not given) likewise, on CUDA or in pinned host memory."""
         if C is None:
             C = self._new_c(A_bfp.device)
         st = (_ext or _launcher()).run(self._spec_address, A_bfp, B, C, None if stream is None else stream.cuda_stream)

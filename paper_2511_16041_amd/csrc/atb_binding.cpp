@@ -29,7 +29,10 @@ bool is_matrix(const at::Tensor &t, int64_t rows, int64_t cols)
     return t.scalar_type() == at::kBFloat16 && t.dim() == 2 && t.size(0) == rows && t.size(1) == cols && t.is_contiguous();
 }
 
-bool is_buffer(const at::Tensor &t, int64_t bytes) { return t.scalar_type() == at::kByte && t.numel() == bytes; }
+bool is_buffer(const at::Tensor &t, int64_t bytes) { return t.scalar_type() == at::kByte && t.numel() == bytes && t.is_contiguous(); }
+
+// Where a kernel can store: C may also be in pinned host memory.
+bool on_device_or_pinned(const at::Tensor &t) { return t.is_cuda() || t.is_pinned(); }
 
 PyObject *refuse()
 {
@@ -68,7 +71,7 @@ PyObject *run(PyObject *, PyObject *const *args, Py_ssize_t n)
         const at::Tensor &a = THPVariable_Unpack(args[1]), &b = THPVariable_Unpack(args[2]), &c = THPVariable_Unpack(args[3]);
         if (!a.is_cuda() || !is_buffer(a, s->a_bytes) || !b.is_cuda()) return refuse();
         if (!(s->b_bytes ? is_buffer(b, s->b_bytes) : is_matrix(b, s->b_rows, s->b_cols))) return refuse();
-        if (!(s->c_bytes ? is_buffer(c, s->c_bytes) : is_matrix(c, s->c_rows, s->c_cols))) return refuse();
+        if (!on_device_or_pinned(c) || !(s->c_bytes ? is_buffer(c, s->c_bytes) : is_matrix(c, s->c_rows, s->c_cols))) return refuse();
         const void *pa = a.data_ptr(), *pb = b.data_ptr();
         void *pc = c.data_ptr(), *stream = nullptr;
         if (!stream_of(args[4], &stream)) return nullptr;
@@ -93,7 +96,7 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     if (PyErr_Occurred() || !tensors(args + 1, 2)) return nullptr;
     try {
         const at::Tensor &a = THPVariable_Unpack(args[1]), &out = THPVariable_Unpack(args[2]);
-        if (!out.is_cuda() || !is_buffer(out, bytes) || !out.is_contiguous()) return refuse();
+        if (!out.is_cuda() || !is_buffer(out, bytes)) return refuse();
         const int64_t rows = a.size(0), cols = a.size(1), lda = a.stride(0);
         const float *pa = static_cast<const float *>(a.data_ptr());
         void *po = out.data_ptr(), *stream = nullptr;
@@ -109,22 +112,25 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     }
 }
 
-// decode(address of atb_bfp16_decode, A, rows, columns, stream handle or None) -> the decoded matrix, or the status if that is not 0
+// decode(address of atb_bfp16_decode, address of atb_bfp16_bytes, A, rows, columns, stream handle or None) -> the decoded matrix, or the
+// status if that is not 0.  A is read as bytes, whatever its type, and may be longer.
 PyObject *decode(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     typedef int (*fn)(const void *, void *, int64_t, int64_t, void *);
-    if (n != 5) return PyErr_Format(PyExc_TypeError, "decode takes 5 arguments");
+    if (n != 6) return PyErr_Format(PyExc_TypeError, "decode takes 6 arguments");
+    typedef size_t (*size_fn)(int64_t, int64_t);
     const fn call = reinterpret_cast<fn>(PyLong_AsVoidPtr(args[0]));
+    const size_fn size = reinterpret_cast<size_fn>(PyLong_AsVoidPtr(args[1]));
     if (PyErr_Occurred()) return nullptr;
-    const int64_t rows = PyLong_AsLongLong(args[2]), cols = PyLong_AsLongLong(args[3]);
-    if (PyErr_Occurred() || !tensors(args + 1, 1)) return nullptr;
+    const int64_t rows = PyLong_AsLongLong(args[3]), cols = PyLong_AsLongLong(args[4]);
+    if (PyErr_Occurred() || !tensors(args + 2, 1)) return nullptr;
     try {
-        const at::Tensor &a = THPVariable_Unpack(args[1]);
-        if (!a.is_cuda()) return refuse();
+        const at::Tensor &a = THPVariable_Unpack(args[2]);
+        if (!a.is_cuda() || !a.is_contiguous() || a.nbytes() < size(rows, cols)) return refuse();     // (a size of 0: the call below says why)
         at::Tensor out = at::empty({rows, cols}, at::TensorOptions().dtype(at::kBFloat16).device(a.device()));
         const void *pa = a.data_ptr();
         void *po = out.data_ptr(), *stream = nullptr;
-        if (!stream_of(args[4], &stream)) return nullptr;
+        if (!stream_of(args[5], &stream)) return nullptr;
         int st;
         Py_BEGIN_ALLOW_THREADS
         st = call(pa, po, rows, cols, stream);

@@ -363,3 +363,54 @@ def test_device_calls_refuse_host_tensors():
     with pytest.raises(AssertionError):
         atb.bfp16_decode(a, 8, 64)
     g.close()
+
+
+def _on_device(size, dtype, strides=None):
+    """A tensor that says that it is on the GPU and has no memory: what is refused before a launch needs no GPU to be tested."""
+    import torch
+
+    class OnDevice(torch.Tensor):
+        @staticmethod
+        def __new__(cls):
+            return torch.Tensor._make_wrapper_subclass(cls, size, strides=strides, dtype=dtype, device="cuda")
+
+        @classmethod
+        def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+            raise NotImplementedError(func)
+    return OnDevice()
+
+
+@pytest.mark.parametrize("b_format,c_format", [("bf16", "bf16"), ("bf16_t", "bf16"), ("bfp16", "bfp16")])
+def test_run_refuses_operands_that_a_kernel_would_read_or_store_past(b_format, c_format):
+    """C in pageable host memory, and buffers whose bytes are not in a row (strided, one element repeated)."""
+    import torch
+    M, N, K = 8, 16, 64
+    g = atb.Gemm(M, N, K, 64, 128, 64, 256, b_format=b_format, c_format=c_format)
+    def buffer(rows, cols, strides=None):
+        return _on_device((atb.bfp16_bytes(rows, cols),), torch.uint8, strides)
+    a = buffer(M, K)
+    b = buffer(N, K) if b_format == "bfp16" else _on_device((K, N) if b_format == "bf16" else (N, K), torch.bfloat16)
+    c = buffer(M, N) if c_format == "bfp16" else _on_device((M, N), torch.bfloat16)
+    host = torch.zeros(c.shape, dtype=c.dtype)
+    bad = [(a, b, host), (buffer(M, K, (2,)), b, c), (buffer(M, K, (0,)), b, c)]
+    if b_format == "bfp16":
+        bad += [(a, buffer(N, K, (2,)), c), (a, buffer(N, K, (0,)), c)]
+    if c_format == "bfp16":
+        bad += [(a, b, buffer(M, N, (2,))), (a, b, buffer(M, N, (0,)))]
+    for args in bad:
+        with pytest.raises(AssertionError):
+            g.run(*args)
+    g.close()
+
+
+def test_quantise_and_decode_refuse_what_a_kernel_would_read_or_store_past():
+    import torch
+    M, K = 8, 64
+    n = atb.bfp16_bytes(M, K)
+    f32 = _on_device((M, K), torch.float32)
+    for out in (torch.zeros(n, dtype=torch.uint8), _on_device((n - 1,), torch.uint8), _on_device((n,), torch.int8), _on_device((n,), torch.uint8, (2,))):
+        with pytest.raises(AssertionError):
+            atb.bfp16_quantize(f32, out=out)
+    for a in (_on_device((n - 1,), torch.uint8), _on_device((n // 4 - 1,), torch.float32), _on_device((n,), torch.uint8, (2,)), _on_device((n,), torch.uint8, (0,))):
+        with pytest.raises(AssertionError):
+            atb.bfp16_decode(a, M, K)

@@ -137,7 +137,11 @@ def test_run_checks_its_operands(b_format, c_format):
         d = g.run(a, b)
     side.synchronize()
     assert np.array_equal(result(e), result(c)) and np.array_equal(result(d), result(c))
-    bad = [(a[:-256], b, c), (a.view(torch.int8), b, c), (a, b, c.float()), (a, b[:-1] if b.dim() == 2 else b[:-256], c), (a, b, c.flatten()[:-1]), (a.cpu(), b, c), (a, b.cpu(), c)]
+    pinned = torch.zeros(c.shape, dtype=c.dtype, pin_memory=True)
+    assert g.run(a, b, pinned) is pinned
+    torch.cuda.synchronize()
+    assert np.array_equal(result(pinned), result(c))
+    bad = [(a[:-256], b, c), (a.view(torch.int8), b, c), (a, b, c.float()), (a, b[:-1] if b.dim() == 2 else b[:-256], c), (a, b, c.flatten()[:-1]), (a.cpu(), b, c), (a, b.cpu(), c), (a, b, c.cpu())]
     if b.dim() == 2:
         bad += [(a, b.t(), c), (a, b.half(), c), (a, torch.empty(b.shape[0], 2 * b.shape[1], dtype=b.dtype, device="cuda")[:, ::2], c)]
     for args in bad:
