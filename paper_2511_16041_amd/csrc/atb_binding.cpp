@@ -2,6 +2,7 @@
 // stream and the C ABI call.  Host time of a call, in Python with ctypes / here, us: run 4.4 / 2.9 (256^3 then takes the 3.9 of its kernel,
 // launch after launch), quantise 4.6 / 3.4, decode (which makes its result) 5.6 / 3.9.
 // The C ABI is reached through the addresses that the binding hands over, so this file links against torch only.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ops/empty.h>
@@ -9,7 +10,6 @@
 #include <c10/hip/HIPStream.h>
 
 #include <cstdint>
-#include <exception>
 
 namespace {
 
@@ -61,29 +61,33 @@ bool tensors(PyObject *const *args, int n)
     return true;
 }
 
+// The interpreter lock given back for a scope, also where that is left by an exception.
+struct WithoutLock {
+    PyThreadState *state = PyEval_SaveThread();
+    ~WithoutLock() { PyEval_RestoreThread(state); }
+};
+
 // run(address of a RunSpec, A, B, C, stream handle or None) -> status
 PyObject *run(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     if (n != 5) return PyErr_Format(PyExc_TypeError, "run takes 5 arguments");
     const RunSpec *s = static_cast<const RunSpec *>(PyLong_AsVoidPtr(args[0]));
     if (PyErr_Occurred() || !tensors(args + 1, 3)) return nullptr;
-    try {
-        const at::Tensor &a = THPVariable_Unpack(args[1]), &b = THPVariable_Unpack(args[2]), &c = THPVariable_Unpack(args[3]);
-        if (!a.is_cuda() || !is_buffer(a, s->a_bytes) || !b.is_cuda()) return refuse();
-        if (!(s->b_bytes ? is_buffer(b, s->b_bytes) : is_matrix(b, s->b_rows, s->b_cols))) return refuse();
-        if (!on_device_or_pinned(c) || !(s->c_bytes ? is_buffer(c, s->c_bytes) : is_matrix(c, s->c_rows, s->c_cols))) return refuse();
-        const void *pa = a.data_ptr(), *pb = b.data_ptr();
-        void *pc = c.data_ptr(), *stream = nullptr;
-        if (!stream_of(args[4], &stream)) return nullptr;
-        int st;
-        Py_BEGIN_ALLOW_THREADS
+    HANDLE_TH_ERRORS                       // torch's exceptions keep their Python types (an allocation's torch.OutOfMemoryError)
+    const at::Tensor &a = THPVariable_Unpack(args[1]), &b = THPVariable_Unpack(args[2]), &c = THPVariable_Unpack(args[3]);
+    if (!a.is_cuda() || !is_buffer(a, s->a_bytes) || !b.is_cuda()) return refuse();
+    if (!(s->b_bytes ? is_buffer(b, s->b_bytes) : is_matrix(b, s->b_rows, s->b_cols))) return refuse();
+    if (!on_device_or_pinned(c) || !(s->c_bytes ? is_buffer(c, s->c_bytes) : is_matrix(c, s->c_rows, s->c_cols))) return refuse();
+    const void *pa = a.data_ptr(), *pb = b.data_ptr();
+    void *pc = c.data_ptr(), *stream = nullptr;
+    if (!stream_of(args[4], &stream)) return nullptr;
+    int st;
+    {
+        WithoutLock unlocked;
         st = s->run(s->plan, pa, pb, pc, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(st);
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
     }
+    return PyLong_FromLong(st);
+    END_HANDLE_TH_ERRORS
 }
 
 // quantize(address of atb_bfp16_quantize, A, out, bytes of out, stream handle or None) -> status
@@ -94,22 +98,20 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     const fn call = reinterpret_cast<fn>(PyLong_AsVoidPtr(args[0]));
     const int64_t bytes = PyLong_AsLongLong(args[3]);
     if (PyErr_Occurred() || !tensors(args + 1, 2)) return nullptr;
-    try {
-        const at::Tensor &a = THPVariable_Unpack(args[1]), &out = THPVariable_Unpack(args[2]);
-        if (!out.is_cuda() || !is_buffer(out, bytes)) return refuse();
-        const int64_t rows = a.size(0), cols = a.size(1), lda = a.stride(0);
-        const float *pa = static_cast<const float *>(a.data_ptr());
-        void *po = out.data_ptr(), *stream = nullptr;
-        if (!stream_of(args[4], &stream)) return nullptr;
-        int st;
-        Py_BEGIN_ALLOW_THREADS
+    HANDLE_TH_ERRORS
+    const at::Tensor &a = THPVariable_Unpack(args[1]), &out = THPVariable_Unpack(args[2]);
+    if (!out.is_cuda() || !is_buffer(out, bytes)) return refuse();
+    const int64_t rows = a.size(0), cols = a.size(1), lda = a.stride(0);
+    const float *pa = static_cast<const float *>(a.data_ptr());
+    void *po = out.data_ptr(), *stream = nullptr;
+    if (!stream_of(args[4], &stream)) return nullptr;
+    int st;
+    {
+        WithoutLock unlocked;
         st = call(pa, lda, po, rows, cols, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(st);
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
     }
+    return PyLong_FromLong(st);
+    END_HANDLE_TH_ERRORS
 }
 
 // decode(address of atb_bfp16_decode, address of atb_bfp16_bytes, A, rows, columns, stream handle or None) -> the decoded matrix, or the
@@ -124,22 +126,24 @@ PyObject *decode(PyObject *, PyObject *const *args, Py_ssize_t n)
     if (PyErr_Occurred()) return nullptr;
     const int64_t rows = PyLong_AsLongLong(args[3]), cols = PyLong_AsLongLong(args[4]);
     if (PyErr_Occurred() || !tensors(args + 2, 1)) return nullptr;
-    try {
-        const at::Tensor &a = THPVariable_Unpack(args[2]);
-        if (!a.is_cuda() || !a.is_contiguous() || a.nbytes() < size(rows, cols)) return refuse();     // (a size of 0: the call below says why)
-        at::Tensor out = at::empty({rows, cols}, at::TensorOptions().dtype(at::kBFloat16).device(a.device()));
-        const void *pa = a.data_ptr();
-        void *po = out.data_ptr(), *stream = nullptr;
-        if (!stream_of(args[5], &stream)) return nullptr;
-        int st;
-        Py_BEGIN_ALLOW_THREADS
-        st = call(pa, po, rows, cols, stream);
-        Py_END_ALLOW_THREADS
-        return st == 0 ? THPVariable_Wrap(out) : PyLong_FromLong(st);
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
+    HANDLE_TH_ERRORS
+    const at::Tensor &a = THPVariable_Unpack(args[2]);
+    if (!a.is_cuda() || !a.is_contiguous() || a.nbytes() < size(rows, cols)) return refuse();     // (a size of 0: the call below says why)
+    at::Tensor out;
+    {
+        WithoutLock unlocked;              // an allocation may wait for the device
+        out = at::empty({rows, cols}, at::TensorOptions().dtype(at::kBFloat16).device(a.device()));
     }
+    const void *pa = a.data_ptr();
+    void *po = out.data_ptr(), *stream = nullptr;
+    if (!stream_of(args[5], &stream)) return nullptr;
+    int st;
+    {
+        WithoutLock unlocked;
+        st = call(pa, po, rows, cols, stream);
+    }
+    return st == 0 ? THPVariable_Wrap(out) : PyLong_FromLong(st);
+    END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef methods[] = {{"run", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(run)), METH_FASTCALL, nullptr},

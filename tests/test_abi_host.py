@@ -414,3 +414,16 @@ def test_quantise_and_decode_refuse_what_a_kernel_would_read_or_store_past():
     for a in (_on_device((n - 1,), torch.uint8), _on_device((n // 4 - 1,), torch.float32), _on_device((n,), torch.uint8, (2,)), _on_device((n,), torch.uint8, (0,))):
         with pytest.raises(AssertionError):
             atb.bfp16_decode(a, M, K)
+
+
+def test_decode_keeps_the_type_of_an_allocation_failure():
+    """A caller that frees memory and retries catches torch.OutOfMemoryError, which the allocation of the result raises."""
+    import torch
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Full(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise torch.OutOfMemoryError("no room")
+    a = _on_device((atb.bfp16_bytes(8, 64),), torch.uint8)
+    with pytest.raises(torch.OutOfMemoryError, match="no room"), Full():
+        atb.bfp16_decode(a, 8, 64)
