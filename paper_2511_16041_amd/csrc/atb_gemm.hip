@@ -306,6 +306,26 @@ struct TileKernel {
     static constexpr int B_ROWS = NTS / S::B_CPR;                                        // rows between a thread's chunks of the B tile
     // row_shr moves a value by up to 15 lanes of 16; a thread's chunks sit at one chunk position of their rows or at that and the one that differs in bit 1
     static_assert(!LAG || (BPT <= 8 && BPT <= S::B_CPR && 64 % S::B_CPR == 0 && B_ROWS % 8 == 0 && ((S::b_swz(8) | S::b_swz(16)) & ~2) == 0 && S::b_swz(32) == 0), "odd N: ends of rows, swizzle of a thread's chunks");
+    // Offset of the dword across the end of a row that the thread whose first chunk is chunk c of row `row` asks for (b_ends), of a tile at
+    // column 0; outside every buffer where it has none.  What a constant expression evaluates has no signed overflow: checked for the
+    // largest odd N that a plan admits (at most 2^23 columns, a tile's byte offsets below 2^31).
+    static constexpr int NO_END = (int)0x80000000;
+    static constexpr int end_offset(int row, int c, int N)
+    {
+        const int i = S::B_CPR - 1 - c;
+        if (i >= BPT) return NO_END;                       // its row would lie outside the tile
+        const int off = ((row + i * B_ROWS) * N + S::T_N) * 2;
+        return (off & 2) != 0 ? off - 2 : NO_END;
+    }
+    static constexpr bool ends_in_reach()
+    {
+        const int N = (std::min((1 << 30) / (S::T_K + 1), 1 << 23) - 1) | 1;
+        for (int t = 0; t < NTS; ++t) {
+            const int off = end_offset(t / S::B_CPR, t % S::B_CPR, N);
+            if (off != NO_END && off < 0) return false;
+        }
+        return true;
+    }
     static constexpr int NPAIR_B = BTPT * 8;                                             // B mantissa pairs per thread per tile
     static constexpr int NSTEP_A = NPAIR == 0 ? 0 : SK ? NPAIR / 4 : NPAIR + 2;          // decode items per phase (A sub-tile): pipeline steps, or blocks
     static constexpr int NSTEP_B = NPAIR_B > 0 ? NPAIR_B / S::RHO + 2 : 0;               // ... and for this phase's share of the B tile
@@ -463,11 +483,11 @@ struct TileKernel {
             for (int ks = 0; ks < S::KS; ++ks) a_rdk[ks] = lds + rrow * S::PA + ((((S::KM / 8) * ks + lane / S::MB) ^ rswz) * 16);
         }
         const int wr_row = (slot0 + lane) / S::B_CPR, wr_c = (slot0 + lane) % S::B_CPR;        // LAG: the first chunk this thread stores
-        {
-            const int i = S::B_CPR - 1 - wr_c, off = ((wr_row + i * B_ROWS) * p.N + S::T_N) * 2;
-            b_end_off = (i < BPT && (off & 2) != 0) ? off - 2 : (int)0x80000000;
+        if constexpr (LAG) {
+            static_assert(ends_in_reach(), "odd N: offsets of the ends of rows");
+            b_end_off = end_offset(wr_row, wr_c, p.N);
+            b_flip = ((wr_c ^ S::b_swz(wr_row)) & 2) ? -32 : 32;
         }
-        b_flip = ((wr_c ^ S::b_swz(wr_row)) & 2) ? -32 : 32;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             char *b_base = lds + S::AB * S::A_BYTES + b * B_BYTES;
