@@ -852,6 +852,26 @@ struct TileKernel {
         }
     }
 
+    // Odd N: offset of chunk i of the B tile.  In ROLE 0, whose waves hold 256 accumulators and, at T_K = 128, 16 chunks of B, it is made
+    // from the first one's where it is used (the chunks lie a multiple of 16 N bytes apart, at the same place of their rows): with an
+    // offset per chunk 61 registers spilled, 40 accesses to scratch per loop body (32,256,128,256, us: 8192 x 8191 x 8192 1796 -> 1219, 3000 x
+    // 5001 x 1000 68.1 -> 54.6).
+    static constexpr bool ONE_OFFSET = (!VEC && ROLE == 0);
+    static_assert(!ONE_OFFSET || (S::b_swz(B_ROWS) == 0 && S::b_swz(2 * B_ROWS) == 0 && S::b_swz(4 * B_ROWS) == 0 && S::b_swz(8 * B_ROWS) == 0), "odd N: a thread's chunks sit at one place of their rows");
+    template <int i>
+    ATB_DEV int odd_offset() const
+    {
+        if constexpr (!ONE_OFFSET || i == 0) {
+            return b_off[i];
+        } else {
+            int n = p.N;
+#if defined(__HIP_DEVICE_COMPILE__)
+            asm volatile("" : "+s"(n));         // else the sum is hoisted out of the K loop, into a register per chunk
+#endif
+            return b_off[0] + i * B_ROWS * 2 * n;
+        }
+    }
+
     // Request i of the next B tile in fetch order, destined for LDS buffer `buf`.
     // VEC (even N: dword-aligned rows): one 16-byte load per lane straight into LDS (no registers, no ds_write);
     // completion is awaited with wait_b_landed() before the barrier that publishes the tile.
@@ -893,13 +913,13 @@ struct TileKernel {
             // a row; those of a tile's odd rows come in one request per wave, spread over lanes (b_ends).  What the requests for it cost was
             // their number, not their bytes: one per chunk / one per tile, us: 1500 x 3001 x 2056 48.2 / 45.9 (N = 3000: 35.1), 600 x 1501 x 1000
             // 11.5 / 11.0, 30 x 33001 x 1000 28.2 / 26.7, 300 x 301 x 304 6.3 / 5.9.
-            const int al = b_off[i] & ~3;
+            const int off = odd_offset<i>(), al = off & ~3;
             const intx4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs.b, al, 0, 0);
             if constexpr (LAG) {         // shifted when it is stored: here the shift would wait for the request
                 b_raw[i] = lo;
                 if constexpr (i == BPT - 1) b_ends = __builtin_amdgcn_raw_buffer_load_b32(rs.b, b_end_off, 0, 0);
             } else {
-                b_raw[i] = shifted(lo, __builtin_amdgcn_raw_buffer_load_b32(rs.b, al + 16, 0, 0), (b_off[i] & 2) * 8);
+                b_raw[i] = shifted(lo, __builtin_amdgcn_raw_buffer_load_b32(rs.b, al + 16, 0, 0), (off & 2) * 8);
             }
         }
         if constexpr (i == BPT - 1) {
@@ -1297,11 +1317,12 @@ struct TileKernel {
     }
 
     // K-steps ki .. KU - 1 of the loop body, of which only the first `left` are wanted.
+    static constexpr bool EARLY_OUT = (ROLE != 0 && !EB);      // see run()
     template <int ki>
     ATB_DEV void ksteps(int left)
     {
         if constexpr (ki < S::KU) {
-            if constexpr (ki > 0 && ROLE != 0 && !EB)
+            if constexpr (ki > 0 && EARLY_OUT)
                 if (ki >= left) return;
             phases<ki, 0>();
             if constexpr (RING) advance_b_ring();
@@ -1378,7 +1399,7 @@ struct TileKernel {
         // out in mid-body makes 200 to 400 registers spill) nor with the early barrier, where K-steps overlap (2048 x 4096 x 14336 256.6 / 259.5).
         for (;;) {
             int next_m0, next_n0;
-            const int steps = tile_at(c_t + t_stride, next_m0, next_n0) ? kt_steps : (p.K + S::T_K - 1) / S::T_K;
+            const int steps = !EARLY_OUT || tile_at(c_t + t_stride, next_m0, next_n0) ? kt_steps : (p.K + S::T_K - 1) / S::T_K;
             for (int kt = 0; kt < steps; kt += S::KU) ksteps<0>(steps - kt);
             if constexpr (!COMPUTE) { } else if constexpr (CBFP) store_c_bfp(); else store_c();
             c_t += t_stride;
