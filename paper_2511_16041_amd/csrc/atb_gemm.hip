@@ -855,7 +855,7 @@ struct TileKernel {
     // Odd N: offset of chunk i of the B tile.  In ROLE 0, whose waves hold 256 accumulators and, at T_K = 128, 16 chunks of B, it is made
     // from the first one's where it is used (the chunks lie a multiple of 16 N bytes apart, at the same place of their rows): with an
     // offset per chunk 61 registers spilled, 40 accesses to scratch per loop body (32,256,128,256, us: 8192 x 8191 x 8192 1796 -> 1219, 3000 x
-    // 5001 x 1000 68.1 -> 54.6).
+    // 5001 x 1000 68.1 -> 54.6; the first one 1176 with the epilogue's present order).
     static constexpr bool ONE_OFFSET = (!VEC && ROLE == 0);
     static_assert(!ONE_OFFSET || (S::b_swz(B_ROWS) == 0 && S::b_swz(2 * B_ROWS) == 0 && S::b_swz(4 * B_ROWS) == 0 && S::b_swz(8 * B_ROWS) == 0), "odd N: a thread's chunks sit at one place of their rows");
     template <int i>
@@ -1550,8 +1550,15 @@ struct TileKernel {
         const int left = o.N - col0;
         o.rows_left = p.M - row0 - o.l % S::MB;
         o.cols_left = left - piece_col(o.l);
+        // Behind the whole pieces the compiler keeps what it has made of those, copies or converted, for the cut ones.  ROLE 0, whose waves
+        // have no registers for that, stores the cut ones first (32,256,128,256, us, last / first: 2048 x 4096 x 256 20.7 / 17.1, 1000 x 2000 x
+        // 800 37.3 / 32.9, 4096 x 4096 x 1024 44.0 / 41.2; the other tiles lose up to 1.8 % by it).
+        const bool cut = (o.N & 7) != 0 && left > 0 && left < S::T_N / S::WN;
+        if constexpr (ROLE == 0)
+            if (cut) store_cut_pair(left / PAIR_COLS, o);
         store_rows<0>(o);
-        if ((o.N & 7) != 0 && left > 0 && left < S::T_N / S::WN) store_cut_pair(left / PAIR_COLS, o);
+        if constexpr (ROLE != 0)
+            if (cut) store_cut_pair(left / PAIR_COLS, o);
     }
 
     template <int a, int j>

@@ -76,9 +76,9 @@ def test_registers_leave_room_for_the_workgroups_that_share_a_cu(tile_kernels):
 
 
 def test_nothing_spills_but_in_the_epilogue_of_the_four_wave_tiles(all_kernels, tile_kernels):
-    """The 256-row tiles on four waves use all 512 registers; what they spill (14 at most) they do outside the K loop."""
+    """The 256-row tiles on four waves use all 512 registers; what they spill (10 at most) they do outside the K loop."""
     four_waves = [(32, 256, 64, 256), (32, 256, 128, 256)]
     spilled = {tiles: max(k["vgpr_spill_count"] for _, k in ks) for tiles, ks in tile_kernels.items()}
-    assert all(n <= 14 for n in (spilled.pop(t) for t in four_waves)) and not any(spilled.values()), spilled
+    assert all(n <= 10 for n in (spilled.pop(t) for t in four_waves)) and not any(spilled.values()), spilled
     others = {name: k for name, k in all_kernels.items() if "atb_gemm_kernel" not in name}
     assert others and not any(k["vgpr_spill_count"] for k in others.values())
