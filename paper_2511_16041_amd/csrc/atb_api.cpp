@@ -189,7 +189,7 @@ extern "C" atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, 
                      x.wave_m, x.wave_n, x.threads, x.lds_bytes, p.tiles_m, p.tiles_n, p.group_m, p.k_panels);
         const atb::StreamRoute r = plan_route(g);
         if (r.streams())       // what runs instead of the instance
-            std::fprintf(stderr, " streaming: tile=%dx%d threads=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.lds_bytes(), (long long)atb::stream_workgroups(p, r));
+            std::fprintf(stderr, " streaming: tile=%dx%d threads=%d depth=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.depth, r.lds_bytes(), (long long)atb::stream_workgroups(p, r));
         std::fputc('\n', stderr);
     }
     *out = g;

@@ -93,6 +93,12 @@ inline int stream_column_blocks(int N, int cus) { return N <= 32 * cus ? 2 : N <
 // 23.9, 64 x 12288 x 2048 13.3 / 13.0; three rounds: 64 x 10000 x 1536 11.3 / 12.9, 65 x 3000 x 1088 7.4 / 8.0; 16 rows are level.
 inline int stream_depth_bfp16(int k_panels, int mb) { return mb >= 2 && (k_panels + 7) / 8 % 2 == 0 ? 2 : 1; }
 
+// With B^T in bf16, 64 columns and four waves: two from 33 rows on, whatever the number of rounds, since what a round of zeros costs here is
+// little against what the second panel gives.  Two over one, M 33 .. 64, N 8200 .. 16384, five to 25 rounds: 0.89 - 1.01 from memory, the odd
+// numbers 0.91 - 1.01; from the cache 0.88 - 1.00 at even and 0.90 - 1.02 at odd numbers (K 1280 and 1792 1.00 - 1.02, K 1088 and 1600 0.97 - 0.99).
+// 64 x 14336 x 4096 31.5 / 29.4 us, 48 x 14336 x 4096 29.4 / 28.6; fewer rows lose up to 6 % at K = 2048.
+inline int stream_depth_bf16_t(int mb) { return mb >= 3 ? 2 : 1; }
+
 // More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
 // none where the tile pipeline is as good or better.  Measured in us, the pipeline / this kernel, or as the ratio of the two; "memory":
 // 700 MB of operands in turns, so that B comes from memory as a model's weights do; "cache": three sets in turns, which the 256 MiB
@@ -177,7 +183,7 @@ inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
     const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N, cus);
     if (b_format == ATB_FMT_BFP16) return {mb, nb, nb == 2 ? 16 : 8, nb == 4 ? stream_depth_bfp16(p.k_panels, mb) : 1};
     if (b_format == ATB_FMT_BF16 && p.N % 2 != 0) return {mb, 2, 8, 1};
-    return {mb, nb, nb == 2 ? 8 : 4, 1};
+    return {mb, nb, nb == 2 ? 8 : 4, b_format == ATB_FMT_BF16_T && nb == 4 ? stream_depth_bf16_t(mb) : 1};
 }
 
 }  // namespace atb

@@ -391,35 +391,32 @@ hipError_t launch_rows(const GemmParams &p, const StreamRoute &r, hipStream_t st
 // The variants that stream_route chooses from; no others are compiled, and a route to another is refused.
 hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r, hipStream_t stream)
 {
-    const int form = 100 * r.nb + r.waves;
+    const int form = 1000 * r.depth + 100 * r.nb + r.waves;
     if (b_format == ATB_FMT_BFP16) {
-        if (form == 216) return launch_rows<kBBfp, 2, 16, 4>(p, r, stream);
-        if (form == 408 && r.depth == 2) {
-            if (r.mb == 2) return launch<kBBfp, 2, 4, 8, 2>(p, r, stream);
-            if (r.mb == 3) return launch<kBBfp, 3, 4, 8, 2>(p, r, stream);
-            if (r.mb == 4) return launch<kBBfp, 4, 4, 8, 2>(p, r, stream);
-        }
-        if (form == 408) return launch_rows<kBBfp, 4, 8, 4>(p, r, stream);
-        if (form == 808) return launch_rows<kBBfp, 8, 8, 3>(p, r, stream);
-        if (form == 208 && r.mb == 4 && r.depth == 2) return launch<kBBfp, 4, 2, 8, 2>(p, r, stream);
-        if (form == 208 && r.mb == 4) return launch<kBBfp, 4, 2, 8>(p, r, stream);
+        if (form == 1216) return launch_rows<kBBfp, 2, 16, 4>(p, r, stream);
+        if (form == 1408) return launch_rows<kBBfp, 4, 8, 4>(p, r, stream);
+        if (form == 1808) return launch_rows<kBBfp, 8, 8, 3>(p, r, stream);
+        if (form == 1208 && r.mb == 4) return launch<kBBfp, 4, 2, 8>(p, r, stream);
+        if (form == 2408 && r.mb == 2) return launch<kBBfp, 2, 4, 8, 2>(p, r, stream);
+        if (form == 2408 && r.mb == 3) return launch<kBBfp, 3, 4, 8, 2>(p, r, stream);
+        if (form == 2408 && r.mb == 4) return launch<kBBfp, 4, 4, 8, 2>(p, r, stream);
+        if (form == 2208 && r.mb == 4) return launch<kBBfp, 4, 2, 8, 2>(p, r, stream);
     } else if (b_format == ATB_FMT_BF16_T) {
-        if (form == 208) return launch_rows<kBT, 2, 8, 4>(p, r, stream);
-        if (form == 404 && r.mb == 8) return launch<kBT, 8, 4, 4>(p, r, stream);
-        // 33 to 64 rows: two panels in flight (64 x 14336 x 4096 31.5 -> 29.4 us, 48 x 14336 x 4096 29.4 -> 28.6; fewer rows lose up to 6 % at K = 2048)
-        if (form == 404 && r.mb == 3) return launch<kBT, 3, 4, 4, 2>(p, r, stream);
-        if (form == 404 && r.mb == 4) return launch<kBT, 4, 4, 4, 2>(p, r, stream);
-        if (form == 404) return launch_rows<kBT, 4, 4, 2>(p, r, stream);
-        if (form == 804) return launch_rows<kBT, 8, 4, 4>(p, r, stream);
-        if (form == 408 && r.mb == 4) return launch<kBT, 4, 4, 8>(p, r, stream);
+        if (form == 1208) return launch_rows<kBT, 2, 8, 4>(p, r, stream);
+        if (form == 1404 && r.mb == 8) return launch<kBT, 8, 4, 4>(p, r, stream);
+        if (form == 1404) return launch_rows<kBT, 4, 4, 2>(p, r, stream);
+        if (form == 2404 && r.mb == 3) return launch<kBT, 3, 4, 4, 2>(p, r, stream);
+        if (form == 2404 && r.mb == 4) return launch<kBT, 4, 4, 4, 2>(p, r, stream);
+        if (form == 1804) return launch_rows<kBT, 8, 4, 4>(p, r, stream);
+        if (form == 1408 && r.mb == 4) return launch<kBT, 4, 4, 8>(p, r, stream);
     } else if (p.N % 2 != 0) {
-        if (form == 208) return launch_rows<kBRowOdd, 2, 8, 4>(p, r, stream);
+        if (form == 1208) return launch_rows<kBRowOdd, 2, 8, 4>(p, r, stream);
     } else {
-        if (form == 208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
-        if (form == 404) return launch_rows<kBRow, 4, 4, 4>(p, r, stream);
-        if (form == 804 && r.depth == 2) return launch<kBRow, 4, 8, 4, 2>(p, r, stream);
-        if (form == 804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
-        if (form == 408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
+        if (form == 1208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
+        if (form == 1404) return launch_rows<kBRow, 4, 4, 4>(p, r, stream);
+        if (form == 2804 && r.mb == 4) return launch<kBRow, 4, 8, 4, 2>(p, r, stream);
+        if (form == 1804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
+        if (form == 1408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
     }
     return hipErrorInvalidValue;
 }

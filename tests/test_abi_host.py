@@ -323,30 +323,50 @@ def test_bfp16_bytes_refuses_floats_also_from_its_cache():
             atb.bfp16_bytes(*bad)
 
 
-def test_gpu_cases_reach_every_streaming_variant():
-    """The shapes of test_gpu_skinny.py go where that file says, and reach every variant that any problem is sent to."""
+def test_gpu_cases_reach_every_streaming_variant(monkeypatch, capfd):
+    """The shapes of test_gpu_skinny.py go where that file says, and reach every variant that any problem is sent to and every one that is
+    compiled (read from the library)."""
     import test_gpu_skinny as t
-    reached = set()
-    for shape in t.SHAPES:
-        for b, c in t.COMBOS:
-            g = t.plan(shape, b, c)
-            assert g.streams() == (c not in t.PIPELINE.get((shape, b), ())), (shape, b, c)
-            reached.add(t.variant(g))
+    from paper_2511_16041_amd import build
+    from test_kernel_resources import READELF, kernels
+    monkeypatch.setenv("ATB_LOG", "1")
+
+    def logged(plans):
+        capfd.readouterr()
+        for g in plans:
             g.close()
-    reached.add(t.variant(t.plan(t.WIDE_AND_LONG, "bf16", "bf16")))
-    reached.discard(None)
-    sent = set()
-    for M in (1, 17, 33, 49, 65, 100, 128, 193, 256, 300, 512, 1000, 4100, 16384):
-        for N in (32, 65, 200, 1024, 2050, 4096, 8001, 8194, 12288, 16384, 16448, 24001, 32768, 33000, 50000, 50257, 70000):
-            for K in (1032, 1288, 2560, 4096, 5632, 8192, 14336):
-                if M * -(-N // 64) * 64 >= 2 ** 31:
-                    continue
-                for b in ("bf16", "bf16_t", "bfp16"):
-                    g = t.plan((M, N, K), b, "bf16")
-                    sent.add(t.variant(g))
-                    g.close()
-    sent.discard(None)
-    assert len(reached) == 43 and sent <= reached, sent - reached
+        return t.variants(capfd.readouterr().err)
+
+    def gpu_cases():
+        for shape in t.SHAPES:
+            for b, c in t.COMBOS:
+                g = t.plan(shape, b, c)
+                assert g.streams() == (c not in t.PIPELINE.get((shape, b), ())), (shape, b, c)
+                yield g
+        yield t.plan(t.WIDE_AND_LONG, "bf16", "bf16")
+
+    def many_problems():
+        for M in (1, 17, 33, 49, 65, 100, 128, 193, 256, 300, 512, 1000, 4100, 16384):
+            for N in (32, 65, 200, 1024, 2050, 4096, 8001, 8194, 12288, 16384, 16448, 24001, 32768, 33000, 50000, 50257, 70000):
+                for K in (1032, 1288, 1600, 2560, 4096, 5632, 8192, 14336):
+                    if M * -(-N // 64) * 64 < 2 ** 31:
+                        for b in ("bf16", "bf16_t", "bfp16"):
+                            yield t.plan((M, N, K), b, "bf16")
+
+    two = logged(t.plan(shape, "bfp16", c) for shape in t.TWO_PANELS for c in t.BOTH)
+    assert {v[1:] for v in two} == {(32, 64, 512, 2), (48, 64, 512, 2), (64, 64, 512, 2), (64, 32, 512, 2)}
+    reached = logged(gpu_cases()) | two
+    sent = logged(many_problems())
+    assert len(reached) == 47 and sent <= reached, sent - reached
+    if os.path.exists(READELF):
+        forms = ["bf16", "bf16_t", "bfp16", "bf16 odd"]            # template arguments: form of B, blocks of 16 rows, of 16 columns, waves, panels
+        compiled = set()
+        for name in kernels(build.ensure_built()):
+            m = re.search(r"skinny_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d+)ELi(\d)E", name)
+            if m:
+                f, mb, nb, w, d = (int(x) for x in m.groups())
+                compiled.add((forms[f], 16 * mb, 16 * nb, 64 * w, d))
+        assert compiled == reached
 
 
 def test_device_calls_refuse_host_tensors():

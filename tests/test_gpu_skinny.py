@@ -3,6 +3,8 @@ stay with them, against the oracle.  The shapes reach every variant of the strea
 test_abi_host.py), the edges of each, K tails, odd N and every storage format; each case asserts which kernel runs.  Exact
 (small-integer) inputs must give the oracle's bits, since every order of the sums is then exact; random ones the GEMM tolerance (and
 half a mantissa step of a BFP16 C)."""
+import re
+
 import numpy as np
 import pytest
 
@@ -40,18 +42,14 @@ def plan(shape, b_format, c_format):
     return atb.Gemm(M, columns(N, c_format), K, *tiles, b_format=b_format, c_format=c_format)
 
 
-def variant(g):
-    """(form of B, blocks of 16 rows, blocks of 16 columns, waves, panels in flight) of the streaming kernel that runs plan g; None for
-    the pipeline."""
-    if not g.streams():
-        return None
-    M, N, _ = g.shape
-    i = g.launch_info()
-    waves = i.threads // 64
-    nb = (i.lds_bytes // (waves * 16 * 4) - 4) // 16
-    form = g.b_format if g.b_format != "bf16" else "bf16 odd" if N % 2 else "bf16"
-    # above 64 rows: 128 x 64 tiles have four waves, 64 x 64 eight
-    return form, -(-M // 16) if M <= 64 else 8 if (nb, waves) == (4, 4) else 4, nb, waves, 2 if M > 64 and nb == 8 else 1
+def variants(log):
+    """From what the library logs of plans as it makes them (ATB_LOG=1): the set of (form of B, rows and columns of a workgroup's tile,
+    threads, panels in flight) of the streaming kernel that runs them."""
+    out = set()
+    for N, b, rest in re.findall(r"^atb_gemm_create: M=\d+ N=(\d+) .* b=(\S+) .* streaming: (.*)$", log, re.M):
+        rows, cols, threads, depth = re.match(r"tile=(\d+)x(\d+) threads=(\d+) depth=(\d+) ", rest).groups()
+        out.add(("bf16 odd" if b == "bf16" and int(N) % 2 else b, int(rows), int(cols), int(threads), int(depth)))
+    return out
 
 
 def _check(g, exact, seed=21):
@@ -104,16 +102,18 @@ def test_streaming_kernel(shape, b_format, c_format, exact):
     _check(g, exact)
 
 
+TWO_PANELS = [(20, 8264, 1608), (48, 8264, 2048), (49, 8264, 1544), (66, 72, 1608), (129, 1032, 1992), (257, 2120, 1992)]
+
+
 @pytest.mark.parametrize("exact", [True, False])
 @pytest.mark.parametrize("c_format", BOTH)
-@pytest.mark.parametrize("shape", [(20, 8264, 1608), (48, 8264, 2048), (49, 8264, 1544), (66, 72, 1608), (129, 1032, 1992), (257, 2120, 1992)])
+@pytest.mark.parametrize("shape", TWO_PANELS)
 def test_two_panels_in_flight(shape, c_format, exact):
     """B in BFP16, four rounds of eight panels: 20 to 64 rows and more, 64 and 32 columns, the last round whole, of one panel (1544) or with a
-    tail."""
+    tail.  (That these plans have two panels in flight is checked in test_abi_host.py.)"""
     print(f"two panels {shape} C={c_format} exact={exact}", flush=True)
-    M, N, K = shape
-    g = atb.Gemm(M, columns(N, c_format), K, 32, 32, 256, 64, b_format="bfp16", c_format=c_format)
-    assert g.streams() and g.launch_info().threads == 512 and (-(-K // 64) + 7) // 8 == 4
+    g = plan(shape, "bfp16", c_format)
+    assert g.streams() and g.launch_info().threads == 512 and (-(-shape[2] // 64) + 7) // 8 == 4
     _check(g, exact, seed=25)
 
 

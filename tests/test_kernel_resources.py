@@ -5,6 +5,7 @@ import re
 import shutil
 import struct
 import subprocess
+import tempfile
 
 import pytest
 
@@ -31,13 +32,14 @@ def code_objects(path):
         at = data.find(MAGIC, at + len(MAGIC))
 
 
-def kernels(path, tmp_path):
+def kernels(path):
     """{mangled name: its notes}"""
     out = {}
-    for i, obj in enumerate(code_objects(path)):
-        f = tmp_path / f"{i}.elf"
-        f.write_bytes(obj)
-        text = subprocess.run([READELF, "--notes", str(f)], capture_output=True, text=True, check=True).stdout
+    for obj in code_objects(path):
+        with tempfile.NamedTemporaryFile(suffix=".elf") as f:
+            f.write(obj)
+            f.flush()
+            text = subprocess.run([READELF, "--notes", f.name], capture_output=True, text=True, check=True).stdout
         for part in re.split(r"\n  - (?=\.)", text):
             m = re.search(r"\.symbol: +'?(\S+?)\.kd", part)
             if m:
@@ -46,8 +48,8 @@ def kernels(path, tmp_path):
 
 
 @pytest.fixture(scope="module")
-def all_kernels(tmp_path_factory):
-    return kernels(build.ensure_built(), tmp_path_factory.mktemp("co"))
+def all_kernels():
+    return kernels(build.ensure_built())
 
 
 @pytest.fixture(scope="module")
