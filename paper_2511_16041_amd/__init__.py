@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import List, Optional, Tuple
@@ -153,9 +154,11 @@ def _launcher():
     if _ext is None:
         _t()
         lib()
-        from . import _launch
+        spec = importlib.util.spec_from_file_location(__name__ + "._launch", _build.ensure_binding())
+        ext = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(ext)
         _entry_points = (_address("atb_bfp16_quantize"), _address("atb_bfp16_decode"), _address("atb_bfp16_bytes"))
-        _ext = _launch
+        _ext = ext
     return _ext
 
 

@@ -1,16 +1,20 @@
-"""Build libatb.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's extension module with g++, in-tree."""
+"""Build libatb.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's extension module with g++, in-tree.  The library needs
+neither torch nor Python's headers; only the extension module does."""
 from __future__ import annotations
 
+import importlib.util
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libatb.so")
-EXT = os.path.join(HERE, "_launch.so")           # the binding's extension module (csrc/atb_binding.cpp)
+BINDING_SOURCE = "atb_binding.cpp"
 OBJ_DIR = os.path.join(HERE, "_build")
 # accumulators stay in ordinary vector registers: with up to 470 of a wave's 512 in use the compiler otherwise parks other
 # values in the accumulation half and moves the accumulators out and in again around every panel (208 moves to 64 MFMAs)
@@ -45,33 +49,50 @@ def _compile(item, extra, verbose: bool) -> str:
     return obj
 
 
+def binding_path() -> str:
+    """The extension module.  Its name holds the Python and the torch that it is built against, so that another of either builds its own."""
+    import torch
+    return os.path.join(HERE, f"_launch.{sysconfig.get_config_var('SOABI')}.torch-{torch.__version__}.so")
+
+
 def build_binding(verbose: bool = False) -> str:
     """The extension module that checks operands and launches; host code only, against torch's headers and libraries."""
-    import sysconfig
     import torch
     from torch.utils.cpp_extension import include_paths
-    includes = include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    out = binding_path()
+    part = f"{out}.{os.getpid()}"                  # several processes may build it at once; each puts a whole file in place
+    rocm = os.path.dirname(os.path.dirname(shutil.which(HIPCC) or HIPCC))
+    includes = include_paths() + [sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
+    includes += [d for d in include_paths("cuda") if d not in includes]          # torch's ROCm, where HIPCC is not inside one
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
     for d in includes:
         cmd += ["-isystem", d]
-    cmd += [os.path.join(CSRC, "atb_binding.cpp"), "-o", EXT, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    cmd += [os.path.join(CSRC, BINDING_SOURCE), "-o", part, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    return EXT
+    os.replace(part, out)
+    return out
 
 
-def build(verbose: bool = False, extra=()) -> str:
+def build_library(verbose: bool = False, extra=()) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
-    build_binding(verbose)
     with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(lambda s: _compile(s, extra, verbose), SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    return OUT
+
+
+def build(verbose: bool = False, extra=()) -> str:
+    """The library, and the extension module where there is a torch to build it against."""
+    build_library(verbose, extra)
+    if importlib.util.find_spec("torch") is not None:
+        build_binding(verbose)
     return OUT
 
 
@@ -88,22 +109,31 @@ def build_microbench(verbose: bool = False) -> str:
     return exe
 
 
+def _older(out: str, sources) -> bool:
+    """True if a built file is missing or older than any of its sources (or this file)."""
+    return not os.path.exists(out) or any(os.path.getmtime(d) > os.path.getmtime(out) for d in [*sources, os.path.abspath(__file__)])
+
+
 def _stale() -> bool:
-    """True if the library or the extension module is missing or older than any of the sources (or this file)."""
-    if not os.path.exists(OUT) or not os.path.exists(EXT):
-        return True
-    built = min(os.path.getmtime(OUT), os.path.getmtime(EXT))
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if os.path.isfile(os.path.join(CSRC, f))]
-    deps += [os.path.join(ROOT, "include", "atb.h"), os.path.abspath(__file__)]
-    return any(os.path.getmtime(d) > built for d in deps)
+    """True if the library is missing or older than any of its sources (or this file)."""
+    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f != BINDING_SOURCE and os.path.isfile(os.path.join(CSRC, f))]
+    return _older(OUT, deps + [os.path.join(ROOT, "include", "atb.h")])
 
 
 def ensure_built() -> str:
     """Path of the library; builds it first if it is missing or a source is newer than it.  (A stale
     library that cannot be rebuilt because there is no compiler is an error, not a silent fallback.)"""
     if _stale():
-        build()
+        build_library()
     return OUT
+
+
+def ensure_binding() -> str:
+    """Path of the extension module, likewise."""
+    out = binding_path()
+    if _older(out, [os.path.join(CSRC, BINDING_SOURCE)]):
+        build_binding()
+    return out
 
 
 if __name__ == "__main__":

@@ -6,6 +6,11 @@ import ctypes
 import numpy as np
 import os
 import re
+import shutil
+import subprocess
+import sys
+import sysconfig
+import textwrap
 
 import pytest
 
@@ -447,3 +452,41 @@ def test_decode_keeps_the_type_of_an_allocation_failure():
     a = _on_device((atb.bfp16_bytes(8, 64),), torch.uint8)
     with pytest.raises(torch.OutOfMemoryError, match="no room"), Full():
         atb.bfp16_decode(a, 8, 64)
+
+
+def _package_copy(tmp_path):
+    """The package as built, without the extension module, in a folder of its own."""
+    for part in ("paper_2511_16041_amd", "include"):
+        shutil.copytree(os.path.join(ROOT, part), tmp_path / part, ignore=shutil.ignore_patterns("_launch*.so", "_build", "__pycache__"))
+    return tmp_path
+
+
+def test_the_library_needs_no_torch(tmp_path):
+    """The C ABI and the host-only calls load, and are not built again, where there is neither torch nor the extension module, and however
+    new the extension module's source is."""
+    root = _package_copy(tmp_path)
+    os.utime(root / "paper_2511_16041_amd" / "csrc" / "atb_binding.cpp", (2 ** 31, 2 ** 31))
+    code = textwrap.dedent("""
+        import os, sys
+        sys.modules["torch"] = None               # importing it raises ImportError
+        os.environ["PATH"] = ""                   # no compiler to be found by name
+        import paper_2511_16041_amd as atb
+        atb._build.HIPCC = "/nonexistent/hipcc"
+        assert atb.bfp16_bytes(8, 64) > 0 and atb.select_tiles(256, 256, 256)
+        atb.Gemm(8, 16, 64, 32, 64, 64, 64).close()
+        print("no-torch ok")
+    """)
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "no-torch ok" in r.stdout, r.stdout + r.stderr
+
+
+def test_the_extension_module_belongs_to_one_python_and_one_torch(monkeypatch):
+    """Another torch does not load what was built against this one: it finds nothing built under its own name."""
+    import torch
+    from paper_2511_16041_amd import build
+    here = build.ensure_binding()
+    assert os.path.exists(here) and sysconfig.get_config_var("SOABI") in here and torch.__version__ in here
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".other")
+    built = []
+    monkeypatch.setattr(build, "build_binding", lambda verbose=False: built.append(build.binding_path()))
+    assert build.ensure_binding() != here and built == [build.binding_path()]
