@@ -271,7 +271,8 @@ struct BandDeal {
 // weight of a linear layer).  Its tile still goes global -> LDS directly, now as [n][k] rows of 2 T_K bytes whose
 // 16-byte chunks are XOR-swizzled by (n / 2) mod 8, and an MFMA fragment is ONE plain 16-byte LDS read per lane
 // instead of two transposing 8-byte reads (half the LDS read instructions for B).
-template <class S, bool VEC, int ROLE, bool BBFP = false, bool CBFP = false, bool SK = false, bool BTR = false>
+// WHOLE: the reduction is known to be a whole number of loop bodies.
+template <class S, bool VEC, int ROLE, bool BBFP = false, bool CBFP = false, bool SK = false, bool BTR = false, bool WHOLE = false>
 struct TileKernel {
     static constexpr int NTS = S::NTS, ACE = S::ACE, A_CPR = S::A_CPR;
     static constexpr int AO = BBFP ? S::A_SLABS : S::AO;                                 // with B in BFP16 the second group has its hands full
@@ -1317,7 +1318,7 @@ struct TileKernel {
     }
 
     // K-steps ki .. KU - 1 of the loop body, of which only the first `left` are wanted.
-    static constexpr bool EARLY_OUT = (ROLE != 0 && !EB);      // see run()
+    static constexpr bool EARLY_OUT = (ROLE != 0 && !EB && !WHOLE);      // see run()
     template <int ki>
     ATB_DEV void ksteps(int left)
     {
@@ -1619,7 +1620,7 @@ struct TileKernel {
 // persistent: it holds only as many workgroups as fit on the chip at once, and workgroup b serves
 // tiles b / 8, b / 8 + gridDim.x / 8, ... of its XCD's run as one pipeline, so no tile waits for a
 // workgroup launch or for its first operands.
-template <class S, bool VEC, int ROLE, bool BBFP, bool CBFP, bool BTR>
+template <class S, bool VEC, int ROLE, bool BBFP, bool CBFP, bool BTR, bool WHOLE>
 __device__ __forceinline__ void tile_loop(const GemmParams &p, char *lds)
 {
     const int total = p.tiles_m * p.tiles_n;
@@ -1638,27 +1639,27 @@ __device__ __forceinline__ void tile_loop(const GemmParams &p, char *lds)
             return;
         }
     }
-    TileKernel<S, VEC, ROLE, BBFP, CBFP, false, BTR> tile(p, lds, first, (int)gridDim.x / 8);
+    TileKernel<S, VEC, ROLE, BBFP, CBFP, false, BTR, WHOLE> tile(p, lds, first, (int)gridDim.x / 8);
     tile.run();
 }
 
-template <class S, bool VEC, bool BBFP = false, bool CBFP = false, bool BTR = false>
+template <class S, bool VEC, bool BBFP = false, bool CBFP = false, bool BTR = false, bool WHOLE = false>
 __global__ void __launch_bounds__(S::NT, S::OCC) atb_gemm_kernel(const GemmParams p)
 {
     __shared__ __attribute__((aligned(16))) char lds[BBFP ? S::LDS_BYTES_BT : S::LDS_BYTES];
     if constexpr (S::HW > 0) {
         if (threadIdx.x < S::CW * 64)
-            tile_loop<S, VEC, 4, BBFP, CBFP, BTR>(p, lds);
+            tile_loop<S, VEC, 4, BBFP, CBFP, BTR, WHOLE>(p, lds);
         else
-            tile_loop<S, VEC, 3, BBFP, CBFP, BTR>(p, lds);
+            tile_loop<S, VEC, 3, BBFP, CBFP, BTR, WHOLE>(p, lds);
     } else if constexpr (S::CW == 8) {
         // wave-uniform branch; both sides execute the same sequence of barriers
         if (threadIdx.x < 256)
-            tile_loop<S, VEC, 1, BBFP, CBFP, BTR>(p, lds);
+            tile_loop<S, VEC, 1, BBFP, CBFP, BTR, WHOLE>(p, lds);
         else
-            tile_loop<S, VEC, 2, BBFP, CBFP, BTR>(p, lds);
+            tile_loop<S, VEC, 2, BBFP, CBFP, BTR, WHOLE>(p, lds);
     } else {
-        tile_loop<S, VEC, 0, BBFP, CBFP, BTR>(p, lds);
+        tile_loop<S, VEC, 0, BBFP, CBFP, BTR, WHOLE>(p, lds);
     }
 }
 
@@ -1679,6 +1680,18 @@ hipError_t launch_kernel(const GemmParams &p, hipStream_t stream)
         const int cus = compute_units();
         if (cus == 0) return hipErrorNoDevice;
         slots = std::min(per_xcd, cus / 8);
+    }
+    // The test for the way out in mid-body parts the body's K-steps, which the small workgroups of the 64 x 64 tiles at T_K = 64 notice:
+    // they have a kernel without it for reductions of whole bodies.  us, before there was a way out / with it / now: 8 x 1000 x 1000 at
+    // 32,64,64,64 9.75 / 10.04 / 9.63, at 64,64,64,64 with B and C in BFP16 9.27 / 9.59 / 9.09; over 100 plans 0.993 of the time with it.
+    // (A second loop in the one kernel spills 159 registers; the larger tiles gained more by the shorter epilogue than they notice.)
+    constexpr bool whole_kernel = S::HW > 0 && S::T_K == 64 && S::T_MC * S::T_N <= 64 * 64;
+    static_assert(!whole_kernel || !persistent, "one tile per workgroup");
+    if constexpr (whole_kernel) {
+        if ((p.K + S::T_K - 1) / S::T_K % S::KU == 0) {
+            hipLaunchKernelGGL((atb_gemm_kernel<S, VEC, BBFP, CBFP, BTR, true>), dim3(slots * 8), dim3(S::NT), 0, stream, p);
+            return hipGetLastError();
+        }
     }
     hipLaunchKernelGGL((atb_gemm_kernel<S, VEC, BBFP, CBFP, BTR>), dim3(slots * 8), dim3(S::NT), 0, stream, p);
     return hipGetLastError();

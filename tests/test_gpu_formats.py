@@ -82,6 +82,25 @@ def test_exact_inputs_bitwise(tiles, fmt):
         assert np.array_equal(got, C_ref)
 
 
+@pytest.mark.parametrize("tiles", [(64, 64, 64, 64), (32, 64, 64, 64)])
+@pytest.mark.parametrize("fmt,N", [(f, 72) for f in COMBOS] + [(("bf16", "bf16"), 72), (("bf16", "bf16"), 67)])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 136, 192, 200, 256, 264])
+def test_kernels_for_whole_and_for_cut_loop_bodies(tiles, fmt, N, K):
+    """One to five K-steps of 64, with and without a tail: an even number runs one kernel, an odd one another."""
+    b_format, c_format = fmt
+    M = tiles[1] + 5
+    print(f"formats loop bodies tiles={tiles} B={b_format} C={c_format} N={N} K={K}", flush=True)
+    A, Bt = _inputs(M, N, K, seed=K, exact=True)
+    mant, expo, bmant, bexpo, Bq_bits = _reference(A, Bt)
+    C_ref, _, S, _ = oracle.gemm(mant, expo, Bq_bits, want_sum=True)
+    got = _run(mant, expo, (bmant, bexpo) if b_format == "bfp16" else Bq_bits, M, N, K, tiles, b_format, c_format)
+    if c_format == "bfp16":
+        rm, re_ = oracle.quantize(S.astype(np.float32))
+        assert np.array_equal(got[0], rm) and np.array_equal(got[1], re_) and not got[2].any()
+    else:
+        assert np.array_equal(got, C_ref)
+
+
 @pytest.mark.parametrize("tiles", FMT_TILES)
 @pytest.mark.parametrize("fmt", COMBOS)
 @pytest.mark.parametrize("shape", [(520, 512, 136), (257, 264, 72), (33, 24, 8), (700, 1032, 320)])
