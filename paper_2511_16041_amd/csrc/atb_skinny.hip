@@ -7,14 +7,15 @@
 // operands straight into registers in MFMA layout, and the W partial C tiles are added once at the end through LDS, in
 // wave order (the sums of a result are therefore W shorter chains; the tile pipeline adds in one).
 //
-// What bounds it: a CU keeps about 200 lines of 128 bytes in flight (measured: 27 GB/s per CU from HBM whatever the
+// What bounds it: a CU keeps about 200 lines of 128 bytes in flight (measured at M = 16: 27 GB/s per CU from HBM whatever the
 // number of waves or of panels in flight per wave, 1 to 4), so all CUs have to take part and every line that is asked for should
-// be used whole.  Hence the tile width (stream_column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
+// be used whole.  With more rows a wave decodes and multiplies for as long as it waits, and a second panel in flight per wave is
+// worth up to 12 % (stream_depth_bfp16, stream_depth_bf16_t).  Hence the tile width (stream_column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
 // <= 8192 that is 32 columns, half a line per row, and the rate stays at 3.9 TB/s against 5.1 with B^T.
 // Measured in us, three sets of operands in turns, the tile pipeline before / this kernel now:
 //   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5     M 64, 14336, 4096: 34.7 / 30.0     M 16, 5001, 4096: 23.7 / 12.9
 //   B^T bf16  M 16, N 8192, K 8192: 105 / 29        M 64, 14336, 4096: 57.7 / 29.4
-//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.5    M 64, 14336, 4096: 26.0 / 21.1 (decoding A takes as long as B's bytes)
+//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.5    M 64, 14336, 4096: 26.0 / 19.3 (decoding A takes as long as B's bytes)
 //
 // MFMA v_mfma_f32_16x16x32_bf16: lane l supplies index l % 16 of its operand and 8 k values of group l / 16.  Which k
 // a group holds is free as long as both operands agree: lane group q takes k = 16 q .. 16 q + 15 of the panel, the
