@@ -375,7 +375,7 @@ def test_gpu_cases_reach_every_streaming_variant(monkeypatch, capfd):
 
 
 def test_device_calls_refuse_host_tensors():
-    """What the extension module checks before any launch (no GPU is needed to be refused)."""
+    """What the binding checks before any launch (no GPU is needed to be refused): in Python what quantise reads, the rest in the extension."""
     import torch
     g = atb.Gemm(8, 16, 64, 32, 64, 64, 64)
     a, b, c = torch.zeros(atb.bfp16_bytes(8, 64), dtype=torch.uint8), torch.zeros(64, 16, dtype=torch.bfloat16), torch.zeros(8, 16, dtype=torch.bfloat16)
