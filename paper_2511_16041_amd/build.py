@@ -19,12 +19,15 @@ OBJ_DIR = os.path.join(HERE, "_build")
 # accumulators stay in ordinary vector registers: with up to 470 of a wave's 512 in use the compiler otherwise parks other
 # values in the accumulation half and moves the accumulators out and in again around every panel (208 moves to 64 MFMAs)
 SKINNY_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+# accumulators stay whole where they are carried round a loop: taken apart (as the compiler does with vectors that begin as constants), each
+# of their registers is moved once per round, 212 moves to 64 MFMAs
+WHOLE_PHIS = ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=0"]
 # loops of the 128-row tiles begin on a line of the instruction cache: the same instructions some bytes further on cost the 64,128,64,128
 # tile with B in BFP16 4 % (706 x 4992 x 3880 50.4 -> 52.5 us); the other forms of these tiles are level (the 64 x 64 tiles lose 2 % by it)
 ALIGNED = ["-falign-loops=64"]
 # (source, object name, extra flags): the GEMM instance table is cut into three groups that compile side by side
 SOURCES = [("atb_gemm.hip", "atb_gemm_g0", ["-DATB_GROUP=0"]), ("atb_gemm.hip", "atb_gemm_g1", ["-DATB_GROUP=1"] + ALIGNED),
-           ("atb_gemm.hip", "atb_gemm_g2", ["-DATB_GROUP=2"]), ("atb_skinny.hip", "atb_skinny", SKINNY_FLAGS), ("atb_bfp16.hip", "atb_bfp16", []), ("atb_probe.hip", "atb_probe", []),
+           ("atb_gemm.hip", "atb_gemm_g2", ["-DATB_GROUP=2"]), ("atb_skinny.hip", "atb_skinny", SKINNY_FLAGS), ("atb_rows.hip", "atb_rows", WHOLE_PHIS), ("atb_bfp16.hip", "atb_bfp16", []), ("atb_probe.hip", "atb_probe", []),
            ("atb_model.cpp", "atb_model", []), ("atb_api.cpp", "atb_api", [])]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

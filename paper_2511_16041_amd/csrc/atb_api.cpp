@@ -32,8 +32,9 @@ atb::StreamRoute plan_route(const atb_gemm *g)
 {
     const bool over = g->b_format == ATB_FMT_BF16_T || atb::instance(g->instance).hands_over;
     if (!over || g->proto.K <= atb::kStreamMinK) return {};
-    const int cus = atb::compute_units();
-    return atb::stream_route(g->proto, g->b_format, cus > 0 ? cus : atb::kDefaultCUs);
+    const int found = atb::compute_units(), cus = found > 0 ? found : atb::kDefaultCUs;
+    const atb::StreamRoute r = atb::stream_route(g->proto, g->b_format, cus);
+    return r.streams() ? r : atb::stream_route_lds(g->proto, g->b_format, cus);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

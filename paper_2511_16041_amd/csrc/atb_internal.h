@@ -55,6 +55,8 @@ int compute_units();
 // that a plan admits; b_format as in atb_format, C in BFP16 where p.Cm is set.
 struct StreamRoute;
 hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r, hipStream_t stream);
+// ... of which the forms with 64 rows, row-major B of even N and two panels in flight are in atb_rows.hip.
+hipError_t launch_lds_rows(const GemmParams &p, const StreamRoute &r, hipStream_t stream);
 
 hipError_t launch_quantize(const float *A, int64_t lda, int8_t *Am, uint8_t *Ae, int64_t M, int64_t K,
                            hipStream_t stream);

@@ -99,14 +99,18 @@ inline int stream_depth_bfp16(int k_panels, int mb) { return mb >= 2 && (k_panel
 // 64 x 14336 x 4096 31.5 / 29.4 us, 48 x 14336 x 4096 29.4 / 28.6; fewer rows lose up to 6 % at K = 2048.
 inline int stream_depth_bf16_t(int mb) { return mb >= 3 ? 2 : 1; }
 
+// With row-major bf16 B, 64 columns and four waves: two, through LDS, at 49 to 64 rows.  One panel through registers over that, N 8256 ..
+// 16320: M 64 1.09 - 1.28 at K 1032, 1.03 - 1.32 at K 4096 (N = 16384 0.98, from memory).  At 33 to 48 rows 1.0 - 1.25 up to N = 14336, but 0.93 - 0.96
+// at 16128 and 16384.
+inline int stream_depth_bf16(int mb) { return mb == 4 ? 2 : 1; }
+
 // More than 64 rows: tiles of 64 x 32, 64 x 64, 64 x 128 or 128 x 64, the smallest that makes at most one per CU, and
 // none where the tile pipeline is as good or better.  Measured in us, the pipeline / this kernel, or as the ratio of the two; "memory":
 // 700 MB of operands in turns, so that B comes from memory as a model's weights do; "cache": three sets in turns, which the 256 MiB
 // memory-side cache holds:
 //   B bf16    64 x 64: M 128, 8192, 8192 54.4 / 47.0, M 256, 4096, 4096 22.3 / 19.5; eight shapes of 130 to 256 tiles, K 1032 to 4096: 1.0 - 1.3
 //             x memory, 0.96 - 1.2 x cache (lowest at K 1536, where the pipeline has whole K-steps)
-//             64 x 128: M 512, 4096, 14336 120 / 80; eight shapes, K 4096 / 4352 / 4608 / 5120 / 5632: 1.07 - 1.46 x memory (M 1024, 2048,
-//             4096 37.4 / 28.1), cache 0.92 - 1.1 / 0.9 - 1.08 / 0.94 - 1.1 / 0.95 - 1.13 / 1.02 - 1.16 x; below, M 1024, 2048, 2048 16.3 / 17.5
+//             64 x 128: M 512, 4096, 14336 120 / 66, M 1024, 2048, 4096 24.9 / 21.3 (operands through registers); below K 4096 see stream_route_lds
 //             not 64 x 32 (M 256, 2048, 2048 9.9 / 10.4) nor odd N (M 512, 5001, 4096 61 / 70), nor 64 x 64 where the pipeline's 32 x 64
 //             tiles fit one to a CU (rows just above a multiple of 64: M 193, 2304, M 129, 3000 and M 96, 5000, K 1032 .. 4096: 0.83 - 0.94 x
 //             memory, 0.72 - 0.91 x cache)
@@ -183,7 +187,17 @@ inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
     const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N, cus);
     if (b_format == ATB_FMT_BFP16) return {mb, nb, nb == 2 ? 16 : 8, nb == 4 ? stream_depth_bfp16(p.k_panels, mb) : 1};
     if (b_format == ATB_FMT_BF16 && p.N % 2 != 0) return {mb, 2, 8, 1};
-    return {mb, nb, nb == 2 ? 8 : 4, b_format == ATB_FMT_BF16_T && nb == 4 ? stream_depth_bf16_t(mb) : 1};
+    return {mb, nb, nb == 2 ? 8 : 4, nb != 4 ? 1 : b_format == ATB_FMT_BF16_T ? stream_depth_bf16_t(mb) : stream_depth_bf16(mb)};
+}
+
+// What stream_route leaves to the pipeline and the 64 x 128 tiles with B through LDS (atb_rows.hip) still take: row-major bf16 B of even N that
+// makes at most one such tile per CU and more 64 x 64 tiles than CUs, from K = 1536 on.  The pipeline's time over theirs, twelve shapes of 136
+// to 250 tiles, K 1032 / 1280 / 1536 / 2048 / 3072: 0.95 - 1.04 / 0.97 - 1.08 / 1.0 - 1.11 / 1.05 - 1.18 / 1.12 - 1.26 (1024 x 2048 x 2048
+// 14.8 / 13.5 us, 512 x 4096 x 3072 20.4 / 17.3).
+inline StreamRoute stream_route_lds(const GemmParams &p, int b_format, int cus)
+{
+    const bool takes = b_format == ATB_FMT_BF16 && p.N % 2 == 0 && p.M > 64 && p.K >= 1536 && tile_count(p, 64, 128) <= cus && tile_count(p, 64, 64) > cus;
+    return takes ? StreamRoute{4, 8, 4, 2} : StreamRoute{};
 }
 
 }  // namespace atb

@@ -245,38 +245,6 @@ struct Skinny {
             }
         }
     }
-
-    // Columns n .. n + 7 of row m of C.
-    ATB_DEV void store_eight(int m, int n, const floatx4 (&sum)[2], int cols) const
-    {
-        if (__builtin_expect(p.Cm != nullptr, 0)) {
-            unsigned e = 0;
-            float x[8];
-#pragma unroll
-            for (int f = 0; f < 8; ++f) {
-                x[f] = n < p.N ? sum[f / 4][f % 4] : 0.0f;        // whole blocks: N % 8 == 0
-                e = max(e, exp_field(x[f]));
-            }
-            if (m < p.M && n < cols) {
-                const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;
-                *reinterpret_cast<intx2 *>(p.Cm + rec * kPanelK + n % kPanelK) = intx2{(int)bfp16_mantissas4(x, 133 - (int)e), (int)bfp16_mantissas4(x + 4, 133 - (int)e)};
-                p.Ce[rec * (kPanelK / 8) + (n % kPanelK) / 8] = (uint8_t)e;
-            }
-        } else if (m < p.M) {
-            typedef bf16x8 bf16x8_u __attribute__((aligned(2)));      // rows of C start anywhere
-            union { bf16x8 v; uint16_t h[8]; } o;
-#pragma unroll
-            for (int f = 0; f < 8; ++f) o.v[f] = (__bf16)sum[f / 4][f % 4];
-            uint16_t *dst = p.C + (int64_t)m * p.N + n;
-            if (n + 8 <= p.N) {
-                *reinterpret_cast<bf16x8_u *>(dst) = o.v;
-            } else {
-#pragma unroll
-                for (int f = 0; f < 8; ++f)
-                    if (n + f < p.N) dst[f] = o.h[f];
-            }
-        }
-    }
 };
 
 template <int FMT, int MB, int NB, int W, int D>
@@ -314,7 +282,7 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
                     sum[0] += src[w * (8 * 64)];
                     sum[1] += src[w * (8 * 64) + 64];
                 }
-                sk.store_eight(m0 + 16 * i + sk.c, n0 + 8 * (4 * sk.q + t), sum, cols);
+                store_eight(p, m0 + 16 * i + sk.c, n0 + 8 * (4 * sk.q + t), sum, cols);
             }
         }
         return;
@@ -414,8 +382,8 @@ hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r
         if (form == 1208) return launch_rows<kBRowOdd, 2, 8, 4>(p, r, stream);
     } else {
         if (form == 1208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
-        if (form == 1404) return launch_rows<kBRow, 4, 4, 4>(p, r, stream);
-        if (form == 2804 && r.mb == 4) return launch<kBRow, 4, 8, 4, 2>(p, r, stream);
+        if (form == 1404) return launch_rows<kBRow, 4, 4, 3>(p, r, stream);
+        if (r.depth == 2) return launch_lds_rows(p, r, stream);
         if (form == 1804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
         if (form == 1408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
     }
