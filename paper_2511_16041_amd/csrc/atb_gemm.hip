@@ -226,7 +226,7 @@ ATB_DEV bool tile_origin(const GemmParams &p, int t, int &tm0, int &tn0)
 // row 0 and take the first per(s) bands of sub-tile s, the second group's the rest.
 template <class S, int ROLE, bool VEC, bool BBFP>
 struct BandDeal {
-    static constexpr bool SKEWED = S::SKEW > 0 && (ROLE == 1 || ROLE == 2) && VEC && !BBFP;   // (the odd-N path has no registers to spare for it)
+    static constexpr bool SKEWED = S::SKEW > 0 && (ROLE == 1 || ROLE == 2) && VEC && !BBFP;
     static constexpr int moved(int s) { return SKEWED ? (S::SKEW * (s + 1)) / S::RHO - (S::SKEW * s) / S::RHO : 0; }   // bands of sub-tile s that change hands
     static constexpr int per(int s) { return ROLE == 1 ? S::PER - moved(s) : ROLE == 2 ? S::PER + moved(s) : S::PER; }
     static constexpr int first_local(int s) { int n = 0; for (int t = 0; t < s; ++t) n += per(t); return n; }         // accumulator band of the wave's first band of sub-tile s
@@ -241,8 +241,6 @@ struct BandDeal {
 //   A sub-tile g   : fetched from memory in phase g-PF into register set g % PF, decoded into LDS
 //                    buffer g % 2 during phase g-1, consumed by the microkernel of phase g.
 //   B tile kt      : requested in the first phase of K-step kt-2 straight into LDS buffer kt % 2
-//                    (odd N: into registers, written to LDS in the last phase of K-step kt-2; with LAG
-//                    requested in K-step kt-3 and written in the first phase of kt-2),
 //                    awaited before the last barrier that precedes the last band of K-step kt-1,
 //                    read into the waves' fragment registers during that band (each fragment
 //                    right after its last use), consumed in K-step kt.
@@ -297,43 +295,21 @@ struct TileKernel {
     static constexpr int B_FIRST = (ROLE == 2) ? S::BO : 0;
     static constexpr int BPT = BBFP ? 0 : (ROLE == 0 || ROLE == 3) ? S::B_SLABS : (ROLE == 1) ? S::BO : (ROLE == 2) ? S::B_SLABS - S::BO : 0;   // bf16 B chunks per thread per tile
     static constexpr int BTPT = !BBFP ? 0 : (ROLE == 1 || ROLE == 4) ? 0 : S::BT_SLABS;               // BFP16 B chunks (16 mantissas) per thread per tile
-    // Odd N: a B tile passes through registers.  LAG: it stays there for a K-step (in K-step kt the tile fetched during
-    // kt - 1 is shifted and stored, the one after it fetched), so that nothing waits for a request of its own K-step.  For the tiles
-    // between: 1500 x 3001 x 2056 50.4 -> 46.1 us, 1000 x 2001 x 4000 42.6 -> 36.8.  256 x 256 has no registers to hold it (4000 x 4001 x 4096: 157 -> 192).  The 64 x 64 tiles
-    // share a CU with three to five others, which cover the wait for a request, and a store first thing in a K-step is in the way at
-    // most sizes the selector gives them: 49 x 39829 x 784 -7 %, 8 x 33001 x 1032 -6 % (but 1500 x 4001 x 2056 +10 %); 73 such sizes
-    // are 3 to 5 % faster without.
-    static constexpr bool LAG = !VEC && S::T_MC * S::T_N < 256 * 256 && !(S::T_MC * S::T_N <= 64 * 64 && S::T_K == 64);
-    static constexpr int B_ROWS = NTS / S::B_CPR;                                        // rows between a thread's chunks of the B tile
-    // row_shr moves a value by up to 15 lanes of 16; a thread's chunks sit at one chunk position of their rows or at that and the one that differs in bit 1
-    static_assert(!LAG || (BPT <= 8 && BPT <= S::B_CPR && 64 % S::B_CPR == 0 && B_ROWS % 8 == 0 && ((S::b_swz(8) | S::b_swz(16)) & ~2) == 0 && S::b_swz(32) == 0), "odd N: ends of rows, swizzle of a thread's chunks");
-    // Offset of the dword across the end of a row that the thread whose first chunk is chunk c of row `row` asks for (b_ends), of a tile at
-    // column 0; outside every buffer where it has none.  What a constant expression evaluates has no signed overflow: checked for the
-    // largest odd N that a plan admits (at most 2^23 columns, a tile's byte offsets below 2^31).
-    static constexpr int NO_END = (int)0x80000000;
-    static constexpr int end_offset(int row, int c, int N)
-    {
-        const int i = S::B_CPR - 1 - c;
-        if (i >= BPT) return NO_END;                       // its row would lie outside the tile
-        const int off = ((row + i * B_ROWS) * N + S::T_N) * 2;
-        return (off & 2) != 0 ? off - 2 : NO_END;
-    }
-    static constexpr bool ends_in_reach()
-    {
-        const int N = (std::min((1 << 30) / (S::T_K + 1), 1 << 23) - 1) | 1;
-        for (int t = 0; t < NTS; ++t) {
-            const int off = end_offset(t / S::B_CPR, t % S::B_CPR, N);
-            if (off != NO_END && off < 0) return false;
-        }
-        return true;
-    }
+    // Odd N (!VEC): rows of B begin at any 2-byte address, and so do the 16-byte requests, which the hardware takes at any.  They come in at 51
+    // GB/s per CU (97 where rows begin at multiples of 16 bytes, 65 of 4); through registers, aligned and shifted there, they also cost the
+    // staging waves their loads, shifts and LDS stores.  us, through registers / now: 8192 x 8191 x 8192 975 / 854, 1500 x 3001 x 2056 42.8 / 41.0 at
+    // 64,128,64,128 and 42.1 / 33.9 at 128,128,64,256, 300 x 1001 x 1000 9.9 / 8.5 at 64,64,64,64; 56 plans, every instance: 1.01 - 1.35 x.
+    // What a request checks against the end of B is whole dwords, and the one that begins with B's last element lies half past it and
+    // reads as zero: the wave whose request that was puts the element into the tile once that has landed (put_last).
+    static constexpr bool LAST = !VEC && BPT > 0;
+    static_assert(!LAST || B_FIRST == 0, "odd N: one wave group stages all of B");
     static constexpr int NPAIR_B = BTPT * 8;                                             // B mantissa pairs per thread per tile
     static constexpr int NSTEP_A = NPAIR == 0 ? 0 : SK ? NPAIR / 4 : NPAIR + 2;          // decode items per phase (A sub-tile): pipeline steps, or blocks
     static constexpr int NSTEP_B = NPAIR_B > 0 ? NPAIR_B / S::RHO + 2 : 0;               // ... and for this phase's share of the B tile
-    static constexpr bool ASM_DMA = VEC && !BBFP && S::RHO <= 2 && APT == 0 && BPT > 0;   // B requests issued by hand, see load_b_chunk
+    static constexpr bool ASM_DMA = !BBFP && S::RHO <= 2 && APT == 0 && BPT > 0;   // B requests issued by hand, see load_b_chunk
     // a wave group that issues requests by hand issues no other loads: the compiler's own vmcnt waits (for loads it
     // knows of) would otherwise count the hand-issued requests as well, and its built-in LDS-direct loads use M0 too
-    static_assert(!ASM_DMA || (APT == 0 && BTPT == 0 && VEC && !BBFP), "hand-issued B requests only in wave groups without compiler-visible loads");
+    static_assert(!ASM_DMA || (APT == 0 && BTPT == 0 && !BBFP), "hand-issued B requests only in wave groups without compiler-visible loads");
     static constexpr int APTN = APT > 0 ? APT : 1, BPTN = BPT > 0 ? BPT : 1, BTPTN = BTPT > 0 ? BTPT : 1;   // array extents
     static constexpr int B_BYTES = BBFP ? S::BT_BYTES : S::B_BYTES;
     static_assert(!BBFP || (NPAIR_B % S::RHO == 0 && S::T_K % 16 == 0 && (S::T_N * S::T_K / 16) % NTS == 0), "BFP16 B staging must split evenly");
@@ -375,12 +351,12 @@ struct TileKernel {
     // The workgroup walks its C tiles t_first, t_first + t_stride, ... (see tile_at) as one unbroken
     // pipeline: the requests for A and for B run ahead of the arithmetic by fixed numbers of K-steps,
     // across tile boundaries too, so each of the three streams keeps its own position in the walk.
-    int t_stride, kt_steps;            // kt_steps: K-steps per tile, rounded up to a whole loop body
+    int t_first, t_stride, kt_steps;   // kt_steps: K-steps per tile, rounded up to a whole loop body
     int c_t, m0, n0;                   // the tile being accumulated (and stored by the epilogue)
     int a_t, a_m0, a_steps;            // A requests: tile, the row origin the offsets are based on, K-steps left to request
     int b_t, b_n0, b_steps;            // B requests: likewise with the column origin
     // LDS byte addresses of this thread's staging writes and fragment reads, per buffer
-    char *a_wr[S::AB], *b_wr[2];
+    char *a_wr[S::AB];
     const char *a_rdk[S::KS];          // ASWZ: this lane's fragment read address per k-slice, in A buffer 0, band 0
     int a_d[4];                        // ASWZ: byte offset of 16-byte piece p of this thread's run of a row from its piece 0 (a_wr points at piece 0)
     static constexpr int NRD = BTR ? S::KS : S::NBASE;
@@ -425,15 +401,15 @@ struct TileKernel {
     bf16x8 afrag[2][S::HB][S::KS];     // A fragments of the current and the next band: [band parity][row block][k-slice]
     intx4 a_mant[S::PF][APTN];
     unsigned a_expo[S::PF][APTN];
-    intx4 b_raw[BPTN];
-    // LAG: the dword after the last four of an odd row of this wave's part of the B tile, chunk i's in the lane i below the row's last (and
-    // where a lane's is, outside the buffer where it has none); from a chunk position to the one that differs in bit 1, in bytes
-    int b_ends, b_end_off, b_flip;
+    // LAST: B's last element; the K-step, counted from the walk's first, that publishes its tile, and the next tile of the walk to look at
+    uint16_t last;
+    int step_no, last_step, last_n;
+    char *b_lds;                       // the first B buffer
     unsigned dec[4];                   // bf16 pairs of the BFP16 block being decoded
     float cvf[2][2], ldf[2][2];        // decode pipeline: converted and scaled pairs in flight
     int shift;
 
-    ATB_DEV TileKernel(const GemmParams &p_, char *lds, int t_first, int t_stride_) : p(p_), t_stride(t_stride_)
+    ATB_DEV TileKernel(const GemmParams &p_, char *lds, int t_first_, int t_stride_) : p(p_), t_first(t_first_), t_stride(t_stride_)
     {
         kt_steps = (p.K + S::T_K * S::KU - 1) / (S::T_K * S::KU) * S::KU;
         tid = threadIdx.x;
@@ -483,17 +459,11 @@ struct TileKernel {
 #pragma unroll
             for (int ks = 0; ks < S::KS; ++ks) a_rdk[ks] = lds + rrow * S::PA + ((((S::KM / 8) * ks + lane / S::MB) ^ rswz) * 16);
         }
-        const int wr_row = (slot0 + lane) / S::B_CPR, wr_c = (slot0 + lane) % S::B_CPR;        // LAG: the first chunk this thread stores
-        if constexpr (LAG) {
-            static_assert(ends_in_reach(), "odd N: offsets of the ends of rows");
-            b_end_off = end_offset(wr_row, wr_c, p.N);
-            b_flip = ((wr_c ^ S::b_swz(wr_row)) & 2) ? -32 : 32;
-        }
+        b_lds = lds + S::AB * S::A_BYTES;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             char *b_base = lds + S::AB * S::A_BYTES + b * B_BYTES;
             b_req[b] = b_base + slot0 * 16;
-            b_wr[b] = !LAG ? b_req[b] + lane * 16 : b_base + wr_row * S::PB + (wr_c ^ S::b_swz(wr_row)) * 16;
             // B fragment through ds_read_b64_tr_b16: within each group of 16 lanes, lane i addresses
             // 4 consecutive columns of row i/4 (8 bytes, half a chunk), and lane j receives column j
             // of those 4 rows; a second read, 4 rows on, completes the lane's 8 k values.
@@ -569,9 +539,7 @@ struct TileKernel {
                 const int row = slot / (S::T_K / 8), c = (slot % (S::T_K / 8)) ^ ((row >> 1) & 7);
                 b_off[i] = (row * p.K + c * 8) * 2;
             } else {
-                // the slot is a place in LDS, and its chunk the one that the swizzle keeps there; LAG: neighbouring lanes take
-                // neighbouring chunks, and the swizzle is in the address of the store
-                const int row = slot / S::B_CPR, c = LAG ? slot % S::B_CPR : (slot % S::B_CPR) ^ S::b_swz(row);
+                const int row = slot / S::B_CPR, c = (slot % S::B_CPR) ^ S::b_swz(row);      // the slot is a place in LDS, its chunk the one that the swizzle keeps there
                 b_off[i] = (row * p.N + c * 8) * 2;
             }
         }
@@ -680,7 +648,6 @@ struct TileKernel {
             b_left = live ? (int64_t)p.K * p.N * 2 : 0;
 #pragma unroll
             for (int i = 0; i < BPT; ++i) b_off[i] += d * 2;
-            if constexpr (LAG) b_end_off += d * 2;
         }
     }
 
@@ -853,76 +820,38 @@ struct TileKernel {
         }
     }
 
-    // Odd N: offset of chunk i of the B tile.  In ROLE 0, whose waves hold 256 accumulators and, at T_K = 128, 16 chunks of B, it is made
-    // from the first one's where it is used (the chunks lie a multiple of 16 N bytes apart, at the same place of their rows): with an
-    // offset per chunk 61 registers spilled, 40 accesses to scratch per loop body (32,256,128,256, us: 8192 x 8191 x 8192 1796 -> 1219, 3000 x
-    // 5001 x 1000 68.1 -> 54.6; the first one 1176 with the epilogue's present order).
-    static constexpr bool ONE_OFFSET = (!VEC && ROLE == 0);
-    static_assert(!ONE_OFFSET || (S::b_swz(B_ROWS) == 0 && S::b_swz(2 * B_ROWS) == 0 && S::b_swz(4 * B_ROWS) == 0 && S::b_swz(8 * B_ROWS) == 0), "odd N: a thread's chunks sit at one place of their rows");
-    template <int i>
-    ATB_DEV int odd_offset() const
-    {
-        if constexpr (!ONE_OFFSET || i == 0) {
-            return b_off[i];
-        } else {
-            int n = p.N;
-#if defined(__HIP_DEVICE_COMPILE__)
-            asm volatile("" : "+s"(n));         // else the sum is hoisted out of the K loop, into a register per chunk
-#endif
-            return b_off[0] + i * B_ROWS * 2 * n;
-        }
-    }
-
     // Request i of the next B tile in fetch order, destined for LDS buffer `buf`.
-    // VEC (even N: dword-aligned rows): one 16-byte load per lane straight into LDS (no registers, no ds_write);
-    // completion is awaited with wait_b_landed() before the barrier that publishes the tile.
-    // !VEC (odd N, rows of B only 2-byte aligned): aligned loads into registers plus a funnel shift;
-    // store_b_chunk() writes them to LDS later.
+    // One 16-byte load per lane straight into LDS (no registers, no ds_write); completion is awaited with wait_vm() before the barrier that
+    // publishes the tile.
     template <int i>
     ATB_DEV void load_b_chunk(int buf)
     {
-        if constexpr (VEC) {
 #if defined(__HIP_DEVICE_COMPILE__)
-            typedef __attribute__((address_space(3))) void lds_void;
-            char *dst = RING ? b_req[0] + b_fill_off : b_req[buf];
-            if constexpr (ASM_DMA) {
-                // Issued by hand so that the compiler does not know of it: it cannot tell the buffer being
-                // filled from the one being read and puts a vmcnt(0) in front of every transposing fragment
-                // read that follows a request it knows of -- a full memory round trip inside the K-step when
-                // requests and fragment reads share a phase, as they do at rho = 1 (measured: the symmetric
-                // 128 x 256 tile 522 -> 992 TFLOP/s).  Completion is awaited by wait_vm() before the publishing
-                // barrier, as for the built-in form.  Requests the compiler does not count make its own vmcnt
-                // waits stricter, which is harmless only for waves that request nothing else: waves that also
-                // fetch A would await the B tile before every decode (measured: helper waves 10 - 20 % slower),
-                // so only wave groups without A requests take this path.
-                const unsigned lds_addr = (unsigned)reinterpret_cast<uintptr_t>(dst + i * (NTS * 16));
-                // M0 (the LDS base of the request) is put back afterwards: the compiler reserves it for its own uses
-                // and is not told about this one
-                int m0_saved;
-                asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                             : "=&s"(m0_saved)
-                             : "s"(__builtin_amdgcn_readfirstlane((int)lds_addr)), "v"(b_off[i]), "s"(rs.b_words) : "memory");
-            } else {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs.b, (lds_void *)(dst + i * (NTS * 16)), 16, b_off[i], 0, 0, 0);
-            }
-#else
-            (void)buf;   // the host pass only parses this function
-#endif
+        typedef __attribute__((address_space(3))) void lds_void;
+        char *dst = RING ? b_req[0] + b_fill_off : b_req[buf];
+        if constexpr (ASM_DMA) {
+            // Issued by hand so that the compiler does not know of it: it cannot tell the buffer being
+            // filled from the one being read and puts a vmcnt(0) in front of every transposing fragment
+            // read that follows a request it knows of -- a full memory round trip inside the K-step when
+            // requests and fragment reads share a phase, as they do at rho = 1 (measured: the symmetric
+            // 128 x 256 tile 522 -> 992 TFLOP/s).  Completion is awaited by wait_vm() before the publishing
+            // barrier, as for the built-in form.  Requests the compiler does not count make its own vmcnt
+            // waits stricter, which is harmless only for waves that request nothing else: waves that also
+            // fetch A would await the B tile before every decode (measured: helper waves 10 - 20 % slower),
+            // so only wave groups without A requests take this path.
+            const unsigned lds_addr = (unsigned)reinterpret_cast<uintptr_t>(dst + i * (NTS * 16));
+            // M0 (the LDS base of the request) is put back afterwards: the compiler reserves it for its own uses
+            // and is not told about this one
+            int m0_saved;
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                         : "=&s"(m0_saved)
+                         : "s"(__builtin_amdgcn_readfirstlane((int)lds_addr)), "v"(b_off[i]), "s"(rs.b_words) : "memory");
         } else {
-            // odd N: a chunk starts at an odd bf16 of its row as often as not.  Fetch the 5 aligned
-            // dwords that contain it and shift by half a dword where needed.  The fifth is the next lane's first, but at the end of
-            // a row; those of a tile's odd rows come in one request per wave, spread over lanes (b_ends).  What the requests for it cost was
-            // their number, not their bytes: one per chunk / one per tile, us: 1500 x 3001 x 2056 48.2 / 45.9 (N = 3000: 35.1), 600 x 1501 x 1000
-            // 11.5 / 11.0, 30 x 33001 x 1000 28.2 / 26.7, 300 x 301 x 304 6.3 / 5.9.
-            const int off = odd_offset<i>(), al = off & ~3;
-            const intx4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs.b, al, 0, 0);
-            if constexpr (LAG) {         // shifted when it is stored: here the shift would wait for the request
-                b_raw[i] = lo;
-                if constexpr (i == BPT - 1) b_ends = __builtin_amdgcn_raw_buffer_load_b32(rs.b, b_end_off, 0, 0);
-            } else {
-                b_raw[i] = shifted(lo, __builtin_amdgcn_raw_buffer_load_b32(rs.b, al + 16, 0, 0), (off & 2) * 8);
-            }
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs.b, (lds_void *)(dst + i * (NTS * 16)), 16, b_off[i], 0, 0, 0);
         }
+#else
+        (void)buf;   // the host pass only parses this function
+#endif
         if constexpr (i == BPT - 1) {
             if (--b_steps == 0) {
                 open_b(b_t + t_stride);
@@ -1042,24 +971,24 @@ struct TileKernel {
         }
     }
 
-    // Odd N: the 16 bytes that start sh bits into five dwords.
-    static ATB_DEV intx4 shifted(intx4 lo, int hi, int sh)
+    // Odd N: B's last element into the tile at buf, which holds it (row and column of the tile as constants of the plan).
+    ATB_DEV void put_last(char *buf) const
     {
-        return intx4{(int)__builtin_amdgcn_alignbit((unsigned)lo.y, (unsigned)lo.x, sh), (int)__builtin_amdgcn_alignbit((unsigned)lo.z, (unsigned)lo.y, sh),
-                     (int)__builtin_amdgcn_alignbit((unsigned)lo.w, (unsigned)lo.z, sh), (int)__builtin_amdgcn_alignbit((unsigned)hi, (unsigned)lo.w, sh)};
+        const int row = (p.K - 1) % S::T_K, col = (p.N - 1) % S::T_N, slot = row * S::B_CPR + ((col / 8) ^ S::b_swz(row));
+        if (tid % NTS == slot % NTS) *reinterpret_cast<uint16_t *>(buf + slot * 16 + col % 8 * 2) = last;
     }
-
-    template <int i>
-    ATB_DEV void store_b_chunk(char *b_dst)
+    // The K-step whose last barrier but none publishes the tile with B's last element, for the first tile from the n-th of the walk on that has it
+    // (below 0: the prologue does).
+    ATB_DEV void next_last(int n)
     {
-        if constexpr (LAG) {
-            const int next = __builtin_amdgcn_update_dpp(0, b_raw[i].x, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
-            const int end = i == 0 ? b_ends : __builtin_amdgcn_update_dpp(0, b_ends, 0x110 + (i == 0 ? 1 : i) /* row_shr:i */, 0xf, 0xf, false);
-            const intx4 v = shifted(b_raw[i], lane % S::B_CPR == S::B_CPR - 1 ? end : next, (b_off[i] & 2) * 8);
-            *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16) + (S::b_swz(i * B_ROWS) != 0 ? b_flip : 0)) = v;
-        } else {
-            *reinterpret_cast<intx4 *>(b_dst + i * (NTS * 16)) = b_raw[i];
-        }
+        int tm0, tn0;
+        last_step = 0x7fffffff;
+        for (; tile_at(t_first + n * t_stride, tm0, tn0); ++n)
+            if (tn0 + S::T_N >= p.N) {
+                last_step = n * kt_steps + (p.K - 1) / S::T_K - (S::RHO == 1 ? 2 : 1);
+                last_n = n + 1;
+                return;
+            }
     }
 
     template <int set>
@@ -1067,15 +996,6 @@ struct TileKernel {
 
     template <int set>
     ATB_DEV void store_bt_all(char *b_dst) { decode_all<true, set, 0, NPAIR_B>(b_dst); }
-
-    template <int i = 0>
-    ATB_DEV void store_b_all(char *b_dst)
-    {
-        if constexpr (i < BPT) {
-            store_b_chunk<i>(b_dst);
-            store_b_all<i + 1>(b_dst);
-        }
-    }
 
     // ---- LDS -> registers ----------------------------------------------------------------
     // B fragment (ks, nt) from LDS buffer `buf`: per lane l, column (wn*NC + nt)*MB + l%MB and
@@ -1140,7 +1060,7 @@ struct TileKernel {
     template <int s>
     static constexpr int n_side()
     {
-        return RQ + APT + (s == 0 ? BPT + BTPT : 0) + NSTEP_A + NSTEP_B + ((!VEC && !LAG && s + 1 == S::RHO) ? BPT : 0);
+        return RQ + APT + (s == 0 ? BPT + BTPT : 0) + NSTEP_A + NSTEP_B;
     }
 
     template <int ki, int s, int j>
@@ -1151,11 +1071,10 @@ struct TileKernel {
         constexpr int n_la = APT, n_lb = (s == 0 ? BPT : 0), n_lt = (s == 0 ? BTPT : 0), n_dt = NPAIR_B / S::RHO;
         // (the raw A requests come first: they are awaited a phase later, the B tile's only three phases later, and
         // requests complete in order)
-        constexpr int j0 = RQ, j1 = j0 + n_lb, j2 = j1 + n_lt, j3 = j2 + n_la, j4 = j3 + NSTEP_A, j5 = j4 + NSTEP_B;
+        constexpr int j0 = RQ, j1 = j0 + n_lb, j2 = j1 + n_lt, j3 = j2 + n_la, j4 = j3 + NSTEP_A;
         if constexpr (j < j0) {
             load_raw_chunk<(g + RAW_LEAD) % S::NR, (s + RAW_LEAD) % S::RHO, j>();
         } else if constexpr (j < j1) {
-            if constexpr (LAG) store_b_chunk<j - j0>(RING ? b_wr[0] + b_fill_off : b_wr[kpar]);
             load_b_chunk<j - j0>(kpar);
         } else if constexpr (j < j2) {
             load_bt_chunk<kpar ^ 1, j - j1>();
@@ -1166,10 +1085,8 @@ struct TileKernel {
                 decode_block<(g + S::DA) % S::PF, j - j3>(a_wr[(g + S::DA) % S::AB], a_mask >> (((s + S::DA) % S::RHO) * APTN));
             else
                 decode_step<false, (g + S::DA) % S::PF, 0, NPAIR, j - j3>(a_wr[(g + S::DA) % S::AB]);
-        } else if constexpr (j < j5) {
-            decode_step<true, kpar, s * n_dt, n_dt, j - j4>(RING ? bt_wr[0] + b_fill_off : bt_wr[kpar]);
         } else {
-            store_b_chunk<j - j5>(RING ? b_wr[0] + b_fill_off : b_wr[kpar]);
+            decode_step<true, kpar, s * n_dt, n_dt, j - j4>(RING ? bt_wr[0] + b_fill_off : bt_wr[kpar]);
         }
     }
 
@@ -1296,12 +1213,20 @@ struct TileKernel {
             // requests of NB - 1 K-steps and NB - 2 further B tiles.  rho >= 2: the barrier ending the
             // last-but-one phase of K-step kt + 1; younger are the A requests of NB rho - 1 phases and
             // NB - 1 further B tiles.  (A smaller count only waits for more than necessary.)
-            if constexpr (VEC && BPT > 0 && S::RHO == 1) wait_vm<vm_cap((S::NB - 1) * A_VMEM + (S::NB - 2) * BPT)>();
+            if constexpr (BPT > 0 && S::RHO == 1) wait_vm<vm_cap((S::NB - 1) * A_VMEM + (S::NB - 2) * BPT)>();
             // ADMA: the raw sub-tile requested in the previous phase is read by the other group in the next one, so
             // everything older than this phase's own requests has to have landed (which covers the B tile as well)
             if constexpr (RQ > 0) wait_vm<vm_cap(RQ + BPT)>();
-            else if constexpr (VEC && BPT > 0 && S::RHO >= 2 && s == S::RHO - 2)
+            else if constexpr (BPT > 0 && S::RHO >= 2 && s == S::RHO - 2)
                 wait_vm<vm_cap((S::NB * S::RHO - 1) * A_VMEM + (S::NB - 1) * BPT)>();
+            if constexpr (LAST && s == (S::RHO == 1 ? 0 : S::RHO - 2)) {
+                if (step_no++ == last_step) {
+                    // rho = 1: the tile of K-step kt + 2, else of kt + 1
+                    if constexpr (RING) put_last(b_lds + (S::RHO >= 2 ? b_read_off : next_buffer(b_read_off)));
+                    else put_last(b_lds + (S::RHO >= 2 ? (ki & 1) ^ 1 : ki & 1) * B_BYTES);
+                    next_last(last_n);
+                }
+            }
             switch_barrier();   // the "kernel switch" of the ATB nest
             if constexpr (COMPUTE) slots<ki, s, (nm(s) - tail(s)) / MG, nm(s) / MG>();
             phases<ki, s + 1>();
@@ -1310,11 +1235,12 @@ struct TileKernel {
 
     static constexpr int vm_cap(int n) { return n < 63 ? n : 63; }     // vmcnt is a 6-bit counter
 
+    static ATB_DEV int next_buffer(int off) { return off + B_BYTES == NBUF * B_BYTES ? 0 : off + B_BYTES; }
     // NB > 2: the ring moves on by one buffer per K-step
     ATB_DEV void advance_b_ring()
     {
-        b_fill_off = (b_fill_off + B_BYTES == NBUF * B_BYTES) ? 0 : b_fill_off + B_BYTES;
-        b_read_off = (b_read_off + B_BYTES == NBUF * B_BYTES) ? 0 : b_read_off + B_BYTES;
+        b_fill_off = next_buffer(b_fill_off);
+        b_read_off = next_buffer(b_read_off);
     }
 
     // K-steps ki .. KU - 1 of the loop body, of which only the first `left` are wanted.
@@ -1344,6 +1270,8 @@ struct TileKernel {
     {
         // prologue: the first NB B tiles into LDS, the first PF A sub-tiles into registers, sub-tile 0
         // into LDS, B tile 0 into fragment registers
+        int bits = 0;
+        if constexpr (LAST) bits = p.B[(int64_t)p.K * p.N - 1];
         if constexpr (RING) b_fill_off = 0;
         if constexpr (ADMA_ON) {
             // the first RAW_LEAD raw sub-tiles into the ring, landed and published before the decoding group reads them
@@ -1354,13 +1282,11 @@ struct TileKernel {
         load_b(0);
         if constexpr (BBFP) { load_bt<0>(); load_bt<1>(); }
         prologue_loads();
-        if constexpr (!VEC) store_b_all(b_wr[0]);
         if constexpr (RING && !BBFP) {
 #pragma unroll
             for (int t = 1; t < S::NB; ++t) {
                 b_fill_off = t * B_BYTES;
                 load_b(0);
-                if constexpr (!VEC) store_b_all(b_wr[0] + b_fill_off);
             }
         } else {
             load_b(1);
@@ -1373,12 +1299,15 @@ struct TileKernel {
         }
         store_a_all<0>(a_wr[0]);
         if constexpr (S::AB == 4) store_a_all<1>(a_wr[1]);
-        if constexpr (VEC && BPT > 0) wait_vm<0>();
-        if constexpr (!VEC && !RING) store_b_all(b_wr[1]);
-        // the tile that K-step 0 stores; where the reduction ends before it, nobody reads what is stored, and a request of zeros is a
-        // round trip all the same (8 x 1001 x 72 at 32,32,256,64: 6.9 -> 6.3 us)
-        if constexpr (LAG)
-            if (kt_steps > S::NB) load_b(0);
+        if constexpr (BPT > 0) wait_vm<0>();
+        if constexpr (LAST) {
+            last = (uint16_t)__builtin_amdgcn_readfirstlane(bits);
+            const int at = (p.K - 1) / S::T_K;
+            if (n0 + S::T_N >= p.N && at < S::NB) put_last(b_lds + at * B_BYTES);
+            step_no = 0;
+            next_last(0);
+            if (last_step < 0) next_last(1);
+        }
         __syncthreads();
         if constexpr (RING) b_read_off = 0;
         if constexpr (COMPUTE) read_b_frags_all(0);
@@ -1700,9 +1629,6 @@ hipError_t launch_kernel(const GemmParams &p, hipStream_t stream)
 template <class S>
 hipError_t launch_instance(const GemmParams &p, hipStream_t stream)
 {
-    // 16-byte requests need dword-aligned addresses: B rows start at multiples of 2 N bytes, chunks at
-    // multiples of 16 bytes within a row, so any even N qualifies (a chunk that straddles the end of
-    // a row only feeds output columns >= N, which are never stored)
     if ((p.N % 2) == 0) return launch_kernel<S, true, false, false>(p, stream);
     return launch_kernel<S, false, false, false>(p, stream);
 }
