@@ -149,8 +149,9 @@ atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, int64_t K,
 /* Launch geometry of a plan, for benches and tests: number of C tiles the
  * launch walks, rounded up to a multiple of 8 (the grid of the large tiles is persistent: it has
  * min(that, workgroups resident on the chip) workgroups, each looping over its
- * tiles), threads per workgroup, static LDS bytes per workgroup: of the kernel for few rows where
- * that is what atb_gemm_run launches (atb_gemm_streams). Any pointer may be NULL. */
+ * tiles), threads per workgroup, static LDS bytes per workgroup: of the kernel that atb_gemm_run
+ * launches (for few rows the streaming kernel, atb_gemm_streams; for odd N on 128 x 128 tiles, where
+ * there are many, the 128 x 256 ones). Any pointer may be NULL. */
 atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroups, int *threads, int *lds_bytes);
 
 /* 1 if atb_gemm_run sends this plan to the kernel for few rows and a long reduction (see

@@ -27,14 +27,31 @@ atb_status hip_status(hipError_t e)
     return ATB_ERR_HIP;
 }
 
+int device_cus()
+{
+    const int cus = atb::compute_units();
+    return cus > 0 ? cus : atb::kDefaultCUs;
+}
+
 // The streaming kernel's form for this plan; it does not stream where the tile pipeline runs it.
 atb::StreamRoute plan_route(const atb_gemm *g)
 {
     const bool over = g->b_format == ATB_FMT_BF16_T || atb::instance(g->instance).hands_over;
     if (!over || g->proto.K <= atb::kStreamMinK) return {};
-    const int found = atb::compute_units(), cus = found > 0 ? found : atb::kDefaultCUs;
+    const int cus = device_cus();
     const atb::StreamRoute r = atb::stream_route(g->proto, g->b_format, cus);
     return r.streams() ? r : atb::stream_route_lds(g->proto, g->b_format, cus);
+}
+
+// The instance that runs a plan that does not stream, and its tiles in p (a copy of the plan's).
+const atb::Instance &plan_instance(const atb_gemm *g, atb::GemmParams &p)
+{
+    const atb::Instance &x = atb::instance(g->instance);
+    if (p.N % 2 == 0 || g->b_format != ATB_FMT_BF16 || !atb::odd_n_runs_wide(p, x.T_MC, x.T_N, device_cus())) return x;
+    const int wide = atb::find_instance(128, 128, 64, 256);
+    if (wide < 0) return x;
+    p.tiles_n = (p.N + 255) / 256;
+    return atb::instance(wide);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -191,6 +208,10 @@ extern "C" atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, 
         const atb::StreamRoute r = plan_route(g);
         if (r.streams())       // what runs instead of the instance
             std::fprintf(stderr, " streaming: tile=%dx%d threads=%d depth=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.depth, r.lds_bytes(), (long long)atb::stream_workgroups(p, r));
+        atb::GemmParams run = p;
+        const atb::Instance &y = plan_instance(g, run);
+        if (!r.streams() && &y != &x)
+            std::fprintf(stderr, " runs: T_MA=%d T_MC=%d T_K=%d T_N=%d tiles=%dx%d", y.T_MA, y.T_MC, y.T_K, y.T_N, run.tiles_m, run.tiles_n);
         std::fputc('\n', stderr);
     }
     *out = g;
@@ -218,7 +239,7 @@ extern "C" atb_status atb_gemm_run(const atb_gemm *g, const void *A_bfp, const v
     }
     const atb::StreamRoute r = plan_route(g);
     if (r.streams()) return hip_status(atb::launch_skinny(p, g->b_format, r, static_cast<hipStream_t>(stream)));
-    const atb::Instance &x = atb::instance(g->instance);
+    const atb::Instance &x = plan_instance(g, p);
     if (g->b_format != ATB_FMT_BF16 || g->c_format != ATB_FMT_BF16)
         return hip_status(x.launch_fmt(p, g->b_format, g->c_format, static_cast<hipStream_t>(stream)));
     return hip_status(x.launch(p, static_cast<hipStream_t>(stream)));
@@ -229,9 +250,10 @@ extern "C" void atb_gemm_destroy(atb_gemm *g) { delete g; }
 extern "C" atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroups, int *threads, int *lds_bytes)
 {
     if (!g) return ATB_ERR_INVALID_ARG;
-    const atb::Instance &x = atb::instance(g->instance);
+    atb::GemmParams p = g->proto;
+    const atb::Instance &x = plan_instance(g, p);
     const atb::StreamRoute r = plan_route(g);
-    const int64_t total = (int64_t)g->proto.tiles_m * g->proto.tiles_n;
+    const int64_t total = (int64_t)p.tiles_m * p.tiles_n;
     if (workgroups) *workgroups = r.streams() ? atb::stream_workgroups(g->proto, r) : (total + 7) / 8 * 8;
     if (threads) *threads = r.streams() ? r.threads() : x.threads;
     if (lds_bytes) *lds_bytes = r.streams() ? r.lds_bytes() : x.lds_bytes;

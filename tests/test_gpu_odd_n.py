@@ -35,3 +35,19 @@ def test_last_element_of_b(tiles, N):
 def test_last_element_of_b_in_a_walk_of_several_tiles(tiles, K):
     print(f"odd N walk {(17000, 1281, K)} tiles={tiles}", flush=True)
     _compare(17000, 1281, K, tiles)                            # 402 tiles for 256 workgroups, 67 of them in the last column
+
+
+@pytest.mark.parametrize("tiles", [(128, 128, 64, 128), (64, 128, 64, 128)])
+@pytest.mark.parametrize("shape", [(2049, 2049, 1024), (16 * 128 + 1, 2177, 1032), (8200, 513, 1288), (3713, 1665, 1024)])
+def test_128_row_tiles_run_as_wide_ones(tiles, shape):
+    """Above one 128 x 128 tile per CU the 128 x 256 tiles run in their place, with the bits that any other instance gives."""
+    import paper_2511_16041_amd as atb
+    M, N, K = shape
+    print(f"odd N wide {shape} tiles={tiles}", flush=True)
+    plan = atb.Gemm(M, N, K, *tiles)
+    assert plan.launch_info().workgroups == -(-(-(-M // 128) * -(-N // 256)) // 8) * 8
+    plan.close()
+    _compare(M, N, K, tiles)
+    A, Bb = workloads.make_inputs(workloads.CONFIGS["ragged"], M=M, N=N, K=K)
+    mant, expo = oracle.quantize(A)
+    assert np.array_equal(_run(mant, expo, Bb, tiles), _run(mant, expo, Bb, (64, 64, 64, 64)))
