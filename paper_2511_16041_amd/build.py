@@ -16,12 +16,12 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libatb.so")
 BINDING_SOURCE = "atb_binding.cpp"
 OBJ_DIR = os.path.join(HERE, "_build")
+# accumulators stay whole where they are carried round a loop: taken apart (as the compiler does with vectors that begin as constants), each
+# of their registers is moved once per round (212 moves to 64 MFMAs in atb_rows; in atb_skinny up to 7 %: 500 x 4096 x 4096 B^T 34.0 -> 32.9 us)
+WHOLE_PHIS = ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=0"]
 # accumulators stay in ordinary vector registers: with up to 470 of a wave's 512 in use the compiler otherwise parks other
 # values in the accumulation half and moves the accumulators out and in again around every panel (208 moves to 64 MFMAs)
-SKINNY_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-# accumulators stay whole where they are carried round a loop: taken apart (as the compiler does with vectors that begin as constants), each
-# of their registers is moved once per round, 212 moves to 64 MFMAs
-WHOLE_PHIS = ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=0"]
+SKINNY_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] + WHOLE_PHIS
 # loops of the 128-row tiles begin on a line of the instruction cache: the same instructions some bytes further on cost the 64,128,64,128
 # tile with B in BFP16 4 % (706 x 4992 x 3880 50.4 -> 52.5 us); the other forms of these tiles are level (the 64 x 64 tiles lose 2 % by it)
 ALIGNED = ["-falign-loops=64"]

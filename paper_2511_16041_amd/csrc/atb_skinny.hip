@@ -15,7 +15,7 @@
 // Measured in us, three sets of operands in turns, the tile pipeline before / this kernel now:
 //   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5     M 64, 14336, 4096: 34.7 / 30.0     M 16, 5001, 4096: 23.7 / 12.9
 //   B^T bf16  M 16, N 8192, K 8192: 105 / 29        M 64, 14336, 4096: 57.7 / 29.4
-//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.5    M 64, 14336, 4096: 26.0 / 19.3 (decoding A takes as long as B's bytes)
+//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.0    M 64, 14336, 4096: 26.0 / 18.6 (decoding A takes as long as B's bytes)
 //
 // MFMA v_mfma_f32_16x16x32_bf16: lane l supplies index l % 16 of its operand and 8 k values of group l / 16.  Which k
 // a group holds is free as long as both operands agree: lane group q takes k = 16 q .. 16 q + 15 of the panel, the
@@ -27,6 +27,8 @@
 //                      v_perm_b32 picks the halves
 //   B^T bf16           two 16-byte requests per 16 columns are the operands as they are
 //   B^T BFP16          one 16-byte request per 16 columns, decoded in registers like A
+#include <type_traits>
+
 #include "atb_device.h"
 #include "atb_route.h"
 
@@ -157,7 +159,15 @@ struct Skinny {
         }
     }
 
-    ATB_DEV static int shift_of(unsigned e, int q, int h) { return (int)((e >> (16 * (q & 1) + 8 * h)) & 0xFFu) - 133; }
+    // With B^T the decode is what the waves wait for, and a multiplication is the shorter instruction: B in BFP16 1.01 - 1.04 x (5 x 5016 x 11328
+    // 16.7 / 16.1 us, 256 x 2048 x 8192 23.4 / 22.5), bf16 1.00 - 1.03; row-major B 0.99 - 1.005.
+    typedef typename std::conditional<ROWS, int, float>::type Scale;
+    ATB_DEV static Scale scale_of(unsigned e, int q, int h)
+    {
+        const int E = (int)((e >> (16 * (q & 1) + 8 * h)) & 0xFFu);
+        if constexpr (ROWS) return E - 133;
+        else return ldexpf(0x1p-133f, E);
+    }
 
     ATB_DEV void multiply(const Panel<FMT, MB, NB> &s)
     {
@@ -187,12 +197,12 @@ struct Skinny {
                     u.w = s.bt[2 * j + h];
                     bf[j] = u.v;
                 } else {
-                    bf[j] = bfp16_decode8(s.bt[j][2 * h], s.bt[j][2 * h + 1], shift_of(s.be[j], q, h));
+                    bf[j] = bfp16_decode8(s.bt[j][2 * h], s.bt[j][2 * h + 1], scale_of(s.be[j], q, h));
                 }
             }
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
-                const bf16x8 af = bfp16_decode8(s.am[i][2 * h], s.am[i][2 * h + 1], shift_of(s.ae[i], q, h));
+                const bf16x8 af = bfp16_decode8(s.am[i][2 * h], s.am[i][2 * h + 1], scale_of(s.ae[i], q, h));
 #pragma unroll
                 for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af, acc[i][j], 0, 0, 0);
             }
