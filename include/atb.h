@@ -151,7 +151,8 @@ atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, int64_t K,
  * min(that, workgroups resident on the chip) workgroups, each looping over its
  * tiles), threads per workgroup, static LDS bytes per workgroup: of the kernel that atb_gemm_run
  * launches (for few rows the streaming kernel, atb_gemm_streams; for odd N on 128 x 128 tiles, where
- * there are many, the 128 x 256 ones). Any pointer may be NULL. */
+ * there are many, the 128 x 256 ones; for a bf16 B^T that makes few tiles, 64 x 64 or 128 x 128 ones).
+ * Any pointer may be NULL. */
 atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroups, int *threads, int *lds_bytes);
 
 /* 1 if atb_gemm_run sends this plan to the kernel for few rows and a long reduction (see

@@ -10,6 +10,7 @@ struct atb_gemm {
     int64_t M, N, K;
     int instance;
     int b_format, c_format;
+    int group_m;                   // 0, or the height of an XCD's patch of C tiles in tile rows
     atb_bfp16_layout_t layout;     // A
     atb_bfp16_layout_t layout_b;   // B^T when b_format is BFP16
     atb_bfp16_layout_t layout_c;   // C when c_format is BFP16
@@ -43,15 +44,26 @@ atb::StreamRoute plan_route(const atb_gemm *g)
     return r.streams() ? r : atb::stream_route_lds(g->proto, g->b_format, cus);
 }
 
+// Tile rows that are walked together: an XCD's patch of C tiles is 2048 rows high.
+int patch_rows(const atb_gemm *g, int T_MC) { return g->group_m > 0 ? g->group_m : std::max(1, 2048 / T_MC); }
+
 // The instance that runs a plan that does not stream, and its tiles in p (a copy of the plan's).
 const atb::Instance &plan_instance(const atb_gemm *g, atb::GemmParams &p)
 {
     const atb::Instance &x = atb::instance(g->instance);
-    if (p.N % 2 == 0 || g->b_format != ATB_FMT_BF16 || !atb::odd_n_runs_wide(p, x.T_MC, x.T_N, device_cus())) return x;
-    const int wide = atb::find_instance(128, 128, 64, 256);
-    if (wide < 0) return x;
-    p.tiles_n = (p.N + 255) / 256;
-    return atb::instance(wide);
+    int run = -1;
+    if (g->b_format == ATB_FMT_BF16_T) {
+        const int side = atb::bt_small_tiles(p, device_cus());
+        if (side != 0) run = atb::find_instance(64, side, 64, side);
+    } else if (g->b_format == ATB_FMT_BF16 && p.N % 2 != 0 && atb::odd_n_runs_wide(p, x.T_MC, x.T_N, device_cus())) {
+        run = atb::find_instance(128, 128, 64, 256);
+    }
+    if (run < 0) return x;
+    const atb::Instance &y = atb::instance(run);
+    p.tiles_m = (p.M + y.T_MC - 1) / y.T_MC;
+    p.tiles_n = (p.N + y.T_N - 1) / y.T_N;
+    p.group_m = patch_rows(g, y.T_MC);
+    return y;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -191,13 +203,14 @@ extern "C" atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, 
     // C in BFP16: the tiles also cover the zero tail of C's last panel (columns N .. 64 * panels - 1),
     // so that the result can be the BFP16 operand of a following GEMM as it is
     if (c_format == ATB_FMT_BFP16) p.tiles_n = (int)((atb::round_up(N, atb::kPanelK) + T_N - 1) / T_N);
-    p.group_m = (int)std::max<int64_t>(1, 2048 / T_MC);   // an XCD's patch of C tiles is 2048 rows high
     // measurement aid: ATB_GROUP_M=<tile rows> overrides the height of the patch, so that the counters can
     // be read with the tiles resident on an XCD laid out as one row (1) or one column (>= 32) of C tiles
+    g->group_m = 0;
     if (const char *gm = std::getenv("ATB_GROUP_M"); gm && gm[0]) {
         const long v = std::strtol(gm, nullptr, 10);
-        if (v >= 1 && v <= 65536) p.group_m = (int)v;   // anything else is ignored
+        if (v >= 1 && v <= 65536) g->group_m = (int)v;   // anything else is ignored
     }
+    p.group_m = patch_rows(g, T_MC);
     if (const char *log = std::getenv("ATB_LOG"); log && log[0] == '1') {
         const atb::Instance &x = atb::instance(idx);
         std::fprintf(stderr, "atb_gemm_create: M=%lld N=%lld K=%lld T_MA=%d T_MC=%d T_K=%d T_N=%d rho=%d b=%s c=%s "

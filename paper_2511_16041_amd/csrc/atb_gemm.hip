@@ -1634,14 +1634,20 @@ hipError_t launch_instance(const GemmParams &p, hipStream_t stream)
     return launch_kernel<S, false, false, false>(p, stream);
 }
 
+template <class S>
+constexpr bool takes_bt() { return S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256; }
+template <class S>
+constexpr bool runs_bt() { return S::T_K == 64 && S::T_MA == 64 && S::T_MC == S::T_N && S::HW > 0; }
+
 // The other storage formats (B and/or C in BFP16); C in BFP16 needs N % 8 == 0 (checked by the caller).
 template <class S>
 hipError_t launch_instance_fmt(const GemmParams &p, int b_format, int c_format, hipStream_t stream)
 {
     const bool bb = (b_format == ATB_FMT_BFP16), cb = (c_format == ATB_FMT_BFP16);
     if (b_format == ATB_FMT_BF16_T) {
-        // bf16 B handed over transposed: compiled for the tiles with K-steps of 64 and a bf16 C
-        if constexpr (S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256) {
+        // bf16 B handed over transposed, with a bf16 C: compiled for the tiles with K-steps of 64 and at least 128 x 256, and for the two that
+        // small problems of theirs run on (bt_small_tiles)
+        if constexpr (takes_bt<S>() || runs_bt<S>()) {
             if (!cb) return launch_kernel<S, true, false, false, true>(p, stream);
         }
         return hipErrorInvalidValue;
@@ -1676,7 +1682,7 @@ Instance make_instance(double eff_scale = 0.0, double lone_cap = 0.0)
     // few rows and a long K go to the streaming kernel from the instances that the selector picks for such problems, and from every
     // instance that takes B^T in bf16 (all of them tiles of 128 rows and more)
     i.hands_over = S::HW > 0 && S::T_K >= 128;
-    i.has_b_transposed = FMT && S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256;
+    i.has_b_transposed = FMT && takes_bt<S>();
     return i;
 }
 

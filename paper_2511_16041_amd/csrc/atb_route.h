@@ -213,4 +213,11 @@ inline bool odd_n_runs_wide(const GemmParams &p, int T_MC, int T_N, int cus)
     return wide <= cus || 4 * wide >= 3 * ((wide + cus - 1) / cus) * cus;
 }
 
+// B^T in bf16 that the pipeline runs: the side of the square tiles (64: 64,64,64,64; 128: 64,128,64,128; the same bits) that take a problem too small
+// for the tiles of 128 x 256 and more that a plan can name; 0 where those run.  The latter over 64 / 128, 200 problems, by the number of the
+// square tiles: up to 256 64 x 64 ones 1.4 - 1.7 / 1.15 - 1.3 at K 72, 1.65 - 1.8 / 1.25 - 1.35 at 264, 1.7 - 1.9 / 1.3 - 1.4 at 520, 1.7 - 2.1 / 1.3 - 1.45 at 1024;
+// 512 of them 1.27 - 1.55 / 1.2 - 1.34, 625 1.18 - 1.38 / 1.27 - 1.38, 1024 0.93 - 0.99 / 1.18 - 1.33 (256 128 x 128 ones); 315 128 x 128 ones 0.9 / 0.96 - 0.99.
+// us: 1000 x 1000 x 1024 16.7 / 8.9, 100 x 2000 x 520 10.9 / 5.8, 88 x 1792 x 72 5.7 / 3.6, 1000 x 4000 x 520 12.7 / 9.7.
+inline int bt_small_tiles(const GemmParams &p, int cus) { return tile_count(p, 64, 64) <= 2 * cus ? 64 : tile_count(p, 128, 128) <= cus ? 128 : 0; }
+
 }  // namespace atb
