@@ -329,8 +329,8 @@ struct TileKernel {
     // For the 8-wave tiles with B in BFP16 (both wave groups decode, the most even phases).  Measured (us, barrier last /
     // early): 2048 x 4096 x 14336 at 64,128,64,256 268.9 / 261.4; 8192^3 at 256 x 256 935 / 918; 2048 x 14336 x 4096, C in
     // BFP16 too, 226.1 / 222.6.  With row-major bf16 B it is level (8192^3, rho = 2: 845 / 849, symmetric 840 / 849; 64,128,64,256: 1018
-    // / 1008) and stays out.  With B^T in bf16 it is not built; a trial gave 867 / 831 and 868 / 837 (8192^3, rho = 1, 2) and 73.8 / 69.2
-    // (2048 x 4096 x 4096 at 64,128,64,256).  Smaller tiles have no room for the buffer.
+    // / 1008) and stays out; so it is with B^T in bf16 (40 plans 0.994 x; 8192^3 829 / 824, 2048 x 4096 x 4096 65.4 / 65.0 at 128,128,64,256 and
+    // 64.2 / 65.1 at 64,128,64,256, up to 11 % slower where an odd number of K-steps is rounded up).  Smaller tiles have no room for the buffer.
     static constexpr bool EB = BBFP && S::EB_BT;
     static constexpr bool RING = BBFP ? EB : S::NB > 2;                                   // B buffers indexed at run time
     static constexpr int NBUF = BBFP ? (EB ? 3 : 2) : S::NB;

@@ -13,7 +13,7 @@
 // worth up to 12 % (stream_depth_bfp16, stream_depth_bf16_t).  Hence the tile width (stream_column_blocks): as wide as leaves one workgroup per CU.  With B row-major and N
 // <= 8192 that is 32 columns, half a line per row, and the rate stays at 3.9 TB/s against 5.1 with B^T.
 // Measured in us, three sets of operands in turns, the tile pipeline before / this kernel now:
-//   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5     M 64, 14336, 4096: 34.7 / 30.0     M 16, 5001, 4096: 23.7 / 12.9
+//   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5  (64 rows: atb_rows.hip)     M 16, 5001, 4096: 23.7 / 12.9
 //   B^T bf16  M 16, N 8192, K 8192: 105 / 29        M 64, 14336, 4096: 57.7 / 29.4
 //   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.0    M 64, 14336, 4096: 26.0 / 18.6 (decoding A takes as long as B's bytes)
 //
