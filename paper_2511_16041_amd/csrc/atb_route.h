@@ -202,15 +202,19 @@ inline StreamRoute stream_route_lds(const GemmParams &p, int b_format, int cus)
 
 // Odd N, row-major bf16 B, on 128 x 128 tiles: whether the 128 x 256 tiles (128,128,64,256; the same bits) run in their place.  A request for rows at odd
 // addresses takes a CU twice as long as an aligned one, the staging waves of the 128 x 128 tiles then wait for A behind B, and two of these tiles on a CU
-// ask for B twice.  The wide tiles stage A and B with different waves and have a third B buffer.  128,128,64,128 and 64,128,64,128 over the wide
-// tiles, eleven shapes from 272 to 800 tiles of 128 x 128, K 520 / 1032 / 2056 / 4104: 0.97 - 1.03 / 1.04 - 1.08 / 1.09 - 1.16 / 1.15 - 1.22 and 0.99 -
-// 1.05 / 1.07 - 1.13 / 1.16 - 1.22 / 1.21 - 1.29 (1500 x 3001 x 2056 37.9 and 41.0 us / 33.6).  Not where one 128 x 128 tile per CU is enough (64
-// wide tiles take twice as long) nor where the last round of wide tiles is nearly empty (288 of them: 0.81 - 0.97).
+// ask for B twice.  The wide tiles stage A and B with different waves and have a third B buffer.  What decides is how many tiles one CU gets through,
+// a wide one counted as two: narrow N, of which the wide tiles multiply up to twice the padding, and last rounds that are nearly empty come out in it.  64,128,64,128
+// over the wide tiles, 110 shapes from 350 to 2000 tiles of 128 x 128, by the wide tiles' count over the small ones', at K 1032 / 2056 / 4104:
+//   1            0.99 - 1.10 (0.94 with 1/7 of padding) / 1.06 - 1.17 / 1.11 - 1.26 (1500 x 3001 x 2056 41.0 us / 33.6)
+//   up to 8/7    0.89 - 0.98 / 0.97 - 1.06 / 1.02 - 1.12
+//   up to 6/5    0.87 - 0.95 / 0.95 - 1.02 / 1.01 - 1.06
+//   4/3          0.81 - 0.89 / 0.90 - 0.95 / 0.95 - 1.00;  2, N below 128: 0.62 - 0.70
+// (from memory 0.02 less at the best and the same at the line).  Not where one 128 x 128 tile per CU is enough (64 wide tiles take twice as long).
 inline bool odd_n_runs_wide(const GemmParams &p, int T_MC, int T_N, int cus)
 {
-    if (p.N % 2 == 0 || T_MC != 128 || T_N != 128 || p.K < 1024 || tile_count(p, 128, 128) <= cus) return false;
-    const int64_t wide = tile_count(p, 128, 256);
-    return wide <= cus || 4 * wide >= 3 * ((wide + cus - 1) / cus) * cus;
+    if (p.N % 2 == 0 || T_MC != 128 || T_N != 128 || p.K < 1024) return false;
+    const int64_t per_cu = (tile_count(p, 128, 128) + cus - 1) / cus, wide = 2 * ((tile_count(p, 128, 256) + cus - 1) / cus);
+    return per_cu > 1 && 100 * wide <= (p.K < 2048 ? 100 : p.K < 4096 ? 112 : 120) * per_cu;
 }
 
 // B^T in bf16 that the pipeline runs: the side of the square tiles (64: 64,64,64,64; 128: 64,128,64,128; the same bits) that take a problem too small

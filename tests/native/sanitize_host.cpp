@@ -268,6 +268,21 @@ static void route_paths()
         {48, 50000, 4096, ATB_FMT_BFP16, 3, 8},  {49, 16448, 4096, ATB_FMT_BFP16, 0, 0}};
     for (const auto &c : many) expect_route(c);
     for (const auto &c : few) expect_route(c);
+    // odd N on 128 x 128 tiles: the 128 x 256 ones in their place, by the tiles that one CU gets through (a wide one is two)
+    const struct { int M, N, K, cus; bool wide; } odd_n[] = {
+        {1500, 3001, 2056, 256, true},  {1500, 3000, 2056, 256, false}, {1500, 3001, 1016, 256, false},    // 288 tiles, 144 wide; even N; short K
+        {2048, 2047, 4104, 256, false}, {2049, 2047, 1032, 256, true},  {2048, 2047, 1032, 255, true},     // one tile per CU, and one more or a CU less
+        {51200, 1, 4104, 256, false},   {64000, 127, 2056, 256, false}, {128000, 65, 1024, 256, false},    // a wide tile has no more of N than a small one
+        {25600, 257, 4104, 256, false}, {25600, 513, 2056, 256, false}, {42624, 301, 4104, 256, false},    // padding to 512 and 768 columns
+        {4096, 3071, 1032, 256, false}, {6144, 2047, 1032, 256, false}, {8192, 2047, 1032, 256, true},     // 3 small against 4, 3 against 4, 4 against 4
+        {14848, 1279, 1032, 256, false}, {14848, 1279, 4104, 256, true}, {36736, 1023, 2056, 256, true},   // 5 against 6, 9 against 10
+        {36736, 1023, 1032, 256, false}, {26880, 1023, 2056, 256, false}, {26880, 1023, 4104, 256, true},  // 7 against 8
+        {1024, 1023, 1032, 32, true},   {512, 511, 1032, 32, false},    {1152, 1023, 1032, 32, false}};
+    for (const auto &c : odd_n) {
+        const bool wide = atb::odd_n_runs_wide(problem(c.M, c.N, c.K), 128, 128, c.cus);
+        if (wide != c.wide) { std::printf("odd N %d x %d x %d on %d CUs: wide %d\n", c.M, c.N, c.K, c.cus, (int)wide); ++failures; }
+    }
+    EXPECT(!atb::odd_n_runs_wide(problem(1500, 3001, 2056), 128, 256, 256) && !atb::odd_n_runs_wide(problem(1500, 3001, 2056), 64, 128, 256));
     // as many rows as one launch can take: 2^28 of up to 512 columns to quantise, M K / 8 < 2^32 blocks to decode
     EXPECT(quantize_route(((int64_t)1 << 27) + 8, 512).steps == 8 && quantize_route(((int64_t)1 << 27) + 8, 512).workgroups == (1 << 23) + 1);
     EXPECT(quantize_route(((int64_t)1 << 28) - 16, 8).workgroups == (1 << 24) - 1 && quantize_route((int64_t)1 << 28, 8).workgroups == 0);
