@@ -47,23 +47,32 @@ atb::StreamRoute plan_route(const atb_gemm *g)
 // Tile rows that are walked together: an XCD's patch of C tiles is 2048 rows high.
 int patch_rows(const atb_gemm *g, int T_MC) { return g->group_m > 0 ? g->group_m : std::max(1, 2048 / T_MC); }
 
-// The instance that runs a plan that does not stream, and its tiles in p (a copy of the plan's).
-const atb::Instance &plan_instance(const atb_gemm *g, atb::GemmParams &p)
+// What runs a plan that does not stream.
+struct TileRun {
+    const atb::Instance *x;
+    bool third_b;                  // its kernel with a third B buffer
+    int lds_bytes() const { return third_b ? x->lds_third_b : x->lds_bytes; }
+};
+
+// ... and its tiles in p (a copy of the plan's).
+TileRun plan_tiles(const atb_gemm *g, atb::GemmParams &p)
 {
     const atb::Instance &x = atb::instance(g->instance);
     int run = -1;
     if (g->b_format == ATB_FMT_BF16_T) {
         const int side = atb::bt_small_tiles(p, device_cus());
         if (side != 0) run = atb::find_instance(64, side, 64, side);
-    } else if (g->b_format == ATB_FMT_BF16 && p.N % 2 != 0 && atb::odd_n_runs_wide(p, x.T_MC, x.T_N, device_cus())) {
-        run = atb::find_instance(128, 128, 64, 256);
+    } else if (g->b_format == ATB_FMT_BF16 && p.N % 2 != 0) {
+        const int cus = device_cus();
+        if (atb::odd_n_runs_wide(p, x.T_MC, x.T_N, cus)) run = atb::find_instance(128, 128, 64, 256);
+        else if (x.launch_third_b && atb::odd_n_third_buffer(p, x.T_MC, x.T_N, cus)) return {&x, true};
     }
-    if (run < 0) return x;
+    if (run < 0) return {&x, false};
     const atb::Instance &y = atb::instance(run);
     p.tiles_m = (p.M + y.T_MC - 1) / y.T_MC;
     p.tiles_n = (p.N + y.T_N - 1) / y.T_N;
     p.group_m = patch_rows(g, y.T_MC);
-    return y;
+    return {&y, false};
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -222,9 +231,9 @@ extern "C" atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, 
         if (r.streams())       // what runs instead of the instance
             std::fprintf(stderr, " streaming: tile=%dx%d threads=%d depth=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.depth, r.lds_bytes(), (long long)atb::stream_workgroups(p, r));
         atb::GemmParams run = p;
-        const atb::Instance &y = plan_instance(g, run);
-        if (!r.streams() && &y != &x)
-            std::fprintf(stderr, " runs: T_MA=%d T_MC=%d T_K=%d T_N=%d tiles=%dx%d", y.T_MA, y.T_MC, y.T_K, y.T_N, run.tiles_m, run.tiles_n);
+        const TileRun t = plan_tiles(g, run);
+        if (!r.streams() && (t.x != &x || t.third_b))
+            std::fprintf(stderr, " runs: T_MA=%d T_MC=%d T_K=%d T_N=%d tiles=%dx%d lds=%d", t.x->T_MA, t.x->T_MC, t.x->T_K, t.x->T_N, run.tiles_m, run.tiles_n, t.lds_bytes());
         std::fputc('\n', stderr);
     }
     *out = g;
@@ -252,10 +261,10 @@ extern "C" atb_status atb_gemm_run(const atb_gemm *g, const void *A_bfp, const v
     }
     const atb::StreamRoute r = plan_route(g);
     if (r.streams()) return hip_status(atb::launch_skinny(p, g->b_format, r, static_cast<hipStream_t>(stream)));
-    const atb::Instance &x = plan_instance(g, p);
+    const TileRun t = plan_tiles(g, p);
     if (g->b_format != ATB_FMT_BF16 || g->c_format != ATB_FMT_BF16)
-        return hip_status(x.launch_fmt(p, g->b_format, g->c_format, static_cast<hipStream_t>(stream)));
-    return hip_status(x.launch(p, static_cast<hipStream_t>(stream)));
+        return hip_status(t.x->launch_fmt(p, g->b_format, g->c_format, static_cast<hipStream_t>(stream)));
+    return hip_status((t.third_b ? t.x->launch_third_b : t.x->launch)(p, static_cast<hipStream_t>(stream)));
 }
 
 extern "C" void atb_gemm_destroy(atb_gemm *g) { delete g; }
@@ -264,12 +273,12 @@ extern "C" atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroup
 {
     if (!g) return ATB_ERR_INVALID_ARG;
     atb::GemmParams p = g->proto;
-    const atb::Instance &x = plan_instance(g, p);
+    const TileRun t = plan_tiles(g, p);
     const atb::StreamRoute r = plan_route(g);
     const int64_t total = (int64_t)p.tiles_m * p.tiles_n;
     if (workgroups) *workgroups = r.streams() ? atb::stream_workgroups(g->proto, r) : (total + 7) / 8 * 8;
-    if (threads) *threads = r.streams() ? r.threads() : x.threads;
-    if (lds_bytes) *lds_bytes = r.streams() ? r.lds_bytes() : x.lds_bytes;
+    if (threads) *threads = r.streams() ? r.threads() : t.x->threads;
+    if (lds_bytes) *lds_bytes = r.streams() ? r.lds_bytes() : t.lds_bytes();
     return ATB_OK;
 }
 

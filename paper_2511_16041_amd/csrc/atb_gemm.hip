@@ -46,6 +46,7 @@ ATB_DEV float mant_to_float(int w, int byte) { return (float)(int)(signed char)(
 
 template <int T_MA_, int T_MC_, int T_K_, int T_N_, int WM_, int WN_, int PF_, int AB_ = 2, int AO_ = -1, int BO_ = 0, int KU_ = 2, int NB_ = 2, int HW_ = 0, int SKEW_ = 0, int MB_ = 0, int OCC_ = 1, bool ADMA_ = false>
 struct Shape {
+    template <int NB2> using WithBuffers = Shape<T_MA_, T_MC_, T_K_, T_N_, WM_, WN_, PF_, AB_, AO_, BO_, KU_, NB2, HW_, SKEW_, MB_, OCC_, ADMA_>;      // NB2 B buffers
     static constexpr int T_MA = T_MA_, T_MC = T_MC_, T_K = T_K_, T_N = T_N_, WM = WM_, WN = WN_;
     static constexpr int PF = PF_;                // A sub-tiles fetched this many phases ahead of their use
     static constexpr int KU = KU_;                // K-steps per iteration of the (unrolled) K loop: every buffer and register-set index is static
@@ -1634,6 +1635,16 @@ hipError_t launch_instance(const GemmParams &p, hipStream_t stream)
     return launch_kernel<S, false, false, false>(p, stream);
 }
 
+// Odd N with a third B buffer (odd_n_third_buffer): the tiles of one sub-tile per K-step whose B tile has but one K-step to arrive, 64,64,128,128 and
+// 128,128,64,128.  (The 64 x 64 ones share a CU with three others, which cover the wait.)
+template <class S>
+constexpr bool has_third_b() { return S::RHO == 1 && S::HW > 0 && S::NB == 2 && S::T_MC * S::T_N > 64 * 64; }
+template <class S>
+hipError_t launch_instance_third_b(const GemmParams &p, hipStream_t stream)
+{
+    return launch_kernel<typename S::template WithBuffers<3>, false, false, false>(p, stream);
+}
+
 template <class S>
 constexpr bool takes_bt() { return S::T_K == 64 && S::T_MC * S::T_N >= 128 * 256; }
 template <class S>
@@ -1683,6 +1694,13 @@ Instance make_instance(double eff_scale = 0.0, double lone_cap = 0.0)
     // instance that takes B^T in bf16 (all of them tiles of 128 rows and more)
     i.hands_over = S::HW > 0 && S::T_K >= 128;
     i.has_b_transposed = FMT && takes_bt<S>();
+    if constexpr (has_third_b<S>()) {
+        i.launch_third_b = &launch_instance_third_b<S>;
+        i.lds_third_b = S::template WithBuffers<3>::LDS_BYTES;
+    } else {
+        i.launch_third_b = nullptr;
+        i.lds_third_b = 0;
+    }
     return i;
 }
 

@@ -41,6 +41,9 @@ struct Instance {
     bool has_b_transposed;  // launch_fmt also takes b_format = ATB_FMT_BF16_T (with a bf16 C)
     // other storage formats (b_format, c_format as in atb_format); null where the instance has none
     hipError_t (*launch_fmt)(const GemmParams &p, int b_format, int c_format, hipStream_t stream);
+    // the kernel for odd N with a third B buffer (odd_n_third_buffer), and its static LDS; null and 0 where the instance has none
+    hipError_t (*launch_third_b)(const GemmParams &p, hipStream_t stream);
+    int lds_third_b;
 };
 
 int instance_count();

@@ -217,6 +217,18 @@ inline bool odd_n_runs_wide(const GemmParams &p, int T_MC, int T_N, int cus)
     return per_cu > 1 && 100 * wide <= (p.K < 2048 ? 100 : p.K < 4096 ? 112 : 120) * per_cu;
 }
 
+// Odd N, row-major bf16 B, on the tiles that have a kernel with a third B buffer (64,64,128,128 and 128,128,64,128): whether that one runs.  B requests
+// at odd addresses are slow, and from memory a K-step is not time enough for them.  Two buffers over three, operands from memory / from the caches,
+// fourteen shapes, K 264 / 520 / 776 / 1032 / 2056 / 4104:
+//   64,64,128,128   0.97 / 1.00 / 1.04 / 1.06 / 1.1 / 1.14    0.95 - 0.98 / 0.98 - 0.99 / 0.98 - 1.00 / 0.99 - 1.01 / 1.00 - 1.03 / 1.01 - 1.03 (600 x 3001 x 4104 46.5 / 40.6 and 34.1 / 33.9 us)
+//   128,128,64,128  1.02 / 1.08 / 1.14 / 1.17 / 1.25 / 1.31   0.97 - 0.98 / 0.98 - 1.00 / 0.98 - 1.01 / 0.97 - 1.02 / 1.00 - 1.04 / 1.00 - 1.05 (300 x 3001 x 4104 59.9 / 45.9 and 44.4 / 43.0)
+// The line is where two buffers begin to lose from memory what B through registers had (600 x 5001 x 776 25.2 / 25.5).  Two workgroups of 128 x 128 tiles
+// fit a CU with two buffers but not with three: 3000 x 1281 x 776 24.9 / 29.8.
+inline bool odd_n_third_buffer(const GemmParams &p, int T_MC, int T_N, int cus)
+{
+    return p.N % 2 != 0 && p.K >= 768 && (T_MC < 128 || tile_count(p, T_MC, T_N) <= cus);
+}
+
 // B^T in bf16 that the pipeline runs: the side of the square tiles (64: 64,64,64,64; 128: 64,128,64,128; the same bits) that take a problem too small
 // for the tiles of 128 x 256 and more that a plan can name; 0 where those run.  The latter over 64 / 128, 200 problems, by the number of the
 // square tiles: up to 256 64 x 64 ones 1.4 - 1.7 / 1.15 - 1.3 at K 72, 1.65 - 1.8 / 1.25 - 1.35 at 264, 1.7 - 1.9 / 1.3 - 1.4 at 520, 1.7 - 2.1 / 1.3 - 1.45 at 1024;

@@ -282,6 +282,11 @@ static void route_paths()
         const bool wide = atb::odd_n_runs_wide(problem(c.M, c.N, c.K), 128, 128, c.cus);
         if (wide != c.wide) { std::printf("odd N %d x %d x %d on %d CUs: wide %d\n", c.M, c.N, c.K, c.cus, (int)wide); ++failures; }
     }
+    // a third buffer for B of odd N: long reductions, and 128 x 128 tiles only up to one per CU
+    EXPECT(atb::odd_n_third_buffer(problem(600, 5001, 768), 64, 128, 256) && !atb::odd_n_third_buffer(problem(600, 5001, 760), 64, 128, 256));
+    EXPECT(!atb::odd_n_third_buffer(problem(600, 5000, 4104), 64, 128, 256) && atb::odd_n_third_buffer(problem(30000, 5001, 1032), 64, 128, 256));
+    EXPECT(atb::odd_n_third_buffer(problem(2048, 2047, 776), 128, 128, 256) && !atb::odd_n_third_buffer(problem(2049, 2047, 776), 128, 128, 256));
+    EXPECT(!atb::odd_n_third_buffer(problem(2048, 2047, 776), 128, 128, 255) && atb::odd_n_third_buffer(problem(512, 511, 776), 128, 128, 32));
     EXPECT(!atb::odd_n_runs_wide(problem(1500, 3001, 2056), 128, 256, 256) && !atb::odd_n_runs_wide(problem(1500, 3001, 2056), 64, 128, 256));
     // as many rows as one launch can take: 2^28 of up to 512 columns to quantise, M K / 8 < 2^32 blocks to decode
     EXPECT(quantize_route(((int64_t)1 << 27) + 8, 512).steps == 8 && quantize_route(((int64_t)1 << 27) + 8, 512).workgroups == (1 << 23) + 1);

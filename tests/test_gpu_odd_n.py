@@ -51,3 +51,20 @@ def test_128_row_tiles_run_as_wide_ones(tiles, shape):
     A, Bb = workloads.make_inputs(workloads.CONFIGS["ragged"], M=M, N=N, K=K)
     mant, expo = oracle.quantize(A)
     assert np.array_equal(_run(mant, expo, Bb, tiles), _run(mant, expo, Bb, (64, 64, 64, 64)))
+
+
+@pytest.mark.parametrize("N", [1, 129, 391])
+@pytest.mark.parametrize("tiles", [(64, 64, 128, 128), (128, 128, 64, 128)])
+def test_third_b_buffer(tiles, N):
+    """From K = 768 on these tiles have three buffers for B of odd N (128 x 128 up to one tile per CU): the last K-step in each of the three, whole or of
+    8 rows."""
+    import paper_2511_16041_amd as atb
+    lds = {}
+    for K in (760, 768, 776, 832, 896, 904, 1024, 1032, 1160, 1288):
+        plan = atb.Gemm(150, N, K, *tiles)
+        assert not plan.streams()
+        lds[K] = plan.launch_info().lds_bytes
+        plan.close()
+        print(f"odd N third buffer {(150, N, K)} tiles={tiles}", flush=True)
+        _compare(150, N, K, tiles)
+    assert all(n - lds[760] == (0 if K < 768 else tiles[2] * tiles[3] * 2) for K, n in lds.items())
