@@ -73,6 +73,7 @@ struct Shape {
     // group stages A slabs [0, AO) and B slabs [0, BO) of every (sub-)tile, the second the rest.
     static constexpr int NTS = (HW > 0) ? HW * 64 : (CW == 8) ? 256 : CW * 64;
     static constexpr int RHO = T_MC / T_MA;
+    static constexpr bool PERSISTENT = T_MC * T_N >= 256 * 256;      // a workgroup walks several C tiles (launch_kernel says why)
     static constexpr int MT = T_MC / 32;          // 32-row bands in the C tile
     static constexpr int SMT = T_MA / 32;         // bands per A sub-tile
     static constexpr int MTW = MT / WM;           // bands per wave
@@ -980,14 +981,16 @@ struct TileKernel {
         if (tid % NTS == slot % NTS) *reinterpret_cast<uint16_t *>(buf + slot * 16 + col % 8 * 2) = last;
     }
     // The K-step whose last barrier but none publishes the tile with B's last element, for the first tile from the n-th of the walk on that has it
-    // (below 0: the prologue does).
+    // (below 0: the prologue does).  A workgroup of one tile needs no walk: its divisions took 0.2 us of the prologue (20000 x 1 x 8 4.42 -> 4.31 us, 300 x 301 x 304 5.00 -> 4.87).
+    static constexpr int NO_STEP = 0x7fffffff;
+    ATB_DEV int put_step() const { return (p.K - 1) / S::T_K - (S::RHO == 1 ? 2 : 1); }
     ATB_DEV void next_last(int n)
     {
         int tm0, tn0;
-        last_step = 0x7fffffff;
+        last_step = NO_STEP;
         for (; tile_at(t_first + n * t_stride, tm0, tn0); ++n)
             if (tn0 + S::T_N >= p.N) {
-                last_step = n * kt_steps + (p.K - 1) / S::T_K - (S::RHO == 1 ? 2 : 1);
+                last_step = n * kt_steps + put_step();
                 last_n = n + 1;
                 return;
             }
@@ -1222,11 +1225,14 @@ struct TileKernel {
             else if constexpr (BPT > 0 && S::RHO >= 2 && s == S::RHO - 2)
                 wait_vm<vm_cap((S::NB * S::RHO - 1) * A_VMEM + (S::NB - 1) * BPT)>();
             if constexpr (LAST && s == (S::RHO == 1 ? 0 : S::RHO - 2)) {
-                if (step_no++ == last_step) {
+                // (said to be rare, the block lies outside the loop also where it is short: 1500 x 3001 x 2056 34.1 -> 33.6 us.  Where the walk makes it
+                // long it does so anyway, and the hint costs the four-wave tiles a register.)
+                const bool put = step_no++ == last_step;
+                if (S::PERSISTENT ? put : __builtin_expect(put, 0)) {
                     // rho = 1: the tile of K-step kt + 2, else of kt + 1
                     if constexpr (RING) put_last(b_lds + (S::RHO >= 2 ? b_read_off : next_buffer(b_read_off)));
                     else put_last(b_lds + (S::RHO >= 2 ? (ki & 1) ^ 1 : ki & 1) * B_BYTES);
-                    next_last(last_n);
+                    if constexpr (S::PERSISTENT) next_last(last_n);
                 }
             }
             switch_barrier();   // the "kernel switch" of the ATB nest
@@ -1305,10 +1311,15 @@ struct TileKernel {
         if constexpr (LAST) {
             last = (uint16_t)__builtin_amdgcn_readfirstlane(bits);
             const int at = (p.K - 1) / S::T_K;
-            if (n0 + S::T_N >= p.N && at < S::NB) put_last(b_lds + at * B_BYTES);
+            const bool here = n0 + S::T_N >= p.N;
+            if (here && at < S::NB) put_last(b_lds + at * B_BYTES);
             step_no = 0;
-            next_last(0);
-            if (last_step < 0) next_last(1);
+            if constexpr (S::PERSISTENT) {
+                next_last(0);
+                if (last_step < 0) next_last(1);
+            } else {
+                last_step = here ? put_step() : NO_STEP;
+            }
         }
         __syncthreads();
         if constexpr (RING) b_read_off = 0;
@@ -1604,7 +1615,7 @@ hipError_t launch_kernel(const GemmParams &p, hipStream_t stream)
     // The 256 x 256 tiles get a persistent grid of one workgroup per CU (the accumulators of one tile are half the
     // CU's 512 KiB of vector registers, so a second workgroup never fits beside the first, whatever the LDS
     // footprint): a grid larger than what is resident would only queue, a smaller one idles CUs.
-    constexpr bool persistent = S::T_MC * S::T_N >= 256 * 256;
+    constexpr bool persistent = S::PERSISTENT;
     static_assert(!persistent || 2 * (S::T_MC * S::T_N * 4) >= 512 * 1024, "the persistent grid assumes one workgroup per CU");
     int slots = per_xcd;                                                           // workgroups per XCD
     if (persistent) {
