@@ -100,7 +100,7 @@ inline int stream_depth_bfp16(int k_panels, int mb) { return mb >= 2 && (k_panel
 inline int stream_depth_bf16_t(int mb) { return mb >= 3 ? 2 : 1; }
 
 // With row-major bf16 B, 64 columns and four waves: two, through LDS, at 49 to 64 rows.  One panel through registers over that, N 8256 ..
-// 16320: M 64 1.09 - 1.28 at K 1032, 1.03 - 1.32 at K 4096 (N = 16384 0.98, from memory).  At 33 to 48 rows 1.0 - 1.25 up to N = 14336, but 0.93 - 0.96
+// 16322: M 64 1.08 - 1.28 at K 1032, 1.03 - 1.29 at K 4096, 1.05 at K 8192; N = 16384 (rows 32 KiB apart) 1.07 at K 1032, 1.00 at 4096, 0.99 from 6144 on.  At 33 to 48 rows 1.0 - 1.25 up to N = 14336, but 0.93 - 0.96
 // at 16128 and 16384.
 inline int stream_depth_bf16(int mb) { return mb == 4 ? 2 : 1; }
 

@@ -244,27 +244,38 @@ struct Rows {
 
     // One panel: slot m is its m-th MFMA and what is done in that one's shadow.
     //   decode           of the next group's A fragment, over the slots of this group (the last group's: the next panel's first)
-    //   requests         of the next panel of A, whose place was read a panel ago, and of the panel of B after the next, into this one's place:
-    //                    its first half from slot NB on, by when every fragment of that half has been used, its second from HALF on
+    //   requests         of the next panel of A, whose place was read a panel ago, and of the panel of B after the next, into this one's place: its first
+    //                    half in slots FROM1 .. TO1 - 1, its second in FROM2 .. TO2 - 1, by when every fragment of that half has been read
     //   B fragments      of this panel's second half during the first, of the next panel's first half at the end
     //   the wait         ahead of those, for the next panel: younger than its requests are those for B since then
-    static constexpr int SLOTS = GROUPS * NB, HALF = SLOTS / 2, WAIT = SLOTS - 2 * NB - 2;
-    static constexpr int first_half(int m) { return (m - NB) * (A_REQ + NB) / (HALF - NB); }            // requests before slot m
-    static constexpr int second_half(int m) { return (m - HALF) * NB / HALF; }
+    // When to ask is a matter of where B is; us with operands through registers / asked for in slots NB .. SLOTS / 2 - 1 and SLOTS / 2 .. SLOTS - 1 / now.
+    // 128 columns: early, and the second half in one go, since from memory it came late: 1024 x 2048 x 8192 48.4 / 48.6 / 45.6, 1000 x 2000 x 8192
+    // 49.8 / 51.5 / 49.6, 700 x 2900 x 8192 51.3 / 54.2 / 52.1 (rows of B that begin at multiples of 8 bytes).  From the caches it costs up to 1.5 %: 1024 x 2048 x
+    // 4096 25.4 / 21.7 / 21.8, x 8192 44.9 / 39.0 / 39.6.
+    // 64 columns: late, since where rows of B are 32 KiB apart all requests of a CU go to one memory channel, and the more in flight the worse: 64 x
+    // 16384 x 14336 88.1 / 91.5 / 89.3, 49 x 16384 x 8192 51.6 / 52.7 / 51.5.  It costs 1 to 2 % where half of the CUs have a tile: 64 x 8256 x 4096
+    // from memory 26.3 / 21.2 / 21.4, from the caches 21.8 / 16.5 / 16.9.
+    static constexpr int SLOTS = GROUPS * NB, WAIT = SLOTS - 2 * NB - 2;
+    static constexpr int FROM1 = 8, TO1 = NB == 8 ? 28 : 17, FROM2 = NB == 8 ? 34 : 22, TO2 = NB == 8 ? 48 : 32;
+    static constexpr int spread(int m, int from, int to, int n) { return m <= from ? 0 : m < to ? (m - from) * n / (to - from) : n; }       // of n requests, those before slot m
+    static constexpr int first_half(int m) { return spread(m, FROM1, TO1, A_REQ + NB); }
+    static constexpr int second_half(int m) { return spread(m, FROM2, TO2, NB); }
     template <int m>
     ATB_DEV void slots()
     {
+        static_assert(TO1 <= FROM2 && FROM2 > 3 * NB && TO2 <= SLOTS, "requests in the order that wait_vm counts, none for a place that is still to be read");
+        static_assert(first_half(WAIT + 1) >= A_REQ, "all of A's requests are older than what may be under way");
         if constexpr (m < SLOTS) {
             constexpr int g = m / NB, j = m % NB, h = g / MB;
             acc[g % MB][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[h][j], af[g % 2], acc[g % MB][j], 0, 0, 0);
             ATB_FENCE();
             decode<(g + 1) % GROUPS, j * OPS / NB, (j + 1) * OPS / NB>();
-            if constexpr (m == NB) { wait_lds(); advance_a(); advance_b(); }
-            if constexpr (m >= NB && m < HALF) requests<first_half(m), first_half(m + 1)>();
+            if constexpr (m == FROM1) { wait_lds(); advance_a(); advance_b(); }
+            if constexpr (m >= FROM1 && m < TO1) requests<first_half(m), first_half(m + 1)>();
             if constexpr (m > NB && m <= 3 * NB) read_b<1, (m - NB - 1) % (2 * NB)>(0);
-            if constexpr (m == HALF) wait_lds();
-            if constexpr (m >= HALF) requests<A_REQ + NB + second_half(m), A_REQ + NB + second_half(m + 1)>();
-            if constexpr (m == WAIT) wait_vm<NB + second_half(WAIT + 1)>();
+            if constexpr (m == FROM2) wait_lds();
+            if constexpr (m >= FROM2) requests<A_REQ + NB + second_half(m), A_REQ + NB + second_half(m + 1)>();
+            if constexpr (m == WAIT) wait_vm<first_half(WAIT + 1) - A_REQ + second_half(WAIT + 1)>();
             read_a_at<m, WAIT>();
             if constexpr (m >= SLOTS - 2 * NB) read_b<0, (m + 2 * NB - SLOTS) % (2 * NB)>(step);
             ATB_FENCE();
