@@ -82,8 +82,11 @@ typedef struct atb_gemm atb_gemm; /* opaque plan, HOST memory */
  * 2 * N * (T_K + 1) < 2^31.
  * Problems of few rows and a long reduction (K > 1024; M <= 64, or few enough rows and columns for one
  * small tile per CU; not all of them, atb_gemm_streams tells) on the instances (64, 64, 128, 128), (32, 64, 256, 64)
- * and (32, 32, 256, 64), and with b_format BF16_T on any, are run by a kernel of their own that streams B through
- * registers; the factors then only select it.
+ * and (32, 32, 256, 64), and with b_format BF16_T on any, are run by a kernel of their own whose waves take turns along K
+ * and share no tiles; the factors then only select it.
+ * Two kinds of plan run on other factors than theirs, where those are faster (the same bits; atb_gemm_kernel tells which):
+ * odd N on (64, 128, 64, 128) and (128, 128, 64, 128) with K >= 1024 and many tiles on (128, 128, 64, 256), and b_format BF16_T
+ * with few tiles on (64, 64, 64, 64) or (64, 128, 64, 128).  To compare factors, compare plans of which that is not so.
  * Bits: a plan gives the same bits on every run.  Plans that do not stream -- all of them up to K = 1024 -- add the
  * products of an element of C in one fp32 chain, k ascending: the same operands give the same bits on every instance,
  * with B row-major or transposed, and a row of C does not depend on M.  Plans that stream add one chain per wave, in
@@ -149,11 +152,20 @@ atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, int64_t K,
 /* Launch geometry of a plan, for benches and tests: number of C tiles the
  * launch walks, rounded up to a multiple of 8 (the grid of the large tiles is persistent: it has
  * min(that, workgroups resident on the chip) workgroups, each looping over its
- * tiles), threads per workgroup, static LDS bytes per workgroup: of the kernel that atb_gemm_run
- * launches (for few rows the streaming kernel, atb_gemm_streams; for odd N on 128 x 128 tiles, where
- * there are many, the 128 x 256 ones; for a bf16 B^T that makes few tiles, 64 x 64 or 128 x 128 ones).
- * Any pointer may be NULL. */
+ * tiles), threads per workgroup, static LDS bytes per workgroup (as with a bf16 B): of the kernel that atb_gemm_run
+ * launches, which atb_gemm_kernel describes in full.  Any pointer may be NULL. */
 atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroups, int *threads, int *lds_bytes);
+
+/* The kernel that atb_gemm_run launches for a plan, whose factors are not always the plan's (atb_gemm_create). */
+typedef struct atb_kernel_info {
+    int T_MA, T_MC, T_K, T_N; /* tile factors of the instance that runs; of a plan that streams T_MA = T_MC the rows and T_N
+                                 the columns of a workgroup's tile of C, T_K the 64 of a panel */
+    int streams;              /* as atb_gemm_streams */
+    int threads;              /* per workgroup */
+    int lds_bytes;            /* all the LDS that a workgroup occupies, static and dynamic */
+    int64_t workgroups;       /* as atb_gemm_launch_info */
+} atb_kernel_info;
+atb_status atb_gemm_kernel(const atb_gemm *g, atb_kernel_info *out);
 
 /* 1 if atb_gemm_run sends this plan to the kernel for few rows and a long reduction (see
  * atb_gemm_create), which has no tile buffers and no use for the plan's factors; else 0 (also g == NULL). */

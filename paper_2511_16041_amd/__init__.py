@@ -65,10 +65,19 @@ class Bfp16Layout(ctypes.Structure):
                 ("exp_stride", ctypes.c_int64), ("exp_off", ctypes.c_int64), ("bytes", ctypes.c_int64)]
 
 
+class KernelInfo(ctypes.Structure):
+    """atb_kernel_info: the kernel that a plan's run() launches."""
+    _fields_ = [("T_MA", ctypes.c_int), ("T_MC", ctypes.c_int), ("T_K", ctypes.c_int), ("T_N", ctypes.c_int), ("streams", ctypes.c_int),
+                ("threads", ctypes.c_int), ("lds_bytes", ctypes.c_int), ("workgroups", ctypes.c_int64)]
+
+    def tiles(self) -> Tuple[int, int, int, int]:
+        return self.T_MA, self.T_MC, self.T_K, self.T_N
+
+
 # every symbol include/atb.h declares
 EXPORTS = [
     "atb_status_string", "atb_last_hip_error", "atb_gemm_create", "atb_gemm_create_fmt", "atb_gemm_run", "atb_gemm_destroy",
-    "atb_gemm_launch_info", "atb_gemm_streams", "atb_instance_count", "atb_instance_get", "atb_bfp16_layout", "atb_bfp16_bytes",
+    "atb_gemm_launch_info", "atb_gemm_kernel", "atb_gemm_streams", "atb_instance_count", "atb_instance_get", "atb_bfp16_layout", "atb_bfp16_bytes",
     "atb_bfp16_quantize", "atb_bfp16_decode", "atb_hw_params_xdna2", "atb_hw_params_mi355x",
     "atb_model_eval", "atb_select_tiles", "atb_model_microkernel", "atb_instance_geometry", "atb_mfma_probe",
 ]
@@ -96,6 +105,8 @@ def lib() -> ctypes.CDLL:
     L.atb_gemm_destroy.argtypes = [vp]
     L.atb_gemm_launch_info.restype = ci
     L.atb_gemm_launch_info.argtypes = [vp, ctypes.POINTER(i64), pi, pi]
+    L.atb_gemm_kernel.restype = ci
+    L.atb_gemm_kernel.argtypes = [vp, ctypes.POINTER(KernelInfo)]
     L.atb_gemm_streams.restype = ci
     L.atb_gemm_streams.argtypes = [vp]
     L.atb_instance_count.restype = ci
@@ -376,6 +387,12 @@ class Gemm:
         _check(lib().atb_gemm_launch_info(self._h, ctypes.byref(wg), ctypes.byref(th), ctypes.byref(lds)),
                "atb_gemm_launch_info")
         return LaunchInfo(wg.value, th.value, lds.value)
+
+    def kernel(self) -> KernelInfo:
+        """What run() launches: not always the instance of `tiles` (some plans of odd N, of "bf16_t" and of few rows run on others)."""
+        info = KernelInfo()
+        _check(lib().atb_gemm_kernel(self._h, ctypes.byref(info)), "atb_gemm_kernel")
+        return info
 
     def streams(self) -> bool:
         """Whether run() launches the kernel for few rows and a long reduction instead of the instance of `tiles`."""

@@ -229,7 +229,7 @@ extern "C" atb_status atb_gemm_create_fmt(atb_gemm **out, int64_t M, int64_t N, 
                      x.wave_m, x.wave_n, x.threads, x.lds_bytes, p.tiles_m, p.tiles_n, p.group_m, p.k_panels);
         const atb::StreamRoute r = plan_route(g);
         if (r.streams())       // what runs instead of the instance
-            std::fprintf(stderr, " streaming: tile=%dx%d threads=%d depth=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.depth, r.lds_bytes(), (long long)atb::stream_workgroups(p, r));
+            std::fprintf(stderr, " streaming: tile=%dx%d threads=%d depth=%d lds=%d workgroups=%lld", 16 * r.mb, 16 * r.nb, r.threads(), r.depth, r.lds_bytes() + r.dynamic_lds(), (long long)atb::stream_workgroups(p, r));
         atb::GemmParams run = p;
         const TileRun t = plan_tiles(g, run);
         if (!r.streams() && (t.x != &x || t.third_b))
@@ -279,6 +279,21 @@ extern "C" atb_status atb_gemm_launch_info(const atb_gemm *g, int64_t *workgroup
     if (workgroups) *workgroups = r.streams() ? atb::stream_workgroups(g->proto, r) : (total + 7) / 8 * 8;
     if (threads) *threads = r.streams() ? r.threads() : t.x->threads;
     if (lds_bytes) *lds_bytes = r.streams() ? r.lds_bytes() : t.lds_bytes();
+    return ATB_OK;
+}
+
+extern "C" atb_status atb_gemm_kernel(const atb_gemm *g, atb_kernel_info *out)
+{
+    if (!g || !out) return ATB_ERR_INVALID_ARG;
+    const atb::StreamRoute r = plan_route(g);
+    atb::GemmParams p = g->proto;
+    if (r.streams()) {
+        *out = {16 * r.mb, 16 * r.mb, atb::kPanelK, 16 * r.nb, 1, r.threads(), r.lds_bytes() + r.dynamic_lds(), atb::stream_workgroups(p, r)};
+    } else {
+        const TileRun t = plan_tiles(g, p);
+        const int lds = g->b_format == ATB_FMT_BFP16 ? t.x->lds_b_bfp16 : t.lds_bytes();
+        *out = {t.x->T_MA, t.x->T_MC, t.x->T_K, t.x->T_N, 0, t.x->threads, lds, ((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8};
+    }
     return ATB_OK;
 }
 

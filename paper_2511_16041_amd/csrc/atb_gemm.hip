@@ -1694,6 +1694,7 @@ Instance make_instance(double eff_scale = 0.0, double lone_cap = 0.0)
     i.wave_n = S::WN;
     i.threads = S::NT;
     i.lds_bytes = S::LDS_BYTES;
+    i.lds_b_bfp16 = S::LDS_BYTES_BT;
     // workgroups that share a CU: one for the 8-wave workgroups (two waves per SIMD that use more than a quarter of
     // the SIMD's registers each); for the others what the LDS footprint and the 8 wave slots of a SIMD admit
     i.wg_per_cu = (S::CW == 8) ? 1 : std::max(1, std::min(std::min(8, (160 * 1024) / S::LDS_BYTES), 8 * 256 / S::NT));

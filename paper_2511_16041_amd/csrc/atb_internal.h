@@ -31,7 +31,8 @@ struct Instance {
     int T_MA, T_MC, T_K, T_N;
     int wave_m, wave_n;     // wave grid inside the workgroup
     int threads;            // wave_m * wave_n * 64
-    int lds_bytes;          // static LDS of the kernel
+    int lds_bytes;          // static LDS of the kernel with B in bf16 ...
+    int lds_b_bfp16;        // ... and in BFP16
     int wg_per_cu;          // workgroups of this instance that share a CU
     int mfma_rows;          // 16: v_mfma_f32_16x16x32_bf16, 32: v_mfma_f32_32x32x16_bf16
     double eff_scale;       // measured full-load throughput of this instance relative to Eq. (12)'s fit; 0: taken from the issue model

@@ -66,13 +66,23 @@ inline DecodeRoute decode_route(int64_t M, int64_t K, bool out_on_lines)
 // every plan of a problem gives the same bits, whatever the instance, B or B^T, and whatever M is for a row of C.
 constexpr int kStreamMinK = 1024;
 
+// Bytes of LDS that the 64-row forms with B in LDS (atb_rows.hip) ask for at the launch: two panels of B for each wave but the first, whose
+// panels lie in the static part, and a panel of A for each; or the partial C tiles of all waves but the first.
+constexpr int rows_dynamic_lds(int mb, int nb, int waves)
+{
+    const int panels = (waves - 1) * 2 * 64 * 32 * nb + waves * (mb * 1024 + (mb + 1) / 2 * 256), partial = (waves - 1) * 16 * mb * (16 * nb + 4) * 4;
+    return panels > partial ? panels : partial;
+}
+
 // The streaming kernel's variant for a problem: a workgroup takes a tile of 16 mb rows x 16 nb columns with `waves` waves,
-// each with `depth` panels of K in flight.  mb == 0: the problem stays with the tile pipeline.
+// each with `depth` panels of K in flight, in LDS (atb_rows.hip) or in registers.  mb == 0: the problem stays with the tile pipeline.
 struct StreamRoute {
     int mb, nb, waves, depth;
+    bool in_lds = false;
     bool streams() const { return mb > 0; }
     int threads() const { return 64 * waves; }
-    int lds_bytes() const { return waves * 16 * (16 * nb + 4) * 4; }         // the partial C tiles
+    int lds_bytes() const { return waves * 16 * (16 * nb + 4) * 4; }         // static: the partial C tiles
+    int dynamic_lds() const { return in_lds ? rows_dynamic_lds(mb, nb, waves) : 0; }
 };
 
 inline int64_t tile_count(const GemmParams &p, int rows, int cols)
@@ -124,7 +134,7 @@ inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int
     if (b_format == ATB_FMT_BF16) {
         if (p.N % 2 != 0 || tile_count(p, 64, 32) <= cus) return {};
         if (tile_count(p, 64, 64) <= cus) return small_tiles ? StreamRoute{} : StreamRoute{4, 4, 8, 1};
-        if (tile_count(p, 64, 128) <= cus && p.K >= 4096) return {4, 8, 4, 2};
+        if (tile_count(p, 64, 128) <= cus && p.K >= 4096) return {4, 8, 4, 2, true};
         return {};
     }
     const int depth = b_format == ATB_FMT_BFP16 ? stream_depth_bfp16(p.k_panels, 4) : 1;
@@ -187,7 +197,8 @@ inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
     const int mb = (p.M + 15) / 16, nb = stream_column_blocks(p.N, cus);
     if (b_format == ATB_FMT_BFP16) return {mb, nb, nb == 2 ? 16 : 8, nb == 4 ? stream_depth_bfp16(p.k_panels, mb) : 1};
     if (b_format == ATB_FMT_BF16 && p.N % 2 != 0) return {mb, 2, 8, 1};
-    return {mb, nb, nb == 2 ? 8 : 4, nb != 4 ? 1 : b_format == ATB_FMT_BF16_T ? stream_depth_bf16_t(mb) : stream_depth_bf16(mb)};
+    const int depth = nb != 4 ? 1 : b_format == ATB_FMT_BF16_T ? stream_depth_bf16_t(mb) : stream_depth_bf16(mb);
+    return {mb, nb, nb == 2 ? 8 : 4, depth, b_format == ATB_FMT_BF16 && depth == 2};
 }
 
 // What stream_route leaves to the pipeline and the 64 x 128 tiles with B through LDS (atb_rows.hip) still take: row-major bf16 B of even N that
@@ -197,7 +208,7 @@ inline StreamRoute stream_route(const GemmParams &p, int b_format, int cus)
 inline StreamRoute stream_route_lds(const GemmParams &p, int b_format, int cus)
 {
     const bool takes = b_format == ATB_FMT_BF16 && p.N % 2 == 0 && p.M > 64 && p.K >= 1536 && tile_count(p, 64, 128) <= cus && tile_count(p, 64, 64) > cus;
-    return takes ? StreamRoute{4, 8, 4, 2} : StreamRoute{};
+    return takes ? StreamRoute{4, 8, 4, 2, true} : StreamRoute{};
 }
 
 // Odd N, row-major bf16 B, on 128 x 128 tiles: whether the 128 x 256 tiles (128,128,64,256; the same bits) run in their place.  A request for rows at odd

@@ -33,7 +33,8 @@ struct RowsLds {
     static constexpr int PART = 16 * MB * PITCH * 4;
     static constexpr int FIXED = W * 16 * PITCH * 4;
     static constexpr int A_AT = (W - 1) * RING;                      // in the dynamic part: the rings of waves 1 .. W - 1, then A
-    static constexpr int DYNAMIC = A_AT + W * A_BYTES > (W - 1) * PART ? A_AT + W * A_BYTES : (W - 1) * PART;
+    static constexpr int DYNAMIC = rows_dynamic_lds(MB, NB, W);
+    static_assert(DYNAMIC >= A_AT + W * A_BYTES && DYNAMIC >= (W - 1) * PART, "the other waves, before and after");
     static_assert(RING <= FIXED && PART <= FIXED, "wave 0 lives in the static part");
     static_assert(FIXED + DYNAMIC <= 160 * 1024, "LDS of a CU");
 };

@@ -393,7 +393,7 @@ hipError_t launch_skinny(const GemmParams &p, int b_format, const StreamRoute &r
     } else {
         if (form == 1208) return launch_rows<kBRow, 2, 8, 3>(p, r, stream);
         if (form == 1404) return launch_rows<kBRow, 4, 4, 3>(p, r, stream);
-        if (r.depth == 2) return launch_lds_rows(p, r, stream);
+        if (r.in_lds) return launch_lds_rows(p, r, stream);
         if (form == 1804) return launch_rows<kBRow, 8, 4, 4>(p, r, stream);
         if (form == 1408 && r.mb == 4) return launch<kBRow, 4, 4, 8>(p, r, stream);
     }

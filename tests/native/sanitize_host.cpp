@@ -137,6 +137,9 @@ static void api_paths()
     EXPECT(atb_gemm_launch_info(g, &wg, &th, &lds) == ATB_OK && wg == 240 && th == 512 && lds == 139264);
     EXPECT(atb_gemm_launch_info(g, nullptr, nullptr, nullptr) == ATB_OK);
     EXPECT(atb_gemm_launch_info(nullptr, &wg, &th, &lds) == ATB_ERR_INVALID_ARG);
+    atb_kernel_info ki;
+    EXPECT(atb_gemm_kernel(nullptr, &ki) == ATB_ERR_INVALID_ARG && atb_gemm_kernel(g, nullptr) == ATB_ERR_INVALID_ARG);
+    EXPECT(atb_gemm_kernel(g, &ki) == ATB_OK && ki.T_MA == 256 && ki.T_MC == 256 && ki.T_K == 64 && ki.T_N == 256 && !ki.streams && ki.threads == 512 && ki.lds_bytes == 139264 && ki.workgroups == 240);
     EXPECT(atb_gemm_run(nullptr, fake, fake, fake, nullptr) == ATB_ERR_INVALID_ARG);
     EXPECT(atb_gemm_run(g, nullptr, fake, fake, nullptr) == ATB_ERR_INVALID_ARG);
     EXPECT(atb_gemm_run(g, fake, fake + 2, fake, nullptr) == ATB_ERR_INVALID_ARG);         // misaligned B

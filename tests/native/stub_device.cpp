@@ -13,7 +13,7 @@ Instance make(int T_MA, int T_MC, int T_K, int T_N, int wm, int wn, int lds, boo
 {
     Instance i{};
     i.T_MA = T_MA; i.T_MC = T_MC; i.T_K = T_K; i.T_N = T_N;
-    i.wave_m = wm; i.wave_n = wn; i.threads = wm * wn * 64; i.lds_bytes = lds;
+    i.wave_m = wm; i.wave_n = wn; i.threads = wm * wn * 64; i.lds_bytes = lds; i.lds_b_bfp16 = lds + 1024;
     i.wg_per_cu = 160 * 1024 / lds;
     i.mfma_rows = (wm * wn == 8) ? 16 : 32;
     i.eff_scale = 1.0; i.lone_cap = 0.0;

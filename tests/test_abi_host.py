@@ -321,6 +321,36 @@ def test_plans_report_the_kernel_that_runs():
     assert atb.lib().atb_gemm_streams(None) == 0
 
 
+def test_plans_name_the_tiles_that_run():
+    """atb_gemm_kernel: the plan's factors, or those that run in their place, and all the LDS that a workgroup takes."""
+    def kernel(shape, tiles, b="bf16", c="bf16"):
+        g = atb.Gemm(*shape, *tiles, b_format=b, c_format=c)
+        k, info = g.kernel(), g.launch_info()
+        assert (k.streams, k.threads, k.workgroups) == (int(g.streams()), info.threads, info.workgroups)
+        g.close()
+        return k
+    for tiles in atb.instances():
+        k = kernel((256, 256, 256), tiles)
+        assert k.tiles() == tiles and not k.streams and k.lds_bytes <= 160 * 1024
+    wide, small, mid = (128, 128, 64, 256), (64, 64, 64, 64), (64, 128, 64, 128)
+    for tiles in (mid, (128, 128, 64, 128)):
+        assert kernel((1500, 3001, 2056), tiles).tiles() == wide                                   # odd N, many tiles
+        assert kernel((1500, 3000, 2056), tiles).tiles() == tiles == kernel((51200, 65, 2056), tiles).tiles()
+    for tiles in ((256, 256, 64, 256), (128, 128, 64, 256)):
+        assert kernel((500, 500, 520), tiles, "bf16_t").tiles() == small and kernel((1500, 1500, 520), tiles, "bf16_t").tiles() == mid
+        assert kernel((4096, 4096, 520), tiles, "bf16_t").tiles() == tiles == kernel((500, 500, 520), tiles).tiles()
+    # LDS: a third B buffer for odd N, B in BFP16, panels of B in LDS (64 rows of row-major B), partial sums alone
+    a, b = 2 * 64 * (128 * 2 + 16), 128 * 128 * 2
+    assert kernel((600, 5001, 760), (64, 64, 128, 128)).lds_bytes == a + 2 * b and kernel((600, 5001, 1024), (64, 64, 128, 128)).lds_bytes == a + 3 * b
+    assert kernel((600, 5000, 760), (64, 64, 128, 128), "bfp16").lds_bytes == a + 2 * 128 * (128 * 2 + 16)
+    for shape, cols in (((1024, 2048, 4096), 128), ((64, 14336, 4096), 64)):
+        k = kernel(shape, (64, 64, 128, 128))
+        ring, panel_a, partial = 2 * 64 * cols * 2, 64 * 72, 64 * (cols + 4) * 4
+        assert k.streams and k.tiles() == (64, 64, 64, cols) and k.lds_bytes == partial + 3 * ring + 4 * panel_a
+    k = kernel((16, 8192, 8192), (32, 32, 256, 64))
+    assert k.streams and k.tiles() == (16, 16, 64, 32) and k.lds_bytes == 8 * 16 * 36 * 4
+
+
 def test_bfp16_bytes_refuses_floats_also_from_its_cache():
     assert atb.bfp16_bytes(24, 136) == atb.bfp16_layout(24, 136).bytes
     for bad in ((24.0, 136), (24, 136.0)):
