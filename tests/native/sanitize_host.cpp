@@ -271,6 +271,28 @@ static void route_paths()
         {48, 50000, 4096, ATB_FMT_BFP16, 3, 8},  {49, 16448, 4096, ATB_FMT_BFP16, 0, 0}};
     for (const auto &c : many) expect_route(c);
     for (const auto &c : few) expect_route(c);
+    // 64 x 128 tiles with B in LDS from K = 1536 on: at most one per CU, and more 64 x 64 ones than CUs
+    const struct { int M, N, K, fmt, cus; bool takes; } lds[] = {
+        {1024, 2048, 2048, ATB_FMT_BF16, 256, true},  {1024, 2048, 1536, ATB_FMT_BF16, 256, true},   {1024, 2048, 1528, ATB_FMT_BF16, 256, false},
+        {1000, 2046, 2048, ATB_FMT_BF16, 256, true},  {1024, 2047, 2048, ATB_FMT_BF16, 256, false},  {1024, 2048, 2048, ATB_FMT_BF16_T, 256, false},
+        {1024, 4096, 2048, ATB_FMT_BF16, 256, false}, {1024, 1024, 2048, ATB_FMT_BF16, 256, false},  {64, 16384, 2048, ATB_FMT_BF16, 256, false},
+        {1024, 2050, 2048, ATB_FMT_BF16, 256, false}, {1024, 2048, 2048, ATB_FMT_BF16, 255, false},  {1024, 2048, 2048, ATB_FMT_BF16, 511, true},
+        {1024, 2048, 2048, ATB_FMT_BF16, 512, false}, {256, 1024, 2048, ATB_FMT_BF16, 32, true},     {256, 1024, 2048, ATB_FMT_BF16, 64, false}};
+    for (const auto &c : lds) {
+        const atb::StreamRoute r = atb::stream_route_lds(problem(c.M, c.N, c.K), c.fmt, c.cus);
+        if (r.streams() != c.takes || (c.takes && (r.mb != 4 || r.nb != 8 || !r.in_lds))) {
+            std::printf("%d x %d x %d, format %d, on %d CUs: through LDS %d\n", c.M, c.N, c.K, c.fmt, c.cus, r.mb);
+            ++failures;
+        }
+    }
+    EXPECT(atb::stream_route_lds(problem(1024, 2040, 2048, true), ATB_FMT_BF16, 256).streams() && !atb::stream_route_lds(problem(1024, 2056, 2048, true), ATB_FMT_BF16, 256).streams());
+    EXPECT(atb::stream_route(problem(64, 14336, 4096), ATB_FMT_BF16, 256).in_lds && !atb::stream_route(problem(48, 14336, 4096), ATB_FMT_BF16, 256).in_lds);
+    EXPECT(!atb::stream_route(problem(64, 14336, 4096), ATB_FMT_BF16_T, 256).in_lds && atb::stream_route(problem(64, 14336, 4096), ATB_FMT_BF16_T, 256).depth == 2);
+    // B^T in bf16 on the pipeline: 64 x 64 tiles up to two per CU, 128 x 128 ones up to one
+    EXPECT(atb::bt_small_tiles(problem(1024, 2048, 520), 256) == 64 && atb::bt_small_tiles(problem(1025, 2048, 520), 256) == 128);
+    EXPECT(atb::bt_small_tiles(problem(2048, 2048, 520), 256) == 128 && atb::bt_small_tiles(problem(2049, 2048, 520), 256) == 0);
+    EXPECT(atb::bt_small_tiles(problem(1, 1, 8), 1) == 64 && atb::bt_small_tiles(problem(512, 512, 72), 32) == 64 && atb::bt_small_tiles(problem(513, 512, 72), 32) == 128);
+    EXPECT(atb::bt_small_tiles(problem(1024, 1024, 72), 32) == 0 && atb::bt_small_tiles(problem(1024, 1024, 72), 64) == 128 && atb::bt_small_tiles(problem(1024, 1024, 72), 128) == 64);
     // odd N on 128 x 128 tiles: the 128 x 256 ones in their place, by the tiles that one CU gets through (a wide one is two)
     const struct { int M, N, K, cus; bool wide; } odd_n[] = {
         {1500, 3001, 2056, 256, true},  {1500, 3000, 2056, 256, false}, {1500, 3001, 1016, 256, false},    // 288 tiles, 144 wide; even N; short K
