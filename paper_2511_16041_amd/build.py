@@ -17,7 +17,7 @@ OUT = os.path.join(HERE, "libatb.so")
 BINDING_SOURCE = "atb_binding.cpp"
 OBJ_DIR = os.path.join(HERE, "_build")
 # accumulators stay whole where they are carried round a loop: taken apart (as the compiler does with vectors that begin as constants), each
-# of their registers is moved once per round (212 moves to 64 MFMAs in atb_rows; in atb_skinny up to 7 %: 500 x 4096 x 4096 B^T 34.0 -> 32.9 us)
+# of their registers is moved once per round (212 moves to 64 MFMAs in atb_rows; in atb_skinny 0.99 to 1.05 x: 500 x 4096 x 4096 B^T 34.0 -> 32.9 us)
 WHOLE_PHIS = ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=0"]
 # accumulators stay in ordinary vector registers: with up to 470 of a wave's 512 in use the compiler otherwise parks other
 # values in the accumulation half and moves the accumulators out and in again around every panel (208 moves to 64 MFMAs)
@@ -35,7 +35,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-    # packed fp32 VALU forms are kept out of the generated code on this machine pool
+    # packed fp32 VALU forms are kept out of the generated code: some of them have given wrong results
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-attributes",
 ]

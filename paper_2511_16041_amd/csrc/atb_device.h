@@ -61,35 +61,35 @@ ATB_DEV unsigned bfp16_mantissas4(const float x[4], int shift)
 }
 
 // Columns n .. n + 7 of row m of C (whose rows end, in BFP16 with their zero tail, at column cols).
-    ATB_DEV void store_eight(const GemmParams &p, int m, int n, const floatx4 (&sum)[2], int cols)
-    {
-        if (__builtin_expect(p.Cm != nullptr, 0)) {
-            unsigned e = 0;
-            float x[8];
+ATB_DEV void store_eight(const GemmParams &p, int m, int n, const floatx4 (&sum)[2], int cols)
+{
+    if (__builtin_expect(p.Cm != nullptr, 0)) {
+        unsigned e = 0;
+        float x[8];
 #pragma unroll
-            for (int f = 0; f < 8; ++f) {
-                x[f] = n < p.N ? sum[f / 4][f % 4] : 0.0f;        // whole blocks: N % 8 == 0
-                e = max(e, exp_field(x[f]));
-            }
-            if (m < p.M && n < cols) {
-                const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;
-                *reinterpret_cast<intx2 *>(p.Cm + rec * kPanelK + n % kPanelK) = intx2{(int)bfp16_mantissas4(x, 133 - (int)e), (int)bfp16_mantissas4(x + 4, 133 - (int)e)};
-                p.Ce[rec * (kPanelK / 8) + (n % kPanelK) / 8] = (uint8_t)e;
-            }
-        } else if (m < p.M) {
-            typedef bf16x8 bf16x8_u __attribute__((aligned(2)));      // rows of C start anywhere
-            union { bf16x8 v; uint16_t h[8]; } o;
+        for (int f = 0; f < 8; ++f) {
+            x[f] = n < p.N ? sum[f / 4][f % 4] : 0.0f;        // whole blocks: N % 8 == 0
+            e = max(e, exp_field(x[f]));
+        }
+        if (m < p.M && n < cols) {
+            const int64_t rec = (int64_t)(n / kPanelK) * p.M + m;
+            *reinterpret_cast<intx2 *>(p.Cm + rec * kPanelK + n % kPanelK) = intx2{(int)bfp16_mantissas4(x, 133 - (int)e), (int)bfp16_mantissas4(x + 4, 133 - (int)e)};
+            p.Ce[rec * (kPanelK / 8) + (n % kPanelK) / 8] = (uint8_t)e;
+        }
+    } else if (m < p.M) {
+        typedef bf16x8 bf16x8_u __attribute__((aligned(2)));      // rows of C start anywhere
+        union { bf16x8 v; uint16_t h[8]; } o;
 #pragma unroll
-            for (int f = 0; f < 8; ++f) o.v[f] = (__bf16)sum[f / 4][f % 4];
-            uint16_t *dst = p.C + (int64_t)m * p.N + n;
-            if (n + 8 <= p.N) {
-                *reinterpret_cast<bf16x8_u *>(dst) = o.v;
-            } else {
+        for (int f = 0; f < 8; ++f) o.v[f] = (__bf16)sum[f / 4][f % 4];
+        uint16_t *dst = p.C + (int64_t)m * p.N + n;
+        if (n + 8 <= p.N) {
+            *reinterpret_cast<bf16x8_u *>(dst) = o.v;
+        } else {
 #pragma unroll
-                for (int f = 0; f < 8; ++f)
-                    if (n + f < p.N) dst[f] = o.h[f];
-            }
+            for (int f = 0; f < 8; ++f)
+                if (n + f < p.N) dst[f] = o.h[f];
         }
     }
+}
 
 }  // namespace atb

@@ -1061,7 +1061,7 @@ struct TileKernel {
     // ---- one microkernel, software-pipelined by hand ---------------------------------------
     // Side work of phase (kpar, s), in issue order: the memory requests for A sub-tile g+PF (and, in
     // the first phase of a K-step, for the B tile two K-steps ahead), the decode + LDS write of A
-    // sub-tile g+1, and (last phase of the K-step) the LDS writes of the B tile fetched in the first.
+    // sub-tile g+1, and (B in BFP16) this phase's share of the decode + LDS write of the next B tile.
     template <int s>
     static constexpr int n_side()
     {

@@ -120,12 +120,16 @@ inline int stream_depth_bf16(int mb) { return mb == 4 ? 2 : 1; }
 // memory-side cache holds:
 //   B bf16    64 x 64: M 128, 8192, 8192 54.4 / 47.0, M 256, 4096, 4096 22.3 / 19.5; eight shapes of 130 to 256 tiles, K 1032 to 4096: 1.0 - 1.3
 //             x memory, 0.96 - 1.2 x cache (lowest at K 1536, where the pipeline has whole K-steps)
-//             64 x 128: M 512, 4096, 14336 120 / 66, M 1024, 2048, 4096 24.9 / 21.3 (operands through registers); below K 4096 see stream_route_lds
+//             64 x 128: M 1024, 2048, 4096 38.2 / 26.7 memory, 26.2 / 21.7 cache, M 512, 4096, 14336 121 / 78; eight shapes, K 4096 to 14336: 1.35 - 1.6 x
+//             memory, 1.15 - 1.55 x cache; below K 4096 see stream_route_lds
 //             not 64 x 32 (M 256, 2048, 2048 9.9 / 10.4) nor odd N (M 512, 5001, 4096 61 / 70), nor 64 x 64 where the pipeline's 32 x 64
 //             tiles fit one to a CU (rows just above a multiple of 64: M 193, 2304, M 129, 3000 and M 96, 5000, K 1032 .. 4096: 0.83 - 0.94 x
 //             memory, 0.72 - 0.91 x cache)
-//   B^T bf16  M 128, 4096, 4096: 52 / 18 (64 x 32)   M 256, 4096, 4096: 55 / 26 (64 x 64)   M 512, 4096, 4096: 57 / 36 (128 x 64;
-//             the pipeline has no tile below 128 x 256 for it, of which this problem fills a quarter of the chip)
+//   B^T bf16  K 1032 / 2048 / 4096 / 8192, the pipeline on its 64 x 64 tiles where these are few (bt_small_tiles): 64 x 32 tiles (M 65 .. 200, N 2000 .. 4096)
+//             1.6 / 1.9 / 2.3 / 2.4 x memory, 1.3 / 1.4 / 1.5 / 1.6 x cache; 64 x 64 (256 x 4096, 100 x 8000, 300 x 3000) 1.25 / 1.4 / 1.65 / 1.75
+//             and 1.05 - 1.1 / 0.97 - 1.0 / 1.06 - 1.1 / 1.05 - 1.8; 128 x 64 (512 x 4096, 1024 x 2048, 129 x 6000) 0.90 - 0.95 / 1.02 - 1.04 / 1.14 - 1.17 /
+//             1.2 - 1.3 and 0.79 - 0.82 / 0.85 - 0.89 / 0.91 - 0.96 / 0.97 - 1.2.  (The last line dates from when the pipeline had no tile below 128 x 256 for
+//             B^T, 57 / 36 us at 512 x 4096 x 4096; with B from the caches the small tiles have overtaken it.)
 //   B^T BFP16 M 128, 4096, 4096: 19.9 / 17.5 (64 x 32)   M 128, 8192, 8192: 47.9 / 38.4 (64 x 64); where 32 x 64 tiles fit one to a CU, K 1032
 //             and 1152 0.98 - 1.16 x, from 1296 on 0.88 - 0.97 x memory
 inline StreamRoute stream_route_many_rows(const GemmParams &p, int b_format, int cus)
@@ -154,8 +158,9 @@ inline bool stream_few_rows(const GemmParams &p, int b_format, int cus)
     const int M = p.M, N = p.N, K = p.K;
     if (b_format == ATB_FMT_BFP16) return N <= 64 * cus || M <= 48;        // 1.0 - 1.9; M 64, N 28672, K 8192 0.87: out of registers
     if (b_format == ATB_FMT_BF16_T) {
-        // 1.35 - 3 up to one tile per CU; beyond, N 33000 .. 48000 0.70 - 0.99, 57344 and 128256 0.90 - 1.17, but 1.01 - 1.29 for N 66000 ..
-        // 90000 and 151936, where 256 columns (the pipeline's tile) come to more rounds than 128
+        // Up to N = 16384 1.13 - 4.2 from memory, 0.98 - 2.9 from the caches.  To 32768 M <= 16 1.0 - 1.3; M 33 .. 48 0.93 - 0.98 at K = 1032, 0.99 - 1.18
+        // above (cache 0.83 - 1.17); M 64 0.87 - 0.93, 0.97 - 1.1 (cache 0.77 - 1.1).  Beyond, N 33000 .. 48000 0.70 - 0.99, 57344 and 128256 0.90 - 1.17, but
+        // 1.01 - 1.29 for N 66000 .. 90000 and 151936, where 256 columns (the pipeline's tile) come to more rounds than 128
         if (N <= 128 * cus) return true;
         const int64_t rounds128 = ((N + 127) / 128 + cus - 1) / cus, rounds256 = ((N + 255) / 256 + cus - 1) / cus;
         return rounds128 < 2 * rounds256;

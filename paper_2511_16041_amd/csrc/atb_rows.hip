@@ -9,8 +9,8 @@
 //     and the requests are spread over the panel: bunched, they fill the queue to the caches and the wave stands still;
 //   * descriptors, LDS addresses and M0 take three scalar instructions per request and about twenty per panel.
 // What is left is bytes into a CU: 84 KB per round of panels at 95 to 100 GB/s, what a loop of such requests alone reaches from the caches.
-// us, operands through registers with the compiler's schedule / now: 1024 x 2048 x 4096 24.9 / 21.3, 512 x 4096 x 4096 25.2 / 21.3, 200 x
-// 8000 x 4096 25.3 / 20.9; 64 x 8256 x 4096 21.8 / 16.4, 64 x 14336 x 4096 29.3 / 28.3 (from memory).
+// us, operands through registers with the compiler's schedule / now: 1024 x 2048 x 4096 25.5 / 21.9 (27.1 / 25.8 from memory), 512 x 4096 x 4096 25.8 / 21.8
+// (27.8 / 26.8), 200 x 8000 x 4096 26.1 / 21.8 (28.8 / 27.0); 64 x 8256 x 4096 21.8 / 16.9 (26.3 / 21.3), 64 x 14336 x 4096 29.3 / 28.3 (29.5 / 28.4).
 #include "atb_device.h"
 #include "atb_route.h"
 
@@ -321,8 +321,9 @@ struct Rows {
     }
 };
 
+// FMT and D have one value each; they stand here so that the name of a compiled form says the same of it as skinny_kernel's does.
 template <int FMT, int MB, int NB, int W, int D>
-__global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
+__global__ void __launch_bounds__(W * 64) rows_skinny_kernel(const GemmParams p)
 {
     static_assert(FMT == 0 && D == 2, "row-major B of even N, two panels in flight");
     typedef RowsLds<MB, NB, W> L;
@@ -363,7 +364,7 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
 template <int MB, int NB, int W>
 hipError_t launch(const GemmParams &p, const StreamRoute &r, hipStream_t stream)
 {
-    hipLaunchKernelGGL((skinny_kernel<0, MB, NB, W, 2>), dim3((unsigned)stream_workgroups(p, r)), dim3(W * 64), (RowsLds<MB, NB, W>::DYNAMIC), stream, p);
+    hipLaunchKernelGGL((rows_skinny_kernel<0, MB, NB, W, 2>), dim3((unsigned)stream_workgroups(p, r)), dim3(W * 64), (RowsLds<MB, NB, W>::DYNAMIC), stream, p);
     return hipGetLastError();
 }
 

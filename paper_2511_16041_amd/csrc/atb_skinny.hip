@@ -15,7 +15,7 @@
 // Measured in us, three sets of operands in turns, the tile pipeline before / this kernel now:
 //   B bf16    M 16, N 8192, K 8192: 39.6 / 34.5  (64 rows: atb_rows.hip)     M 16, 5001, 4096: 23.7 / 12.9
 //   B^T bf16  M 16, N 8192, K 8192: 105 / 29        M 64, 14336, 4096: 57.7 / 29.4
-//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.0    M 64, 14336, 4096: 26.0 / 18.6 (decoding A takes as long as B's bytes)
+//   B^T BFP16 M 16, N 14336, K 4096: 20.1 / 13.0    M 64, 14336, 4096: 26.0 / 18.7 (decoding A takes as long as B's bytes)
 //
 // MFMA v_mfma_f32_16x16x32_bf16: lane l supplies index l % 16 of its operand and 8 k values of group l / 16.  Which k
 // a group holds is free as long as both operands agree: lane group q takes k = 16 q .. 16 q + 15 of the panel, the
@@ -211,7 +211,7 @@ struct Skinny {
 
     // Two panels in flight per wave, the one requested while the other is multiplied.  The fences keep the compiler from sinking the first
     // panel's requests below the second's arithmetic.
-    static constexpr bool FENCED = D > 1 && FMT != kBRow;
+    static constexpr bool FENCED = D > 1;
 
     ATB_DEV void run()
     {
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(W * 64) skinny_kernel(const GemmParams p)
     if (any) sk.run();
     // The sums of the waves' partial tiles, row block by row block.  Four row blocks unrolled are 4 KiB of code that runs once, and such
     // code comes into the instruction cache at about two bytes per ns; for tiles of 128 columns, which have up to four and eight
-    // accumulator blocks in each, one copy serves them all (1024 x 2048 x 4096 26.6 -> 25.5 us; the narrower tiles lose 1 %).
+    // accumulator blocks in each, one copy serves them all (26.6 -> 25.5 us for 1024 x 2048 x 4096 when it ran here; the narrower tiles lose 1 %).
     if constexpr (Skinny<FMT, MB, NB, W, D>::EIGHTS) {
         floatx4 *const mem = reinterpret_cast<floatx4 *>(&part[0][0][0]);
         static_assert(W * 8 * 64 * sizeof(floatx4) <= sizeof(part), "a row block's partial sums");
