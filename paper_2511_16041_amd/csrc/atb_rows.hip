@@ -250,14 +250,14 @@ struct Rows {
     //   B fragments      of this panel's second half during the first, of the next panel's first half at the end
     //   the wait         ahead of those, for the next panel: younger than its requests are those for B since then
     // When to ask is a matter of where B is; us with operands through registers / asked for in slots NB .. SLOTS / 2 - 1 and SLOTS / 2 .. SLOTS - 1 / now.
-    // 128 columns: early, and the second half in one go, since from memory it came late: 1024 x 2048 x 8192 48.4 / 48.6 / 45.6, 1000 x 2000 x 8192
-    // 49.8 / 51.5 / 49.6, 700 x 2900 x 8192 51.3 / 54.2 / 52.1 (rows of B that begin at multiples of 8 bytes).  From the caches it costs up to 1.5 %: 1024 x 2048 x
-    // 4096 25.4 / 21.7 / 21.8, x 8192 44.9 / 39.0 / 39.6.
+    // 128 columns: early, and the second half in one go, since from memory it came late: 1024 x 2048 x 8192 48.7 / 48.3 / 45.6, 1000 x 2000 x 8192
+    // 49.7 / 51.5 / 49.4, 700 x 2900 x 8192 50.9 / 53.9 / 51.7 (rows of B that begin at multiples of 8 bytes).  From the caches it is level: 1024 x 2048 x 4096
+    // 27.1 / 22.6 / 22.6, x 8192 48.1 / 40.0 / 39.9 (earlier still, slots 28 .. 43, 2 % slower).
     // 64 columns: late, since where rows of B are 32 KiB apart all requests of a CU go to one memory channel, and the more in flight the worse: 64 x
     // 16384 x 14336 88.1 / 91.5 / 89.3, 49 x 16384 x 8192 51.6 / 52.7 / 51.5.  It costs 1 to 2 % where half of the CUs have a tile: 64 x 8256 x 4096
     // from memory 26.3 / 21.2 / 21.4, from the caches 21.8 / 16.5 / 16.9.
     static constexpr int SLOTS = GROUPS * NB, WAIT = SLOTS - 2 * NB - 2;
-    static constexpr int FROM1 = 8, TO1 = NB == 8 ? 28 : 17, FROM2 = NB == 8 ? 34 : 22, TO2 = NB == 8 ? 48 : 32;
+    static constexpr int FROM1 = 8, TO1 = NB == 8 ? 28 : 17, FROM2 = NB == 8 ? 36 : 22, TO2 = NB == 8 ? 48 : 32;
     static constexpr int spread(int m, int from, int to, int n) { return m <= from ? 0 : m < to ? (m - from) * n / (to - from) : n; }       // of n requests, those before slot m
     static constexpr int first_half(int m) { return spread(m, FROM1, TO1, A_REQ + NB); }
     static constexpr int second_half(int m) { return spread(m, FROM2, TO2, NB); }
